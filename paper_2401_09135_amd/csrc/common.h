@@ -131,7 +131,7 @@ int rmsnorm_bwd(const float* dy, const float* x, const float* rstd, const float*
 int cross_entropy(const void* logits, int logits_bf16, const int32_t* tok, float* loss_row, void* dlogits,
                   int dl_bf16, int B, int S, int V, hipStream_t st);
 int mean_rows(const float* loss_row, float* out, int T, hipStream_t st);
-// Orders each step's input positions by token id (see elementwise.hip); offset is
+// Orders each step's input positions by token id (see elementwise.hip; rank is scratch); offset is
 // [n_steps][V+1], rank and pos are [n_steps][B*S].
 int embed_sort(const int32_t* tok, int n_steps, int B, int S, int V, int32_t* offset, int32_t* rank,
                int32_t* pos, hipStream_t st);

@@ -422,84 +422,202 @@ int embed_fwd(const int32_t* tok, const float* E, const float* Ppos, float* x, i
 }
 
 // Embedding gradient without float atomics, so that a step is bit-reproducible.
-// (1) embed_sort: one workgroup per step orders the T input positions by token id with a
-//     counting sort whose ranks are fixed by position order: offset[v] .. offset[v+1] delimit
-//     the positions holding token v inside pos[].  It depends on the tokens only, so one
-//     launch prepares every step of a local round.
+// (1) embed_sort: one workgroup per step orders the T input positions by token id, equal tokens in
+//     position order: offset[v] .. offset[v+1] delimit the positions holding token v inside pos[].
+//     It depends on the tokens only, so one launch prepares every step of a local round.
 // (2) embed_bwd: a pass over 32-position chunks of that list and a pass over vocabulary rows
 //     (described at the kernels below).
 // dPpos[s,:] = sum_b dx[b,s,:] in batch order.
-__device__ __forceinline__ int wave_incl_scan(int v, int lane) {
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int n = __shfl_up(v, o, 64);
-    if (lane >= o) v += n;
-  }
-  return v;
-}
+//
+// The order is a least-significant-digit radix sort of the positions by token id (digits of at most
+// 8 bits: one pass for V <= 256, two for V <= 65536).  A tile of at most 16384 positions is ranked at a time:
+// wavefront w owns up to 1024 consecutive ones, 64 per iteration, and finds the lanes that hold the same
+// digit with one ballot per digit bit, so a rank costs one counter access per 64 positions and no
+// comparison of positions with each other.  What bounds it is that chain of 16 counter updates per
+// pass and the gathers of ids through L2; a round has one workgroup per step.  T = 16384, V = 8192: 761 us with
+// every position compared against the 1024 of its chunk, 54 us now; V = 32000: 785 and 69; T = 512: 20 and 13.
+constexpr int SORT_ITEMS = 16, SORT_TILE = 1024 * SORT_ITEMS;
 
 __global__ __launch_bounds__(1024) void embed_sort_kernel(const int32_t* __restrict__ tok, int B,
-                                                          int S, int V, int32_t* offset,
+                                                          int S, int V, int npass, int digit_bits, int32_t* offset,
                                                           int32_t* rank, int32_t* pos) {
-  __shared__ int ids[1024];
-  __shared__ int wsum[16];
-  __shared__ int carry_s;
+  __shared__ int cnt[16][256];   // per wavefront and digit: count, then next output index
+  __shared__ int base[256];      // per digit: next output index of the tile to come
+  __shared__ int wmin[16];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int T = B * S;
+  const int T = B * S, ndig = 1 << digit_bits;
   const int32_t* tk = tok + (int64_t)blockIdx.x * B * (S + 1);
-  int32_t* cnt = offset + (int64_t)blockIdx.x * (V + 1);
-  int32_t* rk = rank + (int64_t)blockIdx.x * T;
-  int32_t* ps = pos + (int64_t)blockIdx.x * T;
-  for (int v = tid; v <= V; v += 1024) cnt[v] = 0;
-  __syncthreads();
-  for (int c0 = 0; c0 < T; c0 += 1024) {
-    int t = c0 + tid;
-    bool active = t < T;
-    int id = active ? tk[(int64_t)(t / S) * (S + 1) + (t % S)] : -1;
-    if (active) id = id < 0 ? 0 : (id >= V ? V - 1 : id);
-    ids[tid] = id;
-    __syncthreads();
-    int before = 0, after = 0;
-    int n = T - c0 < 1024 ? T - c0 : 1024;
-    if (active)
-      for (int j = 0; j < n; j++) {
-        int eq = ids[j] == id;
-        before += eq & (j < tid);
-        after += eq & (j > tid);
+  int32_t* off = offset + (int64_t)blockIdx.x * (V + 1);
+  int32_t* buf[2] = {pos + (int64_t)blockIdx.x * T, rank + (int64_t)blockIdx.x * T};
+  // t / S by multiplication: exact for t < 2^22 and 1 < S <= 1024 (t (M S - 2^32) < 2^32)
+  const unsigned M = S > 1 ? 0xffffffffu / (unsigned)S + 1u : 0u;
+  auto token_at = [&](int t) {
+    const int row = S > 1 ? (int)__umulhi((unsigned)t, M) : t;
+    int id = tk[t + row];   // tokens are [B, S + 1], positions [B, S]
+    return id < 0 ? 0 : (id >= V ? V - 1 : id);
+  };
+  const uint64_t below = (1ull << lane) - 1;
+  // positions per wavefront and tile: a short list is dealt to all 16 wavefronts, 64 at least to each
+  const int per_wave = T >= SORT_TILE ? 64 * SORT_ITEMS : (T + 1023) / 1024 * 64;
+
+  for (int p = 0; p < npass; p++) {
+    const int32_t* src = p == 0 ? nullptr : buf[(npass - p) & 1];   // the first pass reads positions in order
+    int32_t* dst = buf[(npass - 1 - p) & 1];                         // the last one writes pos
+    const int shift = p * digit_bits;
+    auto exclusive_base = [&]() {   // base[] from digit totals to exclusive sums, by one wavefront
+      int carry = 0;
+      for (int d0 = 0; d0 < ndig; d0 += 64) {
+        const int x = d0 + lane < ndig ? base[d0 + lane] : 0;
+        int incl = x;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int n = __shfl_up(incl, o, 64);
+          if (lane >= o) incl += n;
+        }
+        if (d0 + lane < ndig) base[d0 + lane] = carry + incl - x;
+        carry += __shfl(incl, 63, 64);
       }
-    int base = active ? cnt[id] : 0;
-    if (active) rk[t] = base + before;
-    __syncthreads();
-    if (active && after == 0) cnt[id] = base + before + 1;
-    __syncthreads();
+    };
+    int item[SORT_ITEMS], dig[SORT_ITEMS], rk[SORT_ITEMS];
+    auto load_tile = [&](int t0) {   // all loads of a tile in flight together
+#pragma unroll
+      for (int it = 0; it < SORT_ITEMS; it++) {
+        const int i = t0 + wv * per_wave + it * 64 + lane;
+        item[it] = it * 64 < per_wave && i < T ? (src ? src[i] : i) : -1;
+      }
+#pragma unroll
+      for (int it = 0; it < SORT_ITEMS; it++)
+        dig[it] = item[it] >= 0 ? (token_at(item[it]) >> shift) & (ndig - 1) : -1;
+    };
+    if (T > SORT_TILE) {   // several tiles: the digit totals of the whole list first
+      if (tid < 256) base[tid] = 0;
+      __syncthreads();
+      for (int t0 = 0; t0 < T; t0 += SORT_TILE) {
+        load_tile(t0);
+#pragma unroll
+        for (int it = 0; it < SORT_ITEMS; it++)
+          if (dig[it] >= 0) atomicAdd(&base[dig[it]], 1);
+      }
+      __syncthreads();
+      if (wv == 0) exclusive_base();
+    }
+    for (int t0 = 0; t0 < T; t0 += SORT_TILE) {
+      for (int i = tid; i < 16 * 256; i += 1024) (&cnt[0][0])[i] = 0;
+      __syncthreads();
+      load_tile(t0);
+#pragma unroll
+      for (int it = 0; it < SORT_ITEMS; it++) {
+        if (it * 64 < per_wave) {
+          const bool active = dig[it] >= 0;
+          uint64_t same = __ballot(active);
+          for (int b = 0; b < digit_bits; b++) {
+            const bool bit = (dig[it] >> b) & 1;
+            const uint64_t set = __ballot(bit);
+            same &= bit ? set : ~set;
+          }
+          // wavefront-private counters: its LDS operations complete in order
+          volatile int* c = &cnt[wv][active ? dig[it] : 0];
+          const int before = *c;
+          rk[it] = before + __popcll(same & below);
+          if (active && (same & below) == 0) *c = before + __popcll(same);
+        }
+      }
+      __syncthreads();
+      if (T <= SORT_TILE) {   // one tile: its counts are the totals
+        if (tid < ndig) {
+          int n = 0;
+#pragma unroll
+          for (int w = 0; w < 16; w++) n += cnt[w][tid];
+          base[tid] = n;
+        }
+        __syncthreads();
+        if (wv == 0) exclusive_base();
+        __syncthreads();
+      }
+      if (tid < ndig) {
+        int next = base[tid];
+#pragma unroll
+        for (int w = 0; w < 16; w++) {
+          const int c = cnt[w][tid];
+          cnt[w][tid] = next;
+          next += c;
+        }
+        base[tid] = next;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int it = 0; it < SORT_ITEMS; it++)
+        if (dig[it] >= 0) dst[cnt[wv][dig[it]] + rk[it]] = item[it];
+      __syncthreads();
+    }
   }
-  // exclusive prefix sum of cnt[0..V] in place
-  if (tid == 0) carry_s = 0;
+
+  // offset[v] = first index whose token is >= v: T everywhere, the index where a token's run starts,
+  // then the minimum over all larger tokens (from the end of the vocabulary, 4096 entries at a time)
+  const int32_t* sorted = buf[0];
+  for (int v = tid; v <= V; v += 1024) off[v] = T;
   __syncthreads();
-  for (int v0 = 0; v0 <= V; v0 += 1024) {
-    int v = v0 + tid;
-    int x = v <= V ? cnt[v] : 0;
-    int incl = wave_incl_scan(x, lane);
-    if (lane == 63) wsum[wv] = incl;
-    __syncthreads();
-    int add = carry_s;
-    for (int w = 0; w < wv; w++) add += wsum[w];
-    if (v <= V) cnt[v] = incl - x + add;
-    __syncthreads();
-    if (tid == 1023) carry_s = add + incl;
-    __syncthreads();
+  for (int i0 = 0; i0 < T; i0 += 8 * 1024) {   // 8 positions per thread in flight
+    int id[8], prev[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+      const int i = i0 + u * 1024 + tid;
+      id[u] = i < T ? sorted[i] : 0;
+      prev[u] = lane == 0 && i > 0 && i < T ? sorted[i - 1] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+      id[u] = token_at(id[u]);
+      if (lane == 0) prev[u] = token_at(prev[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+      const int i = i0 + u * 1024 + tid;
+      const int left = __shfl_up(id[u], 1, 64);
+      if (i < T && (i == 0 || (lane ? left : prev[u]) != id[u])) off[id[u]] = i;
+    }
   }
-  for (int t = tid; t < T; t += 1024) {
-    int id = tk[(int64_t)(t / S) * (S + 1) + (t % S)];
-    id = id < 0 ? 0 : (id >= V ? V - 1 : id);
-    ps[cnt[id] + rk[t]] = t;
+  __syncthreads();
+  int carry = T;   // minimum over everything behind the current 4096 entries
+  for (int v0 = V / 4096 * 4096; v0 >= 0; v0 -= 4096) {
+    const int v = v0 + 4 * tid;
+    int x[4];
+#pragma unroll
+    for (int e = 3; e >= 0; e--) {
+      x[e] = v + e <= V ? off[v + e] : T;
+      if (e < 3 && x[e + 1] < x[e]) x[e] = x[e + 1];
+    }
+    int m = x[0];
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int n = __shfl_down(m, o, 64);
+      if (lane + o < 64 && n < m) m = n;
+    }
+    const int behind_lane = __shfl_down(m, 1, 64);
+    if (lane == 0) wmin[wv] = m;
+    __syncthreads();
+    int behind = carry, all = carry;
+    for (int w = 0; w < 16; w++) {
+      const int n = wmin[w];
+      if (w > wv && n < behind) behind = n;
+      if (n < all) all = n;
+    }
+    if (lane < 63 && behind_lane < behind) behind = behind_lane;
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      if (v + e <= V) off[v + e] = x[e] < behind ? x[e] : behind;
+    carry = all;
+    __syncthreads();
   }
 }
 
 int embed_sort(const int32_t* tok, int n_steps, int B, int S, int V, int32_t* offset, int32_t* rank,
                int32_t* pos, hipStream_t st) {
   if (n_steps <= 0) return ALS_OK;
-  hipLaunchKernelGGL(embed_sort_kernel, dim3(n_steps), dim3(1024), 0, st, tok, B, S, V, offset, rank, pos);
+  int bits = 1;
+  while (bits < 31 && (1 << bits) < V) bits++;
+  const int npass = (bits + 7) / 8, digit_bits = (bits + npass - 1) / npass;
+  hipLaunchKernelGGL(embed_sort_kernel, dim3(n_steps), dim3(1024), 0, st, tok, B, S, V, npass, digit_bits, offset, rank, pos);
   ALS_CHECK_LAUNCH();
   return ALS_OK;
 }
