@@ -1,6 +1,6 @@
 // Generic causal attention, one wavefront per query (forward, dq) or per key (dk, dv), fp32
-// arithmetic on fp32 or bf16 storage.  Reference-mode path and fallback; the fast path is
-// the MFMA kernel.  qkv is [B*S, 3d]: q at column hd*dh, k at d + hd*dh, v at 2d + hd*dh.
+// arithmetic on fp32 or bf16 storage: any head width up to 64 and any alignment.  Head widths of 32
+// and 64 on aligned tensors go to the fp32 matrix-core kernels (attention_mfma_f32.hip).  qkv is [B*S, 3d]: q at column hd*dh, k at d + hd*dh, v at 2d + hd*dh.
 #include "common.h"
 #include <math.h>
 
@@ -175,6 +175,7 @@ int attention_fwd_generic(const void* qkv, void* o, float* lse, int B, int S, in
                           hipStream_t st) {
   int rc = check_shape(B, S, h, dh);
   if (rc) return rc;
+  if (attention_mfma_f32_supported(qkv, o, qkv, o, B, S, h, dh)) return attention_fwd_mfma_f32(qkv, o, lse, B, S, h, dh, bf, st);
   dim3 grid((S + 3) / 4, h, B), block(256);
   size_t sm = ((size_t)4 * S + 256) * sizeof(float);
   float scale = 1.0f / sqrtf((float)dh);
@@ -191,6 +192,8 @@ int attention_bwd_generic(const void* qkv, const void* o, const void* d_o, const
                           hipStream_t st) {
   int rc = check_shape(B, S, h, dh);
   if (rc) return rc;
+  if (attention_mfma_f32_supported(qkv, o, d_o, dqkv, B, S, h, dh))
+    return attention_bwd_mfma_f32(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, bf, st);
   dim3 grid((S + 3) / 4, h, B), block(256);
   float scale = 1.0f / sqrtf((float)dh);
   size_t sm1 = ((size_t)4 * S + 512) * sizeof(float);

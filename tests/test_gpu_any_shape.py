@@ -7,6 +7,7 @@ import torch
 import als_inputs as I
 import paper_2401_09135_amd as A
 from oracle import lm
+from test_gpu_kernels import _attention_case
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -45,3 +46,41 @@ def test_token_order_of_the_embedding_gradient(V, B, S):
     rloss, rg = lm.loss_and_grad(theta0, tok, w)
     assert abs(loss - rloss) < 1e-5 * abs(rloss)
     assert _rel(lm.views(g, w)["E"], lm.views(rg, w)["E"]) < 1e-5
+
+
+@pytest.mark.parametrize("B,S,h,dh", [(33, 1, 2, 32), (33, 16, 2, 64), (33, 17, 2, 32),   # one tile, one and one row
+                                      (1, 33, 1, 64), (1, 63, 1, 32), (2, 129, 3, 64),     # last tile of 1, 15, 1 rows; idle wavefronts
+                                      (16, 272, 16, 32), (9, 1009, 8, 64),                 # two row blocks per wavefront
+                                      (1, 70, 3, 40)])                                     # a width of the vector kernels
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_attention_in_fp32_arithmetic(B, S, h, dh, dt):
+    """Sums of up to 1009 fp32 products in tile order: 2^-24 sqrt(1009) 4 < 1e-5; bf16 storage: one rounding (2^-9) of o and
+    dqkv, and of the o that the row dots are formed from."""
+    o, ro, lse, rlse, dq, rdq = _attention_case(B, S, h, dh, dt, False)
+    assert _rel(o, ro) < (1e-5 if dt == torch.float32 else 4e-3)
+    np.testing.assert_allclose(lse, rlse, rtol=1e-5, atol=1e-5)
+    if S > 1:
+        assert _rel(dq, rdq) < (1e-5 if dt == torch.float32 else 8e-3)
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_attention_hides_what_a_query_does_not_see(bad):
+    """Row 37 of v (k) is not finite: the output (dq) of every earlier position is what it is without it."""
+    B, S, h, dh = 1, 70, 2, 64
+    d = h * dh
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    qkv = torch.randn(B * S, 3 * d, device=DEV, generator=gen)
+    d_o = torch.randn(B * S, d, device=DEV, generator=gen)
+    res = []
+    for part in (None, 1, 2):
+        x = qkv.clone()
+        if part:
+            x[37, part * d:(part + 1) * d] = bad
+        o, lse, sc, dq = torch.empty(B * S, d, device=DEV), torch.empty(B * h * S, device=DEV), torch.empty(B * h * S, device=DEV), torch.empty_like(x)
+        A.k_attention_fwd(x, o, lse, B, S, h, dh, False)
+        A.k_attention_bwd(x, o, d_o, lse, sc, dq, B, S, h, dh, False)
+        res.append((o.cpu(), dq.cpu()))
+    for o, dq in res[1:]:
+        assert torch.equal(o[:37], res[0][0][:37])
+        assert torch.equal(dq[:37, :d], res[0][1][:37, :d])
+    assert not torch.isfinite(res[2][0][37:]).any()
