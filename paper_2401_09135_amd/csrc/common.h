@@ -60,6 +60,9 @@ struct GemmDesc {
   float* ws; size_t ws_bytes;        // scratch for split-K partials (may be null)
 };
 int gemm_generic(const GemmDesc& g, hipStream_t st);
+// fp32 operands and results on the fp32 matrix instruction (gemm_mfma_f32.hip): any shape, layout and epilogue
+bool gemm_mfma_f32_supported(const GemmDesc& g);
+int gemm_mfma_f32(const GemmDesc& g, hipStream_t st);
 bool gemm_mfma_supported(const GemmDesc& g);
 int gemm_mfma(const GemmDesc& g, hipStream_t st);
 // picks the MFMA kernel when allowed and supported

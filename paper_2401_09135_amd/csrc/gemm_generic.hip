@@ -1,20 +1,10 @@
-// Generic tiled GEMM with fp32 accumulation: any shape, any of the four operand layouts,
-// fp32 or bf16 operands.  This is the reference-mode (fp32) path and the fallback for shapes
-// the MFMA kernel does not take; it is not the fast path.
+// Generic tiled GEMM with fp32 accumulation in vector code: any shape, any of the four operand
+// layouts, fp32 or bf16 operands.  The fallback for shapes that the bf16 MFMA kernels do not take and
+// the independent check of those that they do; fp32 products go to gemm_mfma_f32.hip.
 #include "common.h"
+#include "gelu.h"
 
 namespace als {
-
-__device__ __forceinline__ float gelu_tanh_f(float u) {
-  const float a = 0.7978845608028654f, b = 0.044715f;
-  return 0.5f * u * (1.0f + tanhf(a * (u + b * u * u * u)));
-}
-__device__ __forceinline__ float gelu_tanh_grad_f(float u) {
-  const float a = 0.7978845608028654f, b = 0.044715f;
-  float th = tanhf(a * (u + b * u * u * u));
-  float inner = a * (1.0f + 3.0f * b * u * u);
-  return 0.5f * (1.0f + th) + 0.5f * u * (1.0f - th * th) * inner;
-}
 
 template <typename T>
 __device__ __forceinline__ float ld(const void* p, int64_t i) {
@@ -105,6 +95,7 @@ static int launch_epi(const GemmDesc& g, hipStream_t st) {
 int gemm_generic(const GemmDesc& g, hipStream_t st) {
   if (g.M <= 0 || g.N <= 0 || g.K <= 0) return set_error(ALS_ERR_INVALID, "gemm: empty shape");
   if (g.epi == EPI_RESID && g.c_bf16) return set_error(ALS_ERR_INVALID, "gemm: residual output must be fp32");
+  if (gemm_mfma_f32_supported(g)) return gemm_mfma_f32(g, st);
   if (g.in_bf16) return g.c_bf16 ? launch_epi<bf16, bf16>(g, st) : launch_epi<bf16, float>(g, st);
   return g.c_bf16 ? launch_epi<float, bf16>(g, st) : launch_epi<float, float>(g, st);
 }

@@ -1,0 +1,238 @@
+// fp32 GEMM on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: whole fp32 products and sums), any shape, any operand
+// layout, any alignment, the epilogues of the worker step: the reference mode's products.
+//
+// One workgroup owns a BM x BN tile of C and walks K in slices of BK through two LDS buffers; the loads of the slice after next
+// are in flight while a slice is multiplied.  A wavefront owns a sub-tile of 32 x 32 blocks and, where tiles are few, one of WK shares of
+// every slice (the shares are added through LDS at the end, in order).  An operand is kept in LDS as it lies in
+// memory: [row][BK] when the contraction is contiguous (a lane's 4 steps of a group of 8 are one 16-byte read), [BK][row] when it is strided.
+//   MFMA lane layout (lane l, half hf = l / 32): A row l%32, contraction hf; B column l%32, contraction hf; accumulator
+//   element v: row 8 (v/4) + 4 hf + v%4, column l%32.  Step e of a group of 8 takes contraction 4 hf + e.
+//
+// What bounds it: the fp32 matrix rate, 64 flops per clock and SIMD (157 TFLOP/s at 2.4 GHz), for large products; for small ones the
+// latency of the slice loads and of the 64-cycle MFMAs that follow each other in one wavefront, hence the split of K
+// inside the workgroup.  Against 64 x 64 tiles in vector code with one element per load
+// (gemm_generic.hip): 4096 x 8192 x 512 780 us (44 TFLOP/s) to 307 (112); 1024 x 256 x 1024 163 to 10.4; 256 x 192 x 64 13 to 4.8;
+// error against float64 the same or smaller (shares of K are shorter sums).
+#include "common.h"
+#include "gelu.h"
+#include <atomic>
+
+namespace als {
+
+namespace {
+
+struct __attribute__((packed, aligned(4))) f32x4u { f32x4 v; };   // 16 bytes at any element address
+
+template <int BM, int BN, int BK, int WM, int WN, int WK, int AL, int BL>
+struct F32Tile {
+  static constexpr int NT = 64 * WM * WN * WK;
+  static constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+  static constexpr int A_PITCH = AL == 0 ? BK + 4 : BM + 8, B_PITCH = BL == 1 ? BK + 4 : BN + 8;   // floats
+  static constexpr int A_SIZE = A_PITCH * (AL == 0 ? BM : BK), B_SIZE = B_PITCH * (BL == 1 ? BN : BK);
+  static constexpr int STAGE = A_SIZE + B_SIZE;
+  static constexpr int RED = WK > 1 ? WK * BM * BN : 0;   // partial tiles of the K shares
+  static constexpr int LDS_BYTES = 4 * (2 * STAGE > RED ? 2 * STAGE : RED);
+  static constexpr int NA = BM * BK / 4 / NT, NB = BN * BK / 4 / NT;   // 16-byte chunks per thread
+  static_assert(NA * 4 * NT == BM * BK && NB * 4 * NT == BN * BK && BK % (8 * WK) == 0, "whole chunks and groups");
+};
+
+// One operand's tile: chunk c covers tile row c / (LEN/4), 4 elements from 4 (c % (LEN/4)); LEN is the contiguous direction.
+// lim_row, lim_col: how many rows and contiguous elements exist from the tile's origin on.
+template <int LEN, int N, int NT>
+__device__ __forceinline__ void load_chunks(f32x4 (&r)[N], const float* origin, int64_t ld, int lim_row, int lim_col, bool whole) {
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int i = 0; i < N; i++) {
+    const int c = tid + i * NT, row = c / (LEN / 4), col = c % (LEN / 4) * 4;
+    const float* p = origin + row * ld + col;
+    if (whole) {
+      r[i] = reinterpret_cast<const f32x4u*>(p)->v;
+    } else {
+      f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+        if (row < lim_row && col + e < lim_col) x[e] = p[e];
+      r[i] = x;
+    }
+  }
+}
+template <int LEN, int PITCH, int N, int NT>
+__device__ __forceinline__ void store_chunks(const f32x4 (&r)[N], float* lds) {
+#pragma unroll
+  for (int i = 0; i < N; i++) {
+    const int c = threadIdx.x + i * NT;
+    *reinterpret_cast<f32x4*>(lds + c / (LEN / 4) * PITCH + c % (LEN / 4) * 4) = r[i];
+  }
+}
+
+__device__ __forceinline__ void f32_epilogue(const GemmDesc& g, int m, int n, float x) {
+  if (m >= g.M || n >= g.N) return;
+  const int64_t ci = (int64_t)m * g.ldc + n;
+  if (g.epi == EPI_RESID) x += g.R[(int64_t)m * g.ldr + n];
+  if (g.epi == EPI_DGELU) x *= reinterpret_cast<const float*>(g.U)[ci];
+  if (g.epi == EPI_GELU) {
+    reinterpret_cast<float*>(g.C2)[ci] = gelu_tanh_f(x);
+    x = gelu_tanh_grad_f(x);
+  }
+  reinterpret_cast<float*>(g.C)[ci] = x;
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int WK, int AL, int BL>
+__global__ __launch_bounds__(64 * WM * WN * WK, 2) void gemm_f32_kernel(GemmDesc g, int tiles_n) {
+  typedef F32Tile<BM, BN, BK, WM, WN, WK, AL, BL> TL;
+  constexpr int TM = TL::TM, TN = TL::TN, NG = BK / 8 / WK;   // groups of 8 of one wavefront per slice
+  extern __shared__ __attribute__((aligned(16))) float lds_f32[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, hf = lane >> 5, lr = lane & 31;
+  const int wk = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
+  // every XCD gets a contiguous run of tiles (columns fastest): neighbours share operand panels in its L2
+  const int ntiles = gridDim.x, per = ntiles / 8, id = blockIdx.x;
+  const int tile = id < per * 8 ? (id % 8) * per + id / 8 : id;
+  const int m0 = tile / tiles_n * BM, n0 = tile % tiles_n * BN;
+  const float* A = reinterpret_cast<const float*>(g.A) + (AL == 0 ? m0 * g.lda : (int64_t)m0);
+  const float* B = reinterpret_cast<const float*>(g.B) + (BL == 1 ? n0 * g.ldb : (int64_t)n0);
+  const int lim_m = g.M - m0, lim_n = g.N - n0;
+  const bool whole_mn = lim_m >= BM && lim_n >= BN;
+
+  f32x4 ra[2][TL::NA], rb[2][TL::NB];
+  auto load = [&](int k0, f32x4 (&a)[TL::NA], f32x4 (&b)[TL::NB]) {
+    const int lim_k = g.K - k0;
+    const bool whole = whole_mn && lim_k >= BK;   // uniform
+    if constexpr (AL == 0) load_chunks<BK, TL::NA, TL::NT>(a, A + k0, g.lda, lim_m, lim_k, whole);
+    else load_chunks<BM, TL::NA, TL::NT>(a, A + (int64_t)k0 * g.lda, g.lda, lim_k, lim_m, whole);
+    if constexpr (BL == 1) load_chunks<BK, TL::NB, TL::NT>(b, B + k0, g.ldb, lim_n, lim_k, whole);
+    else load_chunks<BN, TL::NB, TL::NT>(b, B + (int64_t)k0 * g.ldb, g.ldb, lim_k, lim_n, whole);
+  };
+  auto store = [&](float* s, const f32x4 (&a)[TL::NA], const f32x4 (&b)[TL::NB]) {
+    store_chunks<(AL == 0 ? BK : BM), TL::A_PITCH, TL::NA, TL::NT>(a, s);
+    store_chunks<(BL == 1 ? BK : BN), TL::B_PITCH, TL::NB, TL::NT>(b, s + TL::A_SIZE);
+  };
+
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) acc[i][j][v] = 0.0f;
+  auto compute = [&](const float* s) {
+    const float* As = s + (AL == 0 ? (wm * TM * 32 + lr) * TL::A_PITCH + 4 * hf : 4 * hf * TL::A_PITCH + wm * TM * 32 + lr);
+    const float* Bs = s + TL::A_SIZE + (BL == 1 ? (wn * TN * 32 + lr) * TL::B_PITCH + 4 * hf : 4 * hf * TL::B_PITCH + wn * TN * 32 + lr);
+#pragma unroll
+    for (int q = 0; q < NG; q++) {
+      const int k = (wk * NG + q) * 8;
+      f32x4 a[TM], b[TN];
+#pragma unroll
+      for (int i = 0; i < TM; i++) {
+        if constexpr (AL == 0) a[i] = *reinterpret_cast<const f32x4*>(As + i * 32 * TL::A_PITCH + k);
+        else
+#pragma unroll
+          for (int e = 0; e < 4; e++) a[i][e] = As[(k + e) * TL::A_PITCH + i * 32];
+      }
+#pragma unroll
+      for (int j = 0; j < TN; j++) {
+        if constexpr (BL == 1) b[j] = *reinterpret_cast<const f32x4*>(Bs + j * 32 * TL::B_PITCH + k);
+        else
+#pragma unroll
+          for (int e = 0; e < 4; e++) b[j][e] = Bs[(k + e) * TL::B_PITCH + j * 32];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+          for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
+    }
+  };
+
+  const int nk = (g.K + BK - 1) / BK;
+  float* s0 = lds_f32;
+  float* s1 = lds_f32 + TL::STAGE;
+  load(0, ra[0], rb[0]);
+  if (nk > 1) load(BK, ra[1], rb[1]);
+  store(s0, ra[0], rb[0]);
+  __syncthreads();
+  // slice kt is in s0 (s1), slice kt + 1 in registers, slice kt + 2 is requested
+  for (int kt = 0; kt < nk; kt += 2) {
+    if (kt + 2 < nk) load((kt + 2) * BK, ra[0], rb[0]);
+    compute(s0);
+    if (kt + 1 < nk) store(s1, ra[1], rb[1]);
+    __syncthreads();
+    if (kt + 1 < nk) {
+      if (kt + 3 < nk) load((kt + 3) * BK, ra[1], rb[1]);
+      compute(s1);
+      if (kt + 2 < nk) store(s0, ra[0], rb[0]);
+      __syncthreads();
+    }
+  }
+
+  if constexpr (WK == 1) {
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int j = 0; j < TN; j++)
+#pragma unroll
+        for (int v = 0; v < 16; v++)
+          f32_epilogue(g, m0 + (wm * TM + i) * 32 + 8 * (v >> 2) + 4 * hf + (v & 3), n0 + (wn * TN + j) * 32 + lr, acc[i][j][v]);
+  } else {
+    float* part = lds_f32 + wk * BM * BN + wm * TM * 32 * BN + wn * TN * 32 + lr;
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int j = 0; j < TN; j++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) part[(i * 32 + 8 * (v >> 2) + 4 * hf + (v & 3)) * BN + j * 32] = acc[i][j][v];
+    __syncthreads();
+    for (int e = threadIdx.x; e < BM * BN; e += TL::NT) {
+      float x = lds_f32[e];
+#pragma unroll
+      for (int s = 1; s < WK; s++) x += lds_f32[s * BM * BN + e];
+      f32_epilogue(g, m0 + e / BN, n0 + e % BN, x);
+    }
+  }
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int WK, int AL, int BL>
+int launch_f32(const GemmDesc& g, hipStream_t st) {
+  typedef F32Tile<BM, BN, BK, WM, WN, WK, AL, BL> TL;
+  auto kern = gemm_f32_kernel<BM, BN, BK, WM, WN, WK, AL, BL>;
+  if (TL::LDS_BYTES > 65536) {
+    static std::atomic<bool> attr_set{false};  // the call is idempotent: a race only repeats it
+    if (!attr_set.load(std::memory_order_acquire)) {
+      ALS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES));
+      attr_set.store(true, std::memory_order_release);
+    }
+  }
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+  hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(TL::NT), TL::LDS_BYTES, st, g, tiles_n);
+  ALS_CHECK_LAUNCH();
+  return ALS_OK;
+}
+
+inline int64_t tiles(const GemmDesc& g, int bm, int bn) { return (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); }
+
+template <int AL, int BL>
+int pick(const GemmDesc& g, hipStream_t st) {
+  // The largest tile that still gives (almost) every CU a workgroup: a larger tile moves fewer operand bytes per flop, an idle CU
+  // costs its whole rate.  In us, 128 x 128 / 64 x 64 / 32 x 32 with 8 K shares / with 4:
+  //   4096 x 8192 x 512 (2048, 8192 tiles): 307 / 347 / 478 / 420     2048 x 1536 x 512 (192, 768): 48 / 39 / 49 / 44
+  //   1024 x 1024 x 256 (64, 256): 26 / 9.9 / 12 / 10                 256 x 2000 x 1024 (32, 128): 127 / 43 / 26 / 31
+  //   512 x 512 x 512 (16, 64): 44 / 14 / 6.6 / 7.6                   1024 x 256 x 256 (16, 64): 28 / 8.6 / 5.7 / 5.5
+  if (tiles(g, 128, 128) >= 256) return launch_f32<128, 128, 32, 2, 2, 1, AL, BL>(g, st);
+  if (tiles(g, 64, 64) >= 192) return launch_f32<64, 64, 64, 2, 2, 2, AL, BL>(g, st);
+  if (g.K >= 512) return launch_f32<32, 32, 128, 1, 1, 8, AL, BL>(g, st);
+  return launch_f32<32, 32, 64, 1, 1, 4, AL, BL>(g, st);
+}
+
+}  // namespace
+
+bool gemm_mfma_f32_supported(const GemmDesc& g) {
+  if (g.in_bf16 || g.c_bf16 || (g.a_layout | g.b_layout) & ~1) return false;
+  return tiles(g, 32, 32) < (1 << 22);   // blocks of up to 512 threads in one grid dimension
+}
+
+int gemm_mfma_f32(const GemmDesc& g, hipStream_t st) {
+  if (g.a_layout == 0) return g.b_layout == 0 ? pick<0, 0>(g, st) : pick<0, 1>(g, st);
+  return g.b_layout == 0 ? pick<1, 0>(g, st) : pick<1, 1>(g, st);
+}
+
+}  // namespace als

@@ -48,6 +48,32 @@ def test_token_order_of_the_embedding_gradient(V, B, S):
     assert _rel(lm.views(g, w)["E"], lm.views(rg, w)["E"]) < 1e-5
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (33, 31, 63), (32, 65, 65), (31, 33, 513), (40, 96, 640),   # 32 x 32 tiles: 4 and 8 shares of K
+                                   (769, 1025, 65), (832, 960, 128),                # 64 x 64
+                                   (2047, 2049, 33), (2048, 2048, 96)])             # 128 x 128, the least number of tiles
+@pytest.mark.parametrize("al,bl", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_fp32_products(M, N, K, al, bl):
+    """Every layout and epilogue at ragged and whole sizes, from operands that are not 16-byte aligned.  A sum of K fp32
+    products in any order is off by at most K 2^-24 sum |a b|; the epilogue adds a few roundings."""
+    gen = torch.Generator(device=DEV).manual_seed(M + N + K)
+    r = lambda *s: torch.randn(*s, device=DEV, generator=gen)
+    odd = lambda x: torch.cat([x.new_zeros(1), x.flatten()])[1:].view(x.shape)   # one element off the alignment
+    a, b, res, u = r(M, K), r(K, N), r(M, N), r(M, N)
+    ad, bd = odd(a if al == 0 else a.t().contiguous()), odd(b if bl == 0 else b.t().contiguous())
+    ref, bound = a.double() @ b.double(), (K + 4) * 2.0 ** -24 * (a.abs().double() @ b.abs().double()) + 1e-7
+    for epi, want, scale in ((0, ref, 1.0), (1, ref + res.double(), 1.0), (3, ref * u.double(), u.double().abs())):
+        c = torch.full((M, N), float("nan"), device=DEV)
+        A.k_gemm_ex(ad, bd, c, M, N, K, al, bl, epi=epi, R=res if epi == 1 else None, U=u if epi == 3 else None)
+        assert ((c.double() - want).abs() <= bound * scale + 2.0 ** -22 * want.abs()).all(), epi
+    c, c2 = torch.full((M, N), float("nan"), device=DEV), torch.full((M, N), float("nan"), device=DEV)
+    A.k_gemm_ex(ad, bd, c, M, N, K, al, bl, epi=2, C2=c2)
+    x = ref.requires_grad_()
+    y = torch.nn.functional.gelu(x, approximate="tanh")
+    y.sum().backward()
+    assert ((c2.double() - y.detach()).abs() <= 1.2 * bound + 1e-6 * (1 + y.detach().abs())).all()
+    assert ((c.double() - x.grad).abs() <= 1.2 * bound + 1e-5).all()
+
+
 @pytest.mark.parametrize("B,S,h,dh", [(33, 1, 2, 32), (33, 16, 2, 64), (33, 17, 2, 32),   # one tile, one and one row
                                       (1, 33, 1, 64), (1, 63, 1, 32), (2, 129, 3, 64),     # last tile of 1, 15, 1 rows; idle wavefronts
                                       (16, 272, 16, 32), (9, 1009, 8, 64),                 # two row blocks per wavefront
