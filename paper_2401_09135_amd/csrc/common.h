@@ -65,6 +65,9 @@ bool gemm_mfma_f32_supported(const GemmDesc& g);
 int gemm_mfma_f32(const GemmDesc& g, hipStream_t st);
 bool gemm_mfma_supported(const GemmDesc& g);
 int gemm_mfma(const GemmDesc& g, hipStream_t st);
+// bf16 operands, any shape and alignment (gemm_mfma_any.hip); X Y, X Y^T and X^T Y
+bool gemm_mfma_any_supported(const GemmDesc& g);
+int gemm_mfma_any(const GemmDesc& g, hipStream_t st);
 // picks the MFMA kernel when allowed and supported
 int gemm(const GemmDesc& g, bool allow_mfma, hipStream_t st);
 

@@ -102,6 +102,7 @@ int gemm_generic(const GemmDesc& g, hipStream_t st) {
 
 int gemm(const GemmDesc& g, bool allow_mfma, hipStream_t st) {
   if (allow_mfma && gemm_mfma_supported(g)) return gemm_mfma(g, st);
+  if (allow_mfma && gemm_mfma_any_supported(g)) return gemm_mfma_any(g, st);
   return gemm_generic(g, st);
 }
 

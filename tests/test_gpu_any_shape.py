@@ -74,6 +74,68 @@ def test_fp32_products(M, N, K, al, bl):
     assert ((c.double() - x.grad).abs() <= 1.2 * bound + 1e-5).all()
 
 
+@pytest.mark.parametrize("M,N,K", [(128, 128, 512), (512, 256, 1024), (128, 384, 576),   # 32 x 32 tiles, whole slices and a last one of 64
+                                   (1024, 896, 896), (640, 640, 640),               # 64 x 64
+                                   (8192, 256, 512),                                # 128 x 64
+                                   (512, 512, 448), (2048, 1280, 512),              # 128 x 128 kernels on both sides of the rule
+                                   (2048, 2048, 64), (2304, 1792, 64)])             # 64 and 63 tiles of 256 x 256
+@pytest.mark.parametrize("al,bl,epi", [(0, 0, 0), (0, 0, 1), (0, 0, 2), (0, 1, 0), (0, 1, 3), (1, 0, 0)])
+def test_small_aligned_bf16_products(M, N, K, al, bl, epi):
+    """Where the kernel is chosen by the number of tiles: fp32 results within K 2^-24 sum |a b| of float64, bf16 ones
+    within one rounding (2^-9) more."""
+    gen = torch.Generator(device=DEV).manual_seed(M + N + K)
+    r = lambda *s: torch.randn(*s, device=DEV, generator=gen)
+    a, b, res, u = r(M, K).bfloat16(), r(K, N).bfloat16(), r(M, N), r(M, N).bfloat16()
+    ad, bd = a if al == 0 else a.t().contiguous(), b if bl == 0 else b.t().contiguous()
+    out = torch.bfloat16 if epi >= 2 else torch.float32
+    c, c2 = (torch.full((M, N), float("nan"), dtype=out, device=DEV) for _ in range(2))
+    ws = torch.empty(2 * M * N, device=DEV)
+    A.k_gemm_ex(ad, bd, c, M, N, K, al, bl, use_mfma=True, epi=epi, R=res if epi == 1 else None, C2=c2 if epi == 2 else None,
+                U=u if epi == 3 else None, ws=ws)
+    ref, bound = a.double() @ b.double(), (K + 4) * 2.0 ** -24 * (a.abs().double() @ b.abs().double()) + 1e-6
+    if epi == 2:
+        x = ref.requires_grad_()
+        y = torch.nn.functional.gelu(x, approximate="tanh")
+        y.sum().backward()
+        assert ((c2.double() - y.detach()).abs() <= 1.2 * bound + 2.0 ** -8 * y.detach().abs()).all()
+        assert ((c.double() - x.grad).abs() <= 1.2 * bound + 1e-5 + 2.0 ** -8 * x.grad.abs()).all()
+    else:
+        want, scale = (ref + res.double(), 1.0) if epi == 1 else (ref * u.double(), u.double().abs()) if epi == 3 else (ref, 1.0)
+        assert ((c.double() - want).abs() <= bound * scale + (2.0 ** -8 if epi == 3 else 2.0 ** -22) * want.abs()).all()
+
+
+@pytest.mark.parametrize("M,N,K", [(256, 256, 2112), (1024, 896, 8192), (8192, 256, 4160)])
+def test_input_gradient_split_along_k(M, N, K):
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    a, b = torch.randn(M, K, device=DEV, generator=gen).bfloat16(), torch.randn(N, K, device=DEV, generator=gen).bfloat16()
+    for size in (2, 3, 16):   # as many partials as the workspace holds
+        c = torch.full((M, N), float("nan"), device=DEV)
+        A.k_gemm(a, b, c, M, N, K, 0, 1, use_mfma=True, ws=torch.empty(size * M * N, device=DEV))
+        bound = (K + 4) * 2.0 ** -24 * (a.abs().double() @ b.abs().double().t())
+        assert ((c.double() - a.double() @ b.double().t()).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("kw", [dict(d=64, h=1, ff=192, V=201, S=33, B=3),          # nothing is a multiple of 128
+                                dict(d=320, h=5, ff=1280, V=5003, S=200, B=3),
+                                dict(d=128, h=2, ff=128, V=255, S=64, B=2),         # aligned blocks, a ragged head
+                                dict(d=128, h=2, ff=128, V=256, S=65, B=1),         # ragged blocks, an aligned head
+                                dict(d=64, h=1, ff=64, V=2050, S=683, B=3)])        # 17 x 17 tiles of 128 x 128 in the head
+def test_ragged_bf16_models_match_the_generic_products(kw):
+    """The same bf16 operands and roundings in both modes, other orders of fp32 sums: results differ by bf16 roundings that
+    fall the other way (2^-9 each, a random few per sum), an order below the distance of either from fp32 (1e-2)."""
+    w = _model(**kw)
+    w["dtype"] = "bf16"
+    tok = I.TokenStream(1, 0, w["B"], w["S"], w["V"]).take(1)[0]
+    theta0, loss, g = _loss_grad(w, tok)
+    _, gloss, gg = _loss_grad(w, tok, flags=1)
+    assert abs(loss - gloss) < 2e-4 * abs(gloss)
+    a, b = lm.views(g, w), lm.views(gg, w)
+    for name in a:
+        assert _rel(a[name], b[name]) < 5e-3, name
+    _, rg = lm.loss_and_grad(theta0, tok, w)
+    assert _rel(g, rg) < 1.1 * _rel(gg, rg)
+
+
 @pytest.mark.parametrize("B,S,h,dh", [(33, 1, 2, 32), (33, 16, 2, 64), (33, 17, 2, 32),   # one tile, one and one row
                                       (1, 33, 1, 64), (1, 63, 1, 32), (2, 129, 3, 64),     # last tile of 1, 15, 1 rows; idle wavefronts
                                       (16, 272, 16, 32), (9, 1009, 8, 64),                 # two row blocks per wavefront
