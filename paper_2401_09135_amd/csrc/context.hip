@@ -24,6 +24,7 @@ struct Worker {
   float* losses_dev; float* losses_host;
   int32_t *sort_offset, *sort_rank, *sort_pos;
   float* splitk_ws; size_t splitk_bytes;
+  float* head_ws; size_t head_ws_bytes;   // split-K scratch of the output matrix's input gradient
   // Output gradients that the weight-gradient products read (dY), per layer: of the block output
   // (for W2), of the FFN pre-activation (W1), of the attention block output (Wo), of q/k/v (Wqkv).
   // With the grouped launch every layer keeps its own until the end of the backward pass; otherwise
@@ -112,11 +113,16 @@ void carve(als_ctx* c, Carver& cv) {
     w.dy2.assign(L, w.dx_lp); w.dy1.assign(L, w.dff); w.dyo.assign(L, w.dx_lp); w.dyqkv.assign(L, w.dqkv);
     w.dw_probs_dev = nullptr; w.dw_items_dev = nullptr; w.dw_split_dev = nullptr; w.dw_partial = nullptr;
     w.dw_plan = DwPlan{0, 0, 0, 0.0};
+    w.head_ws = w.splitk_ws; w.head_ws_bytes = w.splitk_bytes;
     if (c->grouped_dw) {
       for (int l = 0; l < L; l++) {
         w.dy2[l] = cv.act(T * d, bf); w.dy1[l] = cv.act(T * ff, bf); w.dyo[l] = cv.act(T * d, bf);
         w.dyqkv[l] = cv.act(T * 3 * da, bf);
       }
+      // The input gradient of the output matrix runs before anything is written to these: until then they are its
+      // split-K scratch, one block from the first to the last.
+      w.head_ws = (float*)w.dy2[0];
+      w.head_ws_bytes = (size_t)((char*)w.dyqkv[L - 1] - (char*)w.dy2[0]) + (size_t)T * 3 * da * 2;
       // the products, in the order of the flat parameter layout (pointers are null while only counting)
       w.dw_probs.clear();
       int n_tiles = 0;
@@ -213,7 +219,9 @@ int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot) {
   int nl = g.n_layers;
   // output matrix and final norm
   RUN(gemm(desc_dw(c, w, w.xf, d, w.dlogits, V, d, V, T, w.grad + L.Wout), mf, st));
-  RUN(gemm(desc(c, w.dlogits, 0, V, wptr(c, w, L.Wout), 1, V, T, d, V, w.dtmp, d, false), mf, st));
+  GemmDesc dxf = desc(c, w.dlogits, 0, V, wptr(c, w, L.Wout), 1, V, T, d, V, w.dtmp, d, false);
+  dxf.ws = w.head_ws; dxf.ws_bytes = w.head_ws_bytes;
+  RUN(gemm(dxf, mf, st));
   // the norms leave their gain-gradient partials; one kernel adds all of them after the last layer
   const int64_t pset = (int64_t)rmsnorm_bwd_blocks(T) * d;
   RUN(rmsnorm_bwd(w.dtmp, w.x[nl], w.rstdf, w.theta + L.gf, nullptr, w.dxa, nl ? w.dy2[nl - 1] : w.dx_lp, c->bf,

@@ -413,6 +413,7 @@ static int dispatch(const GemmDesc& g, const MfmaArgs& a, int bm, int bn, int nb
   if (g.a_layout == 0 && g.b_layout == 1) {
     if (g.epi == EPI_DGELU) ALS_TILE_SWITCH(0, 1, EPI_DGELU, bf16, false);
     if (g.c_bf16) ALS_TILE_SWITCH(0, 1, EPI_STORE, bf16, false);
+    if (nsplit > 1) return nbuf == 5 ? launch_ppd<0, 1, EPI_STORE, float, true>(a, nsplit, st) : launch_pp<0, 1, EPI_STORE, float, true>(a, nsplit, st);
     ALS_TILE_SWITCH(0, 1, EPI_STORE, float, false);
   }
   if (nsplit > 1) ALS_TILE_SWITCH(1, 0, EPI_STORE, float, true);
@@ -441,7 +442,19 @@ int gemm_mfma(const GemmDesc& g, hipStream_t st) {
   // microbenchmark and equal or slightly slower inside a step; the register-staged form is the
   // default.
   int bm = 128, bn = 128, nbuf = 1;
-  const bool pp_pays = g.M >= 256 && g.N >= 256;
+  bool pp_pays = g.M >= 256 && g.N >= 256;
+  const bool splittable = g.epi == EPI_STORE && !g.c_bf16 && g.ldc == g.N && g.a_layout + g.b_layout == 1 && g.ws &&
+                          g.ws_bytes >= (size_t)g.M * g.N * 8;
+  // Fewer than 64 tiles of 256 x 256: four streams of such products leave CUs idle, and one fills an eighth of the chip
+  // (64 and more: see above).  A long contraction is split along K below (8192 x 256 x 32000, dY W^T: 576 us to 112).  Else the smaller tiles, and for K >= 512 and too few 128 x 128
+  // tiles the kernels whose wavefronts share K.  In us, 256 x 256 / 128 x 128 / those (gemm_mfma_any.hip):
+  //   512 x 256 x 1024: 24 / 14 / 5.8     8192 x 256 x 1024: 24 / 14 / 12      1024 x 896 x 896: 22 / 12 / 8.5
+  //   1024 x 2688 x 896: 22 / 14.5 / 22   1024 x 3584 x 896: 22 / 15 / 23      2048 x 1024 x 256: 11 / 6.4 / 7.6
+  const int64_t tiles256 = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256);
+  if (!g_force_bm && !g_force_nbuf && tiles256 < 64 && !(splittable && g.K > 2048)) {
+    if (g.K >= 512 && (int64_t)(g.M / 128) * (g.N / 128) < 160) return gemm_mfma_any(g, st);
+    pp_pays = false;
+  }
   if (g_force_bm && g_force_nbuf == 4) { bm = 256; bn = 256; nbuf = 4; }
   else if (g_force_bm && g_force_nbuf == 5) { bm = 256; bn = 256; nbuf = 5; }
   else if (g_force_bm && fits(g.M, g.N, g_force_bm, g_force_bn)) { bm = g_force_bm; bn = g_force_bn; nbuf = g_force_nbuf; }
@@ -458,8 +471,8 @@ int gemm_mfma(const GemmDesc& g, hipStream_t st) {
   a.C = g.C; a.ldc = g.ldc; a.R = g.R; a.ldr = g.ldr; a.C2 = g.C2; a.U = (const bf16*)g.U;
   a.split_stride = 0; a.nsplit = 1;
   int nsplit = 1;
-  if (g.a_layout == 1 && g.b_layout == 0 && g.ldc == g.N) {
-    // Weight-gradient shape: few tiles, long K.  K is split so that the grid fills the chip in
+  if ((g.a_layout == 1 && g.b_layout == 0 && g.ldc == g.N) || (splittable && tiles256 < 64 && bn == 256 && (nbuf == 4 || nbuf == 5))) {
+    // Few tiles, long K: weight gradients, and the input gradient of the output matrix (K = vocabulary).  K is split so that the grid fills the chip in
     // whole rounds of its resident workgroups (2 per CU for the double-buffered 128x128 variant
     // and for 256x128, 3 per CU for the single-buffered 128x128 one).  Candidates are costed in
     // microseconds with measured rates: the product at 700 TFLOP/s times the round-up loss of
