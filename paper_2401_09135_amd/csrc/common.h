@@ -58,6 +58,7 @@ struct GemmDesc {
   void* C2;                          // EPI_GELU second output (same type/ld as C)
   const void* U;                     // EPI_DGELU saved derivative (operand type, ld = ldc)
   float* ws; size_t ws_bytes;        // scratch for split-K partials (may be null)
+  int workers;                       // how many workers run such products side by side (0: one)
 };
 int gemm_generic(const GemmDesc& g, hipStream_t st);
 // fp32 operands and results on the fp32 matrix instruction (gemm_mfma_f32.hip): any shape, layout and epilogue
@@ -68,6 +69,8 @@ int gemm_mfma(const GemmDesc& g, hipStream_t st);
 // bf16 operands, any shape and alignment (gemm_mfma_any.hip); X Y, X Y^T and X^T Y
 bool gemm_mfma_any_supported(const GemmDesc& g);
 int gemm_mfma_any(const GemmDesc& g, hipStream_t st);
+// what gemm_mfma_supported takes with a_layout 0, in tiles of 128 x 128 or 64 x 64 with deep prefetch (gemm_mfma_deep.hip)
+int gemm_mfma_deep(const GemmDesc& g, int tile, hipStream_t st);
 // picks the MFMA kernel when allowed and supported
 int gemm(const GemmDesc& g, bool allow_mfma, hipStream_t st);
 

@@ -445,15 +445,27 @@ int gemm_mfma(const GemmDesc& g, hipStream_t st) {
   bool pp_pays = g.M >= 256 && g.N >= 256;
   const bool splittable = g.epi == EPI_STORE && !g.c_bf16 && g.ldc == g.N && g.a_layout + g.b_layout == 1 && g.ws &&
                           g.ws_bytes >= (size_t)g.M * g.N * 8;
-  // Fewer than 64 tiles of 256 x 256: four streams of such products leave CUs idle, and one fills an eighth of the chip
-  // (64 and more: see above).  A long contraction is split along K below (8192 x 256 x 32000, dY W^T: 576 us to 112).  Else the smaller tiles, and for K >= 512 and too few 128 x 128
-  // tiles the kernels whose wavefronts share K.  In us, 256 x 256 / 128 x 128 / those (gemm_mfma_any.hip):
-  //   512 x 256 x 1024: 24 / 14 / 5.8     8192 x 256 x 1024: 24 / 14 / 12      1024 x 896 x 896: 22 / 12 / 8.5
-  //   1024 x 2688 x 896: 22 / 14.5 / 22   1024 x 3584 x 896: 22 / 15 / 23      2048 x 1024 x 256: 11 / 6.4 / 7.6
-  const int64_t tiles256 = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256);
-  if (!g_force_bm && !g_force_nbuf && tiles256 < 64 && !(splittable && g.K > 2048)) {
-    if (g.K >= 512 && (int64_t)(g.M / 128) * (g.N / 128) < 160) return gemm_mfma_any(g, st);
-    pp_pays = false;
+  const int64_t tiles256 = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256), tiles128 = (int64_t)(g.M / 128) * (g.N / 128);
+  if (!g_force_bm && !g_force_nbuf && !(splittable && tiles256 < 64 && g.K > 2048)) {   // (that one is split along K below)
+    // At most a round of 128 x 128 tiles: 256 x 256 ones leave three quarters of the chip idle.  With 64 and more of them that
+    // is right only while no other workers fill it: per CU they do twice the work (rounds with T = 8192, d = 512
+    // of 1 / 2 / 4 workers: 3161 / 4777 / 8484 us with them, 2678 / 4656 / 8927 without; the number of workers and not of streams, so
+    // that the results do not depend on the streams).  Below 160 tiles of 128 x 128, tiles of 64 x 64; for a few of those and a long
+    // K, the kernels whose wavefronts share K.  In us, kernels before / deep 128 x 128 / deep 64 x 64:
+    //   8192 x 512 x 2048: 47 / 25 / 35 (256 x 256)         4096 x 896 x 3584: 74 / 36 / 50 (256 x 256)
+    //   1024 x 2688 x 896: 13.8 / 13.1 / 14.5 (128 x 128)   1024 x 3584 x 896, dY W^T: 15.5 / 12.9 / 19.5 (128 x 128)
+    //   1024 x 896 x 3584: 26 / 30 / 17 (shared K)          8192 x 256 x 1024: 14.3 / 13.4 / 10.7 (shared K)
+    //   2048 x 256 x 256: 7.0 / 6.5 / 4.4 (128 x 128)       512 x 256 x 1024: 5.7 / 11.7 / 7.7 (shared K)
+    // (its loads have 32-bit offsets inside a tile)
+    if (g.a_layout == 0 && tiles128 <= 256 && (tiles256 < 64 || tiles256 * g.workers <= 128) && g.lda < 1 << 24 && g.ldb < 1 << 24) {
+      if (tiles128 >= 160) return gemm_mfma_deep(g, 128, st);
+      if (tiles128 > 16 || g.K < 512) return gemm_mfma_deep(g, 64, st);
+      return gemm_mfma_any(g, st);
+    }
+    if (tiles256 < 64) {   // X^T dY
+      if (g.K >= 512 && tiles128 < 160) return gemm_mfma_any(g, st);
+      pp_pays = false;
+    }
   }
   if (g_force_bm && g_force_nbuf == 4) { bm = 256; bn = 256; nbuf = 4; }
   else if (g_force_bm && g_force_nbuf == 5) { bm = 256; bn = 256; nbuf = 5; }

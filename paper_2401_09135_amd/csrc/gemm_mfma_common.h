@@ -74,7 +74,7 @@ struct MfmaArgs {
 // 8 % slower on the whole step.)  Outputs are written with non-temporal stores: a round of tiles
 // writes 32-64 MB at once, as much as all L2s hold, and no tile reads them back (3-5 % on the
 // products with short K, one product at a time).
-template <int TM, int TN, int WN, int EPI, typename TO>
+template <int TM, int TN, int WN, int EPI, typename TO, bool NONTEMPORAL = true>
 struct WaveEpilogue {
   static constexpr int PITCH = WN * 4 + 16;  // rows 4 banks apart: 16-byte accesses of 16 rows, or of two row halves, never collide
   static constexpr int CPL = sizeof(TO) == 2 ? 8 : 4;  // consecutive columns per lane
@@ -93,6 +93,11 @@ struct WaveEpilogue {
   const int lane, row0, col0;
   __device__ __forceinline__ WaveEpilogue(const MfmaArgs& g_, int lane_, int row0_, int col0_)
       : g(g_), lane(lane_), row0(row0_), col0(col0_) {}
+  template <typename V>
+  static __device__ __forceinline__ void store16(V v, V* p) {
+    if constexpr (NONTEMPORAL) __builtin_nontemporal_store(v, p);
+    else *p = v;
+  }
   __device__ __forceinline__ void load_aux(int i) {
 #pragma unroll
     for (int pass = 0; pass < NPASS; pass++) {
@@ -147,7 +152,7 @@ struct WaveEpilogue {
         }
         if (sizeof(TO) == 4) {
           f32x4 o = {x[0], x[1], x[2], x[3]};
-          __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(reinterpret_cast<float*>(C) + ci));
+          store16(o, reinterpret_cast<f32x4*>(reinterpret_cast<float*>(C) + ci));
         } else {
           bf16x8 o;
           if (EPI == EPI_GELU) {  // C <- gelu'(acc), C2 <- gelu(acc)
@@ -159,12 +164,12 @@ struct WaveEpilogue {
               o[e & 7] = (bf16)grad;
               o2[e & 7] = (bf16)val;
             }
-            __builtin_nontemporal_store(__builtin_bit_cast(u32x4, o2), reinterpret_cast<u32x4*>(reinterpret_cast<bf16*>(g.C2) + ci));
+            store16(__builtin_bit_cast(u32x4, o2), reinterpret_cast<u32x4*>(reinterpret_cast<bf16*>(g.C2) + ci));
           } else {
 #pragma unroll
             for (int e = 0; e < CPL; e++) o[e & 7] = (bf16)x[e];
           }
-          __builtin_nontemporal_store(__builtin_bit_cast(u32x4, o), reinterpret_cast<u32x4*>(reinterpret_cast<bf16*>(C) + ci));
+          store16(__builtin_bit_cast(u32x4, o), reinterpret_cast<u32x4*>(reinterpret_cast<bf16*>(C) + ci));
         }
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // reads done before the next block overwrites

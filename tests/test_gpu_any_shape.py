@@ -104,6 +104,14 @@ def test_small_aligned_bf16_products(M, N, K, al, bl, epi):
         assert ((c.double() - want).abs() <= bound * scale + (2.0 ** -8 if epi == 3 else 2.0 ** -22) * want.abs()).all()
 
 
+@pytest.mark.parametrize("M,N,K", [(128, 128, 64), (256, 128, 256), (128, 256, 320), (256, 384, 448),   # 64 x 64 tiles: one slice, around the 5 in flight
+                                   (2048, 1152, 192), (384, 896, 832),                                  # the most of them; K beyond the kernels that share K
+                                   (2560, 1024, 192), (2560, 1024, 256), (1280, 2048, 320), (4096, 896, 448)])   # 128 x 128: around the 4 in flight
+@pytest.mark.parametrize("al,bl,epi", [(0, 0, 0), (0, 0, 1), (0, 0, 2), (0, 1, 0), (0, 1, 3)])
+def test_products_with_deep_prefetch(M, N, K, al, bl, epi):
+    test_small_aligned_bf16_products(M, N, K, al, bl, epi)
+
+
 @pytest.mark.parametrize("M,N,K", [(256, 256, 2112), (1024, 896, 8192), (8192, 256, 4160)])
 def test_input_gradient_split_along_k(M, N, K):
     gen = torch.Generator(device=DEV).manual_seed(K)
