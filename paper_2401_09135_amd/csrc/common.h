@@ -144,14 +144,13 @@ int rmsnorm_bwd(const float* dy, const float* x, const float* rstd, const float*
 // logits fp32 or bf16; dlogits may be the same buffer as the logits when the two types are equal
 int cross_entropy(const void* logits, int logits_bf16, const int32_t* tok, float* loss_row, void* dlogits,
                   int dl_bf16, int B, int S, int V, hipStream_t st);
-int mean_rows(const float* loss_row, float* out, int T, hipStream_t st);
 // Orders each step's input positions by token id (see elementwise.hip; rank is scratch); offset is
 // [n_steps][V+1], rank and pos are [n_steps][B*S].
 int embed_sort(const int32_t* tok, int n_steps, int B, int S, int V, int32_t* offset, int32_t* rank,
                int32_t* pos, hipStream_t st);
-// scratch: 2 * ceil(B*S / 32) * d floats (partial rows of position lists that cross 32-position chunks)
+// dE, dPpos and the mean loss; scratch: 2 * ceil(B*S / 32) * d floats (partial rows of position lists that cross 32-position chunks)
 int embed_bwd(const int32_t* tok, const int32_t* offset, const int32_t* pos, const float* dx, float* dE,
-              float* dPpos, float* scratch, int B, int S, int d, int V, hipStream_t st);
+              float* dPpos, float* scratch, const float* loss_row, float* loss_out, int B, int S, int d, int V, hipStream_t st);
 int cast_copy(const float* src, void* dst, int64_t n, int dst_bf16, hipStream_t st);
 
 struct AdamArgs {

@@ -172,7 +172,7 @@ inline const void* wptr(const als_ctx* c, const Worker& w, int64_t off) {
   return c->bf ? (const void*)(w.lp + off) : (const void*)(w.theta + off);
 }
 
-int forward(als_ctx* c, Worker& w, const int32_t* tok, float* loss_out) {
+int forward(als_ctx* c, Worker& w, const int32_t* tok) {
   const als_config& g = c->cfg;
   const Layout& L = c->L;
   hipStream_t st = w.stream;
@@ -204,11 +204,11 @@ int forward(als_ctx* c, Worker& w, const int32_t* tok, float* loss_out) {
   void* logits = c->bf ? w.dlogits : (void*)w.logits;
   RUN(gemm(desc(c, w.xf, 0, d, wptr(c, w, L.Wout), 0, V, T, V, d, logits, V, true), mf, st));
   RUN(cross_entropy(logits, c->bf, tok, w.loss_row, w.dlogits, c->bf, B, S, V, st));
-  RUN(mean_rows(w.loss_row, loss_out, T, st));
   return ALS_OK;
 }
 
-int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot) {
+// also writes the mean of the losses that forward() left per row
+int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot, float* loss_out) {
   const als_config& g = c->cfg;
   const Layout& L = c->L;
   hipStream_t st = w.stream;
@@ -256,7 +256,7 @@ int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot) {
   RUN(rmsnorm_dg_sum(w.partial, w.grad + L.g1[0], T, d, 2 * nl + 1, st));
   // w.dtmp (T x d floats) is free again here: scratch for the embedding gradient's chunk partials
   RUN(embed_bwd(tok, w.sort_offset + (int64_t)slot * (V + 1), w.sort_pos + (int64_t)slot * T, w.dxa,
-                w.grad + L.E, w.grad + L.Ppos, w.dtmp, B, S, d, V, st));
+                w.grad + L.E, w.grad + L.Ppos, w.dtmp, w.loss_row, loss_out, B, S, d, V, st));
   return ALS_OK;
 }
 
@@ -376,8 +376,8 @@ extern "C" int als_worker_local_steps(als_ctx* ctx, int worker, int n_steps, con
   RUN(embed_sort(tokens, n_steps, g.batch, g.seq_len, g.vocab, w.sort_offset, w.sort_rank, w.sort_pos, w.stream));
   for (int s = 0; s < n_steps; s++) {
     const int32_t* tok = tokens + (int64_t)s * per;
-    RUN(forward(ctx, w, tok, w.losses_dev + s));
-    RUN(backward(ctx, w, tok, s));
+    RUN(forward(ctx, w, tok));
+    RUN(backward(ctx, w, tok, s, w.losses_dev + s));
     w.adam_n += 1;
     AdamArgs a;
     a.lr = lr_host[s];
@@ -406,8 +406,8 @@ extern "C" int als_worker_loss_grad(als_ctx* ctx, int worker, const int32_t* tok
   ALS_HIP(hipStreamWaitEvent(w.stream, w.ready_ev, 0));
   RUN(embed_sort(tokens, 1, ctx->cfg.batch, ctx->cfg.seq_len, ctx->cfg.vocab, w.sort_offset, w.sort_rank,
                  w.sort_pos, w.stream));
-  RUN(forward(ctx, w, tokens, w.losses_dev));
-  RUN(backward(ctx, w, tokens, 0));
+  RUN(forward(ctx, w, tokens));
+  RUN(backward(ctx, w, tokens, 0, w.losses_dev));
   ALS_HIP(hipMemcpyAsync(w.losses_host, w.losses_dev, 4, hipMemcpyDeviceToHost, w.stream));
   ALS_HIP(hipEventRecord(w.done_ev, w.stream));
   ALS_HIP(hipStreamSynchronize(w.stream));

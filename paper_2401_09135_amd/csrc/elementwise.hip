@@ -427,7 +427,6 @@ int embed_fwd(const int32_t* tok, const float* E, const float* Ppos, float* x, i
 //     It depends on the tokens only, so one launch prepares every step of a local round.
 // (2) embed_bwd: a pass over 32-position chunks of that list and a pass over vocabulary rows
 //     (described at the kernels below).
-// dPpos[s,:] = sum_b dx[b,s,:] in batch order.
 //
 // The order is a least-significant-digit radix sort of the positions by token id (digits of at most
 // 8 bits: one pass for V <= 256, two for V <= 65536).  A tile of at most 16384 positions is ranked at a time:
@@ -630,30 +629,85 @@ int embed_sort(const int32_t* tok, int n_steps, int B, int S, int V, int32_t* of
 //   rows: one wavefront per vocabulary row: zeros for a token that does not occur, nothing for a
 //     list inside one chunk, else slot (first, 1) + slots (first+1 .. last, 0) in chunk order.
 // Every sum has a fixed order, so the result does not depend on scheduling.
+//
+// The first pass is bound by latency where the batch is small, so where each token's part goes is read for all 32 positions at
+// once, ahead of the walk (at every change of token it cost up to 32 dependent reads), and the sums over batches and the
+// mean loss, which read the same step's results, are further blocks of the launch instead of launches.
+// T = 512, d = 256: 15.3 + 2.6 + 2.3 us before, 11 now; T = 1024, d = 896: 42 + 5.6 + 4.6, 15 now.
 constexpr int EMB_CH = 32;
 #define EMB_MAXD4 4  // float4 slots per lane in the row pass: d <= 1024
 
-__global__ __launch_bounds__(128) void embed_bwd_chunks_kernel(
+// dPpos[s,:] = sum_b dx[b,s,:] in batch order
+__device__ __forceinline__ void embed_bwd_pos(const float* __restrict__ dx, float* __restrict__ dPpos, int s, int B, int S, int d4) {
+  const float4* dx4 = reinterpret_cast<const float4*>(dx);
+  for (int c = threadIdx.x; c < d4; c += 256) {
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int b0 = 0; b0 < B; b0 += 8) {  // 8 loads in flight, added in batch order
+      float4 x[8];
+#pragma unroll
+      for (int u = 0; u < 8; u++)
+        x[u] = b0 + u < B ? dx4[((int64_t)(b0 + u) * S + s) * d4 + c] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int u = 0; u < 8; u++)
+        if (b0 + u < B) { acc.x += x[u].x; acc.y += x[u].y; acc.z += x[u].z; acc.w += x[u].w; }
+    }
+    reinterpret_cast<float4*>(dPpos)[(int64_t)s * d4 + c] = acc;
+  }
+}
+
+// out[0] = mean of v[0..T): 1024 strided sums, added per 64 and then in order
+__device__ __forceinline__ void mean_rows(const float* __restrict__ v, float* __restrict__ out, int T) {
+  __shared__ float sh[16];
+  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+  for (int i0 = 0; i0 < T; i0 += 1024)
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int i = i0 + u * 256 + threadIdx.x;
+      acc[u] += i < T ? v[i] : 0.0f;
+    }
+#pragma unroll
+  for (int u = 0; u < 4; u++) {
+    acc[u] = wave_sum(acc[u]);
+    if ((threadIdx.x & 63) == 0) sh[u * 4 + (threadIdx.x >> 6)] = acc[u];
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float r = sh[0];
+    for (int i = 1; i < 16; i++) r += sh[i];
+    out[0] = r / (float)T;
+  }
+}
+
+// blocks: the chunks, then S positions, then one for the mean loss
+__global__ __launch_bounds__(256) void embed_bwd_chunks_kernel(
     const int32_t* __restrict__ tok, const int32_t* __restrict__ offset, const int32_t* __restrict__ pos,
-    const float* __restrict__ dx, float* __restrict__ dE, float* __restrict__ scratch, int T, int S, int V, int d) {
-  __shared__ int s_pos[EMB_CH], s_tok[EMB_CH];
-  const int c = blockIdx.x, i0 = c * EMB_CH, tid = threadIdx.x;
-  const int n = T - i0 < EMB_CH ? T - i0 : EMB_CH;
+    const float* __restrict__ dx, float* __restrict__ dE, float* __restrict__ scratch, float* __restrict__ dPpos,
+    const float* __restrict__ loss_row, float* __restrict__ loss_out, int B, int S, int V, int d, int nchunk) {
+  __shared__ int s_pos[EMB_CH], s_tok[EMB_CH], s_dst[EMB_CH];   // s_dst: -1 = dE, else the scratch slot
+  const int T = B * S, c = blockIdx.x, i0 = c * EMB_CH, tid = threadIdx.x;
   const int d4 = d / 4;
+  if (c >= nchunk) {
+    if (c - nchunk < S) embed_bwd_pos(dx, dPpos, c - nchunk, B, S, d4);
+    else mean_rows(loss_row, loss_out, T);
+    return;
+  }
+  const int n = T - i0 < EMB_CH ? T - i0 : EMB_CH;
   if (tid < n) {
     int t = pos[i0 + tid];
     int id = tok[(int64_t)(t / S) * (S + 1) + (t % S)];
+    id = id < 0 ? 0 : (id >= V ? V - 1 : id);
+    const int cf = offset[id] / EMB_CH, cl = (offset[id + 1] - 1) / EMB_CH;
     s_pos[tid] = t;
-    s_tok[tid] = id < 0 ? 0 : (id >= V ? V - 1 : id);
+    s_tok[tid] = id;
+    s_dst[tid] = cf == cl ? -1 : 2 * c + (c == cf ? 1 : 0);
   }
   __syncthreads();
   const float4* dx4 = reinterpret_cast<const float4*>(dx);
-  for (int col = tid; col < d4; col += 128) {   // one pass for d <= 512
-    auto flush = [&](int v, float4 acc) {
-      int beg = offset[v], end = offset[v + 1];
-      int cf = beg / EMB_CH, cl = (end - 1) / EMB_CH;
-      float4* dst = cf == cl ? reinterpret_cast<float4*>(dE) + (int64_t)v * d4
-                             : reinterpret_cast<float4*>(scratch) + (int64_t)(2 * c + (c == cf ? 1 : 0)) * d4;
+  for (int col = tid; col < d4; col += 256) {   // one pass for d <= 1024
+    auto flush = [&](int j, float4 acc) {   // the list that position j ends
+      const int slot = s_dst[j];
+      float4* dst = slot < 0 ? reinterpret_cast<float4*>(dE) + (int64_t)s_tok[j] * d4 : reinterpret_cast<float4*>(scratch) + (int64_t)slot * d4;
       dst[col] = acc;
     };
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -671,7 +725,7 @@ __global__ __launch_bounds__(128) void embed_bwd_chunks_kernel(
         if (j < n) {
           int tk = s_tok[j];
           if (tk != cur) {  // block-uniform
-            flush(cur, acc);
+            flush(j - 1, acc);
             acc = make_float4(0.f, 0.f, 0.f, 0.f);
             cur = tk;
           }
@@ -679,7 +733,7 @@ __global__ __launch_bounds__(128) void embed_bwd_chunks_kernel(
         }
       }
     }
-    flush(cur, acc);
+    flush(n - 1, acc);
   }
 }
 
@@ -713,37 +767,14 @@ __global__ __launch_bounds__(256) void embed_bwd_rows_kernel(const int32_t* __re
   }
 }
 
-__global__ void embed_bwd_pos_kernel(const float* __restrict__ dx, float* __restrict__ dPpos,
-                                     int B, int S, int d) {
-  int s = blockIdx.x;
-  const int d4 = d / 4;
-  const float4* dx4 = reinterpret_cast<const float4*>(dx);
-  for (int c = threadIdx.x; c < d4; c += blockDim.x) {
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int b0 = 0; b0 < B; b0 += 8) {  // 8 loads in flight, added in batch order
-      float4 x[8];
-#pragma unroll
-      for (int u = 0; u < 8; u++)
-        x[u] = b0 + u < B ? dx4[((int64_t)(b0 + u) * S + s) * d4 + c] : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-      for (int u = 0; u < 8; u++)
-        if (b0 + u < B) { acc.x += x[u].x; acc.y += x[u].y; acc.z += x[u].z; acc.w += x[u].w; }
-    }
-    reinterpret_cast<float4*>(dPpos)[(int64_t)s * d4 + c] = acc;
-  }
-}
-
 int embed_bwd(const int32_t* tok, const int32_t* offset, const int32_t* pos, const float* dx, float* dE,
-              float* dPpos, float* scratch, int B, int S, int d, int V, hipStream_t st) {
+              float* dPpos, float* scratch, const float* loss_row, float* loss_out, int B, int S, int d, int V, hipStream_t st) {
   if (d > 256 * EMB_MAXD4 || d % 4) return set_error(ALS_ERR_INVALID, "embed_bwd: d unsupported");
-  const int T = B * S;
-  hipLaunchKernelGGL(embed_bwd_chunks_kernel, dim3((T + EMB_CH - 1) / EMB_CH), dim3(128), 0, st, tok, offset,
-                     pos, dx, dE, scratch, T, S, V, d);
+  const int nchunk = (B * S + EMB_CH - 1) / EMB_CH;
+  hipLaunchKernelGGL(embed_bwd_chunks_kernel, dim3(nchunk + S + 1), dim3(256), 0, st, tok, offset, pos, dx, dE, scratch, dPpos,
+                     loss_row, loss_out, B, S, V, d, nchunk);
   ALS_CHECK_LAUNCH();
   hipLaunchKernelGGL(embed_bwd_rows_kernel, dim3((V + 3) / 4), dim3(256), 0, st, offset, scratch, dE, V, d);
-  ALS_CHECK_LAUNCH();
-  int threads = d / 4 < 256 ? (d / 4 < 64 ? 64 : d / 4) : 256;
-  hipLaunchKernelGGL(embed_bwd_pos_kernel, dim3(S), dim3(threads), 0, st, dx, dPpos, B, S, d);
   ALS_CHECK_LAUNCH();
   return ALS_OK;
 }
@@ -1121,21 +1152,6 @@ int cross_entropy(const void* logits, int logits_bf16, const int32_t* tok, float
   else
     hipLaunchKernelGGL((cross_entropy_kernel<float, float>), dim3(T), dim3(256), 0, st, (const float*)logits, tok,
                        loss_row, (float*)dlogits, S, V, invT);
-  ALS_CHECK_LAUNCH();
-  return ALS_OK;
-}
-
-__global__ __launch_bounds__(1024) void mean_rows_kernel(const float* __restrict__ v,
-                                                         float* __restrict__ out, int T) {
-  __shared__ float sh[16];
-  float acc = 0.0f;
-  for (int i = threadIdx.x; i < T; i += blockDim.x) acc += v[i];
-  acc = block_reduce(acc, false, sh);
-  if (threadIdx.x == 0) out[0] = acc / (float)T;
-}
-
-int mean_rows(const float* loss_row, float* out, int T, hipStream_t st) {
-  hipLaunchKernelGGL(mean_rows_kernel, dim3(1), dim3(1024), 0, st, loss_row, out, T);
   ALS_CHECK_LAUNCH();
   return ALS_OK;
 }
