@@ -5,7 +5,9 @@
 //
 // One wavefront owns 16 NT queries (forward, dQ) or 16 NT keys (dK and dV) of one head and walks 16-row tiles of the other
 // side; the four wavefronts of a workgroup take neighbouring blocks of one head, so that they find each other's tiles in
-// the CU's L1, and share nothing else: no LDS, no barrier.  Every operand is loaded straight into MFMA fragments, 16 bytes
+// the CU's L1, and share nothing else: no LDS, no barrier.  Where that gives the chip few wavefronts, the four of a workgroup
+// share one block of 16 rows instead (SPLIT): each walks every fourth tile of the other side, and their results are put
+// together through LDS in order at the end.  Every operand is loaded straight into MFMA fragments, 16 bytes
 // (fp32) or 8 to 16 bytes (bf16) per lane:
 //   MFMA lane layout (lane l, group g = l / 16): A row l%16, contraction g; B column l%16, contraction g; accumulator
 //   element v: row 4 g + v, column l%16.
@@ -19,7 +21,8 @@
 // tile loads and dependent MFMAs of a single wavefront for short ones.  Against one wavefront per query with scalar products
 // in vector code (attention_generic.hip), forward / backward in us, same distance from a float64 reference:
 //   B 8, S 1000, 16 heads of 64, fp32: 2250 / 9484 -> 379 / 1218; bf16: 1382 / 5898 -> 398 / 1255
-//   B 8, S 256, 8 heads of 32, bf16: 53 / 193 -> 15 / 38;   B 3, S 200, 5 heads of 64, bf16: 19 / 66 -> 16 / 47
+//   B 8, S 256, 8 heads of 32, bf16: 53 / 193 -> 12 / 34;   B 3, S 200, 5 heads of 64, bf16: 19 / 66 -> 8.1 / 21
+//   (15 / 39 and 16 / 48 with a row block per wavefront);   B 8, S 1000, 4 heads of 64, bf16: 107 / 347 that way -> 68 / 212
 //   B 8, S 32, 2 heads of 32, fp32: 5.3 / 9.9 -> 7.2 / 9.6, which is why small calls stay with the other kernels.
 #include "common.h"
 #include <math.h>
@@ -169,24 +172,31 @@ struct ColFrag {
 // Wavefront -> (block of 16 NT rows, head, sample).  Consecutive workgroups go to different XCDs: each XCD is given a
 // contiguous run of them, so that the blocks of one head share an L2.
 struct Block { int row0, hd, b; };
+template <bool SPLIT>
 __device__ __forceinline__ bool block_of(int S, int h, int rows, bool last_first, Block& out) {
-  const int nblk = (S + rows - 1) / rows, per_pair = (nblk + 3) / 4;
+  const int nblk = (S + rows - 1) / rows, per_pair = SPLIT ? nblk : (nblk + 3) / 4;
   const int n = gridDim.x, per = n / 8, i = blockIdx.x;
   const int id = i < per * 8 ? (i % 8) * per + i / 8 : i;
   const int pair = id / per_pair;
-  int blk = (id % per_pair) * 4 + (threadIdx.x >> 6);
+  int blk = SPLIT ? id % per_pair : (id % per_pair) * 4 + (threadIdx.x >> 6);
   if (blk >= nblk) return false;
   if (last_first) blk = nblk - 1 - blk;   // the longest rows of keys first
   out = Block{blk * rows, pair % h, pair / h};
   return true;
 }
 
-template <typename T, int DH, int NT>
+// The accumulators that the wavefronts of a SPLIT workgroup leave for the one that adds them.
+template <int N>
+struct Parts { f32x4 v[4][N][64]; };
+
+template <typename T, int DH, int NT, bool SPLIT>
 __global__ __launch_bounds__(256, 2) void attn_fwd_f32_kernel(const T* __restrict__ qkv, T* __restrict__ o,
                                                                   float* __restrict__ lse, int S, int h, float scale) {
   typedef ColFrag<T, DH> CF;
   Block bk;
-  if (!block_of(S, h, 16 * NT, true, bk)) return;
+  if (!block_of<SPLIT>(S, h, 16 * NT, true, bk)) return;   // never in a SPLIT workgroup
+  const int wv = SPLIT ? threadIdx.x >> 6 : 0;
+  constexpr int STEP = SPLIT ? 64 : 16;   // from one tile of this wavefront to its next
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15, last = S - 1, q0 = bk.row0;
   const int d = h * DH;
   const int64_t ld = 3 * (int64_t)d;
@@ -203,11 +213,12 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_f32_kernel(const T* __restric
     for (int t = 0; t < CF::DT; t++) acc[n][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
   }
   const int q_last = q0 + 16 * NT - 1 < last ? q0 + 16 * NT - 1 : last;
-  kf.load(base + d + (int64_t)(c < last ? c : last) * ld, g);
-  for (int k0 = 0; k0 <= q_last; k0 += 16) {
+  const int kr0 = 16 * wv + c;
+  kf.load(base + d + (int64_t)(kr0 < last ? kr0 : last) * ld, g);
+  for (int k0 = 16 * wv; k0 <= q_last; k0 += STEP) {
     CF vf;
     vf.load(base + 2 * d, ld, k0, last, lane);
-    const int kr = k0 + 16 + c;
+    const int kr = k0 + STEP + c;
     kn.load(base + d + (int64_t)(kr < last ? kr : last) * ld, g);
 #pragma unroll
     for (int n = 0; n < NT; n++) {
@@ -233,6 +244,28 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_f32_kernel(const T* __restric
     }
     kf = kn;
   }
+  if constexpr (SPLIT) {   // rescale to the largest maximum of a query and add
+    static_assert(NT == 1, "one block of rows");
+    __shared__ Parts<CF::DT> parts;
+    __shared__ float pm[4][64], pl[4][64];
+#pragma unroll
+    for (int t = 0; t < CF::DT; t++) parts.v[wv][t][lane] = acc[0][t];
+    pm[wv][lane] = m[0];
+    pl[wv][lane] = l[0];
+    __syncthreads();
+    if (wv) return;
+    const float mx = fmaxf(fmaxf(pm[0][lane], pm[1][lane]), fmaxf(pm[2][lane], pm[3][lane]));
+    m[0] = mx; l[0] = 0.0f;
+#pragma unroll
+    for (int t = 0; t < CF::DT; t++) acc[0][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; w++) {
+      const float f = pm[w][lane] == mx ? 1.0f : expf(pm[w][lane] - mx);
+      l[0] += f * pl[w][lane];
+#pragma unroll
+      for (int t = 0; t < CF::DT; t++) acc[0][t] += f * parts.v[w][t][lane];
+    }
+  }
 #pragma unroll
   for (int n = 0; n < NT; n++) {
     const int q = q0 + 16 * n + c;
@@ -244,7 +277,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_f32_kernel(const T* __restric
 }
 
 // dq_i = sum_{j<=i} ds_ij k_j,  ds_ij = p_ij (do_i.v_j - D_i) scale,  D_i = do_i.o_i (left for the other pass)
-template <typename T, int DH, int NT>
+template <typename T, int DH, int NT, bool SPLIT>
 __global__ __launch_bounds__(256, 2) void attn_dq_f32_kernel(const T* __restrict__ qkv, const T* __restrict__ o,
                                                                      const T* __restrict__ d_o, const float* __restrict__ lse,
                                                                      float* __restrict__ Dbuf, T* __restrict__ dqkv, int S,
@@ -252,7 +285,9 @@ __global__ __launch_bounds__(256, 2) void attn_dq_f32_kernel(const T* __restrict
   typedef ColFrag<T, DH> CF;
   typedef RowFrag<T, DH> RF;
   Block bk;
-  if (!block_of(S, h, 16 * NT, true, bk)) return;
+  if (!block_of<SPLIT>(S, h, 16 * NT, true, bk)) return;   // never in a SPLIT workgroup
+  const int wv = SPLIT ? threadIdx.x >> 6 : 0;
+  constexpr int STEP = SPLIT ? 64 : 16;   // from one tile of this wavefront to its next
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15, last = S - 1, q0 = bk.row0;
   const int d = h * DH;
   const int64_t ld = 3 * (int64_t)d;
@@ -276,20 +311,21 @@ __global__ __launch_bounds__(256, 2) void attn_dq_f32_kernel(const T* __restrict
       for (int e = 0; e < RF::CH; e++) s += gf[n].c[i].v[e] * of.c[i].v[e];
     Dq[n] = quad_sum(s);
     lq[n] = lse[stat + qc];
-    if (g == 0 && q <= last) Dbuf[stat + q] = Dq[n];
+    if (wv == 0 && g == 0 && q <= last) Dbuf[stat + q] = Dq[n];
 #pragma unroll
     for (int t = 0; t < CF::DT; t++) acc[n][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
   }
   const int q_last = q0 + 16 * NT - 1 < last ? q0 + 16 * NT - 1 : last;
   {
-    const int64_t kr = (int64_t)(c < last ? c : last) * ld;
+    const int kr0 = 16 * wv + c;
+    const int64_t kr = (int64_t)(kr0 < last ? kr0 : last) * ld;
     kf.load(base + d + kr, g);
     vf.load(base + 2 * d + kr, g);
   }
-  for (int k0 = 0; k0 <= q_last; k0 += 16) {
+  for (int k0 = 16 * wv; k0 <= q_last; k0 += STEP) {
     CF kt;
     kt.load(base + d, ld, k0, last, lane);
-    const int kr = k0 + 16 + c;
+    const int kr = k0 + STEP + c;
     const int64_t ko = (int64_t)(kr < last ? kr : last) * ld;
     kn.load(base + d + ko, g);
     vn.load(base + 2 * d + ko, g);
@@ -309,6 +345,17 @@ __global__ __launch_bounds__(256, 2) void attn_dq_f32_kernel(const T* __restrict
     kf = kn;
     vf = vn;
   }
+  if constexpr (SPLIT) {
+    __shared__ Parts<CF::DT> parts;
+#pragma unroll
+    for (int t = 0; t < CF::DT; t++) parts.v[wv][t][lane] = acc[0][t];
+    __syncthreads();
+    if (wv) return;
+#pragma unroll
+    for (int w = 1; w < 4; w++)
+#pragma unroll
+      for (int t = 0; t < CF::DT; t++) acc[0][t] += parts.v[w][t][lane];
+  }
 #pragma unroll
   for (int n = 0; n < NT; n++) {
     const int q = q0 + 16 * n + c;
@@ -317,14 +364,16 @@ __global__ __launch_bounds__(256, 2) void attn_dq_f32_kernel(const T* __restrict
 }
 
 // dk_j = sum_{i>=j} ds_ij q_i ; dv_j = sum_{i>=j} p_ij do_i
-template <typename T, int DH, int NT>
+template <typename T, int DH, int NT, bool SPLIT>
 __global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void attn_dkv_f32_kernel(
     const T* __restrict__ qkv, const T* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ Dbuf,
     T* __restrict__ dqkv, int S, int h, float scale) {
   typedef ColFrag<T, DH> CF;
   typedef RowFrag<T, DH> RF;
   Block bk;
-  if (!block_of(S, h, 16 * NT, false, bk)) return;
+  if (!block_of<SPLIT>(S, h, 16 * NT, false, bk)) return;   // never in a SPLIT workgroup
+  const int wv = SPLIT ? threadIdx.x >> 6 : 0;
+  constexpr int STEP = SPLIT ? 64 : 16;   // from one tile of this wavefront to its next
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15, last = S - 1, j0 = bk.row0;
   const int d = h * DH;
   const int64_t ld = 3 * (int64_t)d;
@@ -347,8 +396,8 @@ __global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void attn_dkv_f32_kernel(
     q.load(base + (int64_t)i * ld, g);
     go.load(gbase + (int64_t)i * d, g);
   };
-  load_rows(j0, qf, gf);
-  for (int i0 = j0; i0 <= last; i0 += 16) {
+  load_rows(j0 + 16 * wv, qf, gf);
+  for (int i0 = j0 + 16 * wv; i0 <= last; i0 += STEP) {
     CF qt, gt;
     float ls[4], Ds[4];
 #pragma unroll
@@ -359,7 +408,7 @@ __global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void attn_dkv_f32_kernel(
     }
     gt.load(gbase, d, i0, last, lane);
     qt.load(base, ld, i0, last, lane);
-    load_rows(i0 + 16, qn, gn);
+    load_rows(i0 + STEP, qn, gn);
 #pragma unroll
     for (int n = 0; n < NT; n++) {
       const int j = j0 + 16 * n + c;
@@ -387,6 +436,26 @@ __global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void attn_dkv_f32_kernel(
     qf = qn;
     gf = gn;
   }
+  if constexpr (SPLIT) {   // wavefront 0 adds and stores dk, wavefront 1 dv
+    __shared__ Parts<2 * CF::DT> parts;
+#pragma unroll
+    for (int t = 0; t < CF::DT; t++) {
+      parts.v[wv][t][lane] = dk[0][t];
+      parts.v[wv][CF::DT + t][lane] = dv[0][t];
+    }
+    __syncthreads();
+    const int j = j0 + c;
+    if (wv > 1 || j > last) return;
+    f32x4 sum[CF::DT];
+#pragma unroll
+    for (int t = 0; t < CF::DT; t++) {
+      sum[t] = parts.v[0][wv * CF::DT + t][lane];
+#pragma unroll
+      for (int w = 1; w < 4; w++) sum[t] += parts.v[w][wv * CF::DT + t][lane];
+    }
+    CF::store(dqkv + ((int64_t)bk.b * S + j) * ld + bk.hd * DH + (1 + wv) * d, sum, 1.0f, 1.0f, lane);
+    return;
+  }
 #pragma unroll
   for (int n = 0; n < NT; n++) {
     const int j = j0 + 16 * n + c;
@@ -398,28 +467,31 @@ __global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void attn_dkv_f32_kernel(
 }
 
 // Two row blocks per wavefront halve the tile traffic of the other side but also the number of wavefronts: taken once
-// one block each would give every SIMD (1024 on the chip) more than four.
-inline int row_blocks(int B, int S, int h) { return (int64_t)B * h * ((S + 15) / 16) > 4096 ? 2 : 1; }
-inline dim3 grid_of(int B, int S, int h, int nt) {
+// one block each would give every SIMD (1024 on the chip) more than four.  Up to there, four wavefronts per row block (returned as
+// 0) where there is more than a tile for each second one: the chain of tiles is a quarter as long (figures above), and at 4096 blocks,
+// where the chip is full either way, still shorter (16 heads of 32, B 16, S 256, fp32: forward, dQ, dK and dV 35 + 43 + 63 us to 31 + 46 + 54).
+inline int row_blocks(int B, int S, int h) { return (int64_t)B * h * ((S + 15) / 16) > 4096 ? 2 : S > 32 ? 0 : 1; }
+inline dim3 grid_of(int B, int S, int h, int nt, bool split) {
   const int nblk = (S + 16 * nt - 1) / (16 * nt);
-  return dim3((unsigned)((nblk + 3) / 4) * h * B);
+  return dim3((unsigned)(split ? nblk : (nblk + 3) / 4) * h * B);
 }
 
-template <typename T, int DH, int NT>
+template <typename T, int DH, int NT, bool SPLIT>
 int fwd_t(const void* qkv, void* o, float* lse, int B, int S, int h, hipStream_t st) {
-  hipLaunchKernelGGL((attn_fwd_f32_kernel<T, DH, NT>), grid_of(B, S, h, NT), dim3(256), 0, st, (const T*)qkv, (T*)o, lse, S, h,
+  hipLaunchKernelGGL((attn_fwd_f32_kernel<T, DH, NT, SPLIT>), grid_of(B, S, h, NT, SPLIT), dim3(256), 0, st, (const T*)qkv, (T*)o, lse, S, h,
                      1.0f / sqrtf((float)DH));
   ALS_CHECK_LAUNCH();
   return ALS_OK;
 }
-template <typename T, int DH, int NT>
+template <typename T, int DH, int NT, bool SPLIT>
 int bwd_t(const void* qkv, const void* o, const void* d_o, const float* lse, float* dscratch, void* dqkv, int B, int S, int h,
           hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)DH);
-  hipLaunchKernelGGL((attn_dq_f32_kernel<T, DH, NT>), grid_of(B, S, h, NT), dim3(256), 0, st, (const T*)qkv, (const T*)o,
+  const dim3 grid = grid_of(B, S, h, NT, SPLIT);
+  hipLaunchKernelGGL((attn_dq_f32_kernel<T, DH, NT, SPLIT>), grid, dim3(256), 0, st, (const T*)qkv, (const T*)o,
                      (const T*)d_o, lse, dscratch, (T*)dqkv, S, h, scale);
   ALS_CHECK_LAUNCH();
-  hipLaunchKernelGGL((attn_dkv_f32_kernel<T, DH, NT>), grid_of(B, S, h, NT), dim3(256), 0, st, (const T*)qkv, (const T*)d_o,
+  hipLaunchKernelGGL((attn_dkv_f32_kernel<T, DH, NT, SPLIT>), grid, dim3(256), 0, st, (const T*)qkv, (const T*)d_o,
                      lse, dscratch, (T*)dqkv, S, h, scale);
   ALS_CHECK_LAUNCH();
   return ALS_OK;
@@ -427,13 +499,14 @@ int bwd_t(const void* qkv, const void* o, const void* d_o, const float* lse, flo
 
 }  // namespace
 
+#define ALS_ATTN_ROWS(T, DH, CALL) (rows == 2 ? CALL(T, DH, 2, false) : rows == 1 ? CALL(T, DH, 1, false) : CALL(T, DH, 1, true))
 #define ALS_ATTN_SWITCH(CALL)                                                             \
   do {                                                                                    \
-    const bool two = row_blocks(B, S, h) == 2;                                            \
-    if (bf && dh == 64) return two ? CALL(bf16, 64, 2) : CALL(bf16, 64, 1);               \
-    if (bf) return two ? CALL(bf16, 32, 2) : CALL(bf16, 32, 1);                           \
-    if (dh == 64) return two ? CALL(float, 64, 2) : CALL(float, 64, 1);                   \
-    return two ? CALL(float, 32, 2) : CALL(float, 32, 1);                                 \
+    const int rows = row_blocks(B, S, h);                                                 \
+    if (bf && dh == 64) return ALS_ATTN_ROWS(bf16, 64, CALL);                             \
+    if (bf) return ALS_ATTN_ROWS(bf16, 32, CALL);                                         \
+    if (dh == 64) return ALS_ATTN_ROWS(float, 64, CALL);                                  \
+    return ALS_ATTN_ROWS(float, 32, CALL);                                                \
   } while (0)
 
 // Head widths of 32 and 64, 16-byte aligned tensors (rows are then aligned too); the grid is one-dimensional.  Up to 32
@@ -447,14 +520,14 @@ bool attention_mfma_f32_supported(const void* a, const void* b, const void* c, c
 }
 
 int attention_fwd_mfma_f32(const void* qkv, void* o, float* lse, int B, int S, int h, int dh, int bf, hipStream_t st) {
-#define ALS_CALL(T, DH, NT) (fwd_t<T, DH, NT>(qkv, o, lse, B, S, h, st))
+#define ALS_CALL(T, DH, NT, SPLIT) (fwd_t<T, DH, NT, SPLIT>(qkv, o, lse, B, S, h, st))
   ALS_ATTN_SWITCH(ALS_CALL);
 #undef ALS_CALL
 }
 
 int attention_bwd_mfma_f32(const void* qkv, const void* o, const void* d_o, const float* lse, float* dscratch, void* dqkv, int B,
                            int S, int h, int dh, int bf, hipStream_t st) {
-#define ALS_CALL(T, DH, NT) (bwd_t<T, DH, NT>(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, st))
+#define ALS_CALL(T, DH, NT, SPLIT) (bwd_t<T, DH, NT, SPLIT>(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, st))
   ALS_ATTN_SWITCH(ALS_CALL);
 #undef ALS_CALL
 }

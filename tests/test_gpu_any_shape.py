@@ -159,6 +159,14 @@ def test_attention_in_fp32_arithmetic(B, S, h, dh, dt):
         assert _rel(dq, rdq) < (1e-5 if dt == torch.float32 else 8e-3)
 
 
+@pytest.mark.parametrize("B,S,h,dh", [(1, 34, 1, 32), (1, 64, 3, 64), (2, 65, 1, 32),      # 3, 4 and 5 tiles for four wavefronts
+                                      (1, 1024, 2, 64), (16, 256, 16, 32),                 # the longest chains; the most row blocks
+                                      (37, 32, 2, 64), (65, 31, 1, 32)])                   # short rows: a row block per wavefront
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_attention_with_wavefronts_that_share_a_row_block(B, S, h, dh, dt):
+    test_attention_in_fp32_arithmetic(B, S, h, dh, dt)
+
+
 @pytest.mark.parametrize("bad", [np.inf, np.nan])
 def test_attention_hides_what_a_query_does_not_see(bad):
     """Row 37 of v (k) is not finite: the output (dq) of every earlier position is what it is without it."""
