@@ -109,6 +109,43 @@ DwPlan dw_group_plan(const DwProblem* probs, int n_probs, int K, DwItem* items, 
 int dw_group_launch(const DwProblem* d_probs, const DwItem* d_items, const DwSplitTile* d_split, const DwPlan& plan,
                     float* partial_tiles, hipStream_t st);
 
+// The same for products that have no aligned kernel (fp32, odd sizes): whole tiles of the kernels of gemm_mfma_any.hip and
+// gemm_mfma_f32.hip, the list of products in the kernel's arguments.
+constexpr int DW_LIST_MAX = 64;   // products of one launch (the arguments stay below 4 KB); longer lists take several
+struct DwList {
+  struct Product { const void* A; const void* B; float* C; int M, N, tiles_n, tile0; };
+  int n, K;
+  Product p[DW_LIST_MAX];
+  // the product that tile id belongs to (tile0 ascends from 0)
+  __device__ __forceinline__ int find(int tile) const {
+    int lo = 0, hi = n;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) / 2;
+      if (p[mid].tile0 <= tile) lo = mid; else hi = mid;
+    }
+    return lo;
+  }
+  // the next products of a list, in tiles of bm x bn; returns how many
+  int fill(const DwProblem* probs, int count, int K_, int bm, int bn, int* tiles) {
+    n = count < DW_LIST_MAX ? count : DW_LIST_MAX;
+    K = K_;
+    *tiles = 0;
+    for (int i = 0; i < n; i++) {
+      const DwProblem& q = probs[i];
+      p[i] = Product{q.A, q.B, q.C, q.M, q.N, (q.N + bn - 1) / bn, *tiles};
+      *tiles += (q.M + bm - 1) / bm * p[i].tiles_n;
+    }
+    return n;
+  }
+};
+inline int64_t dw_list_tiles(const DwProblem* probs, int n, int bm, int bn) {
+  int64_t t = 0;
+  for (int i = 0; i < n; i++) t += (int64_t)((probs[i].M + bm - 1) / bm) * ((probs[i].N + bn - 1) / bn);
+  return t;
+}
+int gemm_mfma_any_dw_list(const DwProblem* probs, int n, int K, hipStream_t st);   // bf16 operands
+int gemm_mfma_f32_dw_list(const DwProblem* probs, int n, int K, hipStream_t st);   // fp32 operands (A and B point to floats)
+
 // ---- attention ----------------------------------------------------------------------------
 int attention_fwd_generic(const void* qkv, void* o, float* lse, int B, int S, int h, int dh,
                           int bf, hipStream_t st);

@@ -50,6 +50,7 @@ struct als_ctx {
   hipEvent_t server_ev;
   bool bf; bool allow_mfma;
   bool grouped_dw;   // the layers' weight gradients run as one grouped launch at the end of the backward pass
+  bool list_dw;      // the same, the output matrix's too, where they have no aligned kernel
   int T;
 };
 
@@ -77,6 +78,14 @@ void carve(als_ctx* c, Carver& cv) {
   c->w.resize(g.n_workers);
   c->grouped_dw = bf && !(g.flags & 1) && !(g.flags & 2) && g.n_layers > 0 && dw_group_supported((int)d, (int)(3 * da), (int)T, d, 3 * da) &&
                   dw_group_supported((int)da, (int)d, (int)T, da, d) && dw_group_supported((int)d, (int)ff, (int)T, d, ff);
+  // Products without an aligned kernel: each fills a part of the chip (600 tokens, 320 x 1280: 100 tiles of 64 x 64) and costs
+  // a launch.  17 products of four layers and the head took 199 us in fp32 mode (1024 tokens, d = 256, V = 2000) and 137 in bf16
+  // (600 tokens, d = 320, V = 5003); as one list 107 and 50.  Every layer keeps its four dY for it: up to 256 MiB, beyond
+  // which (many tokens) a product fills the chip alone.
+  {
+    const bool aligned = bf && T % 64 == 0 && d % 128 == 0 && (da % 128 == 0 || ff % 128 == 0);
+    c->list_dw = !(g.flags & 3) && !aligned && g.n_layers > 0 && (int64_t)g.n_layers * T * (2 * d + ff + 3 * da) * (bf ? 2 : 4) <= (int64_t)256 << 20;
+  }
   for (Worker& w : c->w) {
     w.theta = cv.f32(P); w.start = cv.f32(P); w.adam_m = cv.f32(P); w.adam_v = cv.f32(P);
     w.grad = cv.f32(P);
@@ -114,28 +123,31 @@ void carve(als_ctx* c, Carver& cv) {
     w.dw_probs_dev = nullptr; w.dw_items_dev = nullptr; w.dw_split_dev = nullptr; w.dw_partial = nullptr;
     w.dw_plan = DwPlan{0, 0, 0, 0.0};
     w.head_ws = w.splitk_ws; w.head_ws_bytes = w.splitk_bytes;
-    if (c->grouped_dw) {
+    w.dw_probs.clear();
+    if (c->grouped_dw || c->list_dw)
       for (int l = 0; l < L; l++) {
         w.dy2[l] = cv.act(T * d, bf); w.dy1[l] = cv.act(T * ff, bf); w.dyo[l] = cv.act(T * d, bf);
         w.dyqkv[l] = cv.act(T * 3 * da, bf);
       }
-      // The input gradient of the output matrix runs before anything is written to these: until then they are its
-      // split-K scratch, one block from the first to the last.
-      w.head_ws = (float*)w.dy2[0];
-      w.head_ws_bytes = (size_t)((char*)w.dyqkv[L - 1] - (char*)w.dy2[0]) + (size_t)T * 3 * da * 2;
-      // the products, in the order of the flat parameter layout (pointers are null while only counting)
-      w.dw_probs.clear();
-      int n_tiles = 0;
-      auto add = [&](const void* X, int64_t M, const void* dY, int64_t N, int64_t off) {
-        w.dw_probs.push_back(DwProblem{(const bf16*)X, (const bf16*)dY, w.grad ? w.grad + off : nullptr, (int)M, (int)N, (int)M, (int)N, {0, 0}});
-        n_tiles += (int)(((M + 255) / 256) * ((N + 255) / 256));
-      };
+    int n_tiles = 0;
+    auto add = [&](const void* X, int64_t M, const void* dY, int64_t N, int64_t off) {
+      w.dw_probs.push_back(DwProblem{(const bf16*)X, (const bf16*)dY, w.grad ? w.grad + off : nullptr, (int)M, (int)N, (int)M, (int)N, {0, 0}});
+      n_tiles += (int)(((M + 255) / 256) * ((N + 255) / 256));
+    };
+    // the products, in the order of the flat parameter layout (pointers are null while only counting)
+    if (c->grouped_dw || c->list_dw)
       for (int l = 0; l < L; l++) {
         add(w.a[l], d, w.dyqkv[l], 3 * da, c->L.Wqkv[l]);
         add(w.o[l], da, w.dyo[l], d, c->L.Wo[l]);
         add(w.b[l], d, w.dy1[l], ff, c->L.W1[l]);
         add(w.gl[l], ff, w.dy2[l], d, c->L.W2[l]);
       }
+    if (c->list_dw) add(w.xf, d, w.dlogits, V, c->L.Wout);
+    if (c->grouped_dw) {
+      // The input gradient of the output matrix runs before anything is written to these: until then they are its
+      // split-K scratch, one block from the first to the last.
+      w.head_ws = (float*)w.dy2[0];
+      w.head_ws_bytes = (size_t)((char*)w.dyqkv[L - 1] - (char*)w.dy2[0]) + (size_t)T * 3 * da * 2;
       w.dw_items.resize(dw_plan_max_items(n_tiles));
       w.dw_split.resize(dw_plan_max_split(n_tiles) + 1);
       w.dw_plan = dw_group_plan(w.dw_probs.data(), (int)w.dw_probs.size(), (int)T, w.dw_items.data(), w.dw_split.data());
@@ -218,7 +230,7 @@ int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot, float* loss_ou
   bool mf = c->allow_mfma;
   int nl = g.n_layers;
   // output matrix and final norm
-  RUN(gemm(desc_dw(c, w, w.xf, d, w.dlogits, V, d, V, T, w.grad + L.Wout), mf, st));
+  if (!c->list_dw) RUN(gemm(desc_dw(c, w, w.xf, d, w.dlogits, V, d, V, T, w.grad + L.Wout), mf, st));
   GemmDesc dxf = desc(c, w.dlogits, 0, V, wptr(c, w, L.Wout), 1, V, T, d, V, w.dtmp, d, false);
   dxf.ws = w.head_ws; dxf.ws_bytes = w.head_ws_bytes;
   RUN(gemm(dxf, mf, st));
@@ -229,7 +241,7 @@ int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot, float* loss_ou
   // The weight gradient of every matrix is X^T dY.  Either each is a product of its own, issued
   // here next to the input gradient that reads the same dY, or (grouped) every layer keeps its four
   // dY until the loop is over and all of them run as one launch.
-  const bool each = !c->grouped_dw;
+  const bool each = !c->grouped_dw && !c->list_dw;
   for (int l = nl - 1; l >= 0; l--) {
     // feed-forward block: x_next = xm + gelu(b W1) W2
     if (each) RUN(gemm(desc_dw(c, w, w.gl[l], ff, w.dy2[l], d, ff, d, T, w.grad + L.W2[l]), mf, st));
@@ -252,7 +264,10 @@ int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot, float* loss_ou
     RUN(rmsnorm_bwd(w.dtmp, w.x[l], w.rstd1[l], w.theta + L.g1[l], w.dxb, w.dxa, l ? w.dy2[l - 1] : w.dx_lp, c->bf,
                     nullptr, w.partial + 2 * l * pset, T, d, ln, st));
   }
-  if (!each) RUN(dw_group_launch(w.dw_probs_dev, w.dw_items_dev, w.dw_split_dev, w.dw_plan, w.dw_partial, st));
+  if (c->grouped_dw) RUN(dw_group_launch(w.dw_probs_dev, w.dw_items_dev, w.dw_split_dev, w.dw_plan, w.dw_partial, st));
+  if (c->list_dw)
+    RUN(c->bf ? gemm_mfma_any_dw_list(w.dw_probs.data(), (int)w.dw_probs.size(), T, st)
+              : gemm_mfma_f32_dw_list(w.dw_probs.data(), (int)w.dw_probs.size(), T, st));
   RUN(rmsnorm_dg_sum(w.partial, w.grad + L.g1[0], T, d, 2 * nl + 1, st));
   // w.dtmp (T x d floats) is free again here: scratch for the embedding gradient's chunk partials
   RUN(embed_bwd(tok, w.sort_offset + (int64_t)slot * (V + 1), w.sort_pos + (int64_t)slot * T, w.dxa,

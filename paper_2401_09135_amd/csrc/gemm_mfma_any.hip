@@ -121,17 +121,13 @@ __device__ __forceinline__ void any_epilogue(const GemmDesc& g, int m, int col, 
   }
 }
 
+// the tile whose first element is (m0, n0)
 template <int BM, int BN, int BK, int WM, int WN, int WK, int AL, int BL>
-__global__ __launch_bounds__(64 * WM * WN * WK, 2) void gemm_any_kernel(GemmDesc g, int tiles_n) {
+__device__ __forceinline__ void any_tile(const GemmDesc& g, const int m0, const int n0, char* lds_any) {
   typedef AnyTile<BM, BN, BK, WM, WN, WK, AL, BL> TL;
   constexpr int TM = TL::TM, TN = TL::TN, NS = BK / 16 / WK;   // 16-wide steps of one wavefront per slice
-  extern __shared__ __attribute__((aligned(16))) char lds_any[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, hf = lane >> 5, lr = lane & 31;
   const int wk = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
-  // every XCD gets a contiguous run of tiles (columns fastest): neighbours share operand panels in its L2
-  const int ntiles = gridDim.x, per = ntiles / 8, id = blockIdx.x;
-  const int tile = id < per * 8 ? (id % 8) * per + id / 8 : id;
-  const int m0 = tile / tiles_n * BM, n0 = tile % tiles_n * BN;
   const bf16* A = reinterpret_cast<const bf16*>(g.A) + (AL == 0 ? m0 * g.lda : (int64_t)m0);
   const bf16* B = reinterpret_cast<const bf16*>(g.B) + (BL == 1 ? n0 * g.ldb : (int64_t)n0);
   const int lim_m = g.M - m0, lim_n = g.N - n0;
@@ -231,6 +227,33 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void gemm_any_kernel(GemmDesc
   }
 }
 
+// every XCD gets a contiguous run of tiles (columns fastest): neighbours share operand panels in its L2
+__device__ __forceinline__ int xcd_tile() {
+  const int ntiles = gridDim.x, per = ntiles / 8, id = blockIdx.x;
+  return id < per * 8 ? (id % 8) * per + id / 8 : id;
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int WK, int AL, int BL>
+__global__ __launch_bounds__(64 * WM * WN * WK, 2) void gemm_any_kernel(GemmDesc g, int tiles_n) {
+  extern __shared__ __attribute__((aligned(16))) char lds_any[];
+  const int tile = xcd_tile();
+  any_tile<BM, BN, BK, WM, WN, WK, AL, BL>(g, tile / tiles_n * BM, tile % tiles_n * BN, lds_any);
+}
+
+// X^T dY of a list of products
+template <int BM, int BN, int BK, int WM, int WN, int WK>
+__global__ __launch_bounds__(64 * WM * WN * WK, 2) void gemm_any_dw_list_kernel(DwList list) {
+  extern __shared__ __attribute__((aligned(16))) char lds_any[];
+  const int id = xcd_tile();
+  const DwList::Product& p = list.p[list.find(id)];
+  GemmDesc g;
+  g.A = p.A; g.B = p.B; g.C = p.C; g.M = p.M; g.N = p.N; g.K = list.K;
+  g.lda = p.M; g.ldb = p.N; g.ldc = p.N; g.epi = EPI_STORE; g.c_bf16 = 0;
+  g.R = nullptr; g.C2 = nullptr; g.U = nullptr; g.ldr = 0;
+  const int tile = id - p.tile0;
+  any_tile<BM, BN, BK, WM, WN, WK, 1, 0>(g, tile / p.tiles_n * BM, tile % p.tiles_n * BN, lds_any);
+}
+
 template <int BM, int BN, int BK, int WM, int WN, int WK, int AL, int BL>
 int launch_any(const GemmDesc& g, hipStream_t st) {
   typedef AnyTile<BM, BN, BK, WM, WN, WK, AL, BL> TL;
@@ -243,6 +266,24 @@ int launch_any(const GemmDesc& g, hipStream_t st) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(TL::NT), TL::LDS_BYTES, st, g, tiles_n);
   ALS_CHECK_LAUNCH();
+  return ALS_OK;
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int WK>
+int launch_dw_list(const DwProblem* probs, int n, int K, hipStream_t st) {
+  typedef AnyTile<BM, BN, BK, WM, WN, WK, 1, 0> TL;
+  auto kern = gemm_any_dw_list_kernel<BM, BN, BK, WM, WN, WK>;
+  static std::atomic<bool> attr_set{false};  // the call is idempotent: a race only repeats it
+  if (!attr_set.load(std::memory_order_acquire)) {
+    ALS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES));
+    attr_set.store(true, std::memory_order_release);
+  }
+  DwList list;
+  for (int i = 0, ntiles; i < n; ) {
+    i += list.fill(probs + i, n - i, K, BM, BN, &ntiles);
+    hipLaunchKernelGGL(kern, dim3(ntiles), dim3(TL::NT), TL::LDS_BYTES, st, list);
+    ALS_CHECK_LAUNCH();
+  }
   return ALS_OK;
 }
 
@@ -273,6 +314,15 @@ int gemm_mfma_any(const GemmDesc& g, hipStream_t st) {
   if (g.epi == EPI_RESID && g.c_bf16) return set_error(ALS_ERR_INVALID, "gemm: residual output must be fp32");
   if (g.a_layout == 1) return pick<1, 0>(g, st);
   return g.b_layout == 0 ? pick<0, 0>(g, st) : pick<0, 1>(g, st);
+}
+
+// the tile by the same rule as for one product (pick()), on the tiles of all
+int gemm_mfma_any_dw_list(const DwProblem* probs, int n, int K, hipStream_t st) {
+  if (n <= 0) return ALS_OK;
+  if (dw_list_tiles(probs, n, 128, 128) >= 256) return launch_dw_list<128, 128, 64, 2, 2, 1>(probs, n, K, st);
+  if (dw_list_tiles(probs, n, 128, 64) >= 192) return launch_dw_list<128, 64, 128, 2, 2, 2>(probs, n, K, st);
+  if (dw_list_tiles(probs, n, 32, 32) > (K >= 1024 ? 512 : 256)) return launch_dw_list<64, 64, 128, 2, 2, 2>(probs, n, K, st);
+  return launch_dw_list<32, 32, 256, 1, 1, 8>(probs, n, K, st);
 }
 
 }  // namespace als

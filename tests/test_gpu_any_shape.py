@@ -144,6 +144,30 @@ def test_ragged_bf16_models_match_the_generic_products(kw):
     assert _rel(g, rg) < 1.1 * _rel(gg, rg)
 
 
+@pytest.mark.parametrize("dtype,kw", [("f32", dict(L=17, S=7, B=1)),                              # more products than one launch takes
+                                      ("f32", dict(L=2, d=192, h=3, ff=320, V=333, S=31, B=2)),       # 32 x 32 tiles, 4 shares of K
+                                      ("f32", dict(L=1, d=128, h=2, ff=192, V=130, S=103, B=5)),      # 8 shares
+                                      ("f32", dict(L=2, d=512, h=8, ff=1024, V=70, S=33, B=1)),       # 64 x 64
+                                      ("f32", dict(L=2, d=512, h=8, ff=2048, V=700, S=17, B=1)),      # 128 x 128
+                                      ("bf16", dict(L=17, S=7, B=1)),
+                                      ("bf16", dict(L=1, d=64, ff=192, V=131, S=31, B=3)),            # 32 x 32
+                                      ("bf16", dict(L=1, d=256, h=4, ff=640, V=333, S=65, B=2)),      # 64 x 64
+                                      ("bf16", dict(L=3, d=320, h=5, ff=1280, V=133, S=33, B=1)),     # 128 x 64
+                                      ("bf16", dict(L=2, d=512, h=8, ff=2048, V=700, S=17, B=1))])    # 128 x 128
+def test_weight_gradients_as_one_list(dtype, kw):
+    """Flag bit 1 keeps one launch per product: the same operands, sums in the order of another tile at most, so fp32 gradients
+    agree to a few roundings of their sums over the tokens (2^-24 sqrt(515) 4 < 1e-5)."""
+    w = _model(**kw)
+    w["dtype"] = dtype
+    tok = I.TokenStream(1, 0, w["B"], w["S"], w["V"]).take(1)[0]
+    _, loss, g = _loss_grad(w, tok)
+    _, loss1, g1 = _loss_grad(w, tok, flags=2)
+    assert loss == loss1
+    a, b = lm.views(g, w), lm.views(g1, w)
+    for name in a:
+        assert _rel(a[name], b[name]) < 1e-5, name
+
+
 @pytest.mark.parametrize("B,S,h,dh", [(33, 1, 2, 32), (33, 16, 2, 64), (33, 17, 2, 32),   # one tile, one and one row
                                       (1, 33, 1, 64), (1, 63, 1, 32), (2, 129, 3, 64),     # last tile of 1, 15, 1 rows; idle wavefronts
                                       (16, 272, 16, 32), (9, 1009, 8, 64),                 # two row blocks per wavefront
