@@ -144,6 +144,28 @@ def test_ragged_bf16_models_match_the_generic_products(kw):
     assert _rel(g, rg) < 1.1 * _rel(gg, rg)
 
 
+@pytest.mark.parametrize("V,B,S", [(3, 1, 1), (1000, 1, 63), (4094, 3, 341),     # one wavefront; V + 1 entries in one run of 4096
+                                   (4097, 16, 1000), (4096, 16, 1024),            # 16000 and 16384 positions, all of the tile
+                                   (32767, 2, 512), (32768, 2, 512)])             # the largest vocabulary in LDS and the next
+def test_token_order_in_lds(V, B, S):
+    test_token_order_of_the_embedding_gradient(V, B, S)
+
+
+@pytest.mark.parametrize("V", [64, 65, 71, 2048, 2049, 8192, 8193, 8200, 32767, 32768, 32769])   # whole and partial groups of 8; 256 and 1024 threads; three passes
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_cross_entropy_of_any_vocabulary(V, dtype):
+    """Loss and the gradients that come straight from dlogits against the oracle: fp32 sums of V values (1e-5), bf16 logits and dlogits as
+    in the other bf16 tests (their distance from fp32 is that of the roundings, 1e-2 of a gradient)."""
+    w = _model(V=V, S=5, B=3)
+    w["dtype"] = dtype
+    tok = I.TokenStream(1, 0, 3, 5, V).take(1)[0]
+    theta0, loss, g = _loss_grad(w, tok)
+    rloss, rg = lm.loss_and_grad(theta0, tok, w)
+    assert abs(loss - rloss) < (1e-5 if dtype == "f32" else 1e-3) * abs(rloss)
+    assert _rel(lm.views(g, w)["Wout"], lm.views(rg, w)["Wout"]) < (1e-5 if dtype == "f32" else 2e-2)
+    assert _rel(lm.views(g, w)["gf"], lm.views(rg, w)["gf"]) < (1e-5 if dtype == "f32" else 2e-2)
+
+
 @pytest.mark.parametrize("dtype,kw", [("f32", dict(L=17, S=7, B=1)),                              # more products than one launch takes
                                       ("f32", dict(L=2, d=192, h=3, ff=320, V=333, S=31, B=2)),       # 32 x 32 tiles, 4 shares of K
                                       ("f32", dict(L=1, d=128, h=2, ff=192, V=130, S=103, B=5)),      # 8 shares
