@@ -3,6 +3,7 @@
 // sync() step (pseudo-gradient, Delayed Nesterov of Alg. 3, restart of Alg. 2) ordered
 // against the workers with events.
 #include "common.h"
+#include <algorithm>
 #include <math.h>
 #include <string.h>
 #include <mutex>
@@ -76,8 +77,12 @@ void carve(als_ctx* c, Carver& cv) {
   int64_t BhS = (int64_t)g.batch * g.n_heads * g.seq_len;
   c->theta = cv.f32(P); c->m = cv.f32(P); c->delta = cv.f32(P);
   c->w.resize(g.n_workers);
-  c->grouped_dw = bf && !(g.flags & 1) && !(g.flags & 2) && g.n_layers > 0 && dw_group_supported((int)d, (int)(3 * da), (int)T, d, 3 * da) &&
+  const bool groupable = bf && !(g.flags & 1) && g.n_layers > 0 && dw_group_supported((int)d, (int)(3 * da), (int)T, d, 3 * da) &&
                   dw_group_supported((int)da, (int)d, (int)T, da, d) && dw_group_supported((int)d, (int)ff, (int)T, d, ff);
+  c->grouped_dw = groupable && !(g.flags & 2);
+  // Scratch of the output matrix's input gradient: 64 MiB hold the partials of a round of 256 x 256 tiles.  The same with and
+  // without the grouped launch, so that the product is split, and rounds, the same way.
+  const size_t head_bytes = std::min((size_t)g.n_layers * T * (2 * d + ff + 3 * da) * 2, (size_t)64 << 20);
   // Products without an aligned kernel: each fills a part of the chip (600 tokens, 320 x 1280: 100 tiles of 64 x 64) and costs
   // a launch.  17 products of four layers and the head took 199 us in fp32 mode (1024 tokens, d = 256, V = 2000) and 137 in bf16
   // (600 tokens, d = 320, V = 5003); as one list 107 and 50.  Every layer keeps its four dY for it: up to 256 MiB, beyond
@@ -123,6 +128,7 @@ void carve(als_ctx* c, Carver& cv) {
     w.dw_probs_dev = nullptr; w.dw_items_dev = nullptr; w.dw_split_dev = nullptr; w.dw_partial = nullptr;
     w.dw_plan = DwPlan{0, 0, 0, 0.0};
     w.head_ws = w.splitk_ws; w.head_ws_bytes = w.splitk_bytes;
+    if (groupable && !c->grouped_dw) { w.head_ws = (float*)cv.take(head_bytes); w.head_ws_bytes = head_bytes; }
     w.dw_probs.clear();
     if (c->grouped_dw || c->list_dw)
       for (int l = 0; l < L; l++) {
@@ -147,7 +153,7 @@ void carve(als_ctx* c, Carver& cv) {
       // The input gradient of the output matrix runs before anything is written to these: until then they are its
       // split-K scratch, one block from the first to the last.
       w.head_ws = (float*)w.dy2[0];
-      w.head_ws_bytes = (size_t)((char*)w.dyqkv[L - 1] - (char*)w.dy2[0]) + (size_t)T * 3 * da * 2;
+      w.head_ws_bytes = head_bytes;
       w.dw_items.resize(dw_plan_max_items(n_tiles));
       w.dw_split.resize(dw_plan_max_split(n_tiles) + 1);
       w.dw_plan = dw_group_plan(w.dw_probs.data(), (int)w.dw_probs.size(), (int)T, w.dw_items.data(), w.dw_split.data());
