@@ -1219,8 +1219,8 @@ __global__ __launch_bounds__(256) void cross_entropy_kernel(const IT* logits, co
 
 // Same, reading the row once: each thread keeps up to 32 logits in registers, so a block of BS
 // threads covers V <= 32 BS.  Rows of an odd V start at any element: 16-byte accesses at element alignment, and the
-// last, partial group of 8 one by one (EDGE).  600 rows of 5003 in bf16: 19 us with three scalar passes, 8.6 now; 1024 rows of
-// 2000 in fp32: 10.4 and 6.6.
+// last, partial group of 8 one by one (EDGE).  600 rows of 5003 in bf16: 19 us with three scalar passes, 8.6
+// now.  fp32 mode keeps the three passes (1024 rows of 2000: 10.4 us, 6.6 this way) and their order of sums.
 struct __attribute__((packed, aligned(2))) ce_b8 { bf16x8 v; };
 struct __attribute__((packed, aligned(4))) ce_f4 { f32x4 v; };
 template <typename IT, typename OT, int BS, bool EDGE>
@@ -1316,7 +1316,7 @@ int cross_entropy(const void* logits, int logits_bf16, const int32_t* tok, float
   int T = B * S;
   float invT = 1.0f / (float)T;
   if (logits_bf16 && !dl_bf16) return set_error(ALS_ERR_INVALID, "cross_entropy: bf16 logits need bf16 dlogits");
-  if (V <= 32 * 1024) {   // longer rows do not fit the registers of a block
+  if (dl_bf16 && V <= 32 * 1024) {   // longer rows do not fit the registers of a block
     const bool big = V > 32 * 256, edge = V % 8 != 0;
 #define ALS_CE_LAUNCH(IT, OT, BS)                                                                                \
   do {                                                                                                           \
@@ -1328,8 +1328,7 @@ int cross_entropy(const void* logits, int logits_bf16, const int32_t* tok, float
                          tok, loss_row, (OT*)dlogits, S, V, invT);                                               \
   } while (0)
     if (logits_bf16) { if (big) ALS_CE_LAUNCH(bf16, bf16, 1024); else ALS_CE_LAUNCH(bf16, bf16, 256); }
-    else if (dl_bf16) { if (big) ALS_CE_LAUNCH(float, bf16, 1024); else ALS_CE_LAUNCH(float, bf16, 256); }
-    else { if (big) ALS_CE_LAUNCH(float, float, 1024); else ALS_CE_LAUNCH(float, float, 256); }
+    else { if (big) ALS_CE_LAUNCH(float, bf16, 1024); else ALS_CE_LAUNCH(float, bf16, 256); }
 #undef ALS_CE_LAUNCH
     ALS_CHECK_LAUNCH();
     return ALS_OK;
