@@ -164,11 +164,12 @@ int attention_bwd_mfma(const void* qkv, const void* o, const void* d_o, const fl
                        float* dscratch, void* dqkv, int B, int S, int h, int dh, hipStream_t st);
 
 // ---- elementwise / reductions ----------------------------------------------------------------
-int embed_fwd(const int32_t* tok, const float* E, const float* Ppos, float* x, int B, int S, int d,
-              int V, hipStream_t st);
 // center = 0: RMSNorm ; 1: LayerNorm with gain and no bias
 int rmsnorm_fwd(const float* x, const float* g, void* y, float* rstd, int T, int d, float eps,
                 int out_bf16, int center, hipStream_t st);
+// the same for the rows E[tok] + Ppos, which are also written to x
+int embed_rmsnorm_fwd(const int32_t* tok, const float* E, const float* Ppos, float* x, const float* g, void* y, float* rstd, int B,
+                      int S, int d, int V, float eps, int out_bf16, int center, hipStream_t st);
 // dx_out = (dx_in ? dx_in : 0) + rmsnorm_backward(dy); optional low-precision copy of dx_out;
 // dg = sum over rows of dy * xhat (uses partial[nblk*d] scratch, nblk = rmsnorm_bwd_blocks()).
 // With dg == nullptr only the partials are left, for one rmsnorm_dg_sum() over nset consecutive

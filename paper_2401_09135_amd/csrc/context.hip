@@ -199,9 +199,9 @@ int forward(als_ctx* c, Worker& w, const int32_t* tok) {
   const int ln = g.norm_kind == ALS_NORM_LAYER;  // LayerNorm (gain, no bias) instead of RMSNorm
   bool mf = c->allow_mfma;
   float eps = (float)g.norm_eps;
-  RUN(embed_fwd(tok, w.theta + L.E, w.theta + L.Ppos, w.x[0], B, S, d, V, st));
+  RUN(embed_rmsnorm_fwd(tok, w.theta + L.E, w.theta + L.Ppos, w.x[0], w.theta + L.g1[0], w.a[0], w.rstd1[0], B, S, d, V, eps, c->bf, ln, st));
   for (int l = 0; l < g.n_layers; l++) {
-    RUN(rmsnorm_fwd(w.x[l], w.theta + L.g1[l], w.a[l], w.rstd1[l], T, d, eps, c->bf, ln, st));
+    if (l) RUN(rmsnorm_fwd(w.x[l], w.theta + L.g1[l], w.a[l], w.rstd1[l], T, d, eps, c->bf, ln, st));
     RUN(gemm(desc(c, w.a[l], 0, d, wptr(c, w, L.Wqkv[l]), 0, 3 * da, T, 3 * da, d, w.qkv[l], 3 * da, true), mf, st));
     if (mf && attention_mfma_supported(S, dh, c->bf))
       RUN(attention_fwd_mfma(w.qkv[l], w.o[l], w.lse[l], B, S, h, dh, st));

@@ -395,33 +395,6 @@ int cast_copy(const float* src, void* dst, int64_t n, int dst_bf16, hipStream_t 
   return restart_copy(src, (float*)dst, nullptr, nullptr, n, st);
 }
 
-// ------------------------------------------------------------------------------------------
-// Embedding: x[b*S+s,:] = E[tok[b,s],:] + Ppos[s,:]   (tokens are [B,S+1]; inputs are s < S)
-// ------------------------------------------------------------------------------------------
-__global__ void embed_fwd_kernel(const int32_t* __restrict__ tok, const float* __restrict__ E,
-                                 const float* __restrict__ Ppos, float* __restrict__ x, int S,
-                                 int d, int V) {
-  int t = blockIdx.x;
-  int b = t / S, s = t % S;
-  int id = tok[(int64_t)b * (S + 1) + s];
-  id = id < 0 ? 0 : (id >= V ? V - 1 : id);  // out-of-range ids are clamped, never dereferenced
-  const float4* e = reinterpret_cast<const float4*>(E + (int64_t)id * d);
-  const float4* p = reinterpret_cast<const float4*>(Ppos + (int64_t)s * d);
-  float4* o = reinterpret_cast<float4*>(x + (int64_t)t * d);
-  for (int c = threadIdx.x; c < d / 4; c += blockDim.x) {
-    float4 a = e[c], q = p[c];
-    o[c] = make_float4(a.x + q.x, a.y + q.y, a.z + q.z, a.w + q.w);
-  }
-}
-
-int embed_fwd(const int32_t* tok, const float* E, const float* Ppos, float* x, int B, int S, int d,
-              int V, hipStream_t st) {
-  int threads = d / 4 < 256 ? (d / 4 < 64 ? 64 : d / 4) : 256;
-  hipLaunchKernelGGL(embed_fwd_kernel, dim3(B * S), dim3(threads), 0, st, tok, E, Ppos, x, S, d, V);
-  ALS_CHECK_LAUNCH();
-  return ALS_OK;
-}
-
 // Embedding gradient without float atomics, so that a step is bit-reproducible.
 // (1) embed_sort: one workgroup per step orders the T input positions by token id, equal tokens in
 //     position order: offset[v] .. offset[v+1] delimit the positions holding token v inside pos[].
@@ -952,9 +925,12 @@ int embed_bwd(const int32_t* tok, const int32_t* offset, const int32_t* pos, con
 //   LayerNorm (CENTER = true):  y = (x - mean(x)) * rsqrt(mean((x - mean(x))^2) + eps) * g   (no bias)
 // rstd[row] is saved for the backward pass (which recomputes the mean from the row it reads).
 // ------------------------------------------------------------------------------------------
+// EMBED: the rows are the embeddings, x[b*S+s,:] = E[tok[b,s],:] + Ppos[s,:] (tokens are [B,S+1]; inputs are s < S), formed and
+// written here on the way into the first norm: one launch and one pass over x less than on their own.
+struct EmbedArgs { const int32_t* tok; const float* E; const float* Ppos; float* x; int S, V; };
 #define RMS_MAXD4 4  // float4 slots per lane: d <= 1024
-template <typename OT, bool CENTER>
-__global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const float* __restrict__ x,
+template <typename OT, bool CENTER, bool EMBED>
+__global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const float* __restrict__ x, EmbedArgs em,
                                                           const float* __restrict__ g,
                                                           OT* __restrict__ y,
                                                           float* __restrict__ rstd, int T, int d,
@@ -964,6 +940,14 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const float* __restric
   if (row >= T) return;
   const int d4 = d / 4;
   const float4* xr = reinterpret_cast<const float4*>(x + (int64_t)row * d);
+  const float4* pr = nullptr;
+  if (EMBED) {
+    const int b = row / em.S, s = row % em.S;
+    int id = em.tok[(int64_t)b * (em.S + 1) + s];
+    id = id < 0 ? 0 : (id >= em.V ? em.V - 1 : id);  // out-of-range ids are clamped, never dereferenced
+    xr = reinterpret_cast<const float4*>(em.E + (int64_t)id * d);
+    pr = reinterpret_cast<const float4*>(em.Ppos + (int64_t)s * d);
+  }
   const float4* g4 = reinterpret_cast<const float4*>(g);
   float4 v[RMS_MAXD4];  // the row is read once and stays in registers (d <= 1024)
   float sum = 0.0f;
@@ -971,6 +955,11 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const float* __restric
   for (int s = 0; s < RMS_MAXD4; s++) {
     int c = lane + 64 * s;
     v[s] = c < d4 ? xr[c] : make_float4(0.f, 0.f, 0.f, 0.f);
+    if (EMBED && c < d4) {
+      const float4 q = pr[c];
+      v[s] = make_float4(v[s].x + q.x, v[s].y + q.y, v[s].z + q.z, v[s].w + q.w);
+      reinterpret_cast<float4*>(em.x + (int64_t)row * d)[c] = v[s];
+    }
     sum += (v[s].x + v[s].y) + (v[s].z + v[s].w);
   }
   const float mean = CENTER ? wave_sum(sum) / (float)d : 0.0f;
@@ -997,19 +986,30 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const float* __restric
   }
 }
 
-int rmsnorm_fwd(const float* x, const float* g, void* y, float* rstd, int T, int d, float eps,
-                int out_bf16, int center, hipStream_t st) {
+template <bool EMBED>
+static int norm_fwd(const float* x, const EmbedArgs& em, const float* g, void* y, float* rstd, int T, int d, float eps,
+                    int out_bf16, int center, hipStream_t st) {
   if (d > 256 * RMS_MAXD4 || d % 4) return set_error(ALS_ERR_INVALID, "rmsnorm_fwd: d unsupported");
   dim3 grid((T + 3) / 4), block(256);
   if (out_bf16) {
-    if (center) hipLaunchKernelGGL((rmsnorm_fwd_kernel<bf16, true>), grid, block, 0, st, x, g, (bf16*)y, rstd, T, d, eps);
-    else hipLaunchKernelGGL((rmsnorm_fwd_kernel<bf16, false>), grid, block, 0, st, x, g, (bf16*)y, rstd, T, d, eps);
+    if (center) hipLaunchKernelGGL((rmsnorm_fwd_kernel<bf16, true, EMBED>), grid, block, 0, st, x, em, g, (bf16*)y, rstd, T, d, eps);
+    else hipLaunchKernelGGL((rmsnorm_fwd_kernel<bf16, false, EMBED>), grid, block, 0, st, x, em, g, (bf16*)y, rstd, T, d, eps);
   } else {
-    if (center) hipLaunchKernelGGL((rmsnorm_fwd_kernel<float, true>), grid, block, 0, st, x, g, (float*)y, rstd, T, d, eps);
-    else hipLaunchKernelGGL((rmsnorm_fwd_kernel<float, false>), grid, block, 0, st, x, g, (float*)y, rstd, T, d, eps);
+    if (center) hipLaunchKernelGGL((rmsnorm_fwd_kernel<float, true, EMBED>), grid, block, 0, st, x, em, g, (float*)y, rstd, T, d, eps);
+    else hipLaunchKernelGGL((rmsnorm_fwd_kernel<float, false, EMBED>), grid, block, 0, st, x, em, g, (float*)y, rstd, T, d, eps);
   }
   ALS_CHECK_LAUNCH();
   return ALS_OK;
+}
+
+int rmsnorm_fwd(const float* x, const float* g, void* y, float* rstd, int T, int d, float eps,
+                int out_bf16, int center, hipStream_t st) {
+  return norm_fwd<false>(x, EmbedArgs{}, g, y, rstd, T, d, eps, out_bf16, center, st);
+}
+
+int embed_rmsnorm_fwd(const int32_t* tok, const float* E, const float* Ppos, float* x, const float* g, void* y, float* rstd, int B,
+                      int S, int d, int V, float eps, int out_bf16, int center, hipStream_t st) {
+  return norm_fwd<true>(nullptr, EmbedArgs{tok, E, Ppos, x, S, V}, g, y, rstd, B * S, d, eps, out_bf16, center, st);
 }
 
 // Backward: xhat = x rstd (RMSNorm) or (x - mean x) rstd (LayerNorm) ; dxhat = dy g ;
