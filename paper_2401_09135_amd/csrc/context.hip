@@ -22,7 +22,8 @@ struct Worker {
   void* xf; float* rstdf; float* logits; void* dlogits; float* loss_row;  // logits: fp32 mode only
   float *dxa, *dxb, *dtmp, *Dbuf, *partial;
   void *dx_lp, *dff, *d_o, *dqkv;
-  float* losses_dev; float* losses_host;
+  // pinned; a step writes its loss there itself: a copy per call cost the host as much as several launches
+  float* losses_host; float* losses_dev;   // losses_dev: its address on the device
   int32_t *sort_offset, *sort_rank, *sort_pos;
   float* splitk_ws; size_t splitk_bytes;
   float* head_ws; size_t head_ws_bytes;   // split-K scratch of the output matrix's input gradient
@@ -112,7 +113,6 @@ void carve(als_ctx* c, Carver& cv) {
     w.partial = cv.f32((int64_t)(2 * g.n_layers + 1) * rmsnorm_bwd_blocks((int)T) * d);
     w.dx_lp = cv.act(T * d, bf); w.dff = cv.act(T * ff, bf); w.d_o = cv.act(T * da, bf);
     w.dqkv = cv.act(T * 3 * da, bf);
-    w.losses_dev = cv.f32(g.max_local_steps);
     w.sort_offset = (int32_t*)cv.take((size_t)g.max_local_steps * (V + 1) * 4);
     w.sort_rank = (int32_t*)cv.take((size_t)g.max_local_steps * T * 4);
     w.sort_pos = (int32_t*)cv.take((size_t)g.max_local_steps * T * 4);
@@ -352,7 +352,8 @@ extern "C" int als_init(const als_config* cfg, void* arena, size_t arena_bytes, 
     w.adam_n = 0; w.last_n = 0; w.t_restart = 0;
     if (hipEventCreateWithFlags(&w.done_ev, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&w.ready_ev, hipEventDisableTiming) != hipSuccess ||
-        hipHostMalloc((void**)&w.losses_host, (size_t)cfg->max_local_steps * 4, hipHostMallocDefault) != hipSuccess)
+        hipHostMalloc((void**)&w.losses_host, (size_t)cfg->max_local_steps * 4, hipHostMallocDefault) != hipSuccess ||
+        hipHostGetDevicePointer((void**)&w.losses_dev, w.losses_host, 0) != hipSuccess)
       return fail(set_error(ALS_ERR_HIP, "als_init: event or pinned-buffer creation failed"));
     if (hipMemsetAsync(w.adam_m, 0, (size_t)P * 4, w.stream) != hipSuccess ||
         hipMemsetAsync(w.adam_v, 0, (size_t)P * 4, w.stream) != hipSuccess ||
@@ -409,8 +410,6 @@ extern "C" int als_worker_local_steps(als_ctx* ctx, int worker, int n_steps, con
     RUN(adamw(w.theta, w.grad, w.adam_m, w.adam_v, w.lp, ctx->L.P, ctx->L.P_decay, a, w.stream));
   }
   w.last_n = n_steps;
-  if (n_steps > 0)
-    ALS_HIP(hipMemcpyAsync(w.losses_host, w.losses_dev, (size_t)n_steps * 4, hipMemcpyDeviceToHost, w.stream));
   ALS_HIP(hipEventRecord(w.done_ev, w.stream));
   if (loss_host) {
     ALS_HIP(hipStreamSynchronize(w.stream));
@@ -429,7 +428,6 @@ extern "C" int als_worker_loss_grad(als_ctx* ctx, int worker, const int32_t* tok
                  w.sort_pos, w.stream));
   RUN(forward(ctx, w, tokens));
   RUN(backward(ctx, w, tokens, 0, w.losses_dev));
-  ALS_HIP(hipMemcpyAsync(w.losses_host, w.losses_dev, 4, hipMemcpyDeviceToHost, w.stream));
   ALS_HIP(hipEventRecord(w.done_ev, w.stream));
   ALS_HIP(hipStreamSynchronize(w.stream));
   *loss_host = w.losses_host[0];
