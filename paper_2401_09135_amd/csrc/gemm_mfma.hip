@@ -17,7 +17,8 @@
 // This file holds that kernel (gemm_mfma_kernel), the launchers, the choice of kernel and split
 // for a product, and the measurement hooks.  Products with at least one whole 256 x 256 tile in
 // each direction go to the kernels of gemm_pingpong.h (one workgroup of two wavefront groups in
-// alternating memory / compute phases per CU); gemm_mfma_common.h has what the kernels share
+// alternating memory / compute phases per CU), those of at most a round of 128 x 128 tiles to gemm_mfma_deep.hip;
+// gemm_mfma_common.h has what the kernels share
 // (LDS tile geometry, fragment reads, the per-wavefront epilogue).
 //
 // Lane layouts of the MFMA (wavefront lane l, 64 lanes):
