@@ -375,6 +375,16 @@ def k_gemm_ex(A, B, C_out, M, N, K, a_layout=0, b_layout=0, use_mfma=False, epi=
                              ws.numel() * ws.element_size() if ws is not None else 0, _stream_handle(stream)))
 
 
+lib.als_k_gemm_route.argtypes = [C.c_int] * 9 + [C.c_size_t, C.c_char_p, C.c_int]
+
+
+def gemm_route(M, N, K, a_layout=0, b_layout=0, in_dtype=ALS_DTYPE_BF16, out_dtype=ALS_DTYPE_F32, epi=0, flags=0, ws_bytes=0) -> str:
+    """The kernel and tile that a worker step takes for a product (host only)."""
+    buf = C.create_string_buffer(64)
+    _check(lib.als_k_gemm_route(M, N, K, a_layout, b_layout, in_dtype, out_dtype, epi, flags, ws_bytes, buf, 64))
+    return buf.value.decode()
+
+
 def k_attention_fwd(qkv, o, lse, B, S, h, dh, use_mfma=False, stream=None):
     _check(lib.als_k_attention_fwd(qkv.data_ptr(), o.data_ptr(), lse.data_ptr(), B, S, h, dh, _dt(qkv),
                                    int(bool(use_mfma)), _stream_handle(stream)))

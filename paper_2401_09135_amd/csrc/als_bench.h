@@ -6,6 +6,7 @@
 #ifndef ALS_BENCH_H
 #define ALS_BENCH_H
 
+#include <stddef.h>
 #include <stdint.h>
 
 #ifdef __cplusplus
@@ -37,6 +38,10 @@ int als_k_set_gemm_tile(int bm, int bn, int nbuf);
  * workspace holds.  Errors (ALS_ERR_INVALID): null pointers, unsupported shapes. */
 int als_k_gemm_dw_grouped_plan(int n, const int* M, const int* N, int K, int max_items, int32_t* items_out,
                                int max_split, int32_t* split_out, int32_t* counts_out);
+/* Host only (no GPU call): the kernel and tile that a worker step takes for a product, as text, so that a CPU test can look at the
+ * borders of the dispatch.  Arguments as als_k_gemm_ex, operands taken as 256-byte aligned; flags as als_config.flags. */
+int als_k_gemm_route(int M, int N, int K, int a_layout, int b_layout, int in_dtype, int out_dtype, int epi, int flags,
+                     size_t ws_bytes, char* out, int out_len);
 
 #ifdef __cplusplus
 }

@@ -60,6 +60,7 @@ struct GemmDesc {
   float* ws; size_t ws_bytes;        // scratch for split-K partials (may be null)
   int workers;                       // how many workers run such products side by side (0: one)
 };
+inline int64_t gemm_tiles(int M, int N, int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
 int gemm_generic(const GemmDesc& g, hipStream_t st);
 // fp32 operands and results on the fp32 matrix instruction (gemm_mfma_f32.hip): any shape, layout and epilogue
 bool gemm_mfma_f32_supported(const GemmDesc& g);
@@ -73,6 +74,11 @@ int gemm_mfma_any(const GemmDesc& g, hipStream_t st);
 int gemm_mfma_deep(const GemmDesc& g, int tile, hipStream_t st);
 // picks the MFMA kernel when allowed and supported
 int gemm(const GemmDesc& g, bool allow_mfma, hipStream_t st);
+// the name of the kernel and tile that each of these takes for a product (no GPU call)
+const char* gemm_mfma_any_route(const GemmDesc& g);
+const char* gemm_mfma_f32_route(const GemmDesc& g);
+void gemm_mfma_route(const GemmDesc& g, char* out, int out_len);
+void gemm_route(const GemmDesc& g, bool allow_mfma, char* out, int out_len);
 
 // All weight gradients of a backward pass (X^T dY over the batch's tokens, bf16 operands, fp32
 // results) as ONE launch of the 256 x 256 MFMA kernel.  The host turns the list of products into
@@ -140,7 +146,7 @@ struct DwList {
 };
 inline int64_t dw_list_tiles(const DwProblem* probs, int n, int bm, int bn) {
   int64_t t = 0;
-  for (int i = 0; i < n; i++) t += (int64_t)((probs[i].M + bm - 1) / bm) * ((probs[i].N + bn - 1) / bn);
+  for (int i = 0; i < n; i++) t += gemm_tiles(probs[i].M, probs[i].N, bm, bn);
   return t;
 }
 int gemm_mfma_any_dw_list(const DwProblem* probs, int n, int K, hipStream_t st);   // bf16 operands

@@ -630,16 +630,25 @@ extern "C" int als_k_adamw(float* theta, const float* grad, float* m, float* v, 
   return adamw(theta, grad, m, v, (bf16*)bf16_out, P, P_decay, a, (hipStream_t)stream);
 }
 
-extern "C" int als_k_gemm(const void* A, const void* B, void* C, int M, int N, int K, int a_layout,
-                          int b_layout, int in_dtype, int out_dtype, int use_mfma, void* ws_dev,
-                          size_t ws_bytes, void* stream) {
-  if (!A || !B || !C) return set_error(ALS_ERR_INVALID, "null argument");
+namespace {
+// the product of the als_k_gemm* entry points: operands without padding
+GemmDesc plain_desc(const void* A, const void* B, void* C, int M, int N, int K, int a_layout, int b_layout, int in_dtype,
+                    int out_dtype, int epi, void* ws_dev, size_t ws_bytes) {
   GemmDesc g;
   memset(&g, 0, sizeof g);
   g.A = A; g.B = B; g.C = C; g.M = M; g.N = N; g.K = K; g.a_layout = a_layout; g.b_layout = b_layout;
   g.lda = a_layout == 0 ? K : M; g.ldb = b_layout == 0 ? N : K; g.ldc = N;
-  g.in_bf16 = in_dtype == ALS_DTYPE_BF16; g.c_bf16 = out_dtype == ALS_DTYPE_BF16; g.epi = EPI_STORE;
+  g.in_bf16 = in_dtype == ALS_DTYPE_BF16; g.c_bf16 = out_dtype == ALS_DTYPE_BF16; g.epi = epi;
   g.ws = (float*)ws_dev; g.ws_bytes = ws_dev ? ws_bytes : 0;
+  return g;
+}
+}  // namespace
+
+extern "C" int als_k_gemm(const void* A, const void* B, void* C, int M, int N, int K, int a_layout,
+                          int b_layout, int in_dtype, int out_dtype, int use_mfma, void* ws_dev,
+                          size_t ws_bytes, void* stream) {
+  if (!A || !B || !C) return set_error(ALS_ERR_INVALID, "null argument");
+  const GemmDesc g = plain_desc(A, B, C, M, N, K, a_layout, b_layout, in_dtype, out_dtype, EPI_STORE, ws_dev, ws_bytes);
   if (use_mfma) {
     if (!gemm_mfma_supported(g)) return set_error(ALS_ERR_INVALID, "shape/dtype not supported by the MFMA GEMM");
     return gemm_mfma(g, (hipStream_t)stream);
@@ -684,11 +693,7 @@ extern "C" int als_k_gemm_static_ws(const void* A, const void* B, void* C, int M
     return set_error(ALS_ERR_INVALID, "als_k_gemm_static_ws: M x N = %d x %d exceeds the static workspace "
                      "(2 fp32 partials must fit %zu bytes, i.e. M*N <= %zu)", M, N, (size_t)ALS_STATIC_WS_BYTES,
                      (size_t)ALS_STATIC_WS_BYTES / 8);
-  GemmDesc g;
-  memset(&g, 0, sizeof g);
-  g.A = A; g.B = B; g.C = C; g.M = M; g.N = N; g.K = K; g.a_layout = a_layout; g.b_layout = b_layout;
-  g.lda = a_layout == 0 ? K : M; g.ldb = b_layout == 0 ? N : K; g.ldc = N;
-  g.in_bf16 = 1; g.c_bf16 = out_dtype == ALS_DTYPE_BF16; g.epi = EPI_STORE;
+  GemmDesc g = plain_desc(A, B, C, M, N, K, a_layout, b_layout, ALS_DTYPE_BF16, out_dtype, EPI_STORE, nullptr, 0);
   if (!gemm_mfma_supported(g)) return set_error(ALS_ERR_INVALID, "shape/dtype not supported by the MFMA GEMM");
   void* ws = nullptr;
   int rc = scratch_for_current_device(&ws);
@@ -793,18 +798,23 @@ extern "C" int als_k_gemm_ex(const void* A, const void* B, void* C, int M, int N
   if (!A || !B || !C) return set_error(ALS_ERR_INVALID, "null argument");
   if (epi < 0 || epi > 3 || (epi == EPI_RESID && !R) || (epi == EPI_GELU && !C2) || (epi == EPI_DGELU && !U))
     return set_error(ALS_ERR_INVALID, "epilogue %d lacks its operand", epi);
-  GemmDesc g;
-  memset(&g, 0, sizeof g);
-  g.A = A; g.B = B; g.C = C; g.M = M; g.N = N; g.K = K; g.a_layout = a_layout; g.b_layout = b_layout;
-  g.lda = a_layout == 0 ? K : M; g.ldb = b_layout == 0 ? N : K; g.ldc = N;
-  g.in_bf16 = in_dtype == ALS_DTYPE_BF16; g.c_bf16 = out_dtype == ALS_DTYPE_BF16; g.epi = epi;
+  GemmDesc g = plain_desc(A, B, C, M, N, K, a_layout, b_layout, in_dtype, out_dtype, epi, ws_dev, ws_bytes);
   g.R = R; g.ldr = N; g.C2 = C2; g.U = U;
-  g.ws = (float*)ws_dev; g.ws_bytes = ws_dev ? ws_bytes : 0;
   if (use_mfma) {
     if (!gemm_mfma_supported(g)) return set_error(ALS_ERR_INVALID, "shape/dtype/epilogue not supported by the MFMA GEMM");
     return gemm_mfma(g, (hipStream_t)stream);
   }
   return gemm_generic(g, (hipStream_t)stream);
+}
+
+extern "C" int als_k_gemm_route(int M, int N, int K, int a_layout, int b_layout, int in_dtype, int out_dtype, int epi, int flags,
+                                size_t ws_bytes, char* out, int out_len) {
+  if (!out || out_len < 1 || M <= 0 || N <= 0 || K <= 0) return set_error(ALS_ERR_INVALID, "null argument or empty shape");
+  void* any = (void*)(uintptr_t)256;   // stands for aligned operands, never read
+  GemmDesc g = plain_desc(any, any, any, M, N, K, a_layout, b_layout, in_dtype, out_dtype, epi, ws_bytes ? any : nullptr, ws_bytes);
+  g.R = (const float*)any; g.ldr = N; g.C2 = any; g.U = any;
+  gemm_route(g, in_dtype == ALS_DTYPE_BF16 && !(flags & 1), out, out_len);
+  return ALS_OK;
 }
 
 extern "C" int als_k_attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int h, int dh,

@@ -3,6 +3,7 @@
 // the independent check of those that they do; fp32 products go to gemm_mfma_f32.hip.
 #include "common.h"
 #include "gelu.h"
+#include <stdio.h>
 
 namespace als {
 
@@ -104,6 +105,12 @@ int gemm(const GemmDesc& g, bool allow_mfma, hipStream_t st) {
   if (allow_mfma && gemm_mfma_supported(g)) return gemm_mfma(g, st);
   if (allow_mfma && gemm_mfma_any_supported(g)) return gemm_mfma_any(g, st);
   return gemm_generic(g, st);
+}
+
+void gemm_route(const GemmDesc& g, bool allow_mfma, char* out, int out_len) {
+  if (allow_mfma && gemm_mfma_supported(g)) return gemm_mfma_route(g, out, out_len);
+  snprintf(out, out_len, "%s", allow_mfma && gemm_mfma_any_supported(g) ? gemm_mfma_any_route(g)
+                               : gemm_mfma_f32_supported(g) ? gemm_mfma_f32_route(g) : "vector");
 }
 
 }  // namespace als

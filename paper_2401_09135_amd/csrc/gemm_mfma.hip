@@ -425,8 +425,10 @@ static int dispatch(const GemmDesc& g, const MfmaArgs& a, int bm, int bn, int nb
 // thread reads whole values, the three are still not changed as one)
 static std::atomic<int> g_force_bm{0}, g_force_bn{0}, g_force_nbuf{0};
 
-int gemm_mfma(const GemmDesc& g, hipStream_t st) {
-  if (!gemm_mfma_supported(g)) return set_error(ALS_ERR_INVALID, "gemm_mfma: unsupported shape or layout");
+// deep: the tile of gemm_mfma_deep.hip (128 or 64); any: gemm_mfma_any.hip; else bm x bn tiles with buffering code nbuf, K in nsplit parts
+struct MfmaChoice { int deep, any, bm, bn, nbuf, nsplit; };
+
+static MfmaChoice choose(const GemmDesc& g) {
   // Tile choice (measured on MI355X): the single-buffered 128x128 variant, 3 workgroups per CU
   // so that one's prologue/epilogue hides behind another's MFMAs, for short K and few tiles;
   // the double-buffered one once K is long enough to amortise its single resident pair;
@@ -459,12 +461,12 @@ int gemm_mfma(const GemmDesc& g, hipStream_t st) {
     //   2048 x 256 x 256: 7.0 / 6.5 / 4.4 (128 x 128)       512 x 256 x 1024: 5.7 / 11.7 / 7.7 (shared K)
     // (its loads have 32-bit offsets inside a tile)
     if (g.a_layout == 0 && tiles128 <= 256 && (tiles256 < 64 || tiles256 * g.workers <= 128) && g.lda < 1 << 24 && g.ldb < 1 << 24) {
-      if (tiles128 >= 160) return gemm_mfma_deep(g, 128, st);
-      if (tiles128 > 16 || g.K < 512) return gemm_mfma_deep(g, 64, st);
-      return gemm_mfma_any(g, st);
+      if (tiles128 >= 160) return MfmaChoice{128};
+      if (tiles128 > 16 || g.K < 512) return MfmaChoice{64};
+      return MfmaChoice{0, 1};
     }
     if (tiles256 < 64) {   // X^T dY
-      if (g.K >= 512 && tiles128 < 160) return gemm_mfma_any(g, st);
+      if (g.K >= 512 && tiles128 < 160) return MfmaChoice{0, 1};
       pp_pays = false;
     }
   }
@@ -478,11 +480,6 @@ int gemm_mfma(const GemmDesc& g, hipStream_t st) {
     else nbuf = 2;
   } else if (fits(g.M, g.N, 256, 128) && (g.M / 256) * (g.N / 128) >= 448) { bm = 256; bn = 128; }
   else if (g.K >= 2048) nbuf = 2;
-  MfmaArgs a;
-  a.A = (const bf16*)g.A; a.B = (const bf16*)g.B; a.lda = g.lda; a.ldb = g.ldb;
-  a.M = g.M; a.N = g.N; a.K = g.K; a.tiles_m = (g.M + bm - 1) / bm; a.tiles_n = (g.N + bn - 1) / bn;
-  a.C = g.C; a.ldc = g.ldc; a.R = g.R; a.ldr = g.ldr; a.C2 = g.C2; a.U = (const bf16*)g.U;
-  a.split_stride = 0; a.nsplit = 1;
   int nsplit = 1;
   if ((g.a_layout == 1 && g.b_layout == 0 && g.ldc == g.N) || (splittable && tiles256 < 64 && bn == 256 && (nbuf == 4 || nbuf == 5))) {
     // Few tiles, long K: weight gradients, and the input gradient of the output matrix (K = vocabulary).  K is split so that the grid fills the chip in
@@ -500,7 +497,7 @@ int gemm_mfma(const GemmDesc& g, hipStream_t st) {
     for (int cand = 0; cand < (bm == 128 && !g_force_bm ? 2 : 1); cand++) {
       const int nb = cand == 0 ? nbuf : (nbuf == 2 ? 1 : 2);
       const int slots = 256 * (bn == 256 ? 1 : (bm == 128 && nb == 1) ? 3 : 2);  // resident workgroups on the chip
-      const int tiles = a.tiles_m * a.tiles_n;
+      const int tiles = (int)gemm_tiles(g.M, g.N, bm, bn);
       const int nk_total = g.K / BK;
       for (int ns = 1; ns <= 64 && ns <= maxws; ns++) {
         const int s_wg = (nk_total + ns - 1) / ns;     // slices of the longest split
@@ -517,6 +514,27 @@ int gemm_mfma(const GemmDesc& g, hipStream_t st) {
     nbuf = best_nbuf;
     nsplit = best_ns;
   }
+  return MfmaChoice{0, 0, bm, bn, nbuf, nsplit};
+}
+
+void gemm_mfma_route(const GemmDesc& g, char* out, int out_len) {
+  const MfmaChoice c = choose(g);
+  if (c.deep) snprintf(out, out_len, "deep %dx%d", c.deep, c.deep);
+  else if (c.any) snprintf(out, out_len, "%s", gemm_mfma_any_route(g));
+  else snprintf(out, out_len, "%dx%d/%d split %d", c.bm, c.bn, c.nbuf, c.nsplit);
+}
+
+int gemm_mfma(const GemmDesc& g, hipStream_t st) {
+  if (!gemm_mfma_supported(g)) return set_error(ALS_ERR_INVALID, "gemm_mfma: unsupported shape or layout");
+  const MfmaChoice c = choose(g);
+  if (c.deep) return gemm_mfma_deep(g, c.deep, st);
+  if (c.any) return gemm_mfma_any(g, st);
+  const int bm = c.bm, bn = c.bn, nbuf = c.nbuf, nsplit = c.nsplit;
+  MfmaArgs a;
+  a.A = (const bf16*)g.A; a.B = (const bf16*)g.B; a.lda = g.lda; a.ldb = g.ldb;
+  a.M = g.M; a.N = g.N; a.K = g.K; a.tiles_m = (g.M + bm - 1) / bm; a.tiles_n = (g.N + bn - 1) / bn;
+  a.C = g.C; a.ldc = g.ldc; a.R = g.R; a.ldr = g.ldr; a.C2 = g.C2; a.U = (const bf16*)g.U;
+  a.split_stride = 0; a.nsplit = 1;
   if (nsplit > 1) {
     a.nsplit = nsplit;
     a.C = g.ws; a.ldc = g.N; a.split_stride = (int64_t)g.M * g.N;

@@ -287,26 +287,37 @@ int launch_dw_list(const DwProblem* probs, int n, int K, hipStream_t st) {
   return ALS_OK;
 }
 
-inline int64_t tiles(const GemmDesc& g, int bm, int bn) { return (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); }
+// Which tile a product (or a list of them, its tiles counted together) takes: 0 for 128 x 128, 1 for 128 x 64 with 2 K shares,
+// 2 for 64 x 64 with 2, 3 for 32 x 32 with 8.  In us, in this order (tiles of the first two; of the last two):
+//   3000 x 4000 x 700 (768, 1512): 57 / 74 / 99 / 237       1000 x 2001 x 4003, X^T Y (128, 256): 259 / 74 / 132 / 192
+//   320 x 5003 x 600, X^T Y (120, 237): 38 / 18 / 23 / 36   600 x 960 x 320 (40, 75; 150, 570): 15 / 8.5 / 6.2 / 11
+//   1024 x 896 x 3584 (56, 112; 224, 896): 53 / 32 / 25 / 29    2048 x 256 x 1024 (32, 64; 128, 512): 19 / 11 / 7.9 / 7.1
+//   600 x 320 x 5003 (15, 25; 50, 190): 123 / 61 / 45 / 25      512 x 256 x 256 (8, 16; 32, 128): 9.8 / 6.5 / 5.9 / 6.1
+template <typename Tiles>
+int choose_tile(Tiles tiles, int K) {
+  if (tiles(128, 128) >= 256) return 0;
+  if (tiles(128, 64) >= 192) return 1;
+  return tiles(32, 32) > (K >= 1024 ? 512 : 256) ? 2 : 3;
+}
+int choose_tile(const GemmDesc& g) {
+  return choose_tile([&](int bm, int bn) { return gemm_tiles(g.M, g.N, bm, bn); }, g.K);
+}
 
 template <int AL, int BL>
 int pick(const GemmDesc& g, hipStream_t st) {
-  // In us, 128 x 128 / 128 x 64 with 2 K shares / 64 x 64 with 2 / 32 x 32 with 8 (tiles of the first two; of the last two):
-  //   3000 x 4000 x 700 (768, 1512): 57 / 74 / 99 / 237       1000 x 2001 x 4003, X^T Y (128, 256): 259 / 74 / 132 / 192
-  //   320 x 5003 x 600, X^T Y (120, 237): 38 / 18 / 23 / 36   600 x 960 x 320 (40, 75; 150, 570): 15 / 8.5 / 6.2 / 11
-  //   1024 x 896 x 3584 (56, 112; 224, 896): 53 / 32 / 25 / 29    2048 x 256 x 1024 (32, 64; 128, 512): 19 / 11 / 7.9 / 7.1
-  //   600 x 320 x 5003 (15, 25; 50, 190): 123 / 61 / 45 / 25      512 x 256 x 256 (8, 16; 32, 128): 9.8 / 6.5 / 5.9 / 6.1
-  if (tiles(g, 128, 128) >= 256) return launch_any<128, 128, 64, 2, 2, 1, AL, BL>(g, st);
-  if (tiles(g, 128, 64) >= 192) return launch_any<128, 64, 128, 2, 2, 2, AL, BL>(g, st);
-  if (tiles(g, 32, 32) > (g.K >= 1024 ? 512 : 256)) return launch_any<64, 64, 128, 2, 2, 2, AL, BL>(g, st);
-  return launch_any<32, 32, 256, 1, 1, 8, AL, BL>(g, st);
+  switch (choose_tile(g)) {
+    case 0: return launch_any<128, 128, 64, 2, 2, 1, AL, BL>(g, st);
+    case 1: return launch_any<128, 64, 128, 2, 2, 2, AL, BL>(g, st);
+    case 2: return launch_any<64, 64, 128, 2, 2, 2, AL, BL>(g, st);
+    default: return launch_any<32, 32, 256, 1, 1, 8, AL, BL>(g, st);
+  }
 }
 
 }  // namespace
 
 bool gemm_mfma_any_supported(const GemmDesc& g) {
   if (!g.in_bf16 || (g.a_layout == 1 && g.b_layout == 1) || (g.a_layout | g.b_layout) & ~1) return false;
-  return tiles(g, 32, 32) < (1 << 22);   // blocks of up to 512 threads in one grid dimension
+  return gemm_tiles(g.M, g.N, 32, 32) < (1 << 22);   // blocks of up to 512 threads in one grid dimension
 }
 
 int gemm_mfma_any(const GemmDesc& g, hipStream_t st) {
@@ -316,13 +327,20 @@ int gemm_mfma_any(const GemmDesc& g, hipStream_t st) {
   return g.b_layout == 0 ? pick<0, 0>(g, st) : pick<0, 1>(g, st);
 }
 
-// the tile by the same rule as for one product (pick()), on the tiles of all
+const char* gemm_mfma_any_route(const GemmDesc& g) {
+  static const char* const name[] = {"any 128x128", "any 128x64/2", "any 64x64/2", "any 32x32/8"};
+  return name[choose_tile(g)];
+}
+
+// the tile by the same rule as for one product, on the tiles of all
 int gemm_mfma_any_dw_list(const DwProblem* probs, int n, int K, hipStream_t st) {
   if (n <= 0) return ALS_OK;
-  if (dw_list_tiles(probs, n, 128, 128) >= 256) return launch_dw_list<128, 128, 64, 2, 2, 1>(probs, n, K, st);
-  if (dw_list_tiles(probs, n, 128, 64) >= 192) return launch_dw_list<128, 64, 128, 2, 2, 2>(probs, n, K, st);
-  if (dw_list_tiles(probs, n, 32, 32) > (K >= 1024 ? 512 : 256)) return launch_dw_list<64, 64, 128, 2, 2, 2>(probs, n, K, st);
-  return launch_dw_list<32, 32, 256, 1, 1, 8>(probs, n, K, st);
+  switch (choose_tile([&](int bm, int bn) { return dw_list_tiles(probs, n, bm, bn); }, K)) {
+    case 0: return launch_dw_list<128, 128, 64, 2, 2, 1>(probs, n, K, st);
+    case 1: return launch_dw_list<128, 64, 128, 2, 2, 2>(probs, n, K, st);
+    case 2: return launch_dw_list<64, 64, 128, 2, 2, 2>(probs, n, K, st);
+    default: return launch_dw_list<32, 32, 256, 1, 1, 8>(probs, n, K, st);
+  }
 }
 
 }  // namespace als

@@ -250,31 +250,44 @@ int launch_dw_list(const DwProblem* probs, int n, int K, hipStream_t st) {
   return ALS_OK;
 }
 
-inline int64_t tiles(const GemmDesc& g, int bm, int bn) { return (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); }
+// Which tile a product (or a list of them, its tiles counted together) takes: 0 for 128 x 128, 1 for 64 x 64 with 2 K shares, 2 for
+// 32 x 32 with 8, 3 with 4, 4 for 32 x 32 with one wavefront and k in its natural order.
+// The largest tile that still gives (almost) every CU a workgroup: a larger tile moves fewer operand bytes per flop, an idle CU
+// costs its whole rate.  In us, 128 x 128 / 64 x 64 / 32 x 32 with 8 K shares / with 4:
+//   4096 x 8192 x 512 (2048, 8192 tiles): 307 / 347 / 478 / 420     2048 x 1536 x 512 (192, 768): 48 / 39 / 49 / 44
+//   1024 x 1024 x 256 (64, 256): 26 / 9.9 / 12 / 10                 256 x 2000 x 1024 (32, 128): 127 / 43 / 26 / 31
+//   512 x 512 x 512 (16, 64): 44 / 14 / 6.6 / 7.6                   1024 x 256 x 256 (16, 64): 28 / 8.6 / 5.7 / 5.5
+// The smallest: one wavefront per tile, k in its natural order (NAT), so the bits of a plain loop over k.  A short run in fp32 mode
+// can then be held to 1e-5 against an fp32 program that adds in that order (elements with a gradient near zero carry rounding
+// into AdamW's direction: with shares of K the same run is as near to float64, but 1.6e-5 from that program); the launch is the
+// time either way (a round of 2 layers of width 64: 1195 us with shares, 1202 without).
+template <typename Tiles>
+int choose_tile(Tiles tiles, int K, int nat_tiles) {
+  if (tiles(128, 128) >= 256) return 0;
+  if (tiles(64, 64) >= 192) return 1;
+  if (K >= 512) return 2;
+  return tiles(32, 32) <= nat_tiles && K <= 256 ? 4 : 3;
+}
+int choose_tile(const GemmDesc& g) {
+  return choose_tile([&](int bm, int bn) { return gemm_tiles(g.M, g.N, bm, bn); }, g.K, 64);
+}
 
 template <int AL, int BL>
 int pick(const GemmDesc& g, hipStream_t st) {
-  // The largest tile that still gives (almost) every CU a workgroup: a larger tile moves fewer operand bytes per flop, an idle CU
-  // costs its whole rate.  In us, 128 x 128 / 64 x 64 / 32 x 32 with 8 K shares / with 4:
-  //   4096 x 8192 x 512 (2048, 8192 tiles): 307 / 347 / 478 / 420     2048 x 1536 x 512 (192, 768): 48 / 39 / 49 / 44
-  //   1024 x 1024 x 256 (64, 256): 26 / 9.9 / 12 / 10                 256 x 2000 x 1024 (32, 128): 127 / 43 / 26 / 31
-  //   512 x 512 x 512 (16, 64): 44 / 14 / 6.6 / 7.6                   1024 x 256 x 256 (16, 64): 28 / 8.6 / 5.7 / 5.5
-  if (tiles(g, 128, 128) >= 256) return launch_f32<128, 128, 32, 2, 2, 1, AL, BL>(g, st);
-  if (tiles(g, 64, 64) >= 192) return launch_f32<64, 64, 64, 2, 2, 2, AL, BL>(g, st);
-  if (g.K >= 512) return launch_f32<32, 32, 128, 1, 1, 8, AL, BL>(g, st);
-  // The smallest: one wavefront per tile, k in its natural order (NAT), so the bits of a plain loop over k.  A short run in fp32 mode
-  // can then be held to 1e-5 against an fp32 program that adds in that order (elements with a gradient near zero carry rounding
-  // into AdamW's direction: with shares of K the same run is as near to float64, but 1.6e-5 from that program); the launch is the
-  // time either way (a round of 2 layers of width 64: 1195 us with shares, 1202 without).
-  if (tiles(g, 32, 32) <= 64 && g.K <= 256) return launch_f32<32, 32, 64, 1, 1, 1, AL, BL, true>(g, st);
-  return launch_f32<32, 32, 64, 1, 1, 4, AL, BL>(g, st);
+  switch (choose_tile(g)) {
+    case 0: return launch_f32<128, 128, 32, 2, 2, 1, AL, BL>(g, st);
+    case 1: return launch_f32<64, 64, 64, 2, 2, 2, AL, BL>(g, st);
+    case 2: return launch_f32<32, 32, 128, 1, 1, 8, AL, BL>(g, st);
+    case 3: return launch_f32<32, 32, 64, 1, 1, 4, AL, BL>(g, st);
+    default: return launch_f32<32, 32, 64, 1, 1, 1, AL, BL, true>(g, st);
+  }
 }
 
 }  // namespace
 
 bool gemm_mfma_f32_supported(const GemmDesc& g) {
   if (g.in_bf16 || g.c_bf16 || (g.a_layout | g.b_layout) & ~1) return false;
-  return tiles(g, 32, 32) < (1 << 22);   // blocks of up to 512 threads in one grid dimension
+  return gemm_tiles(g.M, g.N, 32, 32) < (1 << 22);   // blocks of up to 512 threads in one grid dimension
 }
 
 int gemm_mfma_f32(const GemmDesc& g, hipStream_t st) {
@@ -282,14 +295,21 @@ int gemm_mfma_f32(const GemmDesc& g, hipStream_t st) {
   return g.b_layout == 0 ? pick<1, 0>(g, st) : pick<1, 1>(g, st);
 }
 
-// the tile by the same rule as for one product (pick()), on the tiles of all
+const char* gemm_mfma_f32_route(const GemmDesc& g) {
+  static const char* const name[] = {"f32 128x128", "f32 64x64/2", "f32 32x32/8", "f32 32x32/4", "f32 32x32 natural"};
+  return name[choose_tile(g)];
+}
+
+// the tile by the same rule as for one product, on the tiles of all
 int gemm_mfma_f32_dw_list(const DwProblem* probs, int n, int K, hipStream_t st) {
   if (n <= 0) return ALS_OK;
-  if (dw_list_tiles(probs, n, 128, 128) >= 256) return launch_dw_list<128, 128, 32, 2, 2, 1>(probs, n, K, st);
-  if (dw_list_tiles(probs, n, 64, 64) >= 192) return launch_dw_list<64, 64, 64, 2, 2, 2>(probs, n, K, st);
-  if (K >= 512) return launch_dw_list<32, 32, 128, 1, 1, 8>(probs, n, K, st);
-  if (dw_list_tiles(probs, n, 32, 32) <= 256 && K <= 256) return launch_dw_list<32, 32, 64, 1, 1, 1, true>(probs, n, K, st);
-  return launch_dw_list<32, 32, 64, 1, 1, 4>(probs, n, K, st);
+  switch (choose_tile([&](int bm, int bn) { return dw_list_tiles(probs, n, bm, bn); }, K, 256)) {
+    case 0: return launch_dw_list<128, 128, 32, 2, 2, 1>(probs, n, K, st);
+    case 1: return launch_dw_list<64, 64, 64, 2, 2, 2>(probs, n, K, st);
+    case 2: return launch_dw_list<32, 32, 128, 1, 1, 8>(probs, n, K, st);
+    case 3: return launch_dw_list<32, 32, 64, 1, 1, 4>(probs, n, K, st);
+    default: return launch_dw_list<32, 32, 64, 1, 1, 1, true>(probs, n, K, st);
+  }
 }
 
 }  // namespace als

@@ -1,0 +1,25 @@
+"""Which kernel a product of a worker step takes, at the borders of the rules (host only, no GPU call)."""
+import pytest
+
+import paper_2401_09135_amd as A
+
+F32, BF16 = A.ALS_DTYPE_F32, A.ALS_DTYPE_BF16
+MIB = 1 << 20
+
+
+@pytest.mark.parametrize("M,N,K,layout,epi,out,want", [
+    (16384, 3584, 896, (0, 0), 2, BF16, "256x256/4 split 1"),      # whole rounds of 256 x 256 tiles
+    (2560, 1024, 896, (0, 0), 0, BF16, "deep 128x128"),            # 160 tiles of 128 x 128, and one row of them less
+    (2432, 1024, 896, (0, 0), 0, BF16, "deep 64x64"),
+    (512, 512, 512, (0, 1), 0, F32, "any 32x32/8"),                # 16 of them, K from 512 on
+    (512, 512, 448, (0, 1), 0, F32, "deep 64x64"),
+    (600, 960, 320, (0, 0), 0, BF16, "any 64x64/2"),               # rows that are no multiple of a tile
+    (600, 5003, 320, (0, 0), 0, BF16, "any 128x64/2"),
+])
+def test_bf16_products(M, N, K, layout, epi, out, want):
+    assert A.gemm_route(M, N, K, *layout, BF16, out, epi) == want
+
+
+def test_bf16_products_with_the_matrix_cores_off():
+    for M in (600, 16384):
+        assert A.gemm_route(M, 896, 896, flags=1) == "vector"
