@@ -449,7 +449,10 @@ static MfmaChoice choose(const GemmDesc& g) {
   const bool splittable = g.epi == EPI_STORE && !g.c_bf16 && g.ldc == g.N && g.a_layout + g.b_layout == 1 && g.ws &&
                           g.ws_bytes >= (size_t)g.M * g.N * 8;
   const int64_t tiles256 = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256), tiles128 = (int64_t)(g.M / 128) * (g.N / 128);
-  if (!g_force_bm && !g_force_nbuf && !(splittable && tiles256 < 64 && g.K > 2048)) {   // (that one is split along K below)
+  // A split of the 128 x 128 kernels along K exists for X^T Y only: an X Y^T of 128 rows or columns goes to the small tiles, whatever
+  // its K (T = 1024, d = 128, V = 32000: 8 workgroups of 500 slices each 344 us, 91 with 32 x 32 tiles that share K; 8192 rows 481 and 161).
+  const bool split_below = splittable && tiles256 < 64 && g.K > 2048 && (pp_pays || g.a_layout == 1);
+  if (!g_force_bm && !g_force_nbuf && !split_below) {
     // At most a round of 128 x 128 tiles: 256 x 256 ones leave three quarters of the chip idle.  With 64 and more of them that
     // is right only while no other workers fill it: per CU they do twice the work (rounds with T = 8192, d = 512
     // of 1 / 2 / 4 workers: 3161 / 4777 / 8484 us with them, 2678 / 4656 / 8927 without; the number of workers and not of streams, so

@@ -112,7 +112,8 @@ def test_products_with_deep_prefetch(M, N, K, al, bl, epi):
     test_small_aligned_bf16_products(M, N, K, al, bl, epi)
 
 
-@pytest.mark.parametrize("M,N,K", [(256, 256, 2112), (1024, 896, 8192), (8192, 256, 4160)])
+@pytest.mark.parametrize("M,N,K", [(256, 256, 2112), (1024, 896, 8192), (8192, 256, 4160),
+                                   (1024, 128, 8192), (128, 256, 8192)])           # 128 rows or columns: not split
 def test_input_gradient_split_along_k(M, N, K):
     gen = torch.Generator(device=DEV).manual_seed(K)
     a, b = torch.randn(M, K, device=DEV, generator=gen).bfloat16(), torch.randn(N, K, device=DEV, generator=gen).bfloat16()
@@ -121,6 +122,9 @@ def test_input_gradient_split_along_k(M, N, K):
         A.k_gemm(a, b, c, M, N, K, 0, 1, use_mfma=True, ws=torch.empty(size * M * N, device=DEV))
         bound = (K + 4) * 2.0 ** -24 * (a.abs().double() @ b.abs().double().t())
         assert ((c.double() - a.double() @ b.double().t()).abs() <= bound).all()
+    c = torch.full((M, N), float("nan"), device=DEV)
+    A.k_gemm(a, b, c, M, N, K, 0, 1, use_mfma=True)
+    assert ((c.double() - a.double() @ b.double().t()).abs() <= bound).all()
 
 
 @pytest.mark.parametrize("kw", [dict(d=64, h=1, ff=192, V=201, S=33, B=3),          # nothing is a multiple of 128

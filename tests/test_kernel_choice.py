@@ -23,3 +23,13 @@ def test_bf16_products(M, N, K, layout, epi, out, want):
 def test_bf16_products_with_the_matrix_cores_off():
     for M in (600, 16384):
         assert A.gemm_route(M, 896, 896, flags=1) == "vector"
+
+
+@pytest.mark.parametrize("M,N,K,ws,want", [
+    (1024, 128, 32000, 64 * MIB, "any 32x32/8"), (128, 256, 8192, 64 * MIB, "any 32x32/8"),   # no 256 x 256 tile to split
+    (1024, 128, 32000, 0, "any 32x32/8"),                                                     # (nothing to do with a workspace)
+    (8192, 128, 32000, 64 * MIB, "deep 64x64"),
+    (1024, 256, 32000, 64 * MIB, "256x256/4 split 50"),
+])
+def test_input_gradient_of_the_output_matrix(M, N, K, ws, want):
+    assert A.gemm_route(M, N, K, 0, 1, ws_bytes=ws) == want
