@@ -58,7 +58,6 @@ struct GemmDesc {
   void* C2;                          // EPI_GELU second output (same type/ld as C)
   const void* U;                     // EPI_DGELU saved derivative (operand type, ld = ldc)
   float* ws; size_t ws_bytes;        // scratch for split-K partials (may be null)
-  int workers;                       // how many workers run such products side by side (0: one)
 };
 inline int64_t gemm_tiles(int M, int N, int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
 int gemm_generic(const GemmDesc& g, hipStream_t st);

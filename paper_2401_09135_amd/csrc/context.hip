@@ -171,7 +171,7 @@ GemmDesc desc(const als_ctx* c, const void* A, int a_layout, int64_t lda, const 
   memset(&g, 0, sizeof g);
   g.A = A; g.B = B; g.M = M; g.N = N; g.K = K; g.a_layout = a_layout; g.b_layout = b_layout;
   g.lda = lda; g.ldb = ldb; g.in_bf16 = c->bf; g.C = C; g.ldc = ldc; g.c_bf16 = c_act && c->bf;
-  g.epi = EPI_STORE; g.workers = c->cfg.n_workers;
+  g.epi = EPI_STORE;
   return g;
 }
 

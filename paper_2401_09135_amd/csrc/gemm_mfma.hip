@@ -453,17 +453,18 @@ static MfmaChoice choose(const GemmDesc& g) {
   // its K (T = 1024, d = 128, V = 32000: 8 workgroups of 500 slices each 344 us, 91 with 32 x 32 tiles that share K; 8192 rows 481 and 161).
   const bool split_below = splittable && tiles256 < 64 && g.K > 2048 && (pp_pays || g.a_layout == 1);
   if (!g_force_bm && !g_force_nbuf && !split_below) {
-    // At most a round of 128 x 128 tiles: 256 x 256 ones leave three quarters of the chip idle.  With 64 and more of them that
-    // is right only while no other workers fill it: per CU they do twice the work (rounds with T = 8192, d = 512
-    // of 1 / 2 / 4 workers: 3161 / 4777 / 8484 us with them, 2678 / 4656 / 8927 without; the number of workers and not of streams, so
-    // that the results do not depend on the streams).  Below 160 tiles of 128 x 128, tiles of 64 x 64; for a few of those and a long
-    // K, the kernels whose wavefronts share K.  In us, kernels before / deep 128 x 128 / deep 64 x 64:
-    //   8192 x 512 x 2048: 47 / 25 / 35 (256 x 256)         4096 x 896 x 3584: 74 / 36 / 50 (256 x 256)
+    // Fewer than 64 tiles of 256 x 256 leave three quarters of the chip idle.  Below 160 tiles of 128 x 128, tiles of 64 x 64; for a few
+    // of those and a long K, the kernels whose wavefronts share K.  In us, kernels before / deep 128 x 128 / deep 64 x 64:
+    //   6144 x 512 x 2048: 42 / 20 (256 x 256)              3840 x 896 x 3584: 69 / 32 (256 x 256)
     //   1024 x 2688 x 896: 13.8 / 13.1 / 14.5 (128 x 128)   1024 x 3584 x 896, dY W^T: 15.5 / 12.9 / 19.5 (128 x 128)
     //   1024 x 896 x 3584: 26 / 30 / 17 (shared K)          8192 x 256 x 1024: 14.3 / 13.4 / 10.7 (shared K)
     //   2048 x 256 x 256: 7.0 / 6.5 / 4.4 (128 x 128)       512 x 256 x 1024: 5.7 / 11.7 / 7.7 (shared K)
-    // (its loads have 32-bit offsets inside a tile)
-    if (g.a_layout == 0 && tiles128 <= 256 && (tiles256 < 64 || tiles256 * g.workers <= 128) && g.lda < 1 << 24 && g.ldb < 1 << 24) {
+    // From 64 on the 256 x 256 tiles stay.  Alone on the chip 128 x 128 ones would win there too (8192 x 512 x 2048: 47 / 25), but with
+    // workers that fill it side by side the larger ones do twice the work per CU (rounds with T = 8192, d = 512 of 1 / 2 / 4 workers:
+    // 3161 / 4777 / 8484 us with them, 2678 / 4656 / 8927 without), and a choice by the number of workers would make a worker's
+    // bits depend on the workers beside it.
+    // (the loads of the deep kernels have 32-bit offsets inside a tile)
+    if (g.a_layout == 0 && tiles256 < 64 && g.lda < 1 << 24 && g.ldb < 1 << 24) {
       if (tiles128 >= 160) return MfmaChoice{128};
       if (tiles128 > 16 || g.K < 512) return MfmaChoice{64};
       return MfmaChoice{0, 1};

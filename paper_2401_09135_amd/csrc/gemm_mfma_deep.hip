@@ -9,7 +9,7 @@
 // traffic.  Their halves are added through LDS, share 0 + share 1, and each then writes half of the rows.
 //
 // 1024 x 896 x 3584 (224 tiles of 64 x 64): 26 us with operands through registers, two slices ahead, to 17.4 (378 TFLOP/s);
-// 4096 x 896 x 3584 (224 of 128 x 128): 74 us in 64 tiles of 256 x 256 to 36 (728).  Which product takes which: gemm_mfma().
+// 3840 x 896 x 3584 (210 of 128 x 128): 69 us in 60 tiles of 256 x 256 to 32 (778).  Which product takes which: gemm_mfma().
 //
 // Slice kt lies in LDS buffer kt % NST.  One barrier per slice: before it every wavefront waits for its own loads of slice kt
 // and for its reads of slice kt - 1; behind it the loads of slice kt + NST - 1 go into the buffer of slice kt - 1.  Chunks are

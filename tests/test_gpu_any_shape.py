@@ -106,7 +106,7 @@ def test_small_aligned_bf16_products(M, N, K, al, bl, epi):
 
 @pytest.mark.parametrize("M,N,K", [(128, 128, 64), (256, 128, 256), (128, 256, 320), (256, 384, 448),   # 64 x 64 tiles: one slice, around the 5 in flight
                                    (2048, 1152, 192), (384, 896, 832),                                  # the most of them; K beyond the kernels that share K
-                                   (2560, 1024, 192), (2560, 1024, 256), (1280, 2048, 320), (4096, 896, 448)])   # 128 x 128: around the 4 in flight
+                                   (2560, 1024, 192), (2560, 1024, 256), (1280, 2048, 320), (3840, 896, 448)])   # 128 x 128: around the 4 in flight
 @pytest.mark.parametrize("al,bl,epi", [(0, 0, 0), (0, 0, 1), (0, 0, 2), (0, 1, 0), (0, 1, 3)])
 def test_products_with_deep_prefetch(M, N, K, al, bl, epi):
     test_small_aligned_bf16_products(M, N, K, al, bl, epi)
@@ -238,3 +238,15 @@ def test_attention_hides_what_a_query_does_not_see(bad):
         assert torch.equal(o[:37], res[0][0][:37])
         assert torch.equal(dq[:37, :d], res[0][1][:37, :d])
     assert not torch.isfinite(res[2][0][37:]).any()
+
+
+def test_a_gradient_does_not_depend_on_the_workers_beside_it():
+    """8192 tokens of width 512: 64 tiles of 256 x 256 in the products of a layer, and a context of one and of four workers."""
+    w = _model(d=512, h=8, ff=512, V=512, S=256, B=32)
+    w["dtype"] = "bf16"
+    tok = I.TokenStream(1, 0, w["B"], w["S"], w["V"]).take(1)[0]
+    w["k"] = 1
+    _, loss, g = _loss_grad(w, tok)
+    w["k"] = 4
+    _, loss4, g4 = _loss_grad(w, tok)
+    assert loss == loss4 and np.array_equal(g, g4)

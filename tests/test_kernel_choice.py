@@ -11,6 +11,8 @@ MIB = 1 << 20
     (16384, 3584, 896, (0, 0), 2, BF16, "256x256/4 split 1"),      # whole rounds of 256 x 256 tiles
     (2560, 1024, 896, (0, 0), 0, BF16, "deep 128x128"),            # 160 tiles of 128 x 128, and one row of them less
     (2432, 1024, 896, (0, 0), 0, BF16, "deep 64x64"),
+    (8192, 512, 512, (0, 0), 0, BF16, "256x256/4 split 1"),        # 64 tiles of 256 x 256, and two less
+    (7936, 512, 512, (0, 0), 0, BF16, "deep 128x128"),
     (512, 512, 512, (0, 1), 0, F32, "any 32x32/8"),                # 16 of them, K from 512 on
     (512, 512, 448, (0, 1), 0, F32, "deep 64x64"),
     (600, 960, 320, (0, 0), 0, BF16, "any 64x64/2"),               # rows that are no multiple of a tile
