@@ -69,6 +69,7 @@ int gemm_mfma(const GemmDesc& g, hipStream_t st);
 // bf16 operands, any shape and alignment (gemm_mfma_any.hip); X Y, X Y^T and X^T Y
 bool gemm_mfma_any_supported(const GemmDesc& g);
 int gemm_mfma_any(const GemmDesc& g, hipStream_t st);
+double gemm_mfma_any_us(const GemmDesc& g);   // about what it takes, in microseconds
 // what gemm_mfma_supported takes with a_layout 0, in tiles of 128 x 128 or 64 x 64 with deep prefetch (gemm_mfma_deep.hip)
 int gemm_mfma_deep(const GemmDesc& g, int tile, hipStream_t st);
 // picks the MFMA kernel when allowed and supported

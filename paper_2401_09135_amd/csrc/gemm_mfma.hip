@@ -470,8 +470,12 @@ static MfmaChoice choose(const GemmDesc& g) {
       return MfmaChoice{0, 1};
     }
     if (tiles256 < 64) {   // X^T dY
-      if (g.K >= 512 && tiles128 < 160) return MfmaChoice{0, 1};
-      pp_pays = false;
+      // The kernels that share K inside a workgroup, while they take less than the product split along K below: that one costs 22 to 29 us
+      // of slices, partials and their sum, with 128 rows or columns (128 x 128 tiles, fewer partials) 12 to 17.  In us, split / shared K:
+      //   2048 x 1024 x 1664 (one round of 128 x 64 tiles): 28 / 18      640 x 3584 x 1984 (two): 28 / 40
+      //   384 x 3072 x 2048 (two of 64 x 64): 25 / 31                    128 x 2304 x 1280 (two of 32 x 32): 13.0 / 11.5; x 1920: 12.5 / 18.8
+      if (g.K < 512 || tiles128 >= 160) pp_pays = false;
+      else if (!splittable || gemm_mfma_any_us(g) <= (pp_pays ? 20.0 : 12.0)) return MfmaChoice{0, 1};
     }
   }
   if (g_force_bm && g_force_nbuf == 4) { bm = 256; bn = 256; nbuf = 4; }

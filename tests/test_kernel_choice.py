@@ -35,3 +35,13 @@ def test_bf16_products_with_the_matrix_cores_off():
 ])
 def test_input_gradient_of_the_output_matrix(M, N, K, ws, want):
     assert A.gemm_route(M, N, K, 0, 1, ws_bytes=ws) == want
+
+
+@pytest.mark.parametrize("M,N,K,ws,want", [
+    (2048, 1024, 1664, 64 * MIB, "any 128x64/2"), (640, 3584, 1984, 64 * MIB, "256x256/4 split 4"),   # one round of tiles that share K, two
+    (384, 3072, 2048, 64 * MIB, "256x256/4 split 4"), (384, 3072, 2048, 0, "any 64x64/2"),
+    (128, 2304, 1280, 64 * MIB, "any 32x32/8"), (128, 2304, 1920, 64 * MIB, "128x128/2 split 4"),
+    (256, 512, 2048, 64 * MIB, "any 32x32/8"), (256, 512, 2112, 64 * MIB, "256x256/4 split 4"),
+])
+def test_weight_gradient_of_few_tiles(M, N, K, ws, want):
+    assert A.gemm_route(M, N, K, 1, 0, ws_bytes=ws) == want
