@@ -45,3 +45,14 @@ def test_input_gradient_of_the_output_matrix(M, N, K, ws, want):
 ])
 def test_weight_gradient_of_few_tiles(M, N, K, ws, want):
     assert A.gemm_route(M, N, K, 1, 0, ws_bytes=ws) == want
+
+
+@pytest.mark.parametrize("dtype,want", [(BF16, "any 128x128"), (F32, "f32 128x128")])
+def test_large_products_of_any_shape(dtype, want):
+    """131072 tokens and an odd vocabulary: 4.2 and 6.4 million tiles of 32 x 32, which no kernel launches at that size."""
+    for V in (33001, 50257):
+        assert A.gemm_route(131072, V, 256, in_dtype=dtype, out_dtype=dtype) == want
+        assert A.gemm_route(131072, 256, V, 0, 1, in_dtype=dtype) == want
+    # the last grid that has fewer than 2^32 threads
+    assert A.gemm_route(1 << 22, 512 * 128 - 1, 64, in_dtype=dtype, out_dtype=dtype) == "vector"
+    assert A.gemm_route(1 << 22, 511 * 128 - 1, 64, in_dtype=dtype, out_dtype=dtype) == want
