@@ -69,9 +69,10 @@ typedef struct als_config {
   int32_t n_workers;       /* k, 1..ALS_MAX_WORKERS */
   int32_t dn_N;            /* N >= 1 */
   int32_t max_local_steps; /* capacity of the per-worker loss buffer (>= largest n_steps) */
-  int32_t flags;           /* bit 0: disable the MFMA kernels (use the generic ones); bit 1: one weight-gradient
-                              product per matrix inside the backward loop instead of the grouped launch of all
-                              layers' weight gradients at its end (bf16 with widths that are multiples of 128) */
+  int32_t flags;           /* bit 0: disable the matrix-core kernels (the generic ones in vector code, in both
+                              modes); bit 1: one weight-gradient product per matrix inside the backward loop instead
+                              of one launch of all of them at its end (the layers' in bf16 with widths that are
+                              multiples of 128; the output matrix's too in fp32 or with other sizes) */
   int32_t head_dim;        /* 0 = d/h; otherwise the attention width h*head_dim may differ from d
                               (the paper's 60M / 150M models: 16 heads of 64 on d = 896) */
   int32_t norm_kind;       /* ALS_NORM_RMS (0): y = x rsqrt(mean x^2 + eps) g ; ALS_NORM_LAYER (1): layer
@@ -220,7 +221,8 @@ int als_k_adamw(float* theta, const float* grad, float* m, float* v, void* bf16_
                 double wd, void* stream);
 /* C = A.B with fp32 accumulation.  a_layout 0: A is [M,K] row-major, 1: A is stored [K,M];
  * b_layout 0: B is [K,N] row-major, 1: B is stored [N,K].  in_dtype/out_dtype ALS_DTYPE_*;
- * use_mfma != 0 selects the MFMA kernel (bf16 inputs, M,N multiples of 128, K of 64).
+ * use_mfma != 0 selects the MFMA kernels (bf16 inputs, M,N multiples of 128, K of 64), 0 the generic one in
+ * vector code (any shape).
  * ws_dev/ws_bytes: optional device scratch for split-K partials (may be null / 0). */
 int als_k_gemm(const void* A, const void* B, void* C, int M, int N, int K, int a_layout,
                int b_layout, int in_dtype, int out_dtype, int use_mfma, void* ws_dev,

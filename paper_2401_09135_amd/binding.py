@@ -367,12 +367,36 @@ lib.als_k_gemm_ex.argtypes = [_P, _P, _P, C.c_int, C.c_int, C.c_int, C.c_int, C.
                               _P, _P, _P, _P, C.c_size_t, _P]
 
 
+lib.als_k_step_gemm.argtypes = lib.als_k_gemm_ex.argtypes
+lib.als_k_step_attention_fwd.argtypes = lib.als_k_attention_fwd.argtypes
+lib.als_k_step_attention_bwd.argtypes = lib.als_k_attention_bwd.argtypes
+
+
+def _gemm_ex(fn, A, B, C_out, M, N, K, a_layout, b_layout, how, epi, R, C2, U, ws, stream):
+    p = lambda t: t.data_ptr() if t is not None else None
+    _check(fn(A.data_ptr(), B.data_ptr(), C_out.data_ptr(), M, N, K, a_layout, b_layout, _dt(A), _dt(C_out), how, int(epi), p(R),
+              p(C2), p(U), p(ws), ws.numel() * ws.element_size() if ws is not None else 0, _stream_handle(stream)))
+
+
 def k_gemm_ex(A, B, C_out, M, N, K, a_layout=0, b_layout=0, use_mfma=False, epi=0, R=None, C2=None, U=None,
               ws=None, stream=None):
-    p = lambda t: t.data_ptr() if t is not None else None
-    _check(lib.als_k_gemm_ex(A.data_ptr(), B.data_ptr(), C_out.data_ptr(), M, N, K, a_layout, b_layout, _dt(A),
-                             _dt(C_out), int(bool(use_mfma)), int(epi), p(R), p(C2), p(U), p(ws),
-                             ws.numel() * ws.element_size() if ws is not None else 0, _stream_handle(stream)))
+    _gemm_ex(lib.als_k_gemm_ex, A, B, C_out, M, N, K, a_layout, b_layout, int(bool(use_mfma)), epi, R, C2, U, ws, stream)
+
+
+def step_gemm(A, B, C_out, M, N, K, a_layout=0, b_layout=0, flags=0, epi=0, R=None, C2=None, U=None, ws=None, stream=None):
+    """The product with the kernel that a worker step under these config flags takes for it."""
+    _gemm_ex(lib.als_k_step_gemm, A, B, C_out, M, N, K, a_layout, b_layout, int(flags), epi, R, C2, U, ws, stream)
+
+
+def step_attention_fwd(qkv, o, lse, B, S, h, dh, flags=0, stream=None):
+    """Attention with the kernel that a worker step under these config flags takes for it."""
+    _check(lib.als_k_step_attention_fwd(qkv.data_ptr(), o.data_ptr(), lse.data_ptr(), B, S, h, dh, _dt(qkv), int(flags),
+                                        _stream_handle(stream)))
+
+
+def step_attention_bwd(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, flags=0, stream=None):
+    _check(lib.als_k_step_attention_bwd(qkv.data_ptr(), o.data_ptr(), d_o.data_ptr(), lse.data_ptr(), dscratch.data_ptr(),
+                                        dqkv.data_ptr(), B, S, h, dh, _dt(qkv), int(flags), _stream_handle(stream)))
 
 
 lib.als_k_gemm_route.argtypes = [C.c_int] * 9 + [C.c_size_t, C.c_char_p, C.c_int]

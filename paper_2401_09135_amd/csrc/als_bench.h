@@ -42,6 +42,14 @@ int als_k_gemm_dw_grouped_plan(int n, const int* M, const int* N, int K, int max
  * borders of the dispatch.  Arguments as als_k_gemm_ex, operands taken as 256-byte aligned; flags as als_config.flags. */
 int als_k_gemm_route(int M, int N, int K, int a_layout, int b_layout, int in_dtype, int out_dtype, int epi, int flags,
                      size_t ws_bytes, char* out, int out_len);
+/* A product and an attention as a worker step issues them: the kernel that als_config.flags, the shape and the alignment select.
+ * Arguments as als_k_gemm_ex and als_k_attention_fwd / _bwd, with flags in the place of use_mfma. */
+int als_k_step_gemm(const void* A, const void* B, void* C, int M, int N, int K, int a_layout, int b_layout, int in_dtype,
+                    int out_dtype, int flags, int epi, const float* R, void* C2, const void* U, void* ws_dev, size_t ws_bytes,
+                    void* stream);
+int als_k_step_attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int h, int dh, int dtype, int flags, void* stream);
+int als_k_step_attention_bwd(const void* qkv, const void* o, const void* d_o, const float* lse, float* dscratch, void* dqkv,
+                             int B, int S, int h, int dh, int dtype, int flags, void* stream);
 
 #ifdef __cplusplus
 }

@@ -1,6 +1,8 @@
 // Generic causal attention, one wavefront per query (forward, dq) or per key (dk, dv), fp32
-// arithmetic on fp32 or bf16 storage: any head width up to 64 and any alignment.  Head widths of 32
-// and 64 on aligned tensors go to the fp32 matrix-core kernels (attention_mfma_f32.hip).  qkv is [B*S, 3d]: q at column hd*dh, k at d + hd*dh, v at 2d + hd*dh.
+// arithmetic on fp32 or bf16 storage in vector code: any head width up to 64 and any alignment.  What als_config.flags bit 0 and
+// use_mfma = 0 select, the independent check of the matrix-core kernels and the fallback for what neither of them takes (and the
+// smallest calls); and the choice between the three for a step.
+// qkv is [B*S, 3d]: q at column hd*dh, k at d + hd*dh, v at 2d + hd*dh.
 #include "common.h"
 #include <math.h>
 
@@ -175,7 +177,6 @@ int attention_fwd_generic(const void* qkv, void* o, float* lse, int B, int S, in
                           hipStream_t st) {
   int rc = check_shape(B, S, h, dh);
   if (rc) return rc;
-  if (attention_mfma_f32_supported(qkv, o, qkv, o, B, S, h, dh)) return attention_fwd_mfma_f32(qkv, o, lse, B, S, h, dh, bf, st);
   dim3 grid((S + 3) / 4, h, B), block(256);
   size_t sm = ((size_t)4 * S + 256) * sizeof(float);
   float scale = 1.0f / sqrtf((float)dh);
@@ -192,8 +193,6 @@ int attention_bwd_generic(const void* qkv, const void* o, const void* d_o, const
                           hipStream_t st) {
   int rc = check_shape(B, S, h, dh);
   if (rc) return rc;
-  if (attention_mfma_f32_supported(qkv, o, d_o, dqkv, B, S, h, dh))
-    return attention_bwd_mfma_f32(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, bf, st);
   dim3 grid((S + 3) / 4, h, B), block(256);
   float scale = 1.0f / sqrtf((float)dh);
   size_t sm1 = ((size_t)4 * S + 512) * sizeof(float);
@@ -213,6 +212,20 @@ int attention_bwd_generic(const void* qkv, const void* o, const void* d_o, const
   }
   ALS_CHECK_LAUNCH();
   return ALS_OK;
+}
+
+int attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int h, int dh, int bf, bool allow_mfma, hipStream_t st) {
+  if (allow_mfma && attention_mfma_supported(S, dh, bf)) return attention_fwd_mfma(qkv, o, lse, B, S, h, dh, st);
+  if (allow_mfma && attention_mfma_f32_supported(qkv, o, qkv, o, B, S, h, dh)) return attention_fwd_mfma_f32(qkv, o, lse, B, S, h, dh, bf, st);
+  return attention_fwd_generic(qkv, o, lse, B, S, h, dh, bf, st);
+}
+
+int attention_bwd(const void* qkv, const void* o, const void* d_o, const float* lse, float* dscratch, void* dqkv, int B, int S,
+                  int h, int dh, int bf, bool allow_mfma, hipStream_t st) {
+  if (allow_mfma && attention_mfma_supported(S, dh, bf)) return attention_bwd_mfma(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, st);
+  if (allow_mfma && attention_mfma_f32_supported(qkv, o, d_o, dqkv, B, S, h, dh))
+    return attention_bwd_mfma_f32(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, bf, st);
+  return attention_bwd_generic(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, bf, st);
 }
 
 }  // namespace als

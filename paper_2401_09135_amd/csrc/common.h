@@ -72,7 +72,7 @@ int gemm_mfma_any(const GemmDesc& g, hipStream_t st);
 double gemm_mfma_any_us(const GemmDesc& g);   // about what it takes, in microseconds
 // what gemm_mfma_supported takes with a_layout 0, in tiles of 128 x 128 or 64 x 64 with deep prefetch (gemm_mfma_deep.hip)
 int gemm_mfma_deep(const GemmDesc& g, int tile, hipStream_t st);
-// picks the MFMA kernel when allowed and supported
+// picks a matrix-core kernel when allowed and supported
 int gemm(const GemmDesc& g, bool allow_mfma, hipStream_t st);
 // the name of the kernel and tile that each of these takes for a product (no GPU call)
 const char* gemm_mfma_any_route(const GemmDesc& g);
@@ -168,6 +168,10 @@ int attention_fwd_mfma(const void* qkv, void* o, float* lse, int B, int S, int h
                        hipStream_t st);
 int attention_bwd_mfma(const void* qkv, const void* o, const void* d_o, const float* lse,
                        float* dscratch, void* dqkv, int B, int S, int h, int dh, hipStream_t st);
+// picks a matrix-core kernel when allowed and supported
+int attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int h, int dh, int bf, bool allow_mfma, hipStream_t st);
+int attention_bwd(const void* qkv, const void* o, const void* d_o, const float* lse, float* dscratch, void* dqkv, int B, int S,
+                  int h, int dh, int bf, bool allow_mfma, hipStream_t st);
 
 // ---- elementwise / reductions ----------------------------------------------------------------
 // center = 0: RMSNorm ; 1: LayerNorm with gain and no bias

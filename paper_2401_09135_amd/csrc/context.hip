@@ -203,10 +203,7 @@ int forward(als_ctx* c, Worker& w, const int32_t* tok) {
   for (int l = 0; l < g.n_layers; l++) {
     if (l) RUN(rmsnorm_fwd(w.x[l], w.theta + L.g1[l], w.a[l], w.rstd1[l], T, d, eps, c->bf, ln, st));
     RUN(gemm(desc(c, w.a[l], 0, d, wptr(c, w, L.Wqkv[l]), 0, 3 * da, T, 3 * da, d, w.qkv[l], 3 * da, true), mf, st));
-    if (mf && attention_mfma_supported(S, dh, c->bf))
-      RUN(attention_fwd_mfma(w.qkv[l], w.o[l], w.lse[l], B, S, h, dh, st));
-    else
-      RUN(attention_fwd_generic(w.qkv[l], w.o[l], w.lse[l], B, S, h, dh, c->bf, st));
+    RUN(attention_fwd(w.qkv[l], w.o[l], w.lse[l], B, S, h, dh, c->bf, mf, st));
     GemmDesc po = desc(c, w.o[l], 0, da, wptr(c, w, L.Wo[l]), 0, d, T, d, da, w.xm[l], d, false);
     po.epi = EPI_RESID; po.R = w.x[l]; po.ldr = d;
     RUN(gemm(po, mf, st));
@@ -261,10 +258,7 @@ int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot, float* loss_ou
     // attention block: xm = x + attn(a Wqkv) Wo
     if (each) RUN(gemm(desc_dw(c, w, w.o[l], da, w.dyo[l], d, da, d, T, w.grad + L.Wo[l]), mf, st));
     RUN(gemm(desc(c, w.dyo[l], 0, d, wptr(c, w, L.Wo[l]), 1, d, T, da, d, w.d_o, da, true), mf, st));
-    if (mf && attention_mfma_supported(S, dh, c->bf))
-      RUN(attention_bwd_mfma(w.qkv[l], w.o[l], w.d_o, w.lse[l], w.Dbuf, w.dyqkv[l], B, S, h, dh, st));
-    else
-      RUN(attention_bwd_generic(w.qkv[l], w.o[l], w.d_o, w.lse[l], w.Dbuf, w.dyqkv[l], B, S, h, dh, c->bf, st));
+    RUN(attention_bwd(w.qkv[l], w.o[l], w.d_o, w.lse[l], w.Dbuf, w.dyqkv[l], B, S, h, dh, c->bf, mf, st));
     if (each) RUN(gemm(desc_dw(c, w, w.a[l], d, w.dyqkv[l], 3 * da, d, 3 * da, T, w.grad + L.Wqkv[l]), mf, st));
     RUN(gemm(desc(c, w.dyqkv[l], 0, 3 * da, wptr(c, w, L.Wqkv[l]), 1, 3 * da, T, d, 3 * da, w.dtmp, d, false), mf, st));
     RUN(rmsnorm_bwd(w.dtmp, w.x[l], w.rstd1[l], w.theta + L.g1[l], w.dxb, w.dxa, l ? w.dy2[l - 1] : w.dx_lp, c->bf,
@@ -319,7 +313,7 @@ extern "C" int als_init(const als_config* cfg, void* arena, size_t arena_bytes, 
   make_layout(*cfg, &c->L);
   c->arena = (char*)arena; c->arena_bytes = arena_bytes;
   c->bf = cfg->dtype == ALS_DTYPE_BF16;
-  c->allow_mfma = c->bf && !(cfg->flags & 1);
+  c->allow_mfma = !(cfg->flags & 1);
   c->T = cfg->batch * cfg->seq_len;
   c->t = 0;
   Carver cv{(char*)arena, 0};
@@ -792,19 +786,51 @@ extern "C" int als_k_gemm_dw_grouped_plan(int n, const int* M, const int* N, int
   return ALS_OK;
 }
 
-extern "C" int als_k_gemm_ex(const void* A, const void* B, void* C, int M, int N, int K, int a_layout,
-                             int b_layout, int in_dtype, int out_dtype, int use_mfma, int epi, const float* R,
-                             void* C2, const void* U, void* ws_dev, size_t ws_bytes, void* stream) {
+namespace {
+int desc_ex(GemmDesc* g, const void* A, const void* B, void* C, int M, int N, int K, int a_layout, int b_layout, int in_dtype,
+            int out_dtype, int epi, const float* R, void* C2, const void* U, void* ws_dev, size_t ws_bytes) {
   if (!A || !B || !C) return set_error(ALS_ERR_INVALID, "null argument");
   if (epi < 0 || epi > 3 || (epi == EPI_RESID && !R) || (epi == EPI_GELU && !C2) || (epi == EPI_DGELU && !U))
     return set_error(ALS_ERR_INVALID, "epilogue %d lacks its operand", epi);
-  GemmDesc g = plain_desc(A, B, C, M, N, K, a_layout, b_layout, in_dtype, out_dtype, epi, ws_dev, ws_bytes);
-  g.R = R; g.ldr = N; g.C2 = C2; g.U = U;
+  *g = plain_desc(A, B, C, M, N, K, a_layout, b_layout, in_dtype, out_dtype, epi, ws_dev, ws_bytes);
+  g->R = R; g->ldr = N; g->C2 = C2; g->U = U;
+  return ALS_OK;
+}
+}  // namespace
+
+extern "C" int als_k_gemm_ex(const void* A, const void* B, void* C, int M, int N, int K, int a_layout,
+                             int b_layout, int in_dtype, int out_dtype, int use_mfma, int epi, const float* R,
+                             void* C2, const void* U, void* ws_dev, size_t ws_bytes, void* stream) {
+  GemmDesc g;
+  int rc = desc_ex(&g, A, B, C, M, N, K, a_layout, b_layout, in_dtype, out_dtype, epi, R, C2, U, ws_dev, ws_bytes);
+  if (rc) return rc;
   if (use_mfma) {
     if (!gemm_mfma_supported(g)) return set_error(ALS_ERR_INVALID, "shape/dtype/epilogue not supported by the MFMA GEMM");
     return gemm_mfma(g, (hipStream_t)stream);
   }
   return gemm_generic(g, (hipStream_t)stream);
+}
+
+// Measurement and test hooks: a product and an attention as a worker step issues them.
+extern "C" int als_k_step_gemm(const void* A, const void* B, void* C, int M, int N, int K, int a_layout, int b_layout,
+                               int in_dtype, int out_dtype, int flags, int epi, const float* R, void* C2, const void* U,
+                               void* ws_dev, size_t ws_bytes, void* stream) {
+  GemmDesc g;
+  int rc = desc_ex(&g, A, B, C, M, N, K, a_layout, b_layout, in_dtype, out_dtype, epi, R, C2, U, ws_dev, ws_bytes);
+  if (rc) return rc;
+  return gemm(g, !(flags & 1), (hipStream_t)stream);
+}
+
+extern "C" int als_k_step_attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int h, int dh, int dtype, int flags,
+                                        void* stream) {
+  if (!qkv || !o || !lse) return set_error(ALS_ERR_INVALID, "null argument");
+  return attention_fwd(qkv, o, lse, B, S, h, dh, dtype == ALS_DTYPE_BF16, !(flags & 1), (hipStream_t)stream);
+}
+
+extern "C" int als_k_step_attention_bwd(const void* qkv, const void* o, const void* d_o, const float* lse, float* dscratch,
+                                        void* dqkv, int B, int S, int h, int dh, int dtype, int flags, void* stream) {
+  if (!qkv || !o || !d_o || !lse || !dscratch || !dqkv) return set_error(ALS_ERR_INVALID, "null argument");
+  return attention_bwd(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, dtype == ALS_DTYPE_BF16, !(flags & 1), (hipStream_t)stream);
 }
 
 extern "C" int als_k_gemm_route(int M, int N, int K, int a_layout, int b_layout, int in_dtype, int out_dtype, int epi, int flags,
@@ -813,7 +839,7 @@ extern "C" int als_k_gemm_route(int M, int N, int K, int a_layout, int b_layout,
   void* any = (void*)(uintptr_t)256;   // stands for aligned operands, never read
   GemmDesc g = plain_desc(any, any, any, M, N, K, a_layout, b_layout, in_dtype, out_dtype, epi, ws_bytes ? any : nullptr, ws_bytes);
   g.R = (const float*)any; g.ldr = N; g.C2 = any; g.U = any;
-  gemm_route(g, in_dtype == ALS_DTYPE_BF16 && !(flags & 1), out, out_len);
+  gemm_route(g, !(flags & 1), out, out_len);
   return ALS_OK;
 }
 

@@ -1,6 +1,6 @@
 // Generic tiled GEMM with fp32 accumulation in vector code: any shape, any of the four operand
-// layouts, fp32 or bf16 operands.  The fallback for shapes that the bf16 MFMA kernels do not take and
-// the independent check of those that they do; fp32 products go to gemm_mfma_f32.hip.
+// layouts, fp32 or bf16 operands.  What als_config.flags bit 0 and use_mfma = 0 select, the independent check of the
+// matrix-core kernels and the fallback for what none of them takes; and the choice between them for a product of a step.
 #include "common.h"
 #include "gelu.h"
 #include <stdio.h>
@@ -96,7 +96,6 @@ static int launch_epi(const GemmDesc& g, hipStream_t st) {
 int gemm_generic(const GemmDesc& g, hipStream_t st) {
   if (g.M <= 0 || g.N <= 0 || g.K <= 0) return set_error(ALS_ERR_INVALID, "gemm: empty shape");
   if (g.epi == EPI_RESID && g.c_bf16) return set_error(ALS_ERR_INVALID, "gemm: residual output must be fp32");
-  if (gemm_mfma_f32_supported(g)) return gemm_mfma_f32(g, st);
   if (g.in_bf16) return g.c_bf16 ? launch_epi<bf16, bf16>(g, st) : launch_epi<bf16, float>(g, st);
   return g.c_bf16 ? launch_epi<float, bf16>(g, st) : launch_epi<float, float>(g, st);
 }
@@ -104,13 +103,14 @@ int gemm_generic(const GemmDesc& g, hipStream_t st) {
 int gemm(const GemmDesc& g, bool allow_mfma, hipStream_t st) {
   if (allow_mfma && gemm_mfma_supported(g)) return gemm_mfma(g, st);
   if (allow_mfma && gemm_mfma_any_supported(g)) return gemm_mfma_any(g, st);
+  if (allow_mfma && gemm_mfma_f32_supported(g)) return gemm_mfma_f32(g, st);
   return gemm_generic(g, st);
 }
 
 void gemm_route(const GemmDesc& g, bool allow_mfma, char* out, int out_len) {
   if (allow_mfma && gemm_mfma_supported(g)) return gemm_mfma_route(g, out, out_len);
   snprintf(out, out_len, "%s", allow_mfma && gemm_mfma_any_supported(g) ? gemm_mfma_any_route(g)
-                               : gemm_mfma_f32_supported(g) ? gemm_mfma_f32_route(g) : "vector");
+                               : allow_mfma && gemm_mfma_f32_supported(g) ? gemm_mfma_f32_route(g) : "vector");
 }
 
 }  // namespace als

@@ -63,10 +63,10 @@ def test_fp32_products(M, N, K, al, bl):
     ref, bound = a.double() @ b.double(), (K + 4) * 2.0 ** -24 * (a.abs().double() @ b.abs().double()) + 1e-7
     for epi, want, scale in ((0, ref, 1.0), (1, ref + res.double(), 1.0), (3, ref * u.double(), u.double().abs())):
         c = torch.full((M, N), float("nan"), device=DEV)
-        A.k_gemm_ex(ad, bd, c, M, N, K, al, bl, epi=epi, R=res if epi == 1 else None, U=u if epi == 3 else None)
+        A.step_gemm(ad, bd, c, M, N, K, al, bl, epi=epi, R=res if epi == 1 else None, U=u if epi == 3 else None)
         assert ((c.double() - want).abs() <= bound * scale + 2.0 ** -22 * want.abs()).all(), epi
     c, c2 = torch.full((M, N), float("nan"), device=DEV), torch.full((M, N), float("nan"), device=DEV)
-    A.k_gemm_ex(ad, bd, c, M, N, K, al, bl, epi=2, C2=c2)
+    A.step_gemm(ad, bd, c, M, N, K, al, bl, epi=2, C2=c2)
     x = ref.requires_grad_()
     y = torch.nn.functional.gelu(x, approximate="tanh")
     y.sum().backward()
@@ -202,7 +202,7 @@ def test_weight_gradients_as_one_list(dtype, kw):
 def test_attention_in_fp32_arithmetic(B, S, h, dh, dt):
     """Sums of up to 1009 fp32 products in tile order: 2^-24 sqrt(1009) 4 < 1e-5; bf16 storage: one rounding (2^-9) of o and
     dqkv, and of the o that the row dots are formed from."""
-    o, ro, lse, rlse, dq, rdq = _attention_case(B, S, h, dh, dt, False)
+    o, ro, lse, rlse, dq, rdq = _attention_case(B, S, h, dh, dt, 0, fwd=A.step_attention_fwd, bwd=A.step_attention_bwd)
     assert _rel(o, ro) < (1e-5 if dt == torch.float32 else 4e-3)
     np.testing.assert_allclose(lse, rlse, rtol=1e-5, atol=1e-5)
     if S > 1:
@@ -210,7 +210,7 @@ def test_attention_in_fp32_arithmetic(B, S, h, dh, dt):
 
 
 @pytest.mark.parametrize("B,S,h,dh", [(1, 34, 1, 32), (1, 64, 3, 64), (2, 65, 1, 32),      # 3, 4 and 5 tiles for four wavefronts
-                                      (1, 1024, 2, 64), (16, 256, 16, 32),                 # the longest chains; the most row blocks
+                                      (1, 1023, 2, 64), (1, 1024, 2, 32), (16, 256, 16, 32),   # the longest chains; the most row blocks
                                       (37, 32, 2, 64), (65, 31, 1, 32)])                   # short rows: a row block per wavefront
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
 def test_attention_with_wavefronts_that_share_a_row_block(B, S, h, dh, dt):
@@ -231,8 +231,8 @@ def test_attention_hides_what_a_query_does_not_see(bad):
         if part:
             x[37, part * d:(part + 1) * d] = bad
         o, lse, sc, dq = torch.empty(B * S, d, device=DEV), torch.empty(B * h * S, device=DEV), torch.empty(B * h * S, device=DEV), torch.empty_like(x)
-        A.k_attention_fwd(x, o, lse, B, S, h, dh, False)
-        A.k_attention_bwd(x, o, d_o, lse, sc, dq, B, S, h, dh, False)
+        A.step_attention_fwd(x, o, lse, B, S, h, dh)
+        A.step_attention_bwd(x, o, d_o, lse, sc, dq, B, S, h, dh)
         res.append((o.cpu(), dq.cpu()))
     for o, dq in res[1:]:
         assert torch.equal(o[:37], res[0][0][:37])
@@ -250,3 +250,44 @@ def test_a_gradient_does_not_depend_on_the_workers_beside_it():
     w["k"] = 4
     _, loss4, g4 = _loss_grad(w, tok)
     assert loss == loss4 and np.array_equal(g, g4)
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_flag_bit_0_and_use_mfma_0_are_vector_code(dt):
+    """The same bits from both, whatever the shape: one kernel, and not the matrix cores', whose fp32 sums run in another order."""
+    gen = torch.Generator(device=DEV).manual_seed(11)
+    r = lambda *s: torch.randn(*s, device=DEV, generator=gen).to(dt)
+    M, N, K = 128, 192, 1024
+    a, b = r(M, K), r(K, N)
+    c = [torch.empty(M, N, device=DEV) for _ in range(3)]
+    A.k_gemm(a, b, c[0], M, N, K)
+    A.step_gemm(a, b, c[1], M, N, K, flags=1)
+    A.step_gemm(a, b, c[2], M, N, K)
+    assert torch.equal(c[0], c[1]) and not torch.equal(c[0], c[2])
+    B, S, h, dh = 1, 200, 2, 64
+    qkv, d_o = r(B * S, 3 * h * dh), r(B * S, h * dh)
+    res = []
+    for fwd, bwd, how in ((A.k_attention_fwd, A.k_attention_bwd, False), (A.step_attention_fwd, A.step_attention_bwd, 1),
+                          (A.step_attention_fwd, A.step_attention_bwd, 0)):
+        o, lse, sc, dq = torch.empty_like(d_o), torch.empty(B * h * S, device=DEV), torch.empty(B * h * S, device=DEV), torch.empty_like(qkv)
+        fwd(qkv, o, lse, B, S, h, dh, how)
+        bwd(qkv, o, d_o, lse, sc, dq, B, S, h, dh, how)
+        res.append((o, lse, dq))
+    assert all(torch.equal(x, y) for x, y in zip(res[0], res[1]))
+    assert not all(torch.equal(x, y) for x, y in zip(res[0], res[2]))
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_a_product_of_more_than_2_22_small_tiles(dt):
+    """131072 x 33001: element offsets beyond 2^32.  Rows and columns at the ends and across them against float64."""
+    M, N, K = 131072, 33001, 40
+    gen = torch.Generator(device=DEV).manual_seed(12)
+    a, b = torch.randn(M, K, device=DEV, generator=gen).to(dt), torch.randn(K, N, device=DEV, generator=gen).to(dt)
+    c = torch.full((M, N), float("nan"), dtype=dt, device=DEV)
+    A.step_gemm(a, b, c, M, N, K)
+    half = 2.0 ** -8 if dt == torch.bfloat16 else 2.0 ** -22
+    for rows, cols in ((torch.arange(0, M, 4001), slice(None)), (torch.arange(M - 130, M), slice(None)), (slice(None), torch.arange(0, N, 3001)),
+                       (slice(None), torch.arange(N - 3, N))):
+        x, y = a[rows].double(), b[:, cols].double()
+        bound = (K + 4) * 2.0 ** -24 * (x.abs() @ y.abs()) + half * (x @ y).abs()
+        assert ((c[rows][:, cols] if isinstance(cols, slice) else c[:, cols]).double() - x @ y).abs().le(bound).all()

@@ -109,7 +109,7 @@ def test_gemm_generic(M, N, K, al, bl, dt):
     np.testing.assert_allclose(c.cpu().numpy(), ar @ br, rtol=1e-5, atol=1e-4)
 
 
-def _attention_case(B, S, h, dh, dt, use_mfma, scale=1.0):
+def _attention_case(B, S, h, dh, dt, use_mfma, scale=1.0, fwd=A.k_attention_fwd, bwd=A.k_attention_bwd):
     rng = np.random.default_rng(S + dh)
     d = h * dh
     qkv = _dev(rng.standard_normal((B * S, 3 * d)).astype(np.float32) * scale, dt)
@@ -118,8 +118,8 @@ def _attention_case(B, S, h, dh, dt, use_mfma, scale=1.0):
     lse = torch.empty(B * h * S, dtype=torch.float32, device=DEV)
     dq = torch.empty_like(qkv)
     scratch = torch.empty(B * h * S, dtype=torch.float32, device=DEV)
-    A.k_attention_fwd(qkv, o, lse, B, S, h, dh, use_mfma)
-    A.k_attention_bwd(qkv, o, d_o, lse, scratch, dq, B, S, h, dh, use_mfma)
+    fwd(qkv, o, lse, B, S, h, dh, use_mfma)
+    bwd(qkv, o, d_o, lse, scratch, dq, B, S, h, dh, use_mfma)
     torch.cuda.synchronize()
     x = qkv.float().cpu().numpy().astype(np.float64)
     split = lambda z: z.reshape(B, S, h, dh).transpose(0, 2, 1, 3)

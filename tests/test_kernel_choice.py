@@ -22,9 +22,12 @@ def test_bf16_products(M, N, K, layout, epi, out, want):
     assert A.gemm_route(M, N, K, *layout, BF16, out, epi) == want
 
 
-def test_bf16_products_with_the_matrix_cores_off():
+@pytest.mark.parametrize("dtype", [F32, BF16])
+def test_products_with_the_matrix_cores_off(dtype):
     for M in (600, 16384):
-        assert A.gemm_route(M, 896, 896, flags=1) == "vector"
+        for layout in ((0, 0), (0, 1), (1, 0)):
+            assert A.gemm_route(M, 896, 896, *layout, dtype, flags=1) == "vector"
+            assert A.gemm_route(M, 896, 896, *layout, dtype) != "vector"
 
 
 @pytest.mark.parametrize("M,N,K,ws,want", [
