@@ -317,6 +317,7 @@ int pick(const GemmDesc& g, hipStream_t st) {
 
 bool gemm_mfma_any_supported(const GemmDesc& g) {
   if (!g.in_bf16 || (g.a_layout == 1 && g.b_layout == 1) || (g.a_layout | g.b_layout) & ~1) return false;
+  if (g.epi == EPI_GELU && !g.c_bf16) return false;   // writes both outputs in bf16 only
   // fewer than 2^32 threads in the one grid dimension: beyond 256 tiles of 128 x 128, blocks of 256 threads on those; below, fewer blocks than that
   return gemm_tiles(g.M, g.N, 128, 128) < (1 << 24);
 }

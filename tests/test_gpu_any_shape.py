@@ -291,3 +291,18 @@ def test_a_product_of_more_than_2_22_small_tiles(dt):
         x, y = a[rows].double(), b[:, cols].double()
         bound = (K + 4) * 2.0 ** -24 * (x.abs() @ y.abs()) + half * (x @ y).abs()
         assert ((c[rows][:, cols] if isinstance(cols, slice) else c[:, cols]).double() - x @ y).abs().le(bound).all()
+
+
+@pytest.mark.parametrize("out", [torch.float32, torch.bfloat16])
+def test_both_outputs_of_gelu_are_written_for_any_output_type(out):
+    M, N, K = 50, 70, 30
+    gen = torch.Generator(device=DEV).manual_seed(13)
+    a, b = torch.randn(M, K, device=DEV, generator=gen).bfloat16(), torch.randn(K, N, device=DEV, generator=gen).bfloat16()
+    c, c2 = (torch.full((M, N), float("nan"), dtype=out, device=DEV) for _ in range(2))
+    A.step_gemm(a, b, c, M, N, K, epi=2, C2=c2)
+    x = (a.double() @ b.double()).requires_grad_()
+    y = torch.nn.functional.gelu(x, approximate="tanh")
+    y.sum().backward()
+    half = 2.0 ** -8 if out == torch.bfloat16 else 1e-5   # one rounding; fp32 sums of 30 products and tanhf
+    assert ((c2.double() - y.detach()).abs() <= half * (1 + y.detach().abs())).all()
+    assert ((c.double() - x.grad).abs() <= half * (1 + x.grad.abs())).all()

@@ -59,3 +59,9 @@ def test_large_products_of_any_shape(dtype, want):
     # the last grid that has fewer than 2^32 threads
     assert A.gemm_route(1 << 22, 512 * 128 - 1, 64, in_dtype=dtype, out_dtype=dtype) == "vector"
     assert A.gemm_route(1 << 22, 511 * 128 - 1, 64, in_dtype=dtype, out_dtype=dtype) == want
+
+
+def test_gelu_with_fp32_outputs_has_vector_code_only():
+    for M in (512, 500):
+        assert A.gemm_route(M, 512, 512, out_dtype=F32, epi=2) == "vector"
+        assert A.gemm_route(M, 512, 512, out_dtype=BF16, epi=2) != "vector"
