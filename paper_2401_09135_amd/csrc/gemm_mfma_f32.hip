@@ -23,10 +23,11 @@ namespace {
 
 struct __attribute__((packed, aligned(4))) f32x4u { f32x4 v; };   // 16 bytes at any element address
 
-template <int BM, int BN, int BK, int WM, int WN, int WK, int AL, int BL>
+template <int BM, int BN, int BK, int WM, int WN, int WK, int AL, int BL, bool NAT>
 struct F32Tile {
   static constexpr int NT = 64 * WM * WN * WK;
-  static constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+  static constexpr int MB = NAT ? 16 : 32;   // rows and columns of a block of the matrix instruction
+  static constexpr int TM = BM / WM / MB, TN = BN / WN / MB;
   static constexpr int A_PITCH = AL == 0 ? BK + 4 : BM + 8, B_PITCH = BL == 1 ? BK + 4 : BN + 8;   // floats
   static constexpr int A_SIZE = A_PITCH * (AL == 0 ? BM : BK), B_SIZE = B_PITCH * (BL == 1 ? BN : BK);
   static constexpr int STAGE = A_SIZE + B_SIZE;
@@ -34,6 +35,7 @@ struct F32Tile {
   static constexpr int LDS_BYTES = 4 * (2 * STAGE > RED ? 2 * STAGE : RED);
   static constexpr int NA = BM * BK / 4 / NT, NB = BN * BK / 4 / NT;   // 16-byte chunks per thread
   static_assert(NA * 4 * NT == BM * BK && NB * 4 * NT == BN * BK && BK % (8 * WK) == 0, "whole chunks and groups");
+  static_assert(!NAT || WK == 1, "the natural order has no shares");
 };
 
 // One operand's tile: chunk c covers tile row c / (LEN/4), 4 elements from 4 (c % (LEN/4)); LEN is the contiguous direction.
@@ -77,10 +79,11 @@ __device__ __forceinline__ void f32_epilogue(const GemmDesc& g, int m, int n, fl
   reinterpret_cast<float*>(g.C)[ci] = x;
 }
 
-// The tile whose first element is (m0, n0).  NAT: the contraction in its natural order, two per step (else 4 hf + e, see above).
+// The tile whose first element is (m0, n0).  NAT: blocks of 16 x 16 (v_mfma_f32_16x16x4_f32: lane l holds row or column l%16 of
+// contraction l/16 of a step, accumulator element v is row 4 (l/16) + v), which take the contraction in its natural order, four per step.
 template <int BM, int BN, int BK, int WM, int WN, int WK, int AL, int BL, bool NAT>
 __device__ __forceinline__ void f32_tile(const GemmDesc& g, const int m0, const int n0, float* lds_f32) {
-  typedef F32Tile<BM, BN, BK, WM, WN, WK, AL, BL> TL;
+  typedef F32Tile<BM, BN, BK, WM, WN, WK, AL, BL, NAT> TL;
   constexpr int TM = TL::TM, TN = TL::TN, NG = BK / 8 / WK;   // groups of 8 of one wavefront per slice
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, hf = lane >> 5, lr = lane & 31;
   const int wk = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
@@ -103,41 +106,60 @@ __device__ __forceinline__ void f32_tile(const GemmDesc& g, const int m0, const 
     store_chunks<(BL == 1 ? BK : BN), TL::B_PITCH, TL::NB, TL::NT>(b, s + TL::A_SIZE);
   };
 
-  f32x16 acc[TM][TN];
+  constexpr int ACC = NAT ? 4 : 16;
+  typedef float acc_t __attribute__((ext_vector_type(ACC)));
+  acc_t acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; i++)
 #pragma unroll
     for (int j = 0; j < TN; j++)
 #pragma unroll
-      for (int v = 0; v < 16; v++) acc[i][j][v] = 0.0f;
+      for (int v = 0; v < ACC; v++) acc[i][j][v] = 0.0f;
   auto compute = [&](const float* s) {
-    constexpr int H = NAT ? 1 : 4, E = NAT ? 2 : 1;   // step e of a group of 8: contraction H hf + E e
-    const float* As = s + (AL == 0 ? (wm * TM * 32 + lr) * TL::A_PITCH + H * hf : H * hf * TL::A_PITCH + wm * TM * 32 + lr);
-    const float* Bs = s + TL::A_SIZE + (BL == 1 ? (wn * TN * 32 + lr) * TL::B_PITCH + H * hf : H * hf * TL::B_PITCH + wn * TN * 32 + lr);
+    if constexpr (NAT) {
+      const int r = lane & 15, q = lane >> 4;
+      const float* As = s + (AL == 0 ? (wm * TM * 16 + r) * TL::A_PITCH + q : q * TL::A_PITCH + wm * TM * 16 + r);
+      const float* Bs = s + TL::A_SIZE + (BL == 1 ? (wn * TN * 16 + r) * TL::B_PITCH + q : q * TL::B_PITCH + wn * TN * 16 + r);
 #pragma unroll
-    for (int q = 0; q < NG; q++) {
-      const int k = (wk * NG + q) * 8;
-      f32x4 a[TM], b[TN];
+      for (int k = 0; k < BK; k += 4) {
+        float a[TM], b[TN];
 #pragma unroll
-      for (int i = 0; i < TM; i++) {
-        if constexpr (AL == 0 && !NAT) a[i] = *reinterpret_cast<const f32x4*>(As + i * 32 * TL::A_PITCH + k);
-        else
+        for (int i = 0; i < TM; i++) a[i] = AL == 0 ? As[i * 16 * TL::A_PITCH + k] : As[k * TL::A_PITCH + i * 16];
 #pragma unroll
-          for (int e = 0; e < 4; e++) a[i][e] = AL == 0 ? As[i * 32 * TL::A_PITCH + k + E * e] : As[(k + E * e) * TL::A_PITCH + i * 32];
-      }
-#pragma unroll
-      for (int j = 0; j < TN; j++) {
-        if constexpr (BL == 1 && !NAT) b[j] = *reinterpret_cast<const f32x4*>(Bs + j * 32 * TL::B_PITCH + k);
-        else
-#pragma unroll
-          for (int e = 0; e < 4; e++) b[j][e] = BL == 1 ? Bs[j * 32 * TL::B_PITCH + k + E * e] : Bs[(k + E * e) * TL::B_PITCH + j * 32];
-      }
-#pragma unroll
-      for (int e = 0; e < 4; e++)
+        for (int j = 0; j < TN; j++) b[j] = BL == 1 ? Bs[j * 16 * TL::B_PITCH + k] : Bs[k * TL::B_PITCH + j * 16];
 #pragma unroll
         for (int i = 0; i < TM; i++)
 #pragma unroll
-          for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+      }
+    } else {
+      const float* As = s + (AL == 0 ? (wm * TM * 32 + lr) * TL::A_PITCH + 4 * hf : 4 * hf * TL::A_PITCH + wm * TM * 32 + lr);
+      const float* Bs = s + TL::A_SIZE + (BL == 1 ? (wn * TN * 32 + lr) * TL::B_PITCH + 4 * hf : 4 * hf * TL::B_PITCH + wn * TN * 32 + lr);
+#pragma unroll
+      for (int q = 0; q < NG; q++) {
+        const int k = (wk * NG + q) * 8;
+        f32x4 a[TM], b[TN];
+#pragma unroll
+        for (int i = 0; i < TM; i++) {
+          if constexpr (AL == 0) a[i] = *reinterpret_cast<const f32x4*>(As + i * 32 * TL::A_PITCH + k);
+          else
+#pragma unroll
+            for (int e = 0; e < 4; e++) a[i][e] = As[(k + e) * TL::A_PITCH + i * 32];
+        }
+#pragma unroll
+        for (int j = 0; j < TN; j++) {
+          if constexpr (BL == 1) b[j] = *reinterpret_cast<const f32x4*>(Bs + j * 32 * TL::B_PITCH + k);
+          else
+#pragma unroll
+            for (int e = 0; e < 4; e++) b[j][e] = Bs[(k + e) * TL::B_PITCH + j * 32];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+#pragma unroll
+          for (int i = 0; i < TM; i++)
+#pragma unroll
+            for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
+      }
     }
   };
 
@@ -162,7 +184,15 @@ __device__ __forceinline__ void f32_tile(const GemmDesc& g, const int m0, const 
     }
   }
 
-  if constexpr (WK == 1) {
+  if constexpr (NAT) {
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int j = 0; j < TN; j++)
+#pragma unroll
+        for (int v = 0; v < 4; v++)
+          f32_epilogue(g, m0 + (wm * TM + i) * 16 + 4 * (lane >> 4) + v, n0 + (wn * TN + j) * 16 + (lane & 15), acc[i][j][v]);
+  } else if constexpr (WK == 1) {
 #pragma unroll
     for (int i = 0; i < TM; i++)
 #pragma unroll
@@ -217,7 +247,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void gemm_f32_dw_list_kernel(
 
 template <int BM, int BN, int BK, int WM, int WN, int WK, int AL, int BL, bool NAT = false>
 int launch_f32(const GemmDesc& g, hipStream_t st) {
-  typedef F32Tile<BM, BN, BK, WM, WN, WK, AL, BL> TL;
+  typedef F32Tile<BM, BN, BK, WM, WN, WK, AL, BL, NAT> TL;
   auto kern = gemm_f32_kernel<BM, BN, BK, WM, WN, WK, AL, BL, NAT>;
   if (TL::LDS_BYTES > 65536) {
     static std::atomic<bool> attr_set{false};  // the call is idempotent: a race only repeats it
@@ -234,7 +264,7 @@ int launch_f32(const GemmDesc& g, hipStream_t st) {
 
 template <int BM, int BN, int BK, int WM, int WN, int WK, bool NAT = false>
 int launch_dw_list(const DwProblem* probs, int n, int K, hipStream_t st) {
-  typedef F32Tile<BM, BN, BK, WM, WN, WK, 1, 0> TL;
+  typedef F32Tile<BM, BN, BK, WM, WN, WK, 1, 0, NAT> TL;
   auto kern = gemm_f32_dw_list_kernel<BM, BN, BK, WM, WN, WK, NAT>;
   static std::atomic<bool> attr_set{false};  // the call is idempotent: a race only repeats it
   if (!attr_set.load(std::memory_order_acquire)) {
@@ -251,25 +281,26 @@ int launch_dw_list(const DwProblem* probs, int n, int K, hipStream_t st) {
 }
 
 // Which tile a product (or a list of them, its tiles counted together) takes: 0 for 128 x 128, 1 for 64 x 64 with 2 K shares, 2 for
-// 32 x 32 with 8, 3 with 4, 4 for 32 x 32 with one wavefront and k in its natural order.
+// 32 x 32 with 8, 3 with 4, 4 for 32 x 32 in blocks of 16 x 16 with k in its natural order.
 // The largest tile that still gives (almost) every CU a workgroup: a larger tile moves fewer operand bytes per flop, an idle CU
-// costs its whole rate.  In us, 128 x 128 / 64 x 64 / 32 x 32 with 8 K shares / with 4:
-//   4096 x 8192 x 512 (2048, 8192 tiles): 307 / 347 / 478 / 420     2048 x 1536 x 512 (192, 768): 48 / 39 / 49 / 44
-//   1024 x 1024 x 256 (64, 256): 26 / 9.9 / 12 / 10                 256 x 2000 x 1024 (32, 128): 127 / 43 / 26 / 31
-//   512 x 512 x 512 (16, 64): 44 / 14 / 6.6 / 7.6                   1024 x 256 x 256 (16, 64): 28 / 8.6 / 5.7 / 5.5
-// The smallest: one wavefront per tile, k in its natural order (NAT), so the bits of a plain loop over k.  A short run in fp32 mode
-// can then be held to 1e-5 against an fp32 program that adds in that order (elements with a gradient near zero carry rounding
-// into AdamW's direction: with shares of K the same run is as near to float64, but 1.6e-5 from that program); the launch is the
-// time either way (a round of 2 layers of width 64: 1195 us with shares, 1202 without).
+// costs its whole rate.  In us, 128 x 128 / 64 x 64 / 32 x 32 with 8 K shares / with 4 / in natural order:
+//   4096 x 8192 x 512 (2048, 8192 tiles): 307 / 347 / 478 / 420 / -     2048 x 1536 x 512 (192, 768): 48 / 39 / 49 / 44 / -
+//   1024 x 1024 x 256 (64, 256): 26 / 9.9 / 12 / 10 / -                 256 x 2000 x 1024 (32, 128): 127 / 43 / 26 / 31 / -
+//   512 x 512 x 511 (16, 64): 44 / 14 / 6.6 / 8.5 / 9.1                 1024 x 256 x 256 (16, 64): 28 / 8.6 / 5.7 / 5.4 / 5.6
+//   1024 x 256 x 511 (16, 64): - / - / - / 7.8 / 8.4                    256 x 64 x 256 (1, 4): - / - / - / 5.2 / 5.2
+// Up to K = 256 the natural order costs nothing (1 to 2 % over 260 sizes): the chain of a 16 x 16 block, K/4 instructions of 32
+// cycles, is as long as that of a 32 x 32 one with 4 shares of K, which are added at the end.  Its results have the bits of a plain
+// loop over k, which keeps short runs of the smallest models within 1e-5 of an fp32 program that adds so (elements with a gradient
+// near zero carry rounding into AdamW's direction).  From there on the shares win, 7 % up to 512, and their shorter sums are nearer to
+// float64; a short run is then as near to float64 as that program, but no longer to its bits.
 template <typename Tiles>
-int choose_tile(Tiles tiles, int K, int nat_tiles) {
+int choose_tile(Tiles tiles, int K) {
   if (tiles(128, 128) >= 256) return 0;
   if (tiles(64, 64) >= 192) return 1;
-  if (K >= 512) return 2;
-  return tiles(32, 32) <= nat_tiles && K <= 256 ? 4 : 3;
+  return K >= 512 ? 2 : K > 256 ? 3 : 4;
 }
 int choose_tile(const GemmDesc& g) {
-  return choose_tile([&](int bm, int bn) { return gemm_tiles(g.M, g.N, bm, bn); }, g.K, 64);
+  return choose_tile([&](int bm, int bn) { return gemm_tiles(g.M, g.N, bm, bn); }, g.K);
 }
 
 template <int AL, int BL>
@@ -279,7 +310,7 @@ int pick(const GemmDesc& g, hipStream_t st) {
     case 1: return launch_f32<64, 64, 64, 2, 2, 2, AL, BL>(g, st);
     case 2: return launch_f32<32, 32, 128, 1, 1, 8, AL, BL>(g, st);
     case 3: return launch_f32<32, 32, 64, 1, 1, 4, AL, BL>(g, st);
-    default: return launch_f32<32, 32, 64, 1, 1, 1, AL, BL, true>(g, st);
+    default: return launch_f32<32, 32, 64, 2, 2, 1, AL, BL, true>(g, st);
   }
 }
 
@@ -304,12 +335,12 @@ const char* gemm_mfma_f32_route(const GemmDesc& g) {
 // the tile by the same rule as for one product, on the tiles of all
 int gemm_mfma_f32_dw_list(const DwProblem* probs, int n, int K, hipStream_t st) {
   if (n <= 0) return ALS_OK;
-  switch (choose_tile([&](int bm, int bn) { return dw_list_tiles(probs, n, bm, bn); }, K, 256)) {
+  switch (choose_tile([&](int bm, int bn) { return dw_list_tiles(probs, n, bm, bn); }, K)) {
     case 0: return launch_dw_list<128, 128, 32, 2, 2, 1>(probs, n, K, st);
     case 1: return launch_dw_list<64, 64, 64, 2, 2, 2>(probs, n, K, st);
     case 2: return launch_dw_list<32, 32, 128, 1, 1, 8>(probs, n, K, st);
     case 3: return launch_dw_list<32, 32, 64, 1, 1, 4>(probs, n, K, st);
-    default: return launch_dw_list<32, 32, 64, 1, 1, 1, true>(probs, n, K, st);
+    default: return launch_dw_list<32, 32, 64, 2, 2, 1, true>(probs, n, K, st);
   }
 }
 

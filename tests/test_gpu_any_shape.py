@@ -6,7 +6,7 @@ import torch
 
 import als_inputs as I
 import paper_2401_09135_amd as A
-from oracle import lm
+from oracle import lm, run
 from test_gpu_kernels import _attention_case
 
 pytestmark = pytest.mark.gpu
@@ -48,7 +48,8 @@ def test_token_order_of_the_embedding_gradient(V, B, S):
     assert _rel(lm.views(g, w)["E"], lm.views(rg, w)["E"]) < 1e-5
 
 
-@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (33, 31, 63), (32, 65, 65), (31, 33, 513), (40, 96, 640),   # 32 x 32 tiles: 4 and 8 shares of K
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (33, 31, 63), (32, 65, 65), (130, 70, 256),     # 32 x 32 tiles in natural order
+                                   (31, 33, 257), (70, 40, 511), (31, 33, 513), (40, 96, 640),   # 4 and 8 shares of K
                                    (769, 1025, 65), (832, 960, 128),                # 64 x 64
                                    (2047, 2049, 33), (2048, 2048, 96)])             # 128 x 128, the least number of tiles
 @pytest.mark.parametrize("al,bl", [(0, 0), (0, 1), (1, 0), (1, 1)])
@@ -171,7 +172,7 @@ def test_cross_entropy_of_any_vocabulary(V, dtype):
 
 
 @pytest.mark.parametrize("dtype,kw", [("f32", dict(L=17, S=7, B=1)),                              # more products than one launch takes
-                                      ("f32", dict(L=2, d=192, h=3, ff=320, V=333, S=31, B=2)),       # 32 x 32 tiles, 4 shares of K
+                                      ("f32", dict(L=2, d=192, h=3, ff=320, V=333, S=31, B=2)),       # 32 x 32 tiles
                                       ("f32", dict(L=1, d=128, h=2, ff=192, V=130, S=103, B=5)),      # 8 shares
                                       ("f32", dict(L=2, d=512, h=8, ff=1024, V=70, S=33, B=1)),       # 64 x 64
                                       ("f32", dict(L=2, d=512, h=8, ff=2048, V=700, S=17, B=1)),      # 128 x 128
@@ -306,3 +307,32 @@ def test_both_outputs_of_gelu_are_written_for_any_output_type(out):
     half = 2.0 ** -8 if out == torch.bfloat16 else 1e-5   # one rounding; fp32 sums of 30 products and tanhf
     assert ((c2.double() - y.detach()).abs() <= half * (1 + y.detach().abs())).all()
     assert ((c.double() - x.grad).abs() <= half * (1 + x.grad.abs())).all()
+
+
+@pytest.mark.parametrize("M,N,K", [(5, 3, 2), (64, 48, 200), (512, 512, 256), (100, 900, 255)])
+@pytest.mark.parametrize("al,bl", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_fp32_products_of_few_tiles_have_the_bits_of_a_plain_loop(M, N, K, al, bl):
+    """One fused multiply-add after the other, k ascending, whatever the number of tiles.  (A product of two fp32 numbers is exact in
+    float64; its sum with the accumulator is rounded there first, which changes one result in 2^29.)"""
+    gen = torch.Generator(device=DEV).manual_seed(M + N + K)
+    a, b = torch.randn(M, K, device=DEV, generator=gen), torch.randn(K, N, device=DEV, generator=gen)
+    c = torch.full((M, N), float("nan"), device=DEV)
+    A.step_gemm(a if al == 0 else a.t().contiguous(), b if bl == 0 else b.t().contiguous(), c, M, N, K, al, bl)
+    want = torch.zeros(M, N, device=DEV)
+    for k in range(K):
+        want = (a[:, k:k + 1].double() * b[k].double() + want.double()).float()
+    assert (c != want).sum().item() <= 1 + M * N * K >> 26
+
+
+@pytest.mark.parametrize("kw", [dict(ff=320, V=300, S=36), dict(d=128, h=4, V=300, S=33), dict(d=128, h=4, ff=384, V=511, S=60)])
+def test_short_fp32_runs_are_as_near_to_float64_as_the_fp32_oracle(kw):
+    """Models just past the smallest one, whose sums are longer than those in natural order: what fp32 mode holds there is the accuracy
+    of an fp32 program (a quarter for the spread between two orders of sums), not its bits."""
+    w = dict(I.workload("tiny"), N=1, **kw)
+    theta0 = I.theta0(lm.param_layout(w), w["seed"])
+    stream = lambda i: I.TokenStream(w["seed"], i, w["B"], w["S"], w["V"])
+    rule = dict(poly_exponent=0.5)
+    ref32, ref64 = (run.run_async(w, theta0, stream, rule=rule, dtype=t)["theta"] for t in (np.float32, np.float64))
+    got = A.run_async(w, theta0, stream, rule=dict(rule))
+    got["ctx"].close()
+    assert _rel(got["theta"], ref64) < 1.25 * _rel(ref32, ref64)

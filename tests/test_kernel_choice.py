@@ -65,3 +65,13 @@ def test_gelu_with_fp32_outputs_has_vector_code_only():
     for M in (512, 500):
         assert A.gemm_route(M, 512, 512, out_dtype=F32, epi=2) == "vector"
         assert A.gemm_route(M, 512, 512, out_dtype=BF16, epi=2) != "vector"
+
+
+@pytest.mark.parametrize("M,N,K,layout,want", [
+    (256, 256, 256, (0, 0), "f32 32x32 natural"), (288, 256, 256, (0, 0), "f32 32x32 natural"),   # no border in the number of tiles
+    (1024, 704, 256, (1, 0), "f32 32x32 natural"), (1024, 704, 257, (1, 0), "f32 32x32/4"),       # up to 191 tiles of 64 x 64
+    (1024, 704, 511, (0, 1), "f32 32x32/4"), (1024, 704, 512, (0, 1), "f32 32x32/8"),
+    (1024, 768, 256, (0, 1), "f32 64x64/2"), (2048, 2048, 256, (0, 1), "f32 128x128"),
+])
+def test_fp32_products(M, N, K, layout, want):
+    assert A.gemm_route(M, N, K, *layout, F32) == want
