@@ -13,8 +13,8 @@
 extern "C" {
 #endif
 
-/* Benchmark hooks.  als_prof_enable(n), n >= 1, makes every n-th MFMA GEMM launch record a HIP
- * event before and after itself on its own stream (a timed launch costs about 20 us of host
+/* Benchmark hooks.  als_prof_enable(n), n >= 1, makes every n-th GEMM launch on the matrix cores (single products and the
+ * launches of all weight gradients) record a HIP event before and after itself on its own stream (a timed launch costs about 20 us of host
  * time and orders the stream around it, so a throughput run samples); 0 switches it off;
  * als_prof_collect waits for the device and returns, per kernel instantiation (id), the number of launches, their summed duration in ms and their
  * summed algorithmic FLOPs (2 M N K), then forgets them.  Returns the number of entries

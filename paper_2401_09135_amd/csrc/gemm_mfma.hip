@@ -28,7 +28,7 @@
 // receives element r%4 of lanes r/4, 4 + r/4, 8 + r/4, 12 + r/4.
 #include "common.h"
 #include "als_bench.h"
-#include <hip/hip_ext.h>
+#include "gemm_launch.h"
 #include <stdio.h>
 
 #include <atomic>
@@ -42,11 +42,9 @@ namespace {
 
 #include "gemm_mfma_common.h"
 
-// ---- optional per-kernel timing (benchmarks): HIP events around every MFMA GEMM launch, on
+// ---- optional per-kernel timing (benchmarks): HIP events around every GEMM launch on the matrix cores, on
 // the stream it is launched on, grouped by kernel instantiation -----------------------------
-struct ProfRec { hipEvent_t e0, e1; int id; double flops; };
 std::mutex g_prof_mu;
-bool g_prof_on = false;
 int g_prof_every = 1;        // time one launch in g_prof_every
 unsigned g_prof_count = 0;
 std::vector<ProfRec> g_prof;
@@ -278,31 +276,8 @@ int launch(const MfmaArgs& a, int nsplit, hipStream_t st) {
                                 hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES));
     attr_set.store(true, std::memory_order_release);
   }
-  dim3 grid(a.tiles_m * a.tiles_n * nsplit);
-  ProfRec rec;
-  bool prof = false;
-  if (g_prof_on) {
-    std::lock_guard<std::mutex> lk(g_prof_mu);
-    if (g_prof_on && (g_prof_count++ % (unsigned)g_prof_every) == 0 && hipEventCreate(&rec.e0) == hipSuccess) {
-      if (hipEventCreate(&rec.e1) == hipSuccess) prof = true;
-      else (void)hipEventDestroy(rec.e0);
-    }
-  }
-  if (prof) {
-    // start/stop events attached to the dispatch itself: their difference is the kernel's own
-    // execution time, as a profiler reports it
-    hipExtLaunchKernelGGL(kern, grid, dim3(TL::NT), TL::LDS_BYTES, st, rec.e0, rec.e1, 0, a);
-  } else {
-    hipLaunchKernelGGL(kern, grid, dim3(TL::NT), TL::LDS_BYTES, st, a);
-  }
-  ALS_CHECK_LAUNCH();
-  if (prof) {
-    rec.id = kernel_id(BM, BN, AL, BL, EPI, sizeof(TO) == 2, SPLIT, NBUF);
-    rec.flops = 2.0 * a.M * a.N * (double)a.K;
-    std::lock_guard<std::mutex> lk(g_prof_mu);
-    g_prof.push_back(rec);
-  }
-  return ALS_OK;
+  const int id = kernel_id(BM, BN, AL, BL, EPI, sizeof(TO) == 2, SPLIT, NBUF);
+  return launch_gemm(kern, a.tiles_m * a.tiles_n * nsplit, TL::NT, TL::LDS_BYTES, st, id, product_flops(a.M, a.N, a.K), a);
 }
 
 template <int AL, int BL, int EPI, typename TO, bool SPLIT>
@@ -315,26 +290,8 @@ int launch_pp(const MfmaArgs& a, int nsplit, hipStream_t st) {
                                 hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES));
     attr_set.store(true, std::memory_order_release);
   }
-  dim3 grid(a.tiles_m * a.tiles_n * nsplit);
-  ProfRec rec;
-  bool prof = false;
-  if (g_prof_on) {
-    std::lock_guard<std::mutex> lk(g_prof_mu);
-    if (g_prof_on && (g_prof_count++ % (unsigned)g_prof_every) == 0 && hipEventCreate(&rec.e0) == hipSuccess) {
-      if (hipEventCreate(&rec.e1) == hipSuccess) prof = true;
-      else (void)hipEventDestroy(rec.e0);
-    }
-  }
-  if (prof) hipExtLaunchKernelGGL(kern, grid, dim3(512), TL::LDS_BYTES, st, rec.e0, rec.e1, 0, a);
-  else hipLaunchKernelGGL(kern, grid, dim3(512), TL::LDS_BYTES, st, a);
-  ALS_CHECK_LAUNCH();
-  if (prof) {
-    rec.id = kernel_id(256, 256, AL, BL, EPI, sizeof(TO) == 2, SPLIT, 4);
-    rec.flops = 2.0 * a.M * a.N * (double)a.K;
-    std::lock_guard<std::mutex> lk(g_prof_mu);
-    g_prof.push_back(rec);
-  }
-  return ALS_OK;
+  const int id = kernel_id(256, 256, AL, BL, EPI, sizeof(TO) == 2, SPLIT, 4);
+  return launch_gemm(kern, a.tiles_m * a.tiles_n * nsplit, 512, TL::LDS_BYTES, st, id, product_flops(a.M, a.N, a.K), a);
 }
 
 template <int AL, int BL, int EPI, typename TO, bool SPLIT>
@@ -346,31 +303,28 @@ int launch_ppd(const MfmaArgs& a, int nsplit, hipStream_t st) {
     ALS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS));
     attr_set.store(true, std::memory_order_release);
   }
-  dim3 grid(a.tiles_m * a.tiles_n * nsplit);
-  ProfRec rec;
-  bool prof = false;
-  if (g_prof_on) {
-    std::lock_guard<std::mutex> lk(g_prof_mu);
-    if (g_prof_on && (g_prof_count++ % (unsigned)g_prof_every) == 0 && hipEventCreate(&rec.e0) == hipSuccess) {
-      if (hipEventCreate(&rec.e1) == hipSuccess) prof = true;
-      else (void)hipEventDestroy(rec.e0);
-    }
-  }
-  if (prof) hipExtLaunchKernelGGL(kern, grid, dim3(512), LDS, st, rec.e0, rec.e1, 0, a);
-  else hipLaunchKernelGGL(kern, grid, dim3(512), LDS, st, a);
-  ALS_CHECK_LAUNCH();
-  if (prof) {
-    rec.id = kernel_id(256, 256, AL, BL, EPI, sizeof(TO) == 2, SPLIT, 4) | 1 << 10;   // bit 10: direct-to-LDS form
-    rec.flops = 2.0 * a.M * a.N * (double)a.K;
-    std::lock_guard<std::mutex> lk(g_prof_mu);
-    g_prof.push_back(rec);
-  }
-  return ALS_OK;
+  const int id = kernel_id(256, 256, AL, BL, EPI, sizeof(TO) == 2, SPLIT, 4) | 1 << 10;   // bit 10: direct-to-LDS form
+  return launch_gemm(kern, a.tiles_m * a.tiles_n * nsplit, 512, LDS, st, id, product_flops(a.M, a.N, a.K), a);
 }
 
 inline bool fits(int M, int N, int bm, int bn) { return M % bm == 0 && N % bn == 0; }
 
 }  // namespace
+
+std::atomic<bool> g_prof_on{false};
+
+bool prof_begin(ProfRec* rec) {
+  std::lock_guard<std::mutex> lk(g_prof_mu);
+  if (!g_prof_on || (g_prof_count++ % (unsigned)g_prof_every) != 0 || hipEventCreate(&rec->e0) != hipSuccess) return false;
+  if (hipEventCreate(&rec->e1) == hipSuccess) return true;
+  (void)hipEventDestroy(rec->e0);
+  return false;
+}
+
+void prof_end(const ProfRec& rec) {
+  std::lock_guard<std::mutex> lk(g_prof_mu);
+  g_prof.push_back(rec);
+}
 
 bool gemm_mfma_supported(const GemmDesc& g) {
   if (!g.in_bf16) return false;
@@ -626,24 +580,9 @@ int dw_group_launch(const DwProblem* d_probs, const DwItem* d_items, const DwSpl
                                 hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES));
     attr_set.store(true, std::memory_order_release);
   }
-  ProfRec rec;
-  bool prof = false;
-  if (g_prof_on) {
-    std::lock_guard<std::mutex> lk(g_prof_mu);
-    if (g_prof_on && (g_prof_count++ % (unsigned)g_prof_every) == 0 && hipEventCreate(&rec.e0) == hipSuccess) {
-      if (hipEventCreate(&rec.e1) == hipSuccess) prof = true;
-      else (void)hipEventDestroy(rec.e0);
-    }
-  }
-  if (prof) hipExtLaunchKernelGGL(kern, dim3(plan.n_items), dim3(512), TL::LDS_BYTES, st, rec.e0, rec.e1, 0, d_probs, d_items, partial_tiles);
-  else hipLaunchKernelGGL(kern, dim3(plan.n_items), dim3(512), TL::LDS_BYTES, st, d_probs, d_items, partial_tiles);
-  ALS_CHECK_LAUNCH();
-  if (prof) {
-    rec.id = 1 << 12;   // bit 12: the grouped weight-gradient kernel
-    rec.flops = plan.flops;
-    std::lock_guard<std::mutex> lk(g_prof_mu);
-    g_prof.push_back(rec);
-  }
+  const int id = 1 << 12;   // bit 12: this kernel
+  int rc = launch_gemm(kern, plan.n_items, 512, TL::LDS_BYTES, st, id, plan.flops, d_probs, d_items, partial_tiles);
+  if (rc) return rc;
   if (plan.n_split) {
     hipLaunchKernelGGL(dw_tile_reduce_kernel, dim3(plan.n_split * 16), dim3(256), 0, st, d_probs, d_split, partial_tiles);
     ALS_CHECK_LAUNCH();
@@ -691,6 +630,18 @@ extern "C" int als_prof_collect(int max_entries, int32_t* ids, int64_t* launches
 extern "C" int als_prof_kernel_name(int id, char* out, int out_len) {
   if (!out || out_len < 1) return als::set_error(ALS_ERR_INVALID, "als_prof_kernel_name: null output");
   static const char* epi[4] = {"STORE", "RESID", "GELU", "DGELU"};
+  if (id >> 13) {
+    static const char* const bf16_tile[] = {"128, 128", "128, 64", "64, 64", "32, 32"};
+    static const char* const f32_tile[] = {"128, 128", "64, 64", "32, 32 / 8", "32, 32 / 4", "32, 32 natural"};
+    static const char* const kind[] = {"", "gemm_deep_kernel", "gemm_any_kernel", "gemm_f32_kernel", "gemm_any_dw_list_kernel", "gemm_f32_dw_list_kernel"};
+    const int k = id >> 13, t = id & 7, al = (id >> 3) & 1, bl = (id >> 4) & 1;
+    if (k < 1 || k > als::PROF_F32_LIST || t > 4) return als::set_error(ALS_ERR_INVALID, "als_prof_kernel_name: unknown id %d", id);
+    const char* tile = k == als::PROF_F32 || k == als::PROF_F32_LIST ? f32_tile[t] : bf16_tile[t & 3];
+    if (k == als::PROF_DEEP) snprintf(out, out_len, "%s<%s, %d, %s, %s>", kind[k], tile, bl, epi[(id >> 5) & 3], (id >> 7) & 1 ? "bf16" : "float");
+    else if (k == als::PROF_ANY || k == als::PROF_F32) snprintf(out, out_len, "%s<%s, %d, %d>", kind[k], tile, al, bl);
+    else snprintf(out, out_len, "%s<%s>", kind[k], tile);
+    return ALS_OK;
+  }
   if ((id >> 12) & 1) { snprintf(out, out_len, "gemm_pp_dw_grouped_kernel"); return ALS_OK; }
   int nbuf = ((id >> 8) & 3) + 1, bm = ((id & 1) + 1) * 128, bn = (((id >> 1) & 1) + 1) * 128;
   int occ = nbuf == 2 ? (bm == 128 ? 2 : 1) : nbuf == 3 ? 2 : (bm == 256 ? 2 : 3);

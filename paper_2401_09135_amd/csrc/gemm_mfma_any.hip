@@ -14,6 +14,7 @@
 // float64 the same or smaller (shares of K are shorter sums).
 #include "common.h"
 #include "gelu.h"
+#include "gemm_launch.h"
 
 #include <atomic>
 
@@ -264,9 +265,8 @@ int launch_any(const GemmDesc& g, hipStream_t st) {
     attr_set.store(true, std::memory_order_release);
   }
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(TL::NT), TL::LDS_BYTES, st, g, tiles_n);
-  ALS_CHECK_LAUNCH();
-  return ALS_OK;
+  return launch_gemm(kern, tiles_m * tiles_n, TL::NT, TL::LDS_BYTES, st, prof_id(PROF_ANY, BM == 32 ? 3 : BM == 64 ? 2 : BN == 64 ? 1 : 0, AL, BL), product_flops(g.M, g.N, g.K),
+                     g, tiles_n);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int WK>
@@ -281,8 +281,8 @@ int launch_dw_list(const DwProblem* probs, int n, int K, hipStream_t st) {
   DwList list;
   for (int i = 0, ntiles; i < n; ) {
     i += list.fill(probs + i, n - i, K, BM, BN, &ntiles);
-    hipLaunchKernelGGL(kern, dim3(ntiles), dim3(TL::NT), TL::LDS_BYTES, st, list);
-    ALS_CHECK_LAUNCH();
+    int rc = launch_gemm(kern, ntiles, TL::NT, TL::LDS_BYTES, st, prof_id(PROF_ANY_LIST, BM == 32 ? 3 : BM == 64 ? 2 : BN == 64 ? 1 : 0), list_flops(list), list);
+    if (rc) return rc;
   }
   return ALS_OK;
 }

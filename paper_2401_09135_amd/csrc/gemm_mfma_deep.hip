@@ -19,6 +19,7 @@
 //   contraction-strided, [64 k][2 BN bytes]: k row r keeps its 64-byte group q at q ^ (r & 3) (BN = 128) or q ^ ((r >> 1) & 1)
 //   (BN = 64): the 4 k rows of a transpose read fall into 4 different quarters of the banks.
 #include "common.h"
+#include "gemm_launch.h"
 
 #include <atomic>
 
@@ -185,9 +186,8 @@ int launch_deep(const MfmaArgs& a, hipStream_t st) {
     ALS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES));
     attr_set.store(true, std::memory_order_release);
   }
-  hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n), dim3(TL::NT), TL::LDS_BYTES, st, a);
-  ALS_CHECK_LAUNCH();
-  return ALS_OK;
+  return launch_gemm(kern, a.tiles_m * a.tiles_n, TL::NT, TL::LDS_BYTES, st,
+                     prof_id(PROF_DEEP, BM == 128 ? 0 : 2, 0, BL, EPI, sizeof(TO) == 2), product_flops(a.M, a.N, a.K), a);
 }
 
 template <int BM, int BN, int NST>

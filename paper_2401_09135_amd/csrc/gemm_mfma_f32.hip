@@ -15,6 +15,7 @@
 // error against float64 the same or smaller (shares of K are shorter sums).
 #include "common.h"
 #include "gelu.h"
+#include "gemm_launch.h"
 #include <atomic>
 
 namespace als {
@@ -257,9 +258,8 @@ int launch_f32(const GemmDesc& g, hipStream_t st) {
     }
   }
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(TL::NT), TL::LDS_BYTES, st, g, tiles_n);
-  ALS_CHECK_LAUNCH();
-  return ALS_OK;
+  return launch_gemm(kern, tiles_m * tiles_n, TL::NT, TL::LDS_BYTES, st, prof_id(PROF_F32, NAT ? 4 : BM == 32 ? (WK == 8 ? 2 : 3) : BM == 64 ? 1 : 0, AL, BL), product_flops(g.M, g.N, g.K),
+                     g, tiles_n);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int WK, bool NAT = false>
@@ -274,8 +274,8 @@ int launch_dw_list(const DwProblem* probs, int n, int K, hipStream_t st) {
   DwList list;
   for (int i = 0, ntiles; i < n; ) {
     i += list.fill(probs + i, n - i, K, BM, BN, &ntiles);
-    hipLaunchKernelGGL(kern, dim3(ntiles), dim3(TL::NT), TL::LDS_BYTES, st, list);
-    ALS_CHECK_LAUNCH();
+    int rc = launch_gemm(kern, ntiles, TL::NT, TL::LDS_BYTES, st, prof_id(PROF_F32_LIST, NAT ? 4 : BM == 32 ? (WK == 8 ? 2 : 3) : BM == 64 ? 1 : 0), list_flops(list), list);
+    if (rc) return rc;
   }
   return ALS_OK;
 }

@@ -336,3 +336,29 @@ def test_short_fp32_runs_are_as_near_to_float64_as_the_fp32_oracle(kw):
     got = A.run_async(w, theta0, stream, rule=dict(rule))
     got["ctx"].close()
     assert _rel(got["theta"], ref64) < 1.25 * _rel(ref32, ref64)
+
+
+def test_every_matrix_core_kernel_is_timed_on_request():
+    """One entry per kernel with all of its flops, for products and for both lists of weight gradients."""
+    dev = lambda m, n, dt: torch.zeros(m, n, dtype=dt, device=DEV)
+    bf, f32 = torch.bfloat16, torch.float32
+    cases = [((256, 128, 64), bf, "gemm_deep_kernel<64, 64, 0, STORE, float>"), ((2560, 1024, 64), bf, "gemm_deep_kernel<128, 128, 0, STORE, float>"),
+             ((100, 100, 100), bf, "gemm_any_kernel<32, 32, 0, 0>"), ((2049, 2049, 33), bf, "gemm_any_kernel<128, 128, 0, 0>"),
+             ((100, 100, 100), f32, "gemm_f32_kernel<32, 32 natural, 0, 0>"), ((100, 100, 300), f32, "gemm_f32_kernel<32, 32 / 4, 0, 0>"),
+             ((1024, 768, 64), f32, "gemm_f32_kernel<64, 64, 0, 0>"), ((2048, 2048, 64), f32, "gemm_f32_kernel<128, 128, 0, 0>")]
+    try:
+        A.prof_enable(1)
+        for (M, N, K), dt, name in cases:
+            A.step_gemm(dev(M, K, dt), dev(K, N, dt), dev(M, N, f32), M, N, K)
+            (got,) = A.prof_collect()
+            assert got[0] == name and got[1] == 1 and got[2] > 0 and got[3] == 2.0 * M * N * K
+        for dtype, name in (("f32", "gemm_f32_dw_list_kernel<32, 32 natural>"), ("bf16", "gemm_any_dw_list_kernel<64, 64>")):
+            w = _model(L=17, S=7, B=1)
+            w["dtype"] = dtype
+            _loss_grad(w, I.TokenStream(1, 0, w["B"], w["S"], w["V"]).take(1)[0])
+            got = {n: (l, f) for n, l, _, f in A.prof_collect()}
+            d, T = w["d"], w["B"] * w["S"]
+            assert got[name] == (2, 2.0 * T * d * (17 * (4 * d + 2 * w["ff"]) + w["V"]))   # 69 products, at most 64 in a launch
+    finally:
+        A.prof_enable(0)
+        A.prof_collect()
