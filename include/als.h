@@ -246,8 +246,9 @@ int als_k_gemm_dw_grouped(int n, const void* const* X, const void* const* dY, fl
                           const int* M, const int* N, int K, void* ws_dev, size_t ws_bytes, void* stream);
 /* For callers that cannot allocate device memory and have no workspace to lend (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): als_k_gemm on the MFMA
- * path (bf16 operands, M, N multiples of 128, K of 64) with the split-K partials of the
- * weight-gradient layout (a_layout 1, b_layout 0) kept in a file-scope device array of
+ * path (bf16 operands, M, N multiples of 128, K of 64) with the split-K partials (of the
+ * weight-gradient layout, a_layout 1 and b_layout 0, and of the input-gradient layout, 0 and 1, with
+ * an fp32 result, few tiles and a long K) kept in a file-scope device array of
  * ALS_STATIC_WS_BYTES that every GPU the library runs on holds until the process ends.  Calls no
  * hipMalloc / hipFree or any allocating routine.  Results equal als_k_gemm with a workspace of
  * ALS_STATIC_WS_BYTES, bit for bit.  Errors (ALS_ERR_INVALID): null pointers, shapes the MFMA
