@@ -189,9 +189,9 @@ int rmsnorm_dg_sum(const float* partial, float* dg, int T, int d, int nset, hipS
 int rmsnorm_bwd(const float* dy, const float* x, const float* rstd, const float* g,
                 const float* dx_in, float* dx_out, void* dx_lp, int lp_bf16, float* dg,
                 float* partial, int T, int d, int center, hipStream_t st);
-// logits fp32 or bf16; dlogits may be the same buffer as the logits when the two types are equal
-int cross_entropy(const void* logits, int logits_bf16, const int32_t* tok, float* loss_row, void* dlogits,
-                  int dl_bf16, int B, int S, int V, hipStream_t st);
+// logits and dlogits in bf16 or both in fp32; they may be the same buffer
+int cross_entropy(const void* logits, const int32_t* tok, float* loss_row, void* dlogits, int bf, int B, int S, int V,
+                  hipStream_t st);
 // Orders each step's input positions by token id (see elementwise.hip; rank is scratch); offset is
 // [n_steps][V+1], rank and pos are [n_steps][B*S].
 int embed_sort(const int32_t* tok, int n_steps, int B, int S, int V, int32_t* offset, int32_t* rank,

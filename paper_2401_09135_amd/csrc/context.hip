@@ -78,7 +78,7 @@ void carve(als_ctx* c, Carver& cv) {
   int64_t BhS = (int64_t)g.batch * g.n_heads * g.seq_len;
   c->theta = cv.f32(P); c->m = cv.f32(P); c->delta = cv.f32(P);
   c->w.resize(g.n_workers);
-  const bool groupable = bf && !(g.flags & 1) && g.n_layers > 0 && dw_group_supported((int)d, (int)(3 * da), (int)T, d, 3 * da) &&
+  const bool groupable = bf && !(g.flags & 1) && dw_group_supported((int)d, (int)(3 * da), (int)T, d, 3 * da) &&
                   dw_group_supported((int)da, (int)d, (int)T, da, d) && dw_group_supported((int)d, (int)ff, (int)T, d, ff);
   c->grouped_dw = groupable && !(g.flags & 2);
   // Scratch of the output matrix's input gradient: 64 MiB hold the partials of a round of 256 x 256 tiles.  The same with and
@@ -90,7 +90,7 @@ void carve(als_ctx* c, Carver& cv) {
   // which (many tokens) a product fills the chip alone.
   {
     const bool aligned = bf && T % 64 == 0 && d % 128 == 0 && (da % 128 == 0 || ff % 128 == 0);
-    c->list_dw = !(g.flags & 3) && !aligned && g.n_layers > 0 && (int64_t)g.n_layers * T * (2 * d + ff + 3 * da) * (bf ? 2 : 4) <= (int64_t)256 << 20;
+    c->list_dw = !(g.flags & 3) && !aligned && (int64_t)g.n_layers * T * (2 * d + ff + 3 * da) * (bf ? 2 : 4) <= (int64_t)256 << 20;
   }
   for (Worker& w : c->w) {
     w.theta = cv.f32(P); w.start = cv.f32(P); w.adam_m = cv.f32(P); w.adam_v = cv.f32(P);
@@ -218,7 +218,7 @@ int forward(als_ctx* c, Worker& w, const int32_t* tok) {
   RUN(rmsnorm_fwd(w.x[g.n_layers], w.theta + L.gf, w.xf, w.rstdf, T, d, eps, c->bf, ln, st));
   void* logits = c->bf ? w.dlogits : (void*)w.logits;
   RUN(gemm(desc(c, w.xf, 0, d, wptr(c, w, L.Wout), 0, V, T, V, d, logits, V, true), mf, st));
-  RUN(cross_entropy(logits, c->bf, tok, w.loss_row, w.dlogits, c->bf, B, S, V, st));
+  RUN(cross_entropy(logits, tok, w.loss_row, w.dlogits, c->bf, B, S, V, st));
   return ALS_OK;
 }
 

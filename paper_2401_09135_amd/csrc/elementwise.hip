@@ -1174,9 +1174,8 @@ int rmsnorm_dg_sum(const float* partial, float* dg, int T, int d, int nset, hipS
 
 // ------------------------------------------------------------------------------------------
 // Softmax cross-entropy, one block per row: loss_row = logsumexp - logit[target];
-// dlogits = (softmax - onehot) / T.  Logits are fp32, or bf16 (the bf16 path: the output GEMM
-// rounds them like every other activation); dlogits may overwrite the logits (same pointer, same
-// element type): every element is read before it is written, by the thread that writes it.
+// dlogits = (softmax - onehot) / T.  Logits and dlogits are both fp32, or both bf16 (the output GEMM
+// rounds them like every other activation); dlogits may overwrite the logits: every element is read before it is written, by the thread that writes it.
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ float block_reduce(float v, bool is_max, float* sh) {
   int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -1190,16 +1189,16 @@ __device__ __forceinline__ float block_reduce(float v, bool is_max, float* sh) {
   return r;
 }
 
-template <typename IT, typename OT>
-__global__ __launch_bounds__(256) void cross_entropy_kernel(const IT* logits, const int32_t* __restrict__ tok,
-                                                            float* __restrict__ loss_row, OT* dl, int S, int V,
+template <typename T>
+__global__ __launch_bounds__(256) void cross_entropy_kernel(const T* logits, const int32_t* __restrict__ tok,
+                                                            float* __restrict__ loss_row, T* dl, int S, int V,
                                                             float invT) {
   __shared__ float sh[8];
   int t = blockIdx.x;
   int b = t / S, s = t % S;
   int tgt = tok[(int64_t)b * (S + 1) + s + 1];
   tgt = tgt < 0 ? 0 : (tgt >= V ? V - 1 : tgt);
-  const IT* lr = logits + (int64_t)t * V;
+  const T* lr = logits + (int64_t)t * V;
   const float ltgt = (float)lr[tgt];
   float mx = -INFINITY;
   for (int c = threadIdx.x; c < V; c += blockDim.x) mx = fmaxf(mx, (float)lr[c]);
@@ -1209,23 +1208,22 @@ __global__ __launch_bounds__(256) void cross_entropy_kernel(const IT* logits, co
   sum = block_reduce(sum, false, sh);   // its barriers also order the read of lr[tgt] before the writes below
   float lse = mx + logf(sum);
   if (threadIdx.x == 0) loss_row[t] = lse - ltgt;
-  OT* dr = dl + (int64_t)t * V;
+  T* dr = dl + (int64_t)t * V;
   for (int c = threadIdx.x; c < V; c += blockDim.x) {
     float p = expf((float)lr[c] - lse);
     if (c == tgt) p -= 1.0f;
-    dr[c] = (OT)(p * invT);
+    dr[c] = (T)(p * invT);
   }
 }
 
-// Same, reading the row once: each thread keeps up to 32 logits in registers, so a block of BS
+// Same in bf16, reading the row once: each thread keeps up to 32 logits in registers, so a block of BS
 // threads covers V <= 32 BS.  Rows of an odd V start at any element: 16-byte accesses at element alignment, and the
 // last, partial group of 8 one by one (EDGE).  600 rows of 5003 in bf16: 19 us with three scalar passes, 8.6
 // now.  fp32 mode keeps the three passes (1024 rows of 2000: 10.4 us, 6.6 this way) and their order of sums.
 struct __attribute__((packed, aligned(2))) ce_b8 { bf16x8 v; };
-struct __attribute__((packed, aligned(4))) ce_f4 { f32x4 v; };
-template <typename IT, typename OT, int BS, bool EDGE>
-__global__ __launch_bounds__(BS) void cross_entropy_reg_kernel(const IT* logits, const int32_t* __restrict__ tok,
-                                                               float* __restrict__ loss_row, OT* dl, int S, int V,
+template <int BS, bool EDGE>
+__global__ __launch_bounds__(BS) void cross_entropy_reg_kernel(const bf16* logits, const int32_t* __restrict__ tok,
+                                                               float* __restrict__ loss_row, bf16* dl, int S, int V,
                                                                float invT) {
   __shared__ float sh[16];
   int t = blockIdx.x;
@@ -1233,7 +1231,7 @@ __global__ __launch_bounds__(BS) void cross_entropy_reg_kernel(const IT* logits,
   int tgt = tok[(int64_t)b * (S + 1) + s + 1];
   tgt = tgt < 0 ? 0 : (tgt >= V ? V - 1 : tgt);
   // a lane owns 8 consecutive columns per slot (16-byte loads, one 16-byte bf16 store)
-  const IT* row = logits + (int64_t)t * V;
+  const bf16* row = logits + (int64_t)t * V;
   const float ltgt = (float)row[tgt];
   const int v8 = EDGE ? (V + 7) / 8 : V / 8;
   f32x4 x[4][2];
@@ -1245,14 +1243,10 @@ __global__ __launch_bounds__(BS) void cross_entropy_reg_kernel(const IT* logits,
       if (EDGE && 8 * c + 8 > V) {
 #pragma unroll
         for (int e = 0; e < 8; e++) x[i][e >> 2][e & 3] = 8 * c + e < V ? (float)row[8 * c + e] : -INFINITY;
-      } else if (sizeof(IT) == 2) {
+      } else {
         bf16x8 r = EDGE ? reinterpret_cast<const ce_b8*>(row + 8 * c)->v : reinterpret_cast<const bf16x8*>(row)[c];
 #pragma unroll
         for (int e = 0; e < 8; e++) x[i][e >> 2][e & 3] = (float)r[e];
-      } else {
-#pragma unroll
-        for (int q = 0; q < 2; q++)
-          x[i][q] = EDGE ? reinterpret_cast<const ce_f4*>(row + 8 * c + 4 * q)->v : reinterpret_cast<const f32x4*>(row)[2 * c + q];
       }
 #pragma unroll
       for (int q = 0; q < 2; q++)
@@ -1277,7 +1271,7 @@ __global__ __launch_bounds__(BS) void cross_entropy_reg_kernel(const IT* logits,
   sum = block_reduce(sum, false, sh);
   float inv = 1.0f / sum;
   if (threadIdx.x == 0) loss_row[t] = mx + logf(sum) - ltgt;
-  OT* dr = dl + (int64_t)t * V;
+  bf16* dr = dl + (int64_t)t * V;
 #pragma unroll
   for (int i = 0; i < 4; i++) {
     int c = threadIdx.x + i * BS;
@@ -1292,56 +1286,37 @@ __global__ __launch_bounds__(BS) void cross_entropy_reg_kernel(const IT* logits,
       if (EDGE && 8 * c + 8 > V) {
 #pragma unroll
         for (int e = 0; e < 7; e++)
-          if (8 * c + e < V) dr[8 * c + e] = (OT)p[e];
-      } else if (sizeof(OT) == 2) {
+          if (8 * c + e < V) dr[8 * c + e] = (bf16)p[e];
+      } else {
         bf16x8 o;
 #pragma unroll
         for (int e = 0; e < 8; e++) o[e] = (bf16)p[e];
         if (EDGE) reinterpret_cast<ce_b8*>(dr + 8 * c)->v = o;
-        else *reinterpret_cast<bf16x8*>(reinterpret_cast<bf16*>(dr) + 8 * c) = o;
-      } else {
-#pragma unroll
-        for (int q = 0; q < 2; q++) {
-          const f32x4 o = {p[4 * q], p[4 * q + 1], p[4 * q + 2], p[4 * q + 3]};
-          if (EDGE) reinterpret_cast<ce_f4*>(dr + 8 * c + 4 * q)->v = o;
-          else reinterpret_cast<f32x4*>(dr)[2 * c + q] = o;
-        }
+        else *reinterpret_cast<bf16x8*>(dr + 8 * c) = o;
       }
     }
   }
 }
 
-int cross_entropy(const void* logits, int logits_bf16, const int32_t* tok, float* loss_row, void* dlogits,
-                  int dl_bf16, int B, int S, int V, hipStream_t st) {
-  int T = B * S;
-  float invT = 1.0f / (float)T;
-  if (logits_bf16 && !dl_bf16) return set_error(ALS_ERR_INVALID, "cross_entropy: bf16 logits need bf16 dlogits");
-  if (dl_bf16 && V <= 32 * 1024) {   // longer rows do not fit the registers of a block
+int cross_entropy(const void* logits, const int32_t* tok, float* loss_row, void* dlogits, int bf, int B, int S, int V,
+                  hipStream_t st) {
+  const int T = B * S;
+  const float invT = 1.0f / (float)T;
+  const bf16* lb = (const bf16*)logits;
+  bf16* db = (bf16*)dlogits;
+  if (bf && V <= 32 * 1024) {   // longer rows do not fit the registers of a block
     const bool big = V > 32 * 256, edge = V % 8 != 0;
-#define ALS_CE_LAUNCH(IT, OT, BS)                                                                                \
-  do {                                                                                                           \
-    if (edge)                                                                                                    \
-      hipLaunchKernelGGL((cross_entropy_reg_kernel<IT, OT, BS, true>), dim3(T), dim3(BS), 0, st, (const IT*)logits, \
-                         tok, loss_row, (OT*)dlogits, S, V, invT);                                               \
-    else                                                                                                         \
-      hipLaunchKernelGGL((cross_entropy_reg_kernel<IT, OT, BS, false>), dim3(T), dim3(BS), 0, st, (const IT*)logits, \
-                         tok, loss_row, (OT*)dlogits, S, V, invT);                                               \
-  } while (0)
-    if (logits_bf16) { if (big) ALS_CE_LAUNCH(bf16, bf16, 1024); else ALS_CE_LAUNCH(bf16, bf16, 256); }
-    else { if (big) ALS_CE_LAUNCH(float, bf16, 1024); else ALS_CE_LAUNCH(float, bf16, 256); }
+#define ALS_CE_LAUNCH(BS, EDGE) \
+  hipLaunchKernelGGL((cross_entropy_reg_kernel<BS, EDGE>), dim3(T), dim3(BS), 0, st, lb, tok, loss_row, db, S, V, invT)
+    if (big) { if (edge) ALS_CE_LAUNCH(1024, true); else ALS_CE_LAUNCH(1024, false); }
+    else { if (edge) ALS_CE_LAUNCH(256, true); else ALS_CE_LAUNCH(256, false); }
 #undef ALS_CE_LAUNCH
-    ALS_CHECK_LAUNCH();
-    return ALS_OK;
+  } else if (bf) {
+    hipLaunchKernelGGL(cross_entropy_kernel<bf16>, dim3(T), dim3(256), 0, st, lb, tok, loss_row, db, S, V, invT);
+  } else {
+    hipLaunchKernelGGL(cross_entropy_kernel<float>, dim3(T), dim3(256), 0, st, (const float*)logits, tok, loss_row,
+                       (float*)dlogits, S, V, invT);
   }
-  if (logits_bf16)
-    hipLaunchKernelGGL((cross_entropy_kernel<bf16, bf16>), dim3(T), dim3(256), 0, st, (const bf16*)logits, tok,
-                       loss_row, (bf16*)dlogits, S, V, invT);
-  else if (dl_bf16)
-    hipLaunchKernelGGL((cross_entropy_kernel<float, bf16>), dim3(T), dim3(256), 0, st, (const float*)logits, tok,
-                       loss_row, (bf16*)dlogits, S, V, invT);
-  else
-    hipLaunchKernelGGL((cross_entropy_kernel<float, float>), dim3(T), dim3(256), 0, st, (const float*)logits, tok,
-                       loss_row, (float*)dlogits, S, V, invT);
   ALS_CHECK_LAUNCH();
   return ALS_OK;
 }
