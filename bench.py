@@ -1,17 +1,17 @@
 """Benchmark of the asynchronous Local-SGD hot path on one MI355X.
 
-Headline (default run): the 150M-class workload (benchmark configs[3], the largest configuration
-that runs on one GPU).  A "step" is one outer round of the paper's asynchronous schedule: N = 4 sync
+Headline (default run): the 150M-class workload (the largest configuration that runs on one GPU).
+A "step" is one outer round of the paper's asynchronous schedule: N = 4 sync
 events (pseudo-gradient + Delayed Nesterov + restart) together with the local rounds of the four
 simulated workers (DyLU step counts, each step = forward + backward + AdamW on 16 x 1024 tokens),
 which run on their own HIP streams.  Tokens are synthetic Zipf(1.1) draws, resident in HBM before the
-clock starts.  The default run then also measures the 20M-class workload (configs[1]), the same model
-with 16 workers (configs[4], with the outer-step overhead fraction) and the outer-step
-microbenchmark (configs[2]) and reports them under config.other_workloads.  Prints ONE JSON line.
+clock starts.  The default run then also measures the 20M-class workload, the same model
+with 16 workers (with the outer-step overhead fraction) and the outer-step
+microbenchmark and reports them under config.other_workloads.  Prints ONE JSON line.
 
   python bench.py                                  the default run described above
   python bench.py --workload lm20m                 one workload only
-  python bench.py --workload outer_microbench      configs[2] only
+  python bench.py --workload outer_microbench      the outer-step microbenchmark only
   python bench.py --workload gemm_microbench [--tiles 256x128x1,128x128x2]
                                                    the MFMA GEMM on the step's shapes, one kernel at a
                                                    time on one stream (the program behind the counter
@@ -126,7 +126,7 @@ def cpu_baseline(w):
 
 
 def outer_microbench(steps):
-    """Benchmark configs[2]: pseudo-gradient + Delayed Nesterov (single events, the grouped pass with
+    """Outer-step microbenchmark: pseudo-gradient + Delayed Nesterov (single events, the grouped pass with
     fused restart) and fused AdamW on a 150M-element fp32 vector; achieved HBM GB/s from the
     algorithmic bytes per parameter (DN: 24 non-boundary, 32 boundary, grouped G events with
     restart 8G + 24 + 10G; AdamW: 30 with fp32 gradient and bf16 copy).  Returns the result table."""
@@ -187,7 +187,7 @@ def outer_microbench_line(args):
     mb = I.OUTER_MICROBENCH
     res = outer_microbench(args.steps)
     iters = res.pop("_iters")
-    # configs[2] is the fused pass over 4-16 replicas: the reported value is the grouped pass over 4
+    # the microbenchmark is the fused pass over 4-16 replicas: the reported value is the grouped pass over 4
     # workers with the restart fused in (the single events and the larger groups are in results)
     key = "dn_group_G4_N4_restart"
     out = dict(metric="DN/AdamW HBM GB/s", value=res[key]["GBps"], unit="GB/s", n_gpus=1, steps=iters, warmup=2,
@@ -583,7 +583,7 @@ def main():
                            outer_step_overhead_fraction=r["outer_step_overhead_fraction"]),
                roofline=r.get("roofline"), cpu_baseline=None)
     if not args.workload and not args.no_others:
-        # the other BASELINE configurations, short runs, reported beside the headline
+        # the other configurations, short runs, reported beside the headline
         others = {}
         for oname, st, wu in (("lm20m", 4, 1), ("lm20m_k16", 2, 1)):
             others[oname] = _brief(run_lm(oname, st, wu, args.streams))

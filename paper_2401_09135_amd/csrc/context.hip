@@ -86,8 +86,9 @@ void carve(als_ctx* c, Carver& cv) {
   const size_t head_bytes = std::min((size_t)g.n_layers * T * (2 * d + ff + 3 * da) * 2, (size_t)64 << 20);
   // Products without an aligned kernel: each fills a part of the chip (600 tokens, 320 x 1280: 100 tiles of 64 x 64) and costs
   // a launch.  17 products of four layers and the head took 199 us in fp32 mode (1024 tokens, d = 256, V = 2000) and 137 in bf16
-  // (600 tokens, d = 320, V = 5003); as one list 107 and 50.  Every layer keeps its four dY for it: up to 256 MiB, beyond
-  // which (many tokens) a product fills the chip alone.
+  // (600 tokens, d = 320, V = 5003); as one list 107 and 50.  Every layer keeps its four dY for it, and the line is drawn at the
+  // memory: 256 MiB more in a worker's arena.  It is no line of speed: near it the list still gains (a round of 12 layers, d = 128, 4096
+  // tokens in fp32, 216 MiB: 2880 us, 4190 with a launch per product; 4 layers, d = 320, 8000 tokens in bf16, 175 MiB: 2490 and 3220).
   {
     const bool aligned = bf && T % 64 == 0 && d % 128 == 0 && (da % 128 == 0 || ff % 128 == 0);
     c->list_dw = !(g.flags & 3) && !aligned && (int64_t)g.n_layers * T * (2 * d + ff + 3 * da) * (bf ? 2 : 4) <= (int64_t)256 << 20;

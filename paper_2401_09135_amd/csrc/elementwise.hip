@@ -407,8 +407,9 @@ int cast_copy(const float* src, void* dst, int64_t n, int dst_bf16, hipStream_t 
 // wavefront w owns up to 1024 consecutive ones, 64 per iteration, and finds the lanes that hold the same
 // digit with one ballot per digit bit, so a rank costs one counter access per 64 positions and no
 // comparison of positions with each other.  What bounds it is that chain of 16 counter updates per
-// pass and the gathers of ids through L2; a round has one workgroup per step.  T = 16384, V = 8192: 761 us with
-// every position compared against the 1024 of its chunk, 54 us now; V = 32000: 785 and 69; T = 512: 20 and 13.
+// pass and the gathers of ids through L2; a round has one workgroup per step.  One launch at a time, T = 16384, V = 8192: 761 us
+// with every position compared against the 1024 of its chunk, 54 us so; V = 32000: 785 and 69; T = 512: 20 and 13.  This kernel
+// is left for what the next one does not take: more than one tile, or V from 32768 on.
 constexpr int SORT_ITEMS = 16, SORT_TILE = 1024 * SORT_ITEMS;
 
 __global__ __launch_bounds__(1024) void embed_sort_kernel(const int32_t* __restrict__ tok, int B,
@@ -587,7 +588,7 @@ __global__ __launch_bounds__(1024) void embed_sort_kernel(const int32_t* __restr
 // The same for one tile and a vocabulary whose offsets fit LDS (V < 32768), all of it there: tokens are read once, with
 // their position in the low 14 bits, every pass permutes them through LDS, and the offsets are formed there, each wavefront a
 // run of the vocabulary.  Above, every pass gathers the tokens again and the offsets make the round through L2 once per 4096
-// entries.  In rounds, T = 16384, V = 8192: 68 us to 45; T = 8192, V = 32000: 69 to 38; T = 512, V = 1024: 14.5 to 11.5.
+// entries.  Inside rounds of several workers (slower than alone), the kernel above and this one, T = 16384, V = 8192: 68 us and 45; T = 8192, V = 32000: 69 and 38; T = 512, V = 1024: 14.5 and 11.5.
 constexpr int SORT_LDS_V = 32768, SORT_POS_BITS = 14;
 static_assert(SORT_TILE <= 1 << SORT_POS_BITS, "positions of a tile");
 inline __host__ __device__ int sort_run(int V) { return (V + 1 + 4095) / 4096 * 256; }   // offsets of one wavefront

@@ -301,7 +301,7 @@ def test_full_size_150m_architecture_one_sequence():
 
 @pytest.mark.timeout(1500)
 def test_full_size_lm20m_step_in_bench_launch_configuration():
-    """Benchmark configs[1] at full size, launched as bench.py launches it (4 workers stepping
+    """lm20m at full size, launched as bench.py launches it (4 workers stepping
     concurrently on 4 streams): worker 0's gradient, loss and first AdamW step against the
     oracle; the other workers' first losses against oracle forward passes."""
     w = I.workload("lm20m")
@@ -334,7 +334,7 @@ def test_full_size_lm20m_step_in_bench_launch_configuration():
 @pytest.mark.timeout(900)
 @pytest.mark.parametrize("name,rounds", [("lm20m", 2), ("lm150m", 1)])
 def test_full_size_rounds_make_progress(name, rounds):
-    """Benchmark configs[1] and configs[3] at full size through the same driver loop bench.py
+    """lm20m and lm150m at full size through the same driver loop bench.py
     times (k workers on k streams, DyLU step counts, grouped events): properties that need no
     oracle run.  With N(0, 0.02) weights the logits of a row are near-independent N(0, 0.02^2 d)
     (the final norm gives unit-RMS rows), so the first loss is ln V + 0.02^2 d / 2 to first order;

@@ -1,7 +1,7 @@
 """One full outer round (N sync events = one Delayed-Nesterov period, Alg. 3) at FULL model shapes
 and batch on the GPU against fixtures the CPU oracle wrote (tests/golden/make_full_size_round.py,
-which calls only oracle/ and als_inputs): BASELINE configs[1] (20M-class, H = 50: 128 + 53 worker
-steps), configs[3] (150M-class) and configs[4] (16 workers), the last two with the DyLU maximum H
+which calls only oracle/ and als_inputs): lm20m (20M-class, H = 50: 128 + 53 worker
+steps), lm150m (150M-class) and lm20m_k16 (16 workers), the last two with the DyLU maximum H
 lowered to the value stored in the fixture so that the numpy oracle finishes in minutes.
 
 Checked: DyLU step counts and event order bit for bit; every per-step loss; the server
