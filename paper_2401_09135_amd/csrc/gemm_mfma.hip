@@ -17,7 +17,7 @@
 // This file holds that kernel (gemm_mfma_kernel), the launchers, the choice of kernel and split
 // for a product, and the measurement hooks.  Products with at least one whole 256 x 256 tile in
 // each direction go to the kernels of gemm_pingpong.h (one workgroup of two wavefront groups in
-// alternating memory / compute phases per CU), those of at most a round of 128 x 128 tiles to gemm_mfma_deep.hip;
+// alternating memory / compute phases per CU), those of fewer than 64 such tiles to gemm_mfma_deep.hip and gemm_mfma_any.hip;
 // gemm_mfma_common.h has what the kernels share
 // (LDS tile geometry, fragment reads, the per-wavefront epilogue).
 //
@@ -658,8 +658,8 @@ extern "C" int als_prof_kernel_name(int id, char* out, int out_len) {
 // Tuning hook: force the MFMA GEMM tile (256x256, 256x128 or 128x128) and its LDS buffering
 // (2 = double, 1 = single buffer with more workgroups per CU); 0,0 restores the automatic choice.  Not thread-safe; meant for benchmarks.
 extern "C" int als_k_set_gemm_tile(int bm, int bn, int nbuf) {
-  // (0, 0, 4) / (0, 0, 5): automatic tile choice, but the register-staged (4) or the direct-to-LDS
-  // (5) form of the ping-pong kernel wherever that kernel is chosen
+  // (0, 0, 4) / (0, 0, 5): the automatic choice without the kernels for few tiles (gemm_mfma_deep.hip, gemm_mfma_any.hip), and with the
+  // register-staged (4) or the direct-to-LDS (5) form of the ping-pong kernel wherever that kernel is chosen
   if (bm == 0 && bn == 0 && (nbuf == 4 || nbuf == 5)) { als::g_force_bm = 0; als::g_force_bn = 0; als::g_force_nbuf = nbuf; return ALS_OK; }
   bool ok = (bm == 0 && bn == 0) || (bm == 256 && bn == 256) || (bm == 256 && bn == 128) || (bm == 128 && bn == 128);
   if (!ok || (bm && nbuf != 1 && nbuf != 2 && !(nbuf == 3 && bm == 128) && !((nbuf == 4 || nbuf == 5) && bm == 256 && bn == 256))) return als::set_error(ALS_ERR_INVALID, "unsupported tile %dx%d/%d", bm, bn, nbuf);
