@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libals.so")
 SOURCES = ["host.cpp", "elementwise.hip", "gemm_generic.hip", "gemm_mfma_f32.hip", "gemm_mfma_any.hip", "gemm_mfma_deep.hip", "gemm_mfma.hip",
-           "attention_generic.hip", "attention_mfma_f32.hip", "attention_mfma.hip", "context.hip"]
+           "attention_generic.hip", "attention_mfma_f32.hip", "attention_mfma_any.hip", "attention_mfma.hip", "context.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

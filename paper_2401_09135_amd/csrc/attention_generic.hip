@@ -216,15 +216,17 @@ int attention_bwd_generic(const void* qkv, const void* o, const void* d_o, const
 
 int attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int h, int dh, int bf, bool allow_mfma, hipStream_t st) {
   if (allow_mfma && attention_mfma_supported(S, dh, bf)) return attention_fwd_mfma(qkv, o, lse, B, S, h, dh, st);
-  if (allow_mfma && attention_mfma_f32_supported(qkv, o, qkv, o, B, S, h, dh)) return attention_fwd_mfma_f32(qkv, o, lse, B, S, h, dh, bf, st);
+  if (allow_mfma && attention_mfma_any_supported(qkv, o, qkv, o, B, S, h, dh))
+    return bf ? attention_fwd_mfma_any(qkv, o, lse, B, S, h, dh, st) : attention_fwd_mfma_f32(qkv, o, lse, B, S, h, dh, st);
   return attention_fwd_generic(qkv, o, lse, B, S, h, dh, bf, st);
 }
 
 int attention_bwd(const void* qkv, const void* o, const void* d_o, const float* lse, float* dscratch, void* dqkv, int B, int S,
                   int h, int dh, int bf, bool allow_mfma, hipStream_t st) {
   if (allow_mfma && attention_mfma_supported(S, dh, bf)) return attention_bwd_mfma(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, st);
-  if (allow_mfma && attention_mfma_f32_supported(qkv, o, d_o, dqkv, B, S, h, dh))
-    return attention_bwd_mfma_f32(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, bf, st);
+  if (allow_mfma && attention_mfma_any_supported(qkv, o, d_o, dqkv, B, S, h, dh))
+    return bf ? attention_bwd_mfma_any(qkv, o, d_o, lse, dqkv, B, S, h, dh, st)
+              : attention_bwd_mfma_f32(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, st);
   return attention_bwd_generic(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, bf, st);
 }
 

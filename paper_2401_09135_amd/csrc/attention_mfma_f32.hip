@@ -1,14 +1,13 @@
-// Causal attention for what the bf16 matrix-core kernels do not take (fp32 storage, heads of 32, any sequence length up
-// to 1024): fp32 arithmetic on fp32 or bf16 storage, the products on the fp32 matrix instruction
-// v_mfma_f32_16x16x4_f32 (whole fp32 products and sums, no operand is rounded).  qkv is [B*S, 3d]: q at column hd*dh,
+// Causal attention on fp32 storage, heads of 32 or 64 and any sequence length up to 1024: fp32 arithmetic, the products on
+// the fp32 matrix instruction v_mfma_f32_16x16x4_f32 (whole fp32 products and sums, no operand is rounded).  qkv is [B*S, 3d]: q at column hd*dh,
 // k at d + hd*dh, v at 2d + hd*dh.
 //
 // One wavefront owns 16 NT queries (forward, dQ) or 16 NT keys (dK and dV) of one head and walks 16-row tiles of the other
 // side; the four wavefronts of a workgroup take neighbouring blocks of one head, so that they find each other's tiles in
 // the CU's L1, and share nothing else: no LDS, no barrier.  Where that gives the chip few wavefronts, the four of a workgroup
 // share one block of 16 rows instead (SPLIT): each walks every fourth tile of the other side, and their results are put
-// together through LDS in order at the end.  Every operand is loaded straight into MFMA fragments, 16 bytes
-// (fp32) or 8 to 16 bytes (bf16) per lane:
+// together through LDS in order at the end.  Every operand is loaded straight into MFMA fragments, 8 or
+// 16 bytes per lane:
 //   MFMA lane layout (lane l, group g = l / 16): A row l%16, contraction g; B column l%16, contraction g; accumulator
 //   element v: row 4 g + v, column l%16.
 // The order of the contraction and of the output rows is free as long as both operands agree, and is chosen so that no value
@@ -20,10 +19,8 @@
 // What bounds it: the fp32 matrix rate (64 flops per clock and SIMD, a 16th of bf16's) for long sequences, the chain of
 // tile loads and dependent MFMAs of a single wavefront for short ones.  Against one wavefront per query with scalar products
 // in vector code (attention_generic.hip), forward / backward in us, same distance from a float64 reference:
-//   B 8, S 1000, 16 heads of 64, fp32: 2250 / 9484 -> 379 / 1218; bf16: 1382 / 5898 -> 398 / 1255
-//   B 8, S 256, 8 heads of 32, bf16: 53 / 193 -> 12 / 34;   B 3, S 200, 5 heads of 64, bf16: 19 / 66 -> 8.1 / 21
-//   (15 / 39 and 16 / 48 with a row block per wavefront);   B 8, S 1000, 4 heads of 64, bf16: 107 / 347 that way -> 68 / 212
-//   B 8, S 32, 2 heads of 32, fp32: 5.3 / 9.9 -> 7.2 / 9.6, which is why small calls stay with the other kernels.
+//   B 8, S 1000, 16 heads of 64: 2250 / 9484 -> 379 / 1218
+//   B 8, S 32, 2 heads of 32: 5.3 / 9.9 -> 7.2 / 9.6, which is why small calls stay with the other kernels.
 #include "common.h"
 #include <math.h>
 
@@ -52,30 +49,10 @@ __device__ __forceinline__ Vec<N> ldv(const float* p) {
   return r;
 }
 template <int N>
-__device__ __forceinline__ Vec<N> ldv(const bf16* p) {
-  typedef __bf16 vec __attribute__((ext_vector_type(N)));
-  const vec x = *reinterpret_cast<const vec*>(p);
-  Vec<N> r;
-#pragma unroll
-  for (int e = 0; e < N; e++) r.v[e] = (float)x[e];
-  return r;
-}
-template <int N>
 __device__ __forceinline__ void stv(float* p, const float* v) {
 #pragma unroll
   for (int q = 0; q < N / 4; q++) reinterpret_cast<f32x4*>(p)[q] = (f32x4){v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
 }
-template <int N>
-__device__ __forceinline__ void stv(bf16* p, const float* v) {
-#pragma unroll
-  for (int q = 0; q < N / 8; q++) {
-    bf16x8 o;
-#pragma unroll
-    for (int e = 0; e < 8; e++) o[e] = (bf16)v[8 * q + e];
-    reinterpret_cast<bf16x8*>(p)[q] = o;
-  }
-}
-
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ float quad_sum(float v) {   // over the four lane groups
   v += __shfl_xor(v, 16, 64);
@@ -87,33 +64,33 @@ __device__ __forceinline__ float quad_max(float v) {
 }
 
 // The head dimensions of one row that a lane feeds to the score products: DH/4 values in contraction-step order.
-template <typename T, int DH>
+template <int DH>
 struct RowFrag {
-  static constexpr int CH = sizeof(T) == 2 ? 8 : 4, NL = DH / 4 / CH;
+  static constexpr int CH = 4, NL = DH / 4 / CH;
   Vec<CH> c[NL];
-  __device__ __forceinline__ void load(const T* row, int g) {
+  __device__ __forceinline__ void load(const float* row, int g) {
 #pragma unroll
     for (int i = 0; i < NL; i++) c[i] = ldv<CH>(row + CH * (4 * i + g));
   }
 };
 // acc[row of a][row of b] += a . b over the head width
-template <typename T, int DH>
-__device__ __forceinline__ f32x4 row_product(const RowFrag<T, DH>& a, const RowFrag<T, DH>& b) {
+template <int DH>
+__device__ __forceinline__ f32x4 row_product(const RowFrag<DH>& a, const RowFrag<DH>& b) {
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < RowFrag<T, DH>::NL; i++)
+  for (int i = 0; i < RowFrag<DH>::NL; i++)
 #pragma unroll
-    for (int e = 0; e < RowFrag<T, DH>::CH; e++) acc = mfma4(a.c[i].v[e], b.c[i].v[e], acc);
+    for (int e = 0; e < RowFrag<DH>::CH; e++) acc = mfma4(a.c[i].v[e], b.c[i].v[e], acc);
   return acc;
 }
 
 // A 16-row tile as the first operand of the second products: rows 4 g + v (v = step), DT consecutive dimensions per lane.
-template <typename T, int DH>
+template <int DH>
 struct ColFrag {
   static constexpr int DT = DH / 16;
   Vec<DT> r[4];
   // rows beyond `last` are read from row `last`: their weight is zero
-  __device__ __forceinline__ void load(const T* base, int64_t ld, int row0, int last, int lane) {
+  __device__ __forceinline__ void load(const float* base, int64_t ld, int row0, int last, int lane) {
     const int g = lane >> 4;
 #pragma unroll
     for (int v = 0; v < 4; v++) {
@@ -159,7 +136,7 @@ struct ColFrag {
     }
   }
   // a lane's DH/4 consecutive output dimensions of its column
-  static __device__ __forceinline__ void store(T* row, const f32x4 (&out)[DT], float mul, float div, int lane) {
+  static __device__ __forceinline__ void store(float* row, const f32x4 (&out)[DT], float mul, float div, int lane) {
     float o[4 * DT];
 #pragma unroll
     for (int q = 0; q < 4; q++)
@@ -189,10 +166,10 @@ __device__ __forceinline__ bool block_of(int S, int h, int rows, bool last_first
 template <int N>
 struct Parts { f32x4 v[4][N][64]; };
 
-template <typename T, int DH, int NT, bool SPLIT>
-__global__ __launch_bounds__(256, 2) void attn_fwd_f32_kernel(const T* __restrict__ qkv, T* __restrict__ o,
+template <int DH, int NT, bool SPLIT>
+__global__ __launch_bounds__(256, 2) void attn_fwd_f32_kernel(const float* __restrict__ qkv, float* __restrict__ o,
                                                                   float* __restrict__ lse, int S, int h, float scale) {
-  typedef ColFrag<T, DH> CF;
+  typedef ColFrag<DH> CF;
   Block bk;
   if (!block_of<SPLIT>(S, h, 16 * NT, true, bk)) return;   // never in a SPLIT workgroup
   const int wv = SPLIT ? threadIdx.x >> 6 : 0;
@@ -200,8 +177,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_f32_kernel(const T* __restric
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15, last = S - 1, q0 = bk.row0;
   const int d = h * DH;
   const int64_t ld = 3 * (int64_t)d;
-  const T* base = qkv + (int64_t)bk.b * S * ld + bk.hd * DH;
-  RowFrag<T, DH> qf[NT], kf, kn;
+  const float* base = qkv + (int64_t)bk.b * S * ld + bk.hd * DH;
+  RowFrag<DH> qf[NT], kf, kn;
   f32x4 acc[NT][CF::DT];
   float m[NT], l[NT];
 #pragma unroll
@@ -225,7 +202,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_f32_kernel(const T* __restric
       if (k0 > q0 + 16 * n + 15) continue;   // wave-uniform: no key of the tile is seen
       const int q = q0 + 16 * n + c;
       const bool masked = k0 + 15 > q0 + 16 * n;
-      f32x4 s = row_product<T, DH>(kf, qf[n]);
+      f32x4 s = row_product<DH>(kf, qf[n]);
 #pragma unroll
       for (int v = 0; v < 4; v++) s[v] = masked && k0 + 4 * g + v > q ? -INFINITY : s[v] * scale;
       const float mx = fmaxf(m[n], quad_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))));
@@ -277,13 +254,13 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_f32_kernel(const T* __restric
 }
 
 // dq_i = sum_{j<=i} ds_ij k_j,  ds_ij = p_ij (do_i.v_j - D_i) scale,  D_i = do_i.o_i (left for the other pass)
-template <typename T, int DH, int NT, bool SPLIT>
-__global__ __launch_bounds__(256, 2) void attn_dq_f32_kernel(const T* __restrict__ qkv, const T* __restrict__ o,
-                                                                     const T* __restrict__ d_o, const float* __restrict__ lse,
-                                                                     float* __restrict__ Dbuf, T* __restrict__ dqkv, int S,
+template <int DH, int NT, bool SPLIT>
+__global__ __launch_bounds__(256, 2) void attn_dq_f32_kernel(const float* __restrict__ qkv, const float* __restrict__ o,
+                                                                     const float* __restrict__ d_o, const float* __restrict__ lse,
+                                                                     float* __restrict__ Dbuf, float* __restrict__ dqkv, int S,
                                                                      int h, float scale) {
-  typedef ColFrag<T, DH> CF;
-  typedef RowFrag<T, DH> RF;
+  typedef ColFrag<DH> CF;
+  typedef RowFrag<DH> RF;
   Block bk;
   if (!block_of<SPLIT>(S, h, 16 * NT, true, bk)) return;   // never in a SPLIT workgroup
   const int wv = SPLIT ? threadIdx.x >> 6 : 0;
@@ -291,7 +268,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_f32_kernel(const T* __restrict
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15, last = S - 1, q0 = bk.row0;
   const int d = h * DH;
   const int64_t ld = 3 * (int64_t)d;
-  const T* base = qkv + (int64_t)bk.b * S * ld + bk.hd * DH;
+  const float* base = qkv + (int64_t)bk.b * S * ld + bk.hd * DH;
   const int64_t stat = ((int64_t)bk.b * h + bk.hd) * S;
   RF qf[NT], gf[NT], kf, vf, kn, vn;
   f32x4 acc[NT][CF::DT];
@@ -334,7 +311,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_f32_kernel(const T* __restrict
       if (k0 > q0 + 16 * n + 15) continue;
       const int q = q0 + 16 * n + c;
       const bool masked = k0 + 15 > q0 + 16 * n;
-      const f32x4 s = row_product<T, DH>(kf, qf[n]), dp = row_product<T, DH>(vf, gf[n]);
+      const f32x4 s = row_product<DH>(kf, qf[n]), dp = row_product<DH>(vf, gf[n]);
       f32x4 ds;
 #pragma unroll
       for (int v = 0; v < 4; v++)
@@ -364,12 +341,12 @@ __global__ __launch_bounds__(256, 2) void attn_dq_f32_kernel(const T* __restrict
 }
 
 // dk_j = sum_{i>=j} ds_ij q_i ; dv_j = sum_{i>=j} p_ij do_i
-template <typename T, int DH, int NT, bool SPLIT>
+template <int DH, int NT, bool SPLIT>
 __global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void attn_dkv_f32_kernel(
-    const T* __restrict__ qkv, const T* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ Dbuf,
-    T* __restrict__ dqkv, int S, int h, float scale) {
-  typedef ColFrag<T, DH> CF;
-  typedef RowFrag<T, DH> RF;
+    const float* __restrict__ qkv, const float* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ Dbuf,
+    float* __restrict__ dqkv, int S, int h, float scale) {
+  typedef ColFrag<DH> CF;
+  typedef RowFrag<DH> RF;
   Block bk;
   if (!block_of<SPLIT>(S, h, 16 * NT, false, bk)) return;   // never in a SPLIT workgroup
   const int wv = SPLIT ? threadIdx.x >> 6 : 0;
@@ -377,15 +354,15 @@ __global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void attn_dkv_f32_kernel(
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15, last = S - 1, j0 = bk.row0;
   const int d = h * DH;
   const int64_t ld = 3 * (int64_t)d;
-  const T* base = qkv + (int64_t)bk.b * S * ld + bk.hd * DH;
-  const T* gbase = d_o + (int64_t)bk.b * S * d + bk.hd * DH;
+  const float* base = qkv + (int64_t)bk.b * S * ld + bk.hd * DH;
+  const float* gbase = d_o + (int64_t)bk.b * S * d + bk.hd * DH;
   const int64_t stat = ((int64_t)bk.b * h + bk.hd) * S;
   RF kf[NT], vf[NT], qf, gf, qn, gn;
   f32x4 dk[NT][CF::DT], dv[NT][CF::DT];
 #pragma unroll
   for (int n = 0; n < NT; n++) {
     const int j = j0 + 16 * n + c;
-    const T* row = base + (int64_t)(j < last ? j : last) * ld;
+    const float* row = base + (int64_t)(j < last ? j : last) * ld;
     kf[n].load(row + d, g);
     vf[n].load(row + 2 * d, g);
 #pragma unroll
@@ -414,8 +391,8 @@ __global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void attn_dkv_f32_kernel(
       const int j = j0 + 16 * n + c;
       if (i0 + 15 < j0 + 16 * n) continue;   // wave-uniform: every query of the tile precedes every key
       const bool masked = i0 < j0 + 16 * n + 15 || i0 + 15 > last;
-      f32x4 p = row_product<T, DH>(qf, kf[n]);
-      const f32x4 dp = row_product<T, DH>(gf, vf[n]);
+      f32x4 p = row_product<DH>(qf, kf[n]);
+      const f32x4 dp = row_product<DH>(gf, vf[n]);
       f32x4 ds;
 #pragma unroll
       for (int v = 0; v < 4; v++) {
@@ -460,7 +437,7 @@ __global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void attn_dkv_f32_kernel(
   for (int n = 0; n < NT; n++) {
     const int j = j0 + 16 * n + c;
     if (j > last) continue;
-    T* row = dqkv + ((int64_t)bk.b * S + j) * ld + bk.hd * DH;
+    float* row = dqkv + ((int64_t)bk.b * S + j) * ld + bk.hd * DH;
     CF::store(row + d, dk[n], 1.0f, 1.0f, lane);
     CF::store(row + 2 * d, dv[n], 1.0f, 1.0f, lane);
   }
@@ -476,59 +453,53 @@ inline dim3 grid_of(int B, int S, int h, int nt, bool split) {
   return dim3((unsigned)(split ? nblk : (nblk + 3) / 4) * h * B);
 }
 
-template <typename T, int DH, int NT, bool SPLIT>
+template <int DH, int NT, bool SPLIT>
 int fwd_t(const void* qkv, void* o, float* lse, int B, int S, int h, hipStream_t st) {
-  hipLaunchKernelGGL((attn_fwd_f32_kernel<T, DH, NT, SPLIT>), grid_of(B, S, h, NT, SPLIT), dim3(256), 0, st, (const T*)qkv, (T*)o, lse, S, h,
+  hipLaunchKernelGGL((attn_fwd_f32_kernel<DH, NT, SPLIT>), grid_of(B, S, h, NT, SPLIT), dim3(256), 0, st, (const float*)qkv, (float*)o, lse, S, h,
                      1.0f / sqrtf((float)DH));
   ALS_CHECK_LAUNCH();
   return ALS_OK;
 }
-template <typename T, int DH, int NT, bool SPLIT>
+template <int DH, int NT, bool SPLIT>
 int bwd_t(const void* qkv, const void* o, const void* d_o, const float* lse, float* dscratch, void* dqkv, int B, int S, int h,
           hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)DH);
   const dim3 grid = grid_of(B, S, h, NT, SPLIT);
-  hipLaunchKernelGGL((attn_dq_f32_kernel<T, DH, NT, SPLIT>), grid, dim3(256), 0, st, (const T*)qkv, (const T*)o,
-                     (const T*)d_o, lse, dscratch, (T*)dqkv, S, h, scale);
+  hipLaunchKernelGGL((attn_dq_f32_kernel<DH, NT, SPLIT>), grid, dim3(256), 0, st, (const float*)qkv, (const float*)o,
+                     (const float*)d_o, lse, dscratch, (float*)dqkv, S, h, scale);
   ALS_CHECK_LAUNCH();
-  hipLaunchKernelGGL((attn_dkv_f32_kernel<T, DH, NT, SPLIT>), grid, dim3(256), 0, st, (const T*)qkv, (const T*)d_o,
-                     lse, dscratch, (T*)dqkv, S, h, scale);
+  hipLaunchKernelGGL((attn_dkv_f32_kernel<DH, NT, SPLIT>), grid, dim3(256), 0, st, (const float*)qkv, (const float*)d_o,
+                     lse, dscratch, (float*)dqkv, S, h, scale);
   ALS_CHECK_LAUNCH();
   return ALS_OK;
 }
 
 }  // namespace
 
-#define ALS_ATTN_ROWS(T, DH, CALL) (rows == 2 ? CALL(T, DH, 2, false) : rows == 1 ? CALL(T, DH, 1, false) : CALL(T, DH, 1, true))
-#define ALS_ATTN_SWITCH(CALL)                                                             \
-  do {                                                                                    \
-    const int rows = row_blocks(B, S, h);                                                 \
-    if (bf && dh == 64) return ALS_ATTN_ROWS(bf16, 64, CALL);                             \
-    if (bf) return ALS_ATTN_ROWS(bf16, 32, CALL);                                         \
-    if (dh == 64) return ALS_ATTN_ROWS(float, 64, CALL);                                  \
-    return ALS_ATTN_ROWS(float, 32, CALL);                                                \
-  } while (0)
+#define ALS_ATTN_ROWS(DH, CALL) (rows == 2 ? CALL(DH, 2, false) : rows == 1 ? CALL(DH, 1, false) : CALL(DH, 1, true))
 
 // Head widths of 32 and 64, 16-byte aligned tensors (rows are then aligned too); the grid is one-dimensional.  Up to 32
 // positions of up to 64 heads the kernels with one wavefront per row are as fast or faster: a row there is one load and one
 // exponential per lane, while here two tiles of dependent MFMAs follow each other in a single wavefront (figures above).
-bool attention_mfma_f32_supported(const void* a, const void* b, const void* c, const void* e, int B, int S, int h, int dh) {
+bool attention_mfma_any_supported(const void* a, const void* b, const void* c, const void* e, int B, int S, int h, int dh) {
   if (dh != 32 && dh != 64) return false;
   if (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)e) % 16) return false;
   if (S <= 32 && (int64_t)B * h <= 64) return false;
   return B > 0 && S > 0 && h > 0 && S <= 1024 && (int64_t)((S + 63) / 64) * h * B < (1 << 23);
 }
 
-int attention_fwd_mfma_f32(const void* qkv, void* o, float* lse, int B, int S, int h, int dh, int bf, hipStream_t st) {
-#define ALS_CALL(T, DH, NT, SPLIT) (fwd_t<T, DH, NT, SPLIT>(qkv, o, lse, B, S, h, st))
-  ALS_ATTN_SWITCH(ALS_CALL);
+int attention_fwd_mfma_f32(const void* qkv, void* o, float* lse, int B, int S, int h, int dh, hipStream_t st) {
+#define ALS_CALL(DH, NT, SPLIT) (fwd_t<DH, NT, SPLIT>(qkv, o, lse, B, S, h, st))
+  const int rows = row_blocks(B, S, h);
+  return dh == 64 ? ALS_ATTN_ROWS(64, ALS_CALL) : ALS_ATTN_ROWS(32, ALS_CALL);
 #undef ALS_CALL
 }
 
 int attention_bwd_mfma_f32(const void* qkv, const void* o, const void* d_o, const float* lse, float* dscratch, void* dqkv, int B,
-                           int S, int h, int dh, int bf, hipStream_t st) {
-#define ALS_CALL(T, DH, NT, SPLIT) (bwd_t<T, DH, NT, SPLIT>(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, st))
-  ALS_ATTN_SWITCH(ALS_CALL);
+                           int S, int h, int dh, hipStream_t st) {
+#define ALS_CALL(DH, NT, SPLIT) (bwd_t<DH, NT, SPLIT>(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, st))
+  const int rows = row_blocks(B, S, h);
+  return dh == 64 ? ALS_ATTN_ROWS(64, ALS_CALL) : ALS_ATTN_ROWS(32, ALS_CALL);
 #undef ALS_CALL
 }
 

@@ -158,11 +158,15 @@ int attention_fwd_generic(const void* qkv, void* o, float* lse, int B, int S, in
 int attention_bwd_generic(const void* qkv, const void* o, const void* d_o, const float* lse,
                           float* dscratch, void* dqkv, int B, int S, int h, int dh, int bf,
                           hipStream_t st);
-// the same in fp32 arithmetic on the fp32 matrix instruction (attention_mfma_f32.hip); fp32 or bf16 storage
-bool attention_mfma_f32_supported(const void* a, const void* b, const void* c, const void* e, int B, int S, int h, int dh);
-int attention_fwd_mfma_f32(const void* qkv, void* o, float* lse, int B, int S, int h, int dh, int bf, hipStream_t st);
+// the same in fp32 arithmetic for heads of 32 and 64 and any length up to 1024: fp32 storage on the fp32 matrix instruction
+// (attention_mfma_f32.hip), bf16 storage on the bf16 one (attention_mfma_any.hip)
+bool attention_mfma_any_supported(const void* a, const void* b, const void* c, const void* e, int B, int S, int h, int dh);
+int attention_fwd_mfma_f32(const void* qkv, void* o, float* lse, int B, int S, int h, int dh, hipStream_t st);
 int attention_bwd_mfma_f32(const void* qkv, const void* o, const void* d_o, const float* lse, float* dscratch, void* dqkv, int B,
-                           int S, int h, int dh, int bf, hipStream_t st);
+                           int S, int h, int dh, hipStream_t st);
+int attention_fwd_mfma_any(const void* qkv, void* o, float* lse, int B, int S, int h, int dh, hipStream_t st);
+int attention_bwd_mfma_any(const void* qkv, const void* o, const void* d_o, const float* lse, void* dqkv, int B, int S, int h, int dh,
+                           hipStream_t st);
 bool attention_mfma_supported(int S, int dh, int bf);
 int attention_fwd_mfma(const void* qkv, void* o, float* lse, int B, int S, int h, int dh,
                        hipStream_t st);

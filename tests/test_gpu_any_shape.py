@@ -241,6 +241,46 @@ def test_attention_hides_what_a_query_does_not_see(bad):
     assert not torch.isfinite(res[2][0][37:]).any()
 
 
+@pytest.mark.parametrize("B,S,h,dh", [(2, 33, 2, 32), (3, 200, 5, 64), (1, 1023, 1, 64),      # wavefronts that share a row block
+                                      (33, 257, 16, 32), (33, 257, 16, 64),                # two row blocks per wavefront in both directions
+                                      (65, 32, 1, 64)])                                    # one
+def test_computed_operands_of_bf16_attention_stay_fp32(B, S, h, dh):
+    """With whole fp32 probabilities and sums of up to 1024 products an output is within 2^-24 sqrt(1024) 4 of the exact one, less
+    than a 500th of the spacing of bf16: all but 1 % of the outputs are the correctly rounded ones.  (Probabilities rounded to
+    bf16 would move more than a tenth of them.)"""
+    o, ro, lse, rlse, dq, rdq = _attention_case(B, S, h, dh, torch.bfloat16, 0, fwd=A.step_attention_fwd, bwd=A.step_attention_bwd)
+    want = torch.from_numpy(ro).to(torch.bfloat16).float().numpy()
+    assert (o != want).mean() < 0.01
+    np.testing.assert_allclose(lse, rlse, rtol=1e-5, atol=1e-5)
+    assert _rel(dq, rdq) < 8e-3
+
+
+@pytest.mark.parametrize("B,S,h,dh", [(1, 70, 2, 64), (1, 70, 2, 32), (520, 33, 6, 64)])
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_bf16_attention_hides_what_a_query_does_not_see(B, S, h, dh, bad):
+    """Row 17 of v (k) of the first sample is not finite: the output (dq) of every earlier position and of every other sample is what it
+    is without it, and an infinite v gives infinite outputs, not NaN, wherever it has a weight (parts of it that are 0 included)."""
+    d = h * dh
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    qkv = torch.randn(B * S, 3 * d, device=DEV, generator=gen).bfloat16()
+    d_o = torch.randn(B * S, d, device=DEV, generator=gen).bfloat16()
+    res = []
+    for part in (None, 1, 2):
+        x = qkv.clone()
+        if part:
+            x[17, part * d:(part + 1) * d] = bad
+        o, lse, sc = torch.empty(B * S, d, device=DEV, dtype=torch.bfloat16), torch.empty(B * h * S, device=DEV), torch.empty(B * h * S, device=DEV)
+        dq = torch.empty_like(x)
+        A.step_attention_fwd(x, o, lse, B, S, h, dh)
+        A.step_attention_bwd(x, o, d_o, lse, sc, dq, B, S, h, dh)
+        res.append((o.cpu(), dq.cpu()))
+    for o, dq in res[1:]:
+        assert torch.equal(o[:17], res[0][0][:17]) and torch.equal(o[S:], res[0][0][S:])
+        assert torch.equal(dq[:17, :d], res[0][1][:17, :d]) and torch.equal(dq[S:], res[0][1][S:])
+    v_out = res[2][0][17:S].float()
+    assert torch.isinf(v_out).all() if np.isinf(bad) else torch.isnan(v_out).all()
+
+
 def test_a_gradient_does_not_depend_on_the_workers_beside_it():
     """8192 tokens of width 512: 64 tiles of 256 x 256 in the products of a layer, and a context of one and of four workers."""
     w = _model(d=512, h=8, ff=512, V=512, S=256, B=32)
