@@ -15,6 +15,12 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+// 16 bytes per lane from base + voff straight into 1 KB of LDS at lds_addr, lane l to bytes 16 l .. 16 l + 15.  Outside the compiler's wait
+// tracking: the wavefront waits for its own (vmcnt) before the barrier that precedes the first read.
+__device__ __forceinline__ void global_to_lds_16(const void* base, unsigned voff, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base) : "memory");
+}
+
 int set_error(int code, const char* fmt, ...);
 
 #define ALS_HIP(expr)                                                                      \
@@ -72,6 +78,8 @@ int gemm_mfma_any(const GemmDesc& g, hipStream_t st);
 double gemm_mfma_any_us(const GemmDesc& g);   // about what it takes, in microseconds
 // what gemm_mfma_supported takes with a_layout 0, in tiles of 128 x 128 or 64 x 64 with deep prefetch (gemm_mfma_deep.hip)
 int gemm_mfma_deep(const GemmDesc& g, int tile, hipStream_t st);
+// als_prof_enable or als_k_set_gemm_tile is in force
+bool gemm_hooks_active();
 // picks a matrix-core kernel when allowed and supported
 int gemm(const GemmDesc& g, bool allow_mfma, hipStream_t st);
 // the name of the kernel and tile that each of these takes for a product (no GPU call)
@@ -178,12 +186,25 @@ int attention_bwd(const void* qkv, const void* o, const void* d_o, const float* 
                   int h, int dh, int bf, bool allow_mfma, hipStream_t st);
 
 // ---- elementwise / reductions ----------------------------------------------------------------
+struct AdamArgs {
+  float lr, beta1, beta2, eps, wd, bc1, bc2;
+};
+// What changes from one step of a worker to the next, in device memory: a step that is replayed as a graph has the same kernel
+// arguments every time.  The kernels that need any of it take a pointer to it, and with a null pointer their own arguments.
+struct StepState {
+  const int32_t* tok;      // [B, S + 1]
+  const int32_t* offset;   // what embed_sort made of them
+  const int32_t* pos;
+  float* loss_out;
+  AdamArgs adam;
+};
+int set_step_state(StepState* ss, const StepState& v, hipStream_t st);
 // center = 0: RMSNorm ; 1: LayerNorm with gain and no bias
 int rmsnorm_fwd(const float* x, const float* g, void* y, float* rstd, int T, int d, float eps,
                 int out_bf16, int center, hipStream_t st);
 // the same for the rows E[tok] + Ppos, which are also written to x
 int embed_rmsnorm_fwd(const int32_t* tok, const float* E, const float* Ppos, float* x, const float* g, void* y, float* rstd, int B,
-                      int S, int d, int V, float eps, int out_bf16, int center, hipStream_t st);
+                      int S, int d, int V, float eps, int out_bf16, int center, hipStream_t st, const StepState* ss);
 // dx_out = (dx_in ? dx_in : 0) + rmsnorm_backward(dy); optional low-precision copy of dx_out;
 // dg = sum over rows of dy * xhat (uses partial[nblk*d] scratch, nblk = rmsnorm_bwd_blocks()).
 // With dg == nullptr only the partials are left, for one rmsnorm_dg_sum() over nset consecutive
@@ -195,21 +216,19 @@ int rmsnorm_bwd(const float* dy, const float* x, const float* rstd, const float*
                 float* partial, int T, int d, int center, hipStream_t st);
 // logits and dlogits in bf16 or both in fp32; they may be the same buffer
 int cross_entropy(const void* logits, const int32_t* tok, float* loss_row, void* dlogits, int bf, int B, int S, int V,
-                  hipStream_t st);
+                  hipStream_t st, const StepState* ss);
 // Orders each step's input positions by token id (see elementwise.hip; rank is scratch); offset is
 // [n_steps][V+1], rank and pos are [n_steps][B*S].
 int embed_sort(const int32_t* tok, int n_steps, int B, int S, int V, int32_t* offset, int32_t* rank,
                int32_t* pos, hipStream_t st);
 // dE, dPpos and the mean loss; scratch: 2 * ceil(B*S / 32) * d floats (partial rows of position lists that cross 32-position chunks)
 int embed_bwd(const int32_t* tok, const int32_t* offset, const int32_t* pos, const float* dx, float* dE,
-              float* dPpos, float* scratch, const float* loss_row, float* loss_out, int B, int S, int d, int V, hipStream_t st);
+              float* dPpos, float* scratch, const float* loss_row, float* loss_out, int B, int S, int d, int V, hipStream_t st,
+              const StepState* ss);
 int cast_copy(const float* src, void* dst, int64_t n, int dst_bf16, hipStream_t st);
 
-struct AdamArgs {
-  float lr, beta1, beta2, eps, wd, bc1, bc2;
-};
 int adamw(float* theta, const float* grad, float* m, float* v, bf16* lp, int64_t P,
-          int64_t P_decay, const AdamArgs& a, hipStream_t st);
+          int64_t P_decay, const AdamArgs& a, hipStream_t st, const StepState* ss = nullptr);
 
 #define ALS_DN_MAX_GROUP 16
 struct DnGroup {

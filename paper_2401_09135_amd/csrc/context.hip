@@ -38,6 +38,9 @@ struct Worker {
   int64_t adam_n; int last_n;
   int64_t t_restart;  // server event count when this replica last (re)started
   hipStream_t stream; hipEvent_t done_ev, ready_ev;
+  hipStream_t done_st, ready_st;   // where these were last recorded
+  StepState* state;            // of the step that runs next, in the arena
+  hipGraphExec_t step_graph;   // one local step with its arguments in *state; null: launched kernel by kernel
 };
 
 }  // namespace
@@ -49,7 +52,7 @@ struct als_ctx {
   float *theta, *m, *delta;
   int64_t t;
   std::vector<Worker> w;
-  hipEvent_t server_ev;
+  hipEvent_t server_ev; hipStream_t server_st;
   bool bf; bool allow_mfma;
   bool grouped_dw;   // the layers' weight gradients run as one grouped launch at the end of the backward pass
   bool list_dw;      // the same, the output matrix's too, where they have no aligned kernel
@@ -96,6 +99,7 @@ void carve(als_ctx* c, Carver& cv) {
   for (Worker& w : c->w) {
     w.theta = cv.f32(P); w.start = cv.f32(P); w.adam_m = cv.f32(P); w.adam_v = cv.f32(P);
     w.grad = cv.f32(P);
+    w.state = (StepState*)cv.take(sizeof(StepState));
     w.lp = bf ? (bf16*)cv.take((size_t)P * 2) : nullptr;
     int L = g.n_layers;
     w.x.resize(L + 1); w.xm.resize(L); w.rstd1.resize(L); w.rstd2.resize(L); w.lse.resize(L);
@@ -191,16 +195,16 @@ inline const void* wptr(const als_ctx* c, const Worker& w, int64_t off) {
   return c->bf ? (const void*)(w.lp + off) : (const void*)(w.theta + off);
 }
 
-int forward(als_ctx* c, Worker& w, const int32_t* tok) {
+// ss (forward, backward): take the tokens and what depends on them from there
+int forward(als_ctx* c, Worker& w, const int32_t* tok, hipStream_t st, const StepState* ss) {
   const als_config& g = c->cfg;
   const Layout& L = c->L;
-  hipStream_t st = w.stream;
   int T = c->T, d = g.d_model, ff = g.d_ff, V = g.vocab, B = g.batch, S = g.seq_len, h = g.n_heads;
   const int dh = head_width(g), da = h * dh;
   const int ln = g.norm_kind == ALS_NORM_LAYER;  // LayerNorm (gain, no bias) instead of RMSNorm
   bool mf = c->allow_mfma;
   float eps = (float)g.norm_eps;
-  RUN(embed_rmsnorm_fwd(tok, w.theta + L.E, w.theta + L.Ppos, w.x[0], w.theta + L.g1[0], w.a[0], w.rstd1[0], B, S, d, V, eps, c->bf, ln, st));
+  RUN(embed_rmsnorm_fwd(tok, w.theta + L.E, w.theta + L.Ppos, w.x[0], w.theta + L.g1[0], w.a[0], w.rstd1[0], B, S, d, V, eps, c->bf, ln, st, ss));
   for (int l = 0; l < g.n_layers; l++) {
     if (l) RUN(rmsnorm_fwd(w.x[l], w.theta + L.g1[l], w.a[l], w.rstd1[l], T, d, eps, c->bf, ln, st));
     RUN(gemm(desc(c, w.a[l], 0, d, wptr(c, w, L.Wqkv[l]), 0, 3 * da, T, 3 * da, d, w.qkv[l], 3 * da, true), mf, st));
@@ -219,15 +223,14 @@ int forward(als_ctx* c, Worker& w, const int32_t* tok) {
   RUN(rmsnorm_fwd(w.x[g.n_layers], w.theta + L.gf, w.xf, w.rstdf, T, d, eps, c->bf, ln, st));
   void* logits = c->bf ? w.dlogits : (void*)w.logits;
   RUN(gemm(desc(c, w.xf, 0, d, wptr(c, w, L.Wout), 0, V, T, V, d, logits, V, true), mf, st));
-  RUN(cross_entropy(logits, tok, w.loss_row, w.dlogits, c->bf, B, S, V, st));
+  RUN(cross_entropy(logits, tok, w.loss_row, w.dlogits, c->bf, B, S, V, st, ss));
   return ALS_OK;
 }
 
 // also writes the mean of the losses that forward() left per row
-int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot, float* loss_out) {
+int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot, float* loss_out, hipStream_t st, const StepState* ss) {
   const als_config& g = c->cfg;
   const Layout& L = c->L;
-  hipStream_t st = w.stream;
   int T = c->T, d = g.d_model, ff = g.d_ff, V = g.vocab, B = g.batch, S = g.seq_len, h = g.n_heads;
   const int dh = head_width(g), da = h * dh;
   const int ln = g.norm_kind == ALS_NORM_LAYER;  // LayerNorm (gain, no bias) instead of RMSNorm
@@ -272,13 +275,34 @@ int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot, float* loss_ou
   RUN(rmsnorm_dg_sum(w.partial, w.grad + L.g1[0], T, d, 2 * nl + 1, st));
   // w.dtmp (T x d floats) is free again here: scratch for the embedding gradient's chunk partials
   RUN(embed_bwd(tok, w.sort_offset + (int64_t)slot * (V + 1), w.sort_pos + (int64_t)slot * T, w.dxa,
-                w.grad + L.E, w.grad + L.Ppos, w.dtmp, w.loss_row, loss_out, B, S, d, V, st));
+                w.grad + L.E, w.grad + L.Ppos, w.dtmp, w.loss_row, loss_out, B, S, d, V, st, ss));
   return ALS_OK;
 }
 
 int check_ctx_worker(als_ctx* ctx, int worker) {
   if (!ctx) return set_error(ALS_ERR_INVALID, "context is null");
   if (worker < 0 || worker >= (int)ctx->w.size()) return set_error(ALS_ERR_INVALID, "worker %d out of range", worker);
+  return ALS_OK;
+}
+
+// The step of one worker as a graph, captured on a stream of its own (nothing runs there).  On any failure the context goes on
+// without: a step is then launched kernel by kernel.
+void capture_step(als_ctx* ctx, Worker& w, hipStream_t cs) {
+  hipGraph_t graph = nullptr;
+  if (hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed) != hipSuccess) { (void)hipGetLastError(); return; }
+  int rc = forward(ctx, w, nullptr, cs, w.state);
+  if (!rc) rc = backward(ctx, w, nullptr, 0, nullptr, cs, w.state);
+  if (!rc) rc = adamw(w.theta, w.grad, w.adam_m, w.adam_v, w.lp, ctx->L.P, ctx->L.P_decay, AdamArgs{}, cs, w.state);
+  const bool ok = hipStreamEndCapture(cs, &graph) == hipSuccess && !rc;
+  if (!ok || hipGraphInstantiate(&w.step_graph, graph, nullptr, nullptr, 0) != hipSuccess) w.step_graph = nullptr;
+  if (graph) (void)hipGraphDestroy(graph);
+  (void)hipGetLastError();
+}
+
+// A wait costs the host 4 to 6 us: none where the stream's own order gives it.  (The handle of the per-thread default stream stands
+// for another stream in every thread.)
+int wait_event(hipStream_t st, hipEvent_t ev, hipStream_t recorded_on) {
+  if (st != recorded_on || st == hipStreamPerThread) ALS_HIP(hipStreamWaitEvent(st, ev, 0));
   return ALS_OK;
 }
 
@@ -332,7 +356,7 @@ extern "C" int als_init(const als_config* cfg, void* arena, size_t arena_bytes, 
   int64_t P = c->L.P;
   hipStream_t s0 = (hipStream_t)streams[0];
   c->server_ev = nullptr;
-  for (Worker& w : c->w) { w.done_ev = nullptr; w.ready_ev = nullptr; w.losses_host = nullptr; }
+  for (Worker& w : c->w) { w.done_ev = nullptr; w.ready_ev = nullptr; w.losses_host = nullptr; w.step_graph = nullptr; }
   auto fail = [&](int code) { als_destroy(c); return code; };
   if (hipEventCreateWithFlags(&c->server_ev, hipEventDisableTiming) != hipSuccess)
     return fail(set_error(ALS_ERR_HIP, "hipEventCreate failed"));
@@ -345,6 +369,7 @@ extern "C" int als_init(const als_config* cfg, void* arena, size_t arena_bytes, 
     Worker& w = c->w[i];
     w.stream = (hipStream_t)streams[i % n_streams];
     w.adam_n = 0; w.last_n = 0; w.t_restart = 0;
+    w.ready_st = w.done_st = w.stream;
     if (hipEventCreateWithFlags(&w.done_ev, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&w.ready_ev, hipEventDisableTiming) != hipSuccess ||
         hipHostMalloc((void**)&w.losses_host, (size_t)cfg->max_local_steps * 4, hipHostMallocDefault) != hipSuccess ||
@@ -359,9 +384,26 @@ extern "C" int als_init(const als_config* cfg, void* arena, size_t arena_bytes, 
     if (hipEventRecord(w.ready_ev, w.stream) != hipSuccess || hipEventRecord(w.done_ev, w.stream) != hipSuccess)
       return fail(set_error(ALS_ERR_HIP, "als_init: hipEventRecord failed"));
   }
+  c->server_st = s0;
   if (hipEventRecord(c->server_ev, s0) != hipSuccess) return fail(set_error(ALS_ERR_HIP, "hipEventRecord failed"));
   rc = sync_all(c);
   if (rc) return fail(rc);
+  // Whether the launches of the workers' steps hold the host longer than the chip.  A launch takes the host 2.4 us, a node of a graph
+  // 0.4 to 1.2; of the workers that run side by side each advances by one kernel in about 5 us where the kernels are small.  Where the
+  // chip is the slower side a graph's start costs more than it saves.  Rounds in us, kernel by kernel / as graphs: 4 streams of 32 x 8
+  // tokens, d = 64: 1191 / 647; 4 of 128 x 4, d = 256: 1274 / 922; 2 of 256 x 8, d = 256: 702 / 715; one of 128 x 8, d = 256 in fp32: 445 / 452.
+  const int64_t T = c->T, da = (int64_t)cfg->n_heads * head_width(*cfg), d = cfg->d_model;
+  const double flops = 6.0 * T * (cfg->n_layers * (4.0 * d * da + 2.0 * d * cfg->d_ff + (double)cfg->seq_len * da) + (double)d * cfg->vocab);
+  const int launches = 15 * cfg->n_layers + 12, side_by_side = std::min(cfg->n_workers, n_streams);
+  if (side_by_side * 2.4 > 5.0 + flops / launches / 250e6 && !gemm_hooks_active()) {
+    hipStream_t cs = nullptr;
+    if (hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) == hipSuccess) {
+      for (Worker& w : c->w) capture_step(c, w, cs);
+      (void)hipStreamDestroy(cs);
+    } else {
+      (void)hipGetLastError();
+    }
+  }
   *out = c;
   return ALS_OK;
 }
@@ -373,6 +415,7 @@ extern "C" int als_destroy(als_ctx* c) {
     if (w.done_ev) (void)hipEventDestroy(w.done_ev);
     if (w.ready_ev) (void)hipEventDestroy(w.ready_ev);
     if (w.losses_host) (void)hipHostFree(w.losses_host);
+    if (w.step_graph) (void)hipGraphExecDestroy(w.step_graph);
   }
   if (c->server_ev) (void)hipEventDestroy(c->server_ev);
   delete c;
@@ -388,13 +431,22 @@ extern "C" int als_worker_local_steps(als_ctx* ctx, int worker, int n_steps, con
     return set_error(ALS_ERR_INVALID, "n_steps %d outside 0..max_local_steps=%d", n_steps, g.max_local_steps);
   if (n_steps > 0 && (!tokens || !lr_host)) return set_error(ALS_ERR_INVALID, "tokens_dev and lr_host must be non-null");
   Worker& w = ctx->w[worker];
-  ALS_HIP(hipStreamWaitEvent(w.stream, w.ready_ev, 0));
+  RUN(wait_event(w.stream, w.ready_ev, w.ready_st));
   int64_t per = (int64_t)g.batch * (g.seq_len + 1);
   RUN(embed_sort(tokens, n_steps, g.batch, g.seq_len, g.vocab, w.sort_offset, w.sort_rank, w.sort_pos, w.stream));
+  // The graph is left out where a call has to see the launches: under the measurement hooks of the GEMM kernels and while the
+  // caller captures this stream.
+  bool replay = w.step_graph && !gemm_hooks_active();
+  if (replay) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    replay = hipStreamIsCapturing(w.stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+  }
   for (int s = 0; s < n_steps; s++) {
     const int32_t* tok = tokens + (int64_t)s * per;
-    RUN(forward(ctx, w, tok));
-    RUN(backward(ctx, w, tok, s, w.losses_dev + s));
+    if (!replay) {
+      RUN(forward(ctx, w, tok, w.stream, nullptr));
+      RUN(backward(ctx, w, tok, s, w.losses_dev + s, w.stream, nullptr));
+    }
     w.adam_n += 1;
     AdamArgs a;
     a.lr = lr_host[s];
@@ -402,10 +454,17 @@ extern "C" int als_worker_local_steps(als_ctx* ctx, int worker, int n_steps, con
     a.wd = (float)g.weight_decay;
     a.bc1 = (float)(1.0 - pow(g.adam_beta1, (double)w.adam_n));
     a.bc2 = (float)(1.0 - pow(g.adam_beta2, (double)w.adam_n));
-    RUN(adamw(w.theta, w.grad, w.adam_m, w.adam_v, w.lp, ctx->L.P, ctx->L.P_decay, a, w.stream));
+    if (replay) {
+      RUN(set_step_state(w.state, StepState{tok, w.sort_offset + (int64_t)s * (g.vocab + 1), w.sort_pos + (int64_t)s * ctx->T,
+                                            w.losses_dev + s, a}, w.stream));
+      ALS_HIP(hipGraphLaunch(w.step_graph, w.stream));
+    } else {
+      RUN(adamw(w.theta, w.grad, w.adam_m, w.adam_v, w.lp, ctx->L.P, ctx->L.P_decay, a, w.stream));
+    }
   }
   w.last_n = n_steps;
   ALS_HIP(hipEventRecord(w.done_ev, w.stream));
+  w.done_st = w.stream;
   if (loss_host) {
     ALS_HIP(hipStreamSynchronize(w.stream));
     memcpy(loss_host, w.losses_host, (size_t)n_steps * 4);
@@ -418,12 +477,13 @@ extern "C" int als_worker_loss_grad(als_ctx* ctx, int worker, const int32_t* tok
   if (rc) return rc;
   if (!tokens || !loss_host) return set_error(ALS_ERR_INVALID, "tokens_dev and loss_host must be non-null");
   Worker& w = ctx->w[worker];
-  ALS_HIP(hipStreamWaitEvent(w.stream, w.ready_ev, 0));
+  RUN(wait_event(w.stream, w.ready_ev, w.ready_st));
   RUN(embed_sort(tokens, 1, ctx->cfg.batch, ctx->cfg.seq_len, ctx->cfg.vocab, w.sort_offset, w.sort_rank,
                  w.sort_pos, w.stream));
-  RUN(forward(ctx, w, tokens));
-  RUN(backward(ctx, w, tokens, 0, w.losses_dev));
+  RUN(forward(ctx, w, tokens, w.stream, nullptr));
+  RUN(backward(ctx, w, tokens, 0, w.losses_dev, w.stream, nullptr));
   ALS_HIP(hipEventRecord(w.done_ev, w.stream));
+  w.done_st = w.stream;
   ALS_HIP(hipStreamSynchronize(w.stream));
   *loss_host = w.losses_host[0];
   return ALS_OK;
@@ -444,8 +504,8 @@ static int outer_apply(als_ctx* ctx, const int32_t* workers, int n_group, int re
   }
   const als_config& g = ctx->cfg;
   hipStream_t st = ctx->w[workers[0]].stream;
-  ALS_HIP(hipStreamWaitEvent(st, ctx->server_ev, 0));
-  for (int j = 0; j < n_group; j++) ALS_HIP(hipStreamWaitEvent(st, ctx->w[workers[j]].done_ev, 0));
+  RUN(wait_event(st, ctx->server_ev, ctx->server_st));
+  for (int j = 0; j < n_group; j++) RUN(wait_event(st, ctx->w[workers[j]].done_ev, ctx->w[workers[j]].done_st));
   int64_t P = ctx->L.P;
   // Which events are applied: a worker whose staleness (server events since it started)
   // exceeds the threshold is discarded -- no server change, no event counted -- but still restarts.
@@ -493,11 +553,13 @@ static int outer_apply(als_ctx* ctx, const int32_t* workers, int n_group, int re
   if (restart_flag)
     for (int j = 0; j < n_group; j++) ctx->w[workers[j]].t_restart = ctx->t;
   ALS_HIP(hipEventRecord(ctx->server_ev, st));
+  ctx->server_st = st;
   // Whatever touches these replicas next (their local steps, or a later sync) is ordered
   // after this call.
   for (int j = 0; j < n_group; j++) {
     ALS_HIP(hipEventRecord(ctx->w[workers[j]].ready_ev, st));
     ALS_HIP(hipEventRecord(ctx->w[workers[j]].done_ev, st));
+    ctx->w[workers[j]].ready_st = ctx->w[workers[j]].done_st = st;
   }
   return ALS_OK;
 }

@@ -71,7 +71,8 @@ __global__ __launch_bounds__(256) void adamw_kernel(float* __restrict__ theta,
                                                     const float* __restrict__ grad,
                                                     float* __restrict__ m, float* __restrict__ v,
                                                     bf16* __restrict__ lp, int64_t n4,
-                                                    int64_t decay4, AdamArgs a) {
+                                                    int64_t decay4, AdamArgs a, const StepState* ss) {
+  if (ss) a = ss->adam;
   const int64_t stride = (int64_t)gridDim.x * 256 * STREAM_U;
   for (int64_t i0 = (int64_t)blockIdx.x * 256 * STREAM_U + threadIdx.x; i0 < n4; i0 += stride) {
     f32x4 th[STREAM_U], g[STREAM_U], mm[STREAM_U], vv[STREAM_U];
@@ -99,7 +100,8 @@ __global__ __launch_bounds__(256) void adamw_kernel(float* __restrict__ theta,
 }
 
 __global__ void adamw_tail_kernel(float* theta, const float* grad, float* m, float* v, bf16* lp,
-                                  int64_t begin, int64_t P, int64_t P_decay, AdamArgs a) {
+                                  int64_t begin, int64_t P, int64_t P_decay, AdamArgs a, const StepState* ss) {
+  if (ss) a = ss->adam;
   int64_t i = begin + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= P) return;
   float th = theta[i], mm = m[i], vv = v[i];
@@ -109,7 +111,7 @@ __global__ void adamw_tail_kernel(float* theta, const float* grad, float* m, flo
 }
 
 int adamw(float* theta, const float* grad, float* m, float* v, bf16* lp, int64_t P,
-          int64_t P_decay, const AdamArgs& a, hipStream_t st) {
+          int64_t P_decay, const AdamArgs& a, hipStream_t st, const StepState* ss) {
   if (P <= 0) return ALS_OK;
   // the vector body covers whole float4 groups that do not straddle the decay boundary
   int64_t n4 = 0, decay4 = 0;
@@ -119,16 +121,25 @@ int adamw(float* theta, const float* grad, float* m, float* v, bf16* lp, int64_t
   }
   if (n4 > 0) {
     hipLaunchKernelGGL(adamw_kernel, dim3(stream_blocks(n4, STREAM_U)), dim3(256), 0, st, theta, grad, m, v,
-                       lp, n4, decay4, a);
+                       lp, n4, decay4, a, ss);
     ALS_CHECK_LAUNCH();
   }
   int64_t begin = n4 * 4;
   if (begin < P) {
     int blocks = blocks_for(P - begin, 256, 1 << 30);
     hipLaunchKernelGGL(adamw_tail_kernel, dim3(blocks), dim3(256), 0, st, theta, grad, m, v, lp,
-                       begin, P, P_decay, a);
+                       begin, P, P_decay, a, ss);
     ALS_CHECK_LAUNCH();
   }
+  return ALS_OK;
+}
+
+__global__ void set_step_state_kernel(StepState* ss, StepState v) {
+  if (threadIdx.x == 0) *ss = v;
+}
+int set_step_state(StepState* ss, const StepState& v, hipStream_t st) {
+  hipLaunchKernelGGL(set_step_state_kernel, dim3(1), dim3(64), 0, st, ss, v);
+  ALS_CHECK_LAUNCH();
   return ALS_OK;
 }
 
@@ -824,7 +835,8 @@ __device__ __forceinline__ void mean_rows(const float* __restrict__ v, float* __
 __global__ __launch_bounds__(256) void embed_bwd_chunks_kernel(
     const int32_t* __restrict__ tok, const int32_t* __restrict__ offset, const int32_t* __restrict__ pos,
     const float* __restrict__ dx, float* __restrict__ dE, float* __restrict__ scratch, float* __restrict__ dPpos,
-    const float* __restrict__ loss_row, float* __restrict__ loss_out, int B, int S, int V, int d, int nchunk) {
+    const float* __restrict__ loss_row, float* __restrict__ loss_out, int B, int S, int V, int d, int nchunk, const StepState* ss) {
+  if (ss) { tok = ss->tok; offset = ss->offset; pos = ss->pos; loss_out = ss->loss_out; }
   __shared__ int s_pos[EMB_CH], s_tok[EMB_CH], s_dst[EMB_CH];   // s_dst: -1 = dE, else the scratch slot
   const int T = B * S, c = blockIdx.x, i0 = c * EMB_CH, tid = threadIdx.x;
   const int d4 = d / 4;
@@ -880,7 +892,8 @@ __global__ __launch_bounds__(256) void embed_bwd_chunks_kernel(
 
 __global__ __launch_bounds__(256) void embed_bwd_rows_kernel(const int32_t* __restrict__ offset,
                                                              const float* __restrict__ scratch,
-                                                             float* __restrict__ dE, int V, int d) {
+                                                             float* __restrict__ dE, int V, int d, const StepState* ss) {
+  if (ss) offset = ss->offset;
   const int lane = threadIdx.x & 63;
   const int v = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (v >= V) return;
@@ -909,13 +922,14 @@ __global__ __launch_bounds__(256) void embed_bwd_rows_kernel(const int32_t* __re
 }
 
 int embed_bwd(const int32_t* tok, const int32_t* offset, const int32_t* pos, const float* dx, float* dE,
-              float* dPpos, float* scratch, const float* loss_row, float* loss_out, int B, int S, int d, int V, hipStream_t st) {
+              float* dPpos, float* scratch, const float* loss_row, float* loss_out, int B, int S, int d, int V, hipStream_t st,
+              const StepState* ss) {
   if (d > 256 * EMB_MAXD4 || d % 4) return set_error(ALS_ERR_INVALID, "embed_bwd: d unsupported");
   const int nchunk = (B * S + EMB_CH - 1) / EMB_CH;
   hipLaunchKernelGGL(embed_bwd_chunks_kernel, dim3(nchunk + S + 1), dim3(256), 0, st, tok, offset, pos, dx, dE, scratch, dPpos,
-                     loss_row, loss_out, B, S, V, d, nchunk);
+                     loss_row, loss_out, B, S, V, d, nchunk, ss);
   ALS_CHECK_LAUNCH();
-  hipLaunchKernelGGL(embed_bwd_rows_kernel, dim3((V + 3) / 4), dim3(256), 0, st, offset, scratch, dE, V, d);
+  hipLaunchKernelGGL(embed_bwd_rows_kernel, dim3((V + 3) / 4), dim3(256), 0, st, offset, scratch, dE, V, d, ss);
   ALS_CHECK_LAUNCH();
   return ALS_OK;
 }
@@ -928,7 +942,7 @@ int embed_bwd(const int32_t* tok, const int32_t* offset, const int32_t* pos, con
 // ------------------------------------------------------------------------------------------
 // EMBED: the rows are the embeddings, x[b*S+s,:] = E[tok[b,s],:] + Ppos[s,:] (tokens are [B,S+1]; inputs are s < S), formed and
 // written here on the way into the first norm: one launch and one pass over x less than on their own.
-struct EmbedArgs { const int32_t* tok; const float* E; const float* Ppos; float* x; int S, V; };
+struct EmbedArgs { const int32_t* tok; const float* E; const float* Ppos; float* x; int S, V; const StepState* ss; };
 #define RMS_MAXD4 4  // float4 slots per lane: d <= 1024
 template <typename OT, bool CENTER, bool EMBED>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const float* __restrict__ x, EmbedArgs em,
@@ -944,7 +958,8 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const float* __restric
   const float4* pr = nullptr;
   if (EMBED) {
     const int b = row / em.S, s = row % em.S;
-    int id = em.tok[(int64_t)b * (em.S + 1) + s];
+    const int32_t* tok = em.ss ? em.ss->tok : em.tok;
+    int id = tok[(int64_t)b * (em.S + 1) + s];
     id = id < 0 ? 0 : (id >= em.V ? em.V - 1 : id);  // out-of-range ids are clamped, never dereferenced
     xr = reinterpret_cast<const float4*>(em.E + (int64_t)id * d);
     pr = reinterpret_cast<const float4*>(em.Ppos + (int64_t)s * d);
@@ -1009,8 +1024,8 @@ int rmsnorm_fwd(const float* x, const float* g, void* y, float* rstd, int T, int
 }
 
 int embed_rmsnorm_fwd(const int32_t* tok, const float* E, const float* Ppos, float* x, const float* g, void* y, float* rstd, int B,
-                      int S, int d, int V, float eps, int out_bf16, int center, hipStream_t st) {
-  return norm_fwd<true>(nullptr, EmbedArgs{tok, E, Ppos, x, S, V}, g, y, rstd, B * S, d, eps, out_bf16, center, st);
+                      int S, int d, int V, float eps, int out_bf16, int center, hipStream_t st, const StepState* ss) {
+  return norm_fwd<true>(nullptr, EmbedArgs{tok, E, Ppos, x, S, V, ss}, g, y, rstd, B * S, d, eps, out_bf16, center, st);
 }
 
 // Backward: xhat = x rstd (RMSNorm) or (x - mean x) rstd (LayerNorm) ; dxhat = dy g ;
@@ -1193,7 +1208,8 @@ __device__ __forceinline__ float block_reduce(float v, bool is_max, float* sh) {
 template <typename T>
 __global__ __launch_bounds__(256) void cross_entropy_kernel(const T* logits, const int32_t* __restrict__ tok,
                                                             float* __restrict__ loss_row, T* dl, int S, int V,
-                                                            float invT) {
+                                                            float invT, const StepState* ss) {
+  if (ss) tok = ss->tok;
   __shared__ float sh[8];
   int t = blockIdx.x;
   int b = t / S, s = t % S;
@@ -1225,7 +1241,8 @@ struct __attribute__((packed, aligned(2))) ce_b8 { bf16x8 v; };
 template <int BS, bool EDGE>
 __global__ __launch_bounds__(BS) void cross_entropy_reg_kernel(const bf16* logits, const int32_t* __restrict__ tok,
                                                                float* __restrict__ loss_row, bf16* dl, int S, int V,
-                                                               float invT) {
+                                                               float invT, const StepState* ss) {
+  if (ss) tok = ss->tok;
   __shared__ float sh[16];
   int t = blockIdx.x;
   int b = t / S, s = t % S;
@@ -1300,7 +1317,7 @@ __global__ __launch_bounds__(BS) void cross_entropy_reg_kernel(const bf16* logit
 }
 
 int cross_entropy(const void* logits, const int32_t* tok, float* loss_row, void* dlogits, int bf, int B, int S, int V,
-                  hipStream_t st) {
+                  hipStream_t st, const StepState* ss) {
   const int T = B * S;
   const float invT = 1.0f / (float)T;
   const bf16* lb = (const bf16*)logits;
@@ -1308,15 +1325,15 @@ int cross_entropy(const void* logits, const int32_t* tok, float* loss_row, void*
   if (bf && V <= 32 * 1024) {   // longer rows do not fit the registers of a block
     const bool big = V > 32 * 256, edge = V % 8 != 0;
 #define ALS_CE_LAUNCH(BS, EDGE) \
-  hipLaunchKernelGGL((cross_entropy_reg_kernel<BS, EDGE>), dim3(T), dim3(BS), 0, st, lb, tok, loss_row, db, S, V, invT)
+  hipLaunchKernelGGL((cross_entropy_reg_kernel<BS, EDGE>), dim3(T), dim3(BS), 0, st, lb, tok, loss_row, db, S, V, invT, ss)
     if (big) { if (edge) ALS_CE_LAUNCH(1024, true); else ALS_CE_LAUNCH(1024, false); }
     else { if (edge) ALS_CE_LAUNCH(256, true); else ALS_CE_LAUNCH(256, false); }
 #undef ALS_CE_LAUNCH
   } else if (bf) {
-    hipLaunchKernelGGL(cross_entropy_kernel<bf16>, dim3(T), dim3(256), 0, st, lb, tok, loss_row, db, S, V, invT);
+    hipLaunchKernelGGL(cross_entropy_kernel<bf16>, dim3(T), dim3(256), 0, st, lb, tok, loss_row, db, S, V, invT, ss);
   } else {
     hipLaunchKernelGGL(cross_entropy_kernel<float>, dim3(T), dim3(256), 0, st, (const float*)logits, tok, loss_row,
-                       (float*)dlogits, S, V, invT);
+                       (float*)dlogits, S, V, invT, ss);
   }
   ALS_CHECK_LAUNCH();
   return ALS_OK;

@@ -379,6 +379,8 @@ static int dispatch(const GemmDesc& g, const MfmaArgs& a, int bm, int bn, int nb
 // thread reads whole values, the three are still not changed as one)
 static std::atomic<int> g_force_bm{0}, g_force_bn{0}, g_force_nbuf{0};
 
+bool gemm_hooks_active() { return g_prof_on.load() || g_force_bm.load() || g_force_bn.load() || g_force_nbuf.load(); }
+
 // deep: the tile of gemm_mfma_deep.hip (128 or 64); any: gemm_mfma_any.hip; else bm x bn tiles with buffering code nbuf, K in nsplit parts
 struct MfmaChoice { int deep, any, bm, bn, nbuf, nsplit; };
 

@@ -308,9 +308,6 @@ __global__ __launch_bounds__(256) void dw_tile_reduce_kernel(const DwProblem* __
 //     fall into 4 different quarters of the banks).
 // These loads are outside the compiler's wait tracking (inline assembly): every wavefront waits
 // for its own (vmcnt(0)) before the last barrier that precedes the first read of the buffer.
-__device__ __forceinline__ void global_to_lds_16(const void* base, unsigned voff, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base) : "memory");
-}
 
 template <int AL, int BL, int EPI, typename TO>
 __device__ __forceinline__ void ppd_tile(const MfmaArgs& g, const int m0, const int n0, const int slice0, const int nk,

@@ -500,3 +500,43 @@ def test_bf16_operand_rounding_sets_the_scale_of_the_deviation(name):
             f"{u_lib:.3e} / {u_round:.3e}; worst per-step loss rel {worst_lib:.3e} / {worst_round:.3e}")
     assert d_lib < 3.0 * d_round and u_lib < 3.0 * u_round
     assert worst_lib < max(3.0 * worst_round, TOL["bf16"]["loss"])
+
+
+@pytest.mark.parametrize("name", ["tiny", "tiny_ln", "mini_bf16"])
+def test_steps_replayed_as_graphs_equal_launched_ones(name):
+    """Four small workers on four streams replay their steps as graphs; under als_prof_enable the same calls launch kernel by
+    kernel.  The kernels and their operands are the same, so every vector and loss is, bit for bit: over several rounds, with
+    other step counts, learning rates and tokens each, eager work, gradients and synchronisations between them."""
+    w = I.workload(name)
+    theta0 = I.theta0(lm.param_layout(w), w["seed"])
+    busy = torch.randn(256, 256, device="cuda:0")
+    out = []
+    for launched in (False, True):
+        cfg = A.Config.from_workload(w)
+        cfg.n_workers, cfg.max_local_steps = 4, 3
+        ctx = A.Context(cfg, theta0, n_streams=4)
+        streams = [_stream(w)(i) for i in range(4)]
+        seen = []
+        A.prof_enable(launched)
+        try:
+            for rnd in range(3):
+                for i in range(4):
+                    n = 1 + (i + rnd) % 3
+                    tok = torch.from_numpy(np.ascontiguousarray(streams[i].take(n))).to("cuda:0")
+                    seen.append(ctx.worker_local_steps(i, tok, [1e-3 * (1 + rnd + s) for s in range(n)], want_losses=rnd == 1))
+                    busy = busy @ busy * 1e-3
+                tok = torch.from_numpy(np.ascontiguousarray(streams[rnd].take(1))).to("cuda:0")
+                seen.extend(ctx.worker_loss_grad(rnd, tok[0]))
+                ctx.outer_apply_dn([0, 1, 2, 3], restart=rnd != 1)
+                torch.cuda.synchronize()
+        finally:
+            A.prof_enable(False)
+            A.prof_collect()
+        vec = [ctx.get_vector(v) for v in ("theta", "momentum", "delta")]
+        vec += [ctx.get_vector(v, i) for i in range(4) for v in ("worker_theta", "worker_start", "adam_m", "adam_v", "grad")]
+        ctx.close()
+        out.append((seen, vec))
+    for a, b in zip(out[0][0], out[1][0]):
+        assert (a is None and b is None) or np.array_equal(a, b)
+    for a, b in zip(out[0][1], out[1][1]):
+        assert np.array_equal(a, b)
