@@ -203,6 +203,13 @@ def test_attention_mfma(B, S, h):
         assert _rel(dq[:, sl], rdq[:, sl]) < 1.5e-2, nm
 
 
+# Four wavefronts to a block of 64 queries (128 blocks, the last that do), two (144; and one tile for two, so that one has none), one with
+# pairs that are no multiple of 8 (650 blocks), and pairs in two groups of unequal size (518 pairs).
+@pytest.mark.parametrize("B,S,h", [(1, 1024, 8), (1, 1024, 9), (2, 128, 3), (5, 640, 13), (37, 128, 14)])
+def test_attention_mfma_sharing_and_order_of_blocks(B, S, h):
+    test_attention_mfma(B, S, h)
+
+
 @pytest.mark.parametrize("scale", [3.0, 0.05])
 def test_attention_mfma_score_ranges(scale):
     """Scores with a standard deviation of 9 (the running reference point of the online softmax must
