@@ -206,14 +206,10 @@ int rmsnorm_fwd(const float* x, const float* g, void* y, float* rstd, int T, int
 int embed_rmsnorm_fwd(const int32_t* tok, const float* E, const float* Ppos, float* x, const float* g, void* y, float* rstd, int B,
                       int S, int d, int V, float eps, int out_bf16, int center, hipStream_t st, const StepState* ss);
 // dx_out = (dx_in ? dx_in : 0) + rmsnorm_backward(dy); optional low-precision copy of dx_out;
-// dg = sum over rows of dy * xhat (uses partial[nblk*d] scratch, nblk = rmsnorm_bwd_blocks()).
-// With dg == nullptr only the partials are left, for one rmsnorm_dg_sum() over nset consecutive
-// sets of partials into nset consecutive gain gradients.
+// the gain gradient, sum over rows of dy * xhat, is left in partial[nblk][d], nblk = rmsnorm_bwd_blocks(T), for embed_bwd to add.
 int rmsnorm_bwd_blocks(int T);
-int rmsnorm_dg_sum(const float* partial, float* dg, int T, int d, int nset, hipStream_t st);
 int rmsnorm_bwd(const float* dy, const float* x, const float* rstd, const float* g,
-                const float* dx_in, float* dx_out, void* dx_lp, int lp_bf16, float* dg,
-                float* partial, int T, int d, int center, hipStream_t st);
+                const float* dx_in, float* dx_out, void* dx_lp, int lp_bf16, float* partial, int T, int d, int center, hipStream_t st);
 // logits and dlogits in bf16 or both in fp32; they may be the same buffer
 int cross_entropy(const void* logits, const int32_t* tok, float* loss_row, void* dlogits, int bf, int B, int S, int V,
                   hipStream_t st, const StepState* ss);
@@ -221,10 +217,12 @@ int cross_entropy(const void* logits, const int32_t* tok, float* loss_row, void*
 // [n_steps][V+1], rank and pos are [n_steps][B*S].
 int embed_sort(const int32_t* tok, int n_steps, int B, int S, int V, int32_t* offset, int32_t* rank,
                int32_t* pos, hipStream_t st);
-// dE, dPpos and the mean loss; scratch: 2 * ceil(B*S / 32) * d floats (partial rows of position lists that cross 32-position chunks)
+// nset consecutive sets of [nblk][d] partials and the gain gradients that they add up to, nset consecutive rows of d
+struct NormPartials { const float* partial; float* dg; int nblk, nset; };
+// dE, dPpos, the mean loss and the norms' gain gradients; scratch: 2 * ceil(B*S / 32) * d floats (partial rows of position lists that cross 32-position chunks)
 int embed_bwd(const int32_t* tok, const int32_t* offset, const int32_t* pos, const float* dx, float* dE,
-              float* dPpos, float* scratch, const float* loss_row, float* loss_out, int B, int S, int d, int V, hipStream_t st,
-              const StepState* ss);
+              float* dPpos, float* scratch, const float* loss_row, float* loss_out, int B, int S, int d, int V, const NormPartials& np,
+              hipStream_t st, const StepState* ss);
 int cast_copy(const float* src, void* dst, int64_t n, int dst_bf16, hipStream_t st);
 
 int adamw(float* theta, const float* grad, float* m, float* v, bf16* lp, int64_t P,

@@ -241,10 +241,10 @@ int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot, float* loss_ou
   GemmDesc dxf = desc(c, w.dlogits, 0, V, wptr(c, w, L.Wout), 1, V, T, d, V, w.dtmp, d, false);
   dxf.ws = w.head_ws; dxf.ws_bytes = w.head_ws_bytes;
   RUN(gemm(dxf, mf, st));
-  // the norms leave their gain-gradient partials; one kernel adds all of them after the last layer
+  // the norms leave their gain-gradient partials, which are added after the last layer
   const int64_t pset = (int64_t)rmsnorm_bwd_blocks(T) * d;
   RUN(rmsnorm_bwd(w.dtmp, w.x[nl], w.rstdf, w.theta + L.gf, nullptr, w.dxa, nl ? w.dy2[nl - 1] : w.dx_lp, c->bf,
-                  nullptr, w.partial + 2 * nl * pset, T, d, ln, st));
+                  w.partial + 2 * nl * pset, T, d, ln, st));
   // The weight gradient of every matrix is X^T dY.  Either each is a product of its own, issued
   // here next to the input gradient that reads the same dY, or (grouped) every layer keeps its four
   // dY until the loop is over and all of them run as one launch.
@@ -258,7 +258,7 @@ int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot, float* loss_ou
     if (each) RUN(gemm(desc_dw(c, w, w.b[l], d, w.dy1[l], ff, d, ff, T, w.grad + L.W1[l]), mf, st));
     RUN(gemm(desc(c, w.dy1[l], 0, ff, wptr(c, w, L.W1[l]), 1, ff, T, d, ff, w.dtmp, d, false), mf, st));
     RUN(rmsnorm_bwd(w.dtmp, w.xm[l], w.rstd2[l], w.theta + L.g2[l], w.dxa, w.dxb, w.dyo[l], c->bf,
-                    nullptr, w.partial + (2 * l + 1) * pset, T, d, ln, st));
+                    w.partial + (2 * l + 1) * pset, T, d, ln, st));
     // attention block: xm = x + attn(a Wqkv) Wo
     if (each) RUN(gemm(desc_dw(c, w, w.o[l], da, w.dyo[l], d, da, d, T, w.grad + L.Wo[l]), mf, st));
     RUN(gemm(desc(c, w.dyo[l], 0, d, wptr(c, w, L.Wo[l]), 1, d, T, da, d, w.d_o, da, true), mf, st));
@@ -266,16 +266,16 @@ int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot, float* loss_ou
     if (each) RUN(gemm(desc_dw(c, w, w.a[l], d, w.dyqkv[l], 3 * da, d, 3 * da, T, w.grad + L.Wqkv[l]), mf, st));
     RUN(gemm(desc(c, w.dyqkv[l], 0, 3 * da, wptr(c, w, L.Wqkv[l]), 1, 3 * da, T, d, 3 * da, w.dtmp, d, false), mf, st));
     RUN(rmsnorm_bwd(w.dtmp, w.x[l], w.rstd1[l], w.theta + L.g1[l], w.dxb, w.dxa, l ? w.dy2[l - 1] : w.dx_lp, c->bf,
-                    nullptr, w.partial + 2 * l * pset, T, d, ln, st));
+                    w.partial + 2 * l * pset, T, d, ln, st));
   }
   if (c->grouped_dw) RUN(dw_group_launch(w.dw_probs_dev, w.dw_items_dev, w.dw_split_dev, w.dw_plan, w.dw_partial, st));
   if (c->list_dw)
     RUN(c->bf ? gemm_mfma_any_dw_list(w.dw_probs.data(), (int)w.dw_probs.size(), T, st)
               : gemm_mfma_f32_dw_list(w.dw_probs.data(), (int)w.dw_probs.size(), T, st));
-  RUN(rmsnorm_dg_sum(w.partial, w.grad + L.g1[0], T, d, 2 * nl + 1, st));
   // w.dtmp (T x d floats) is free again here: scratch for the embedding gradient's chunk partials
   RUN(embed_bwd(tok, w.sort_offset + (int64_t)slot * (V + 1), w.sort_pos + (int64_t)slot * T, w.dxa,
-                w.grad + L.E, w.grad + L.Ppos, w.dtmp, w.loss_row, loss_out, B, S, d, V, st, ss));
+                w.grad + L.E, w.grad + L.Ppos, w.dtmp, w.loss_row, loss_out, B, S, d, V,
+                NormPartials{w.partial, w.grad + L.g1[0], rmsnorm_bwd_blocks(T), 2 * nl + 1}, st, ss));
   return ALS_OK;
 }
 

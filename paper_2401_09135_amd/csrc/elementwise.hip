@@ -748,9 +748,58 @@ __global__ __launch_bounds__(1024) void embed_sort_lds_kernel(const int32_t* __r
   }
 }
 
+// The same by counting, for small steps: a position's place in the order is the number of (token, position) pairs before its own, and
+// offset[v] the number of tokens below v.  A lane has one of the T + V + 1 questions and the 16 wavefronts of a workgroup share the pairs,
+// read from LDS by all lanes at once; the questions of a step are dealt to as many workgroups as they need, where the sort above is
+// a chain of passes in one.  Between the two by the number of comparisons, one launch at a time in us, sort / counting:
+//   T = 256, V = 256: 9.5 / 3.3    T = 512, V = 1024: 11 / 3.9    T = 2048, V = 4096: 13 / 8.5    T = 1024, V = 32000: 24 / 17
+constexpr int64_t RANK_MAX = 150000000;   // comparisons of all steps of a call
+__global__ __launch_bounds__(1024) void embed_rank_kernel(const int32_t* __restrict__ tok, int B, int S, int V,
+                                                          int32_t* __restrict__ offset, int32_t* __restrict__ pos) {
+  extern __shared__ __attribute__((aligned(16))) unsigned pair[];   // token and position, padded to 64 with the largest value
+  __shared__ int part[16][64];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int T = B * S, Tp = (T + 63) & ~63;
+  const int32_t* tk = tok + (int64_t)blockIdx.y * B * (S + 1);
+  for (int i = tid; i < Tp; i += 1024) {
+    unsigned k = 0xffffffffu;
+    if (i < T) {
+      const int id = tk[i + i / S];   // tokens are [B, S + 1], positions [B, S]
+      k = (unsigned)(id < 0 ? 0 : (id >= V ? V - 1 : id)) << SORT_POS_BITS | (unsigned)i;
+    }
+    pair[i] = k;
+  }
+  __syncthreads();
+  const int question = blockIdx.x * 64 + lane, t = question - (V + 1);   // first the V + 1 offsets, then the T positions
+  const unsigned q = t < 0 ? (unsigned)question << SORT_POS_BITS : t < T ? pair[t] : 0u;
+  int n = 0;
+#pragma unroll 4
+  for (int i = wv * (Tp / 16); i < (wv + 1) * (Tp / 16); i += 4) {
+    const u32x4 k = *reinterpret_cast<const u32x4*>(pair + i);
+    n += (k[0] < q) + (k[1] < q) + (k[2] < q) + (k[3] < q);
+  }
+  part[wv][lane] = n;
+  __syncthreads();
+  if (wv == 0 && t < T) {
+#pragma unroll
+    for (int w = 1; w < 16; w++) n += part[w][lane];
+    if (t < 0) offset[(int64_t)blockIdx.y * (V + 1) + question] = n;
+    else pos[(int64_t)blockIdx.y * T + n] = t;
+  }
+}
+
 int embed_sort(const int32_t* tok, int n_steps, int B, int S, int V, int32_t* offset, int32_t* rank,
                int32_t* pos, hipStream_t st) {
   if (n_steps <= 0) return ALS_OK;
+  {
+    const int64_t T = (int64_t)B * S, questions = T + V + 1;
+    if (T <= SORT_TILE && V <= 1 << 17 && n_steps <= 4096 && T * questions <= RANK_MAX / n_steps) {
+      hipLaunchKernelGGL(embed_rank_kernel, dim3((unsigned)((questions + 63) / 64), n_steps), dim3(1024), (size_t)((T + 63) & ~63) * 4, st, tok,
+                         B, S, V, offset, pos);
+      ALS_CHECK_LAUNCH();
+      return ALS_OK;
+    }
+  }
   int bits = 1;
   while (bits < 31 && (1 << bits) < V) bits++;
   const int npass = (bits + 7) / 8, digit_bits = (bits + npass - 1) / npass;
@@ -785,7 +834,8 @@ int embed_sort(const int32_t* tok, int n_steps, int B, int S, int V, int32_t* of
 // The first pass is bound by latency where the batch is small, so where each token's part goes is read for all 32 positions at
 // once, ahead of the walk (at every change of token it cost up to 32 dependent reads), and the sums over batches and the
 // mean loss, which read the same step's results, are further blocks of the launch instead of launches.
-// T = 512, d = 256: 15.3 + 2.6 + 2.3 us before, 11 now; T = 1024, d = 896: 42 + 5.6 + 4.6, 15 now.
+// T = 512, d = 256: 15.3 + 2.6 + 2.3 us before, 11 now; T = 1024, d = 896: 42 + 5.6 + 4.6, 15 now.  So are the sums of the norms' partials,
+// a launch of 3 to 5 us (13 for 25 norms of d = 896) until then.
 constexpr int EMB_CH = 32;
 #define EMB_MAXD4 4  // float4 slots per lane in the row pass: d <= 1024
 
@@ -831,18 +881,53 @@ __device__ __forceinline__ void mean_rows(const float* __restrict__ v, float* __
   }
 }
 
-// blocks: the chunks, then S positions, then one for the mean loss
+// out[j][c] = sum_b partial[j][b][c] for consecutive sets of partials: 32 columns of one set per block, 32 row groups of 32 threads' columns
+// each adding every 32nd partial (8 independent loads in flight: it is pure load latency), combined in a fixed order.
+__device__ __forceinline__ void sum_partials(const float* __restrict__ partial, float* __restrict__ out, int j, int c0, int nblk, int d) {
+  __shared__ float sh[32][33];
+  partial += (int64_t)j * nblk * d;
+  const int cl = threadIdx.x & 31, c = c0 + cl;
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const int rg = (threadIdx.x >> 5) + 8 * q;
+    float acc = 0.0f;
+    if (c < d)
+      for (int b0 = rg; b0 < nblk; b0 += 32 * 8) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+          const int b = b0 + 32 * u;
+          v[u] = b < nblk ? partial[(int64_t)b * d + c] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; u++) acc += v[u];
+      }
+    sh[rg][cl] = acc;
+  }
+  __syncthreads();
+  if (threadIdx.x < 32 && c < d) {
+    float t = sh[0][cl];
+#pragma unroll
+    for (int r = 1; r < 32; r++) t += sh[r][cl];
+    out[(int64_t)j * d + c] = t;
+  }
+}
+
+// blocks: the chunks, then S positions, then one for the mean loss, then the sums of the gain-gradient partials
 __global__ __launch_bounds__(256) void embed_bwd_chunks_kernel(
     const int32_t* __restrict__ tok, const int32_t* __restrict__ offset, const int32_t* __restrict__ pos,
     const float* __restrict__ dx, float* __restrict__ dE, float* __restrict__ scratch, float* __restrict__ dPpos,
-    const float* __restrict__ loss_row, float* __restrict__ loss_out, int B, int S, int V, int d, int nchunk, const StepState* ss) {
+    const float* __restrict__ loss_row, float* __restrict__ loss_out, int B, int S, int V, int d, int nchunk, NormPartials np,
+    const StepState* ss) {
   if (ss) { tok = ss->tok; offset = ss->offset; pos = ss->pos; loss_out = ss->loss_out; }
   __shared__ int s_pos[EMB_CH], s_tok[EMB_CH], s_dst[EMB_CH];   // s_dst: -1 = dE, else the scratch slot
   const int T = B * S, c = blockIdx.x, i0 = c * EMB_CH, tid = threadIdx.x;
   const int d4 = d / 4;
   if (c >= nchunk) {
-    if (c - nchunk < S) embed_bwd_pos(dx, dPpos, c - nchunk, B, S, d4);
-    else mean_rows(loss_row, loss_out, T);
+    const int e = c - nchunk - S;
+    if (e < 0) embed_bwd_pos(dx, dPpos, e + S, B, S, d4);
+    else if (e == 0) mean_rows(loss_row, loss_out, T);
+    else sum_partials(np.partial, np.dg, (e - 1) / ((d + 31) / 32), (e - 1) % ((d + 31) / 32) * 32, np.nblk, d);
     return;
   }
   const int n = T - i0 < EMB_CH ? T - i0 : EMB_CH;
@@ -922,12 +1007,12 @@ __global__ __launch_bounds__(256) void embed_bwd_rows_kernel(const int32_t* __re
 }
 
 int embed_bwd(const int32_t* tok, const int32_t* offset, const int32_t* pos, const float* dx, float* dE,
-              float* dPpos, float* scratch, const float* loss_row, float* loss_out, int B, int S, int d, int V, hipStream_t st,
-              const StepState* ss) {
+              float* dPpos, float* scratch, const float* loss_row, float* loss_out, int B, int S, int d, int V, const NormPartials& np,
+              hipStream_t st, const StepState* ss) {
   if (d > 256 * EMB_MAXD4 || d % 4) return set_error(ALS_ERR_INVALID, "embed_bwd: d unsupported");
   const int nchunk = (B * S + EMB_CH - 1) / EMB_CH;
-  hipLaunchKernelGGL(embed_bwd_chunks_kernel, dim3(nchunk + S + 1), dim3(256), 0, st, tok, offset, pos, dx, dE, scratch, dPpos,
-                     loss_row, loss_out, B, S, V, d, nchunk, ss);
+  hipLaunchKernelGGL(embed_bwd_chunks_kernel, dim3(nchunk + S + 1 + np.nset * ((d + 31) / 32)), dim3(256), 0, st, tok, offset, pos, dx, dE, scratch, dPpos,
+                     loss_row, loss_out, B, S, V, d, nchunk, np, ss);
   ALS_CHECK_LAUNCH();
   hipLaunchKernelGGL(embed_bwd_rows_kernel, dim3((V + 3) / 4), dim3(256), 0, st, offset, scratch, dE, V, d, ss);
   ALS_CHECK_LAUNCH();
@@ -1031,7 +1116,7 @@ int embed_rmsnorm_fwd(const int32_t* tok, const float* E, const float* Ppos, flo
 // Backward: xhat = x rstd (RMSNorm) or (x - mean x) rstd (LayerNorm) ; dxhat = dy g ;
 // dx = rstd (dxhat - xhat mean(dxhat xhat))  [LayerNorm: also - mean(dxhat)] ;
 // dg = sum_rows dy xhat.  Each block walks rows with a fixed stride and leaves one partial dg
-// row; a second kernel adds the partials in a fixed order.
+// row; embed_bwd adds the partials in a fixed order.
 #define RMS_BWD_MAXD4 4  // per-lane float4 slots: supports d <= 1024
 // One wavefront per row, each row read once into registers; a wave keeps two rows in flight.
 template <typename LT, bool CENTER>
@@ -1123,47 +1208,13 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(
     partial[(int64_t)blockIdx.x * d + c] = smem[c] + smem[d + c] + smem[2 * d + c] + smem[3 * d + c];
 }
 
-// out[j][c] = sum_b partial[j][b][c] for nset consecutive sets of partials (blockIdx.y = j; the
-// outputs are consecutive rows of d floats): 32 columns per block, 32 row groups each adding
-// every 32nd partial (8 independent loads in flight: the kernel is pure load latency), combined
-// in a fixed order.
-__global__ __launch_bounds__(1024) void sum_partials_kernel(const float* __restrict__ partial,
-                                                            float* __restrict__ out, int nblk, int d) {
-  __shared__ float sh[32][33];
-  partial += (int64_t)blockIdx.y * nblk * d;
-  out += (int64_t)blockIdx.y * d;
-  int cl = threadIdx.x & 31, rg = threadIdx.x >> 5;
-  int c = blockIdx.x * 32 + cl;
-  float acc = 0.0f;
-  if (c < d)
-    for (int b0 = rg; b0 < nblk; b0 += 32 * 8) {
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; u++) {
-        int b = b0 + 32 * u;
-        v[u] = b < nblk ? partial[(int64_t)b * d + c] : 0.0f;
-      }
-#pragma unroll
-      for (int u = 0; u < 8; u++) acc += v[u];
-    }
-  sh[rg][cl] = acc;
-  __syncthreads();
-  if (rg == 0 && c < d) {
-    float t = sh[0][cl];
-#pragma unroll
-    for (int r = 1; r < 32; r++) t += sh[r][cl];
-    out[c] = t;
-  }
-}
-
 int rmsnorm_bwd_blocks(int T) {
   int b = (T + 3) / 4;
   return b > 256 ? 256 : b;
 }
 
 int rmsnorm_bwd(const float* dy, const float* x, const float* rstd, const float* g,
-                const float* dx_in, float* dx_out, void* dx_lp, int lp_bf16, float* dg,
-                float* partial, int T, int d, int center, hipStream_t st) {
+                const float* dx_in, float* dx_out, void* dx_lp, int lp_bf16, float* partial, int T, int d, int center, hipStream_t st) {
   if (d > 256 * RMS_BWD_MAXD4 || d % 4) return set_error(ALS_ERR_INVALID, "rmsnorm_bwd: d unsupported");
   int nblk = rmsnorm_bwd_blocks(T);
   size_t sm = (size_t)4 * d * sizeof(float);
@@ -1176,14 +1227,6 @@ int rmsnorm_bwd(const float* dy, const float* x, const float* rstd, const float*
     if (center) ALS_NORM_BWD(float, true); else ALS_NORM_BWD(float, false);
   }
 #undef ALS_NORM_BWD
-  ALS_CHECK_LAUNCH();
-  if (dg) return rmsnorm_dg_sum(partial, dg, T, d, 1, st);
-  return ALS_OK;
-}
-
-int rmsnorm_dg_sum(const float* partial, float* dg, int T, int d, int nset, hipStream_t st) {
-  hipLaunchKernelGGL(sum_partials_kernel, dim3((d + 31) / 32, nset), dim3(1024), 0, st, partial, dg,
-                     rmsnorm_bwd_blocks(T), d);
   ALS_CHECK_LAUNCH();
   return ALS_OK;
 }
