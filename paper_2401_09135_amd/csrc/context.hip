@@ -83,7 +83,10 @@ void carve(als_ctx* c, Carver& cv) {
   c->w.resize(g.n_workers);
   const bool groupable = bf && !(g.flags & 1) && dw_group_supported((int)d, (int)(3 * da), (int)T, d, 3 * da) &&
                   dw_group_supported((int)da, (int)d, (int)T, da, d) && dw_group_supported((int)d, (int)ff, (int)T, d, ff);
-  c->grouped_dw = groupable && !(g.flags & 2);
+  int64_t tiles = gemm_tiles((int)d, (int)V, 256, 256);
+  tiles += g.n_layers * (gemm_tiles((int)d, (int)(3 * da), 256, 256) + gemm_tiles((int)da, (int)d, 256, 256) + 2 * gemm_tiles((int)d, (int)ff, 256, 256));
+  const bool few = groupable && T <= 2048 && tiles <= 128;   // see below
+  c->grouped_dw = groupable && !(g.flags & 2) && !few;
   // Scratch of the output matrix's input gradient: 64 MiB hold the partials of a round of 256 x 256 tiles.  The same with and
   // without the grouped launch, so that the product is split, and rounds, the same way.
   const size_t head_bytes = std::min((size_t)g.n_layers * T * (2 * d + ff + 3 * da) * 2, (size_t)64 << 20);
@@ -92,9 +95,13 @@ void carve(als_ctx* c, Carver& cv) {
   // (600 tokens, d = 320, V = 5003); as one list 107 and 50.  Every layer keeps its four dY for it, and the line is drawn at the
   // memory: 256 MiB more in a worker's arena.  It is no line of speed: near it the list still gains (a round of 12 layers, d = 128, 4096
   // tokens in fp32, 216 MiB: 2880 us, 4190 with a launch per product; 4 layers, d = 320, 8000 tokens in bf16, 175 MiB: 2490 and 3220).
+  // Aligned products of few 256 x 256 tiles and a short K too: grouped, they are split 5 to 8 times along K and their partials are most of
+  // the traffic (2048 tokens, d = 256, 4 layers, V = 4096: 28 us, 18 for the partials' sum and 19 for the output matrix; as a list 41).
+  // Rounds of one worker, grouped / list: 64 tiles, 2048 tokens: 557 / 531; 128, 1024: 506 / 482; 28, 512: 253 / 240; above the line 148, 1024:
+  // 1109 / 1115; 208, 2048: 915 / 921; 64, 8192: 1035 / 1055; 197, 8192: 2232 / 2294.
   {
     const bool aligned = bf && T % 64 == 0 && d % 128 == 0 && (da % 128 == 0 || ff % 128 == 0);
-    c->list_dw = !(g.flags & 3) && !aligned && (int64_t)g.n_layers * T * (2 * d + ff + 3 * da) * (bf ? 2 : 4) <= (int64_t)256 << 20;
+    c->list_dw = !(g.flags & 3) && (!aligned || few) && (int64_t)g.n_layers * T * (2 * d + ff + 3 * da) * (bf ? 2 : 4) <= (int64_t)256 << 20;
   }
   for (Worker& w : c->w) {
     w.theta = cv.f32(P); w.start = cv.f32(P); w.adam_m = cv.f32(P); w.adam_v = cv.f32(P);
@@ -133,7 +140,7 @@ void carve(als_ctx* c, Carver& cv) {
     w.dw_probs_dev = nullptr; w.dw_items_dev = nullptr; w.dw_split_dev = nullptr; w.dw_partial = nullptr;
     w.dw_plan = DwPlan{0, 0, 0, 0.0};
     w.head_ws = w.splitk_ws; w.head_ws_bytes = w.splitk_bytes;
-    if (groupable && !c->grouped_dw) { w.head_ws = (float*)cv.take(head_bytes); w.head_ws_bytes = head_bytes; }
+    if (groupable && !c->grouped_dw && !c->list_dw) { w.head_ws = (float*)cv.take(head_bytes); w.head_ws_bytes = head_bytes; }
     w.dw_probs.clear();
     if (c->grouped_dw || c->list_dw)
       for (int l = 0; l < L; l++) {
@@ -154,11 +161,10 @@ void carve(als_ctx* c, Carver& cv) {
         add(w.gl[l], ff, w.dy2[l], d, c->L.W2[l]);
       }
     if (c->list_dw) add(w.xf, d, w.dlogits, V, c->L.Wout);
+    // The input gradient of the output matrix runs before anything is written to these: until then they are its
+    // split-K scratch, one block from the first to the last.
+    if (groupable && (c->grouped_dw || c->list_dw)) { w.head_ws = (float*)w.dy2[0]; w.head_ws_bytes = head_bytes; }
     if (c->grouped_dw) {
-      // The input gradient of the output matrix runs before anything is written to these: until then they are its
-      // split-K scratch, one block from the first to the last.
-      w.head_ws = (float*)w.dy2[0];
-      w.head_ws_bytes = head_bytes;
       w.dw_items.resize(dw_plan_max_items(n_tiles));
       w.dw_split.resize(dw_plan_max_split(n_tiles) + 1);
       w.dw_plan = dw_group_plan(w.dw_probs.data(), (int)w.dw_probs.size(), (int)T, w.dw_items.data(), w.dw_split.data());

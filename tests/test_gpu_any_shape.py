@@ -156,6 +156,15 @@ def test_token_order_in_lds(V, B, S):
     test_token_order_of_the_embedding_gradient(V, B, S)
 
 
+# Small steps order their positions by counting: whole and partial groups of 64 positions and questions, the largest vocabulary, the most
+# comparisons; and the sorts at the sizes that are left to them: just more comparisons (one bit, one digit and two, the largest vocabulary in
+# LDS), a larger vocabulary (three digits), more of both.
+@pytest.mark.parametrize("V,B,S", [(2, 1, 63), (63, 1, 64), (64, 5, 13), (131072, 1, 65), (13, 12, 1020),
+                                   (14, 12, 1020), (256, 12, 1020), (257, 12, 1020), (32767, 5, 820), (32768, 5, 820), (131073, 1, 65), (65537, 4, 600)])
+def test_token_order_by_counting_and_sorting(V, B, S):
+    test_token_order_of_the_embedding_gradient(V, B, S)
+
+
 @pytest.mark.parametrize("V", [64, 65, 71, 2048, 2049, 8192, 8193, 8200, 32767, 32768, 32769])   # whole and partial groups of 8; 256 and 1024 threads; three passes
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_cross_entropy_of_any_vocabulary(V, dtype):
@@ -180,6 +189,7 @@ def test_cross_entropy_of_any_vocabulary(V, dtype):
                                       ("bf16", dict(L=1, d=64, ff=192, V=131, S=31, B=3)),            # 32 x 32
                                       ("bf16", dict(L=1, d=256, h=4, ff=640, V=333, S=65, B=2)),      # 64 x 64
                                       ("bf16", dict(L=3, d=320, h=5, ff=1280, V=133, S=33, B=1)),     # 128 x 64
+                                      ("bf16", dict(L=2, d=384, h=6, ff=1536, V=2048, S=64, B=3)),    # aligned, 92 tiles of 256 x 256
                                       ("bf16", dict(L=2, d=512, h=8, ff=2048, V=700, S=17, B=1))])    # 128 x 128
 def test_weight_gradients_as_one_list(dtype, kw):
     """Flag bit 1 keeps one launch per product: the same operands, sums in the order of another tile at most, so fp32 gradients
