@@ -190,13 +190,19 @@ struct AdamArgs {
   float lr, beta1, beta2, eps, wd, bc1, bc2;
 };
 // What changes from one step of a worker to the next, in device memory: a step that is replayed as a graph has the same kernel
-// arguments every time.  The kernels that need any of it take a pointer to it, and with a null pointer their own arguments.
+// arguments every time.  The kernels that need any of it take a pointer to it, and with a null pointer their own arguments.  It holds
+// up to ALS_STATE_STEPS steps in a row; the first kernel of a step sets its AdamW scalars, the last one goes on to the next step.
+#define ALS_STATE_STEPS 64
 struct StepState {
-  const int32_t* tok;      // [B, S + 1]
-  const int32_t* offset;   // what embed_sort made of them
+  const int32_t* tok;      // [steps][B, S + 1]
+  const int32_t* offset;   // what embed_sort made of them, [steps][V + 1] and [steps][B S]
   const int32_t* pos;
-  float* loss_out;
-  AdamArgs adam;
+  float* loss_out;         // [steps]
+  int64_t tok_step;        // elements of a step
+  int offset_step, pos_step;
+  int step;                // the one that runs
+  AdamArgs adam;           // its own
+  struct { float lr, bc1, bc2; } scalars[ALS_STATE_STEPS];
 };
 int set_step_state(StepState* ss, const StepState& v, hipStream_t st);
 // center = 0: RMSNorm ; 1: LayerNorm with gain and no bias
@@ -204,7 +210,7 @@ int rmsnorm_fwd(const float* x, const float* g, void* y, float* rstd, int T, int
                 int out_bf16, int center, hipStream_t st);
 // the same for the rows E[tok] + Ppos, which are also written to x
 int embed_rmsnorm_fwd(const int32_t* tok, const float* E, const float* Ppos, float* x, const float* g, void* y, float* rstd, int B,
-                      int S, int d, int V, float eps, int out_bf16, int center, hipStream_t st, const StepState* ss);
+                      int S, int d, int V, float eps, int out_bf16, int center, hipStream_t st, StepState* ss);
 // dx_out = (dx_in ? dx_in : 0) + rmsnorm_backward(dy); optional low-precision copy of dx_out;
 // the gain gradient, sum over rows of dy * xhat, is left in partial[nblk][d], nblk = rmsnorm_bwd_blocks(T), for embed_bwd to add.
 int rmsnorm_bwd_blocks(int T);
@@ -215,8 +221,9 @@ int cross_entropy(const void* logits, const int32_t* tok, float* loss_row, void*
                   hipStream_t st, const StepState* ss);
 // Orders each step's input positions by token id (see elementwise.hip; rank is scratch); offset is
 // [n_steps][V+1], rank and pos are [n_steps][B*S].
+// first (with its contents v): the state that the replayed steps begin with
 int embed_sort(const int32_t* tok, int n_steps, int B, int S, int V, int32_t* offset, int32_t* rank,
-               int32_t* pos, hipStream_t st);
+               int32_t* pos, hipStream_t st, StepState* first = nullptr, const StepState* v = nullptr);
 // nset consecutive sets of [nblk][d] partials and the gain gradients that they add up to, nset consecutive rows of d
 struct NormPartials { const float* partial; float* dg; int nblk, nset; };
 // dE, dPpos, the mean loss and the norms' gain gradients; scratch: 2 * ceil(B*S / 32) * d floats (partial rows of position lists that cross 32-position chunks)
@@ -226,7 +233,7 @@ int embed_bwd(const int32_t* tok, const int32_t* offset, const int32_t* pos, con
 int cast_copy(const float* src, void* dst, int64_t n, int dst_bf16, hipStream_t st);
 
 int adamw(float* theta, const float* grad, float* m, float* v, bf16* lp, int64_t P,
-          int64_t P_decay, const AdamArgs& a, hipStream_t st, const StepState* ss = nullptr);
+          int64_t P_decay, const AdamArgs& a, hipStream_t st, StepState* ss = nullptr);
 
 #define ALS_DN_MAX_GROUP 16
 struct DnGroup {

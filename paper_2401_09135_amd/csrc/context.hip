@@ -39,7 +39,7 @@ struct Worker {
   int64_t t_restart;  // server event count when this replica last (re)started
   hipStream_t stream; hipEvent_t done_ev, ready_ev;
   hipStream_t done_st, ready_st;   // where these were last recorded
-  StepState* state;            // of the step that runs next, in the arena
+  StepState* state;            // of the steps that are replayed, in the arena
   hipGraphExec_t step_graph;   // one local step with its arguments in *state; null: launched kernel by kernel
 };
 
@@ -202,7 +202,7 @@ inline const void* wptr(const als_ctx* c, const Worker& w, int64_t off) {
 }
 
 // ss (forward, backward): take the tokens and what depends on them from there
-int forward(als_ctx* c, Worker& w, const int32_t* tok, hipStream_t st, const StepState* ss) {
+int forward(als_ctx* c, Worker& w, const int32_t* tok, hipStream_t st, StepState* ss) {
   const als_config& g = c->cfg;
   const Layout& L = c->L;
   int T = c->T, d = g.d_model, ff = g.d_ff, V = g.vocab, B = g.batch, S = g.seq_len, h = g.n_heads;
@@ -234,7 +234,7 @@ int forward(als_ctx* c, Worker& w, const int32_t* tok, hipStream_t st, const Ste
 }
 
 // also writes the mean of the losses that forward() left per row
-int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot, float* loss_out, hipStream_t st, const StepState* ss) {
+int backward(als_ctx* c, Worker& w, const int32_t* tok, int slot, float* loss_out, hipStream_t st, StepState* ss) {
   const als_config& g = c->cfg;
   const Layout& L = c->L;
   int T = c->T, d = g.d_model, ff = g.d_ff, V = g.vocab, B = g.batch, S = g.seq_len, h = g.n_heads;
@@ -439,7 +439,6 @@ extern "C" int als_worker_local_steps(als_ctx* ctx, int worker, int n_steps, con
   Worker& w = ctx->w[worker];
   RUN(wait_event(w.stream, w.ready_ev, w.ready_st));
   int64_t per = (int64_t)g.batch * (g.seq_len + 1);
-  RUN(embed_sort(tokens, n_steps, g.batch, g.seq_len, g.vocab, w.sort_offset, w.sort_rank, w.sort_pos, w.stream));
   // The graph is left out where a call has to see the launches: under the measurement hooks of the GEMM kernels and while the
   // caller captures this stream.
   bool replay = w.step_graph && !gemm_hooks_active();
@@ -447,26 +446,46 @@ extern "C" int als_worker_local_steps(als_ctx* ctx, int worker, int n_steps, con
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     replay = hipStreamIsCapturing(w.stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
   }
-  for (int s = 0; s < n_steps; s++) {
-    const int32_t* tok = tokens + (int64_t)s * per;
-    if (!replay) {
-      RUN(forward(ctx, w, tok, w.stream, nullptr));
-      RUN(backward(ctx, w, tok, s, w.losses_dev + s, w.stream, nullptr));
-    }
-    w.adam_n += 1;
+  auto adam_args = [&](int s, int64_t n) {   // of step s, the worker's n-th
     AdamArgs a;
     a.lr = lr_host[s];
     a.beta1 = (float)g.adam_beta1; a.beta2 = (float)g.adam_beta2; a.eps = (float)g.adam_eps;
     a.wd = (float)g.weight_decay;
-    a.bc1 = (float)(1.0 - pow(g.adam_beta1, (double)w.adam_n));
-    a.bc2 = (float)(1.0 - pow(g.adam_beta2, (double)w.adam_n));
-    if (replay) {
-      RUN(set_step_state(w.state, StepState{tok, w.sort_offset + (int64_t)s * (g.vocab + 1), w.sort_pos + (int64_t)s * ctx->T,
-                                            w.losses_dev + s, a}, w.stream));
-      ALS_HIP(hipGraphLaunch(w.step_graph, w.stream));
-    } else {
-      RUN(adamw(w.theta, w.grad, w.adam_m, w.adam_v, w.lp, ctx->L.P, ctx->L.P_decay, a, w.stream));
+    a.bc1 = (float)(1.0 - pow(g.adam_beta1, (double)n));
+    a.bc2 = (float)(1.0 - pow(g.adam_beta2, (double)n));
+    return a;
+  };
+  StepState state;
+  auto state_from = [&](int s) {   // of the steps from s on
+    memset(&state, 0, sizeof state);
+    state.tok = tokens + (int64_t)s * per;
+    state.offset = w.sort_offset + (int64_t)s * (g.vocab + 1);
+    state.pos = w.sort_pos + (int64_t)s * ctx->T;
+    state.loss_out = w.losses_dev + s;
+    state.tok_step = per; state.offset_step = g.vocab + 1; state.pos_step = ctx->T;
+    for (int i = 0; i < ALS_STATE_STEPS && s + i < n_steps; i++) {
+      state.adam = adam_args(s + i, w.adam_n + 1 + i);
+      state.scalars[i].lr = state.adam.lr; state.scalars[i].bc1 = state.adam.bc1; state.scalars[i].bc2 = state.adam.bc2;
     }
+  };
+  if (replay && n_steps) state_from(0);
+  RUN(embed_sort(tokens, n_steps, g.batch, g.seq_len, g.vocab, w.sort_offset, w.sort_rank, w.sort_pos, w.stream,
+                 replay ? w.state : nullptr, &state));
+  for (int s = 0; s < n_steps; s++) {
+    if (replay) {
+      if (s && s % ALS_STATE_STEPS == 0) {
+        state_from(s);
+        RUN(set_step_state(w.state, state, w.stream));
+      }
+      ALS_HIP(hipGraphLaunch(w.step_graph, w.stream));
+      w.adam_n += 1;
+      continue;
+    }
+    const int32_t* tok = tokens + (int64_t)s * per;
+    RUN(forward(ctx, w, tok, w.stream, nullptr));
+    RUN(backward(ctx, w, tok, s, w.losses_dev + s, w.stream, nullptr));
+    w.adam_n += 1;
+    RUN(adamw(w.theta, w.grad, w.adam_m, w.adam_v, w.lp, ctx->L.P, ctx->L.P_decay, adam_args(s, w.adam_n), w.stream));
   }
   w.last_n = n_steps;
   ALS_HIP(hipEventRecord(w.done_ev, w.stream));

@@ -71,8 +71,9 @@ __global__ __launch_bounds__(256) void adamw_kernel(float* __restrict__ theta,
                                                     const float* __restrict__ grad,
                                                     float* __restrict__ m, float* __restrict__ v,
                                                     bf16* __restrict__ lp, int64_t n4,
-                                                    int64_t decay4, AdamArgs a, const StepState* ss) {
+                                                    int64_t decay4, AdamArgs a, StepState* ss, bool last) {
   if (ss) a = ss->adam;
+  if (ss && last && blockIdx.x == 0 && threadIdx.x == 0) ss->step++;   // nothing in this kernel reads it
   const int64_t stride = (int64_t)gridDim.x * 256 * STREAM_U;
   for (int64_t i0 = (int64_t)blockIdx.x * 256 * STREAM_U + threadIdx.x; i0 < n4; i0 += stride) {
     f32x4 th[STREAM_U], g[STREAM_U], mm[STREAM_U], vv[STREAM_U];
@@ -100,8 +101,9 @@ __global__ __launch_bounds__(256) void adamw_kernel(float* __restrict__ theta,
 }
 
 __global__ void adamw_tail_kernel(float* theta, const float* grad, float* m, float* v, bf16* lp,
-                                  int64_t begin, int64_t P, int64_t P_decay, AdamArgs a, const StepState* ss) {
+                                  int64_t begin, int64_t P, int64_t P_decay, AdamArgs a, StepState* ss) {
   if (ss) a = ss->adam;
+  if (ss && blockIdx.x == 0 && threadIdx.x == 0) ss->step++;
   int64_t i = begin + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= P) return;
   float th = theta[i], mm = m[i], vv = v[i];
@@ -111,7 +113,7 @@ __global__ void adamw_tail_kernel(float* theta, const float* grad, float* m, flo
 }
 
 int adamw(float* theta, const float* grad, float* m, float* v, bf16* lp, int64_t P,
-          int64_t P_decay, const AdamArgs& a, hipStream_t st, const StepState* ss) {
+          int64_t P_decay, const AdamArgs& a, hipStream_t st, StepState* ss) {
   if (P <= 0) return ALS_OK;
   // the vector body covers whole float4 groups that do not straddle the decay boundary
   int64_t n4 = 0, decay4 = 0;
@@ -121,7 +123,7 @@ int adamw(float* theta, const float* grad, float* m, float* v, bf16* lp, int64_t
   }
   if (n4 > 0) {
     hipLaunchKernelGGL(adamw_kernel, dim3(stream_blocks(n4, STREAM_U)), dim3(256), 0, st, theta, grad, m, v,
-                       lp, n4, decay4, a, ss);
+                       lp, n4, decay4, a, ss, n4 * 4 == P);
     ALS_CHECK_LAUNCH();
   }
   int64_t begin = n4 * 4;
@@ -755,7 +757,12 @@ __global__ __launch_bounds__(1024) void embed_sort_lds_kernel(const int32_t* __r
 //   T = 256, V = 256: 9.5 / 3.3    T = 512, V = 1024: 11 / 3.9    T = 2048, V = 4096: 13 / 8.5    T = 1024, V = 32000: 24 / 17
 constexpr int64_t RANK_MAX = 150000000;   // comparisons of all steps of a call
 __global__ __launch_bounds__(1024) void embed_rank_kernel(const int32_t* __restrict__ tok, int B, int S, int V,
-                                                          int32_t* __restrict__ offset, int32_t* __restrict__ pos) {
+                                                          int32_t* __restrict__ offset, int32_t* __restrict__ pos, StepState* first,
+                                                          StepState state) {
+  if (first && blockIdx.x == 0 && blockIdx.y == 0) {   // word by word: a copy by one thread is a chain of 110 stores
+    const unsigned* src = reinterpret_cast<const unsigned*>(&state);
+    for (unsigned i = threadIdx.x; i < sizeof(StepState) / 4; i += 1024) reinterpret_cast<unsigned*>(first)[i] = src[i];
+  }
   extern __shared__ __attribute__((aligned(16))) unsigned pair[];   // token and position, padded to 64 with the largest value
   __shared__ int part[16][64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -789,16 +796,20 @@ __global__ __launch_bounds__(1024) void embed_rank_kernel(const int32_t* __restr
 }
 
 int embed_sort(const int32_t* tok, int n_steps, int B, int S, int V, int32_t* offset, int32_t* rank,
-               int32_t* pos, hipStream_t st) {
+               int32_t* pos, hipStream_t st, StepState* first, const StepState* v) {
   if (n_steps <= 0) return ALS_OK;
   {
     const int64_t T = (int64_t)B * S, questions = T + V + 1;
     if (T <= SORT_TILE && V <= 1 << 17 && n_steps <= 4096 && T * questions <= RANK_MAX / n_steps) {
       hipLaunchKernelGGL(embed_rank_kernel, dim3((unsigned)((questions + 63) / 64), n_steps), dim3(1024), (size_t)((T + 63) & ~63) * 4, st, tok,
-                         B, S, V, offset, pos);
+                         B, S, V, offset, pos, first, first ? *v : StepState{});
       ALS_CHECK_LAUNCH();
       return ALS_OK;
     }
+  }
+  if (first) {
+    const int rc = set_step_state(first, *v, st);
+    if (rc) return rc;
   }
   int bits = 1;
   while (bits < 31 && (1 << bits) < V) bits++;
@@ -913,21 +924,31 @@ __device__ __forceinline__ void sum_partials(const float* __restrict__ partial, 
   }
 }
 
-// blocks: the chunks, then S positions, then one for the mean loss, then the sums of the gain-gradient partials
+// What else reads the same step's results, one block each: S positions, the mean loss, the sums of the gain-gradient partials.
+__device__ __forceinline__ void embed_bwd_rest(int e, const float* dx, float* dPpos, const float* loss_row, float* loss_out, int B, int S, int d,
+                                               const NormPartials& np) {
+  const int cols = (d + 31) / 32;
+  if (e < S) embed_bwd_pos(dx, dPpos, e, B, S, d / 4);
+  else if (e == S) mean_rows(loss_row, loss_out, B * S);
+  else sum_partials(np.partial, np.dg, (e - S - 1) / cols, (e - S - 1) % cols * 32, np.nblk, d);
+}
+
+// blocks: the chunks, then the rest
 __global__ __launch_bounds__(256) void embed_bwd_chunks_kernel(
     const int32_t* __restrict__ tok, const int32_t* __restrict__ offset, const int32_t* __restrict__ pos,
     const float* __restrict__ dx, float* __restrict__ dE, float* __restrict__ scratch, float* __restrict__ dPpos,
     const float* __restrict__ loss_row, float* __restrict__ loss_out, int B, int S, int V, int d, int nchunk, NormPartials np,
     const StepState* ss) {
-  if (ss) { tok = ss->tok; offset = ss->offset; pos = ss->pos; loss_out = ss->loss_out; }
+  if (ss) {
+    const int step = ss->step;
+    tok = ss->tok + step * ss->tok_step; offset = ss->offset + (int64_t)step * ss->offset_step;
+    pos = ss->pos + (int64_t)step * ss->pos_step; loss_out = ss->loss_out + step;
+  }
   __shared__ int s_pos[EMB_CH], s_tok[EMB_CH], s_dst[EMB_CH];   // s_dst: -1 = dE, else the scratch slot
   const int T = B * S, c = blockIdx.x, i0 = c * EMB_CH, tid = threadIdx.x;
   const int d4 = d / 4;
   if (c >= nchunk) {
-    const int e = c - nchunk - S;
-    if (e < 0) embed_bwd_pos(dx, dPpos, e + S, B, S, d4);
-    else if (e == 0) mean_rows(loss_row, loss_out, T);
-    else sum_partials(np.partial, np.dg, (e - 1) / ((d + 31) / 32), (e - 1) % ((d + 31) / 32) * 32, np.nblk, d);
+    embed_bwd_rest(c - nchunk, dx, dPpos, loss_row, loss_out, B, S, d, np);
     return;
   }
   const int n = T - i0 < EMB_CH ? T - i0 : EMB_CH;
@@ -978,7 +999,7 @@ __global__ __launch_bounds__(256) void embed_bwd_chunks_kernel(
 __global__ __launch_bounds__(256) void embed_bwd_rows_kernel(const int32_t* __restrict__ offset,
                                                              const float* __restrict__ scratch,
                                                              float* __restrict__ dE, int V, int d, const StepState* ss) {
-  if (ss) offset = ss->offset;
+  if (ss) offset = ss->offset + (int64_t)ss->step * ss->offset_step;
   const int lane = threadIdx.x & 63;
   const int v = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (v >= V) return;
@@ -1006,12 +1027,58 @@ __global__ __launch_bounds__(256) void embed_bwd_rows_kernel(const int32_t* __re
   }
 }
 
+// Small steps in one launch: a workgroup per vocabulary row, whose four wavefronts share its list, every fourth position each, and add
+// their sums in order.  T = 512, V = 1024, d = 256: 10.2 + 4.8 us in two launches, 10.6 in one; at T = 1024, V = 2000 (10.4 + 4.8 and 17.5) and
+// T = 2048, V = 4096 (10.5 + 4.9 and 30) the most frequent token's list, a sixth of the positions of a Zipf(1.1) text, is too long for one workgroup.
+__global__ __launch_bounds__(256) void embed_bwd_lists_kernel(const int32_t* __restrict__ offset, const int32_t* __restrict__ pos,
+                                                              const float* __restrict__ dx, float* __restrict__ dE, float* __restrict__ dPpos,
+                                                              const float* __restrict__ loss_row, float* __restrict__ loss_out, int B, int S, int V,
+                                                              int d, NormPartials np, const StepState* ss) {
+  if (ss) {
+    const int step = ss->step;
+    offset = ss->offset + (int64_t)step * ss->offset_step; pos = ss->pos + (int64_t)step * ss->pos_step; loss_out = ss->loss_out + step;
+  }
+  __shared__ f32x4 sums[3][64];
+  const int v = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6, d4 = d / 4;
+  if (v >= V) {
+    embed_bwd_rest(v - V, dx, dPpos, loss_row, loss_out, B, S, d, np);
+    return;
+  }
+  const int beg = offset[v], end = offset[v + 1];
+  const f32x4* dx4 = reinterpret_cast<const f32x4*>(dx);
+  for (int c0 = 0; c0 < d4; c0 += 64) {
+    const int col = c0 + lane;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int j0 = beg + w; j0 < end; j0 += 32) {   // 8 rows in flight
+      f32x4 x[8];
+#pragma unroll
+      for (int u = 0; u < 8; u++) x[u] = j0 + 4 * u < end && col < d4 ? dx4[(int64_t)pos[j0 + 4 * u] * d4 + col] : (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int u = 0; u < 8; u++) acc += x[u];
+    }
+    if (end - beg > 1) {   // workgroup-uniform
+      if (c0) __syncthreads();
+      if (w) sums[w - 1][lane] = acc;
+      __syncthreads();
+      if (w == 0) acc = acc + sums[0][lane] + sums[1][lane] + sums[2][lane];
+    }
+    if (w == 0 && col < d4) reinterpret_cast<f32x4*>(dE)[(int64_t)v * d4 + col] = acc;
+  }
+}
+
 int embed_bwd(const int32_t* tok, const int32_t* offset, const int32_t* pos, const float* dx, float* dE,
               float* dPpos, float* scratch, const float* loss_row, float* loss_out, int B, int S, int d, int V, const NormPartials& np,
               hipStream_t st, const StepState* ss) {
   if (d > 256 * EMB_MAXD4 || d % 4) return set_error(ALS_ERR_INVALID, "embed_bwd: d unsupported");
+  const int rest = S + 1 + np.nset * ((d + 31) / 32);
+  if (B * S <= 512 && V <= 8192) {
+    hipLaunchKernelGGL(embed_bwd_lists_kernel, dim3(V + rest), dim3(256), 0, st, offset, pos, dx, dE, dPpos, loss_row, loss_out, B, S, V, d, np,
+                       ss);
+    ALS_CHECK_LAUNCH();
+    return ALS_OK;
+  }
   const int nchunk = (B * S + EMB_CH - 1) / EMB_CH;
-  hipLaunchKernelGGL(embed_bwd_chunks_kernel, dim3(nchunk + S + 1 + np.nset * ((d + 31) / 32)), dim3(256), 0, st, tok, offset, pos, dx, dE, scratch, dPpos,
+  hipLaunchKernelGGL(embed_bwd_chunks_kernel, dim3(nchunk + rest), dim3(256), 0, st, tok, offset, pos, dx, dE, scratch, dPpos,
                      loss_row, loss_out, B, S, V, d, nchunk, np, ss);
   ALS_CHECK_LAUNCH();
   hipLaunchKernelGGL(embed_bwd_rows_kernel, dim3((V + 3) / 4), dim3(256), 0, st, offset, scratch, dE, V, d, ss);
@@ -1027,7 +1094,7 @@ int embed_bwd(const int32_t* tok, const int32_t* offset, const int32_t* pos, con
 // ------------------------------------------------------------------------------------------
 // EMBED: the rows are the embeddings, x[b*S+s,:] = E[tok[b,s],:] + Ppos[s,:] (tokens are [B,S+1]; inputs are s < S), formed and
 // written here on the way into the first norm: one launch and one pass over x less than on their own.
-struct EmbedArgs { const int32_t* tok; const float* E; const float* Ppos; float* x; int S, V; const StepState* ss; };
+struct EmbedArgs { const int32_t* tok; const float* E; const float* Ppos; float* x; int S, V; StepState* ss; };
 #define RMS_MAXD4 4  // float4 slots per lane: d <= 1024
 template <typename OT, bool CENTER, bool EMBED>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const float* __restrict__ x, EmbedArgs em,
@@ -1043,7 +1110,16 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const float* __restric
   const float4* pr = nullptr;
   if (EMBED) {
     const int b = row / em.S, s = row % em.S;
-    const int32_t* tok = em.ss ? em.ss->tok : em.tok;
+    const int32_t* tok = em.tok;
+    if (em.ss) {
+      const int step = em.ss->step;
+      tok = em.ss->tok + step * em.ss->tok_step;
+      if (blockIdx.x == 0 && threadIdx.x == 0) {
+        em.ss->adam.lr = em.ss->scalars[step].lr;
+        em.ss->adam.bc1 = em.ss->scalars[step].bc1;
+        em.ss->adam.bc2 = em.ss->scalars[step].bc2;
+      }
+    }
     int id = tok[(int64_t)b * (em.S + 1) + s];
     id = id < 0 ? 0 : (id >= em.V ? em.V - 1 : id);  // out-of-range ids are clamped, never dereferenced
     xr = reinterpret_cast<const float4*>(em.E + (int64_t)id * d);
@@ -1109,7 +1185,7 @@ int rmsnorm_fwd(const float* x, const float* g, void* y, float* rstd, int T, int
 }
 
 int embed_rmsnorm_fwd(const int32_t* tok, const float* E, const float* Ppos, float* x, const float* g, void* y, float* rstd, int B,
-                      int S, int d, int V, float eps, int out_bf16, int center, hipStream_t st, const StepState* ss) {
+                      int S, int d, int V, float eps, int out_bf16, int center, hipStream_t st, StepState* ss) {
   return norm_fwd<true>(nullptr, EmbedArgs{tok, E, Ppos, x, S, V, ss}, g, y, rstd, B * S, d, eps, out_bf16, center, st);
 }
 
@@ -1252,7 +1328,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void cross_entropy_kernel(const T* logits, const int32_t* __restrict__ tok,
                                                             float* __restrict__ loss_row, T* dl, int S, int V,
                                                             float invT, const StepState* ss) {
-  if (ss) tok = ss->tok;
+  if (ss) tok = ss->tok + ss->step * ss->tok_step;
   __shared__ float sh[8];
   int t = blockIdx.x;
   int b = t / S, s = t % S;
@@ -1285,7 +1361,7 @@ template <int BS, bool EDGE>
 __global__ __launch_bounds__(BS) void cross_entropy_reg_kernel(const bf16* logits, const int32_t* __restrict__ tok,
                                                                float* __restrict__ loss_row, bf16* dl, int S, int V,
                                                                float invT, const StepState* ss) {
-  if (ss) tok = ss->tok;
+  if (ss) tok = ss->tok + ss->step * ss->tok_step;
   __shared__ float sh[16];
   int t = blockIdx.x;
   int b = t / S, s = t % S;
