@@ -214,17 +214,26 @@ int attention_bwd_generic(const void* qkv, const void* o, const void* d_o, const
   return ALS_OK;
 }
 
+// Heads of 64 with S a multiple of 128 have kernels of their own in bf16.  Their backward pass is two launches; up to 64 blocks of 64 rows it
+// takes longer than the one of attention_mfma_any.hip, which also keeps the probabilities in fp32 (forward + backward in us, S a multiple of 128 / any
+// S): B 4, S 128, 4 heads: 4.8 + 11.4 / 4.5 + 5.7; B 3, S 256, 5 heads: 6.0 + 14.3 / 5.9 + 10.8; B 2, S 512, 4 heads: 7.2 + 18.6 / 8.1 + 16.9;
+// B 4, S 256, 8 heads (128 blocks): 6.1 + 14.5 / 8.0 + 17.7.
+static bool wide_pays(int B, int S, int h) { return S > 256 || (int64_t)B * h * (S / 64) > 64; }
+
 int attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int h, int dh, int bf, bool allow_mfma, hipStream_t st) {
-  if (allow_mfma && attention_mfma_supported(S, dh, bf)) return attention_fwd_mfma(qkv, o, lse, B, S, h, dh, st);
-  if (allow_mfma && attention_mfma_any_supported(qkv, o, qkv, o, B, S, h, dh))
+  const bool any = attention_mfma_any_supported(qkv, o, qkv, o, B, S, h, dh);
+  if (allow_mfma && attention_mfma_supported(S, dh, bf) && (wide_pays(B, S, h) || !any)) return attention_fwd_mfma(qkv, o, lse, B, S, h, dh, st);
+  if (allow_mfma && any)
     return bf ? attention_fwd_mfma_any(qkv, o, lse, B, S, h, dh, st) : attention_fwd_mfma_f32(qkv, o, lse, B, S, h, dh, st);
   return attention_fwd_generic(qkv, o, lse, B, S, h, dh, bf, st);
 }
 
 int attention_bwd(const void* qkv, const void* o, const void* d_o, const float* lse, float* dscratch, void* dqkv, int B, int S,
                   int h, int dh, int bf, bool allow_mfma, hipStream_t st) {
-  if (allow_mfma && attention_mfma_supported(S, dh, bf)) return attention_bwd_mfma(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, st);
-  if (allow_mfma && attention_mfma_any_supported(qkv, o, d_o, dqkv, B, S, h, dh))
+  const bool any = attention_mfma_any_supported(qkv, o, d_o, dqkv, B, S, h, dh);
+  if (allow_mfma && attention_mfma_supported(S, dh, bf) && (wide_pays(B, S, h) || !any))
+    return attention_bwd_mfma(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, st);
+  if (allow_mfma && any)
     return bf ? attention_bwd_mfma_any(qkv, o, d_o, lse, dqkv, B, S, h, dh, st)
               : attention_bwd_mfma_f32(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, st);
   return attention_bwd_generic(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, bf, st);

@@ -210,6 +210,15 @@ def test_attention_mfma_sharing_and_order_of_blocks(B, S, h):
     test_attention_mfma(B, S, h)
 
 
+# the last that a step takes with the kernels for any length (64 blocks of 64 rows), and the first with those for heads of 64
+@pytest.mark.parametrize("B,S,h", [(8, 128, 4), (1, 256, 16), (5, 256, 4), (3, 384, 1)])
+def test_step_attention_on_both_sides_of_the_choice(B, S, h):
+    o, ro, lse, rlse, dq, rdq = _attention_case(B, S, h, 64, torch.bfloat16, 0, fwd=A.step_attention_fwd, bwd=A.step_attention_bwd)
+    assert _rel(o, ro) < 1e-2
+    np.testing.assert_allclose(lse, rlse, rtol=1e-4, atol=1e-4)
+    assert _rel(dq, rdq) < 1.5e-2
+
+
 @pytest.mark.parametrize("scale", [3.0, 0.05])
 def test_attention_mfma_score_ranges(scale):
     """Scores with a standard deviation of 9 (the running reference point of the online softmax must
