@@ -396,8 +396,8 @@ extern "C" int als_init(const als_config* cfg, void* arena, size_t arena_bytes, 
   if (rc) return fail(rc);
   // Whether the launches of the workers' steps hold the host longer than the chip.  A launch takes the host 2.4 us, a node of a graph
   // 0.4 to 1.2; of the workers that run side by side each advances by one kernel in about 5 us where the kernels are small.  Where the
-  // chip is the slower side a graph's start costs more than it saves.  Rounds in us, kernel by kernel / as graphs: 4 streams of 32 x 8
-  // tokens, d = 64: 1191 / 647; 4 of 128 x 4, d = 256: 1274 / 922; 2 of 256 x 8, d = 256: 702 / 715; one of 128 x 8, d = 256 in fp32: 445 / 452.
+  // chip is the slower side a graph's start costs more than it saves.  Rounds in us, kernel by kernel / as graphs, when graphs came in: 4 streams
+  // of 32 x 8 tokens, d = 64: 1191 / 647; 4 of 128 x 4, d = 256: 1274 / 922; 2 of 256 x 8, d = 256: 702 / 715; one of 128 x 8, d = 256 in fp32: 445 / 452.
   const int64_t T = c->T, da = (int64_t)cfg->n_heads * head_width(*cfg), d = cfg->d_model;
   const double flops = 6.0 * T * (cfg->n_layers * (4.0 * d * da + 2.0 * d * cfg->d_ff + (double)cfg->seq_len * da) + (double)d * cfg->vocab);
   const int launches = 15 * cfg->n_layers + 12, side_by_side = std::min(cfg->n_workers, n_streams);
@@ -445,6 +445,7 @@ extern "C" int als_worker_local_steps(als_ctx* ctx, int worker, int n_steps, con
   if (replay) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     replay = hipStreamIsCapturing(w.stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    if (!replay) (void)hipGetLastError();   // the launches report what is wrong with the stream, if anything is
   }
   auto adam_args = [&](int s, int64_t n) {   // of step s, the worker's n-th
     AdamArgs a;

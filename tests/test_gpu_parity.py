@@ -513,7 +513,7 @@ def test_steps_replayed_as_graphs_equal_launched_ones(name):
     out = []
     for launched in (False, True):
         cfg = A.Config.from_workload(w)
-        cfg.n_workers, cfg.max_local_steps = 4, 3
+        cfg.n_workers, cfg.max_local_steps = 4, 70
         ctx = A.Context(cfg, theta0, n_streams=4)
         streams = [_stream(w)(i) for i in range(4)]
         seen = []
@@ -521,7 +521,7 @@ def test_steps_replayed_as_graphs_equal_launched_ones(name):
         try:
             for rnd in range(3):
                 for i in range(4):
-                    n = 1 + (i + rnd) % 3
+                    n = 70 if name == "tiny" and rnd == 2 and i == 1 else 1 + (i + rnd) % 3   # more than the 64 that one state holds
                     tok = torch.from_numpy(np.ascontiguousarray(streams[i].take(n))).to("cuda:0")
                     seen.append(ctx.worker_local_steps(i, tok, [1e-3 * (1 + rnd + s) for s in range(n)], want_losses=rnd == 1))
                     busy = busy @ busy * 1e-3
