@@ -67,13 +67,17 @@ static inline int stream_blocks(int64_t n4, int u) {
   return (int)(b < 1 ? 1 : (b > 65536 ? 65536 : b));
 }
 
+// STATE: the scalars from the state of replayed steps (a template: a vector of 0.8 M took 0.1 us of 6 longer with the question in the kernel)
+template <bool STATE>
 __global__ __launch_bounds__(256) void adamw_kernel(float* __restrict__ theta,
                                                     const float* __restrict__ grad,
                                                     float* __restrict__ m, float* __restrict__ v,
                                                     bf16* __restrict__ lp, int64_t n4,
                                                     int64_t decay4, AdamArgs a, StepState* ss, bool last) {
-  if (ss) a = ss->adam;
-  if (ss && last && blockIdx.x == 0 && threadIdx.x == 0) ss->step++;   // nothing in this kernel reads it
+  if (STATE) {
+    a = ss->adam;
+    if (last && blockIdx.x == 0 && threadIdx.x == 0) ss->step++;   // nothing in this kernel reads it
+  }
   const int64_t stride = (int64_t)gridDim.x * 256 * STREAM_U;
   for (int64_t i0 = (int64_t)blockIdx.x * 256 * STREAM_U + threadIdx.x; i0 < n4; i0 += stride) {
     f32x4 th[STREAM_U], g[STREAM_U], mm[STREAM_U], vv[STREAM_U];
@@ -122,8 +126,9 @@ int adamw(float* theta, const float* grad, float* m, float* v, bf16* lp, int64_t
     decay4 = P_decay >= P ? n4 : P_decay / 4;
   }
   if (n4 > 0) {
-    hipLaunchKernelGGL(adamw_kernel, dim3(stream_blocks(n4, STREAM_U)), dim3(256), 0, st, theta, grad, m, v,
-                       lp, n4, decay4, a, ss, n4 * 4 == P);
+    const dim3 grid(stream_blocks(n4, STREAM_U));
+    if (ss) hipLaunchKernelGGL(adamw_kernel<true>, grid, dim3(256), 0, st, theta, grad, m, v, lp, n4, decay4, a, ss, n4 * 4 == P);
+    else hipLaunchKernelGGL(adamw_kernel<false>, grid, dim3(256), 0, st, theta, grad, m, v, lp, n4, decay4, a, ss, false);
     ALS_CHECK_LAUNCH();
   }
   int64_t begin = n4 * 4;
