@@ -39,6 +39,7 @@ constexpr float LN2 = 0.6931471805599453f;
 
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ bf16x8 lds_direct(const char* p) { return *reinterpret_cast<const bf16x8*>(p); }
 __device__ __forceinline__ bf16x8 lds_tr2(const char* lo, const char* hi) {
@@ -555,9 +556,10 @@ __global__ __launch_bounds__(64 * QW * KS, 2) void attn_bwd_dq_kernel(const bf16
 //   S = Q K^T ; dP = dO V^T ; P = exp(S - lse) ; dS = P (dP - D) ;
 //   dV^T += dO^T P ; dK^T += Q^T dS
 // A lane's accumulator holds 16 queries, so that the row statistics would be 32 more values per lane and half, 8 KB of LDS reads
-// beside the 16 KB of the operands.  They enter through the matrix cores instead: one more contraction step whose A operand holds, per
-// query, -lse / scale and -D, each cut into three bf16 parts of 8 significant bits that give it back exactly, and whose B operand is
-// ones where the value's parts stand.
+// beside the 16 KB of the operands.  They enter through the matrix cores instead: one more contraction step each, whose A operand holds, per
+// query, -lse / scale or -D cut into three bf16 parts of 8 significant bits (their sum is the value, to 2^-133 below 2^-110), and whose
+// B operand is ones.  Each has an operand of its own with zeros in the other slots: with both in one, and zeros in B to pick between
+// them, a D that is not finite made 0 x infinity = NaN of the scores, and so of the probabilities and of dV, which does not depend on D.
 // ------------------------------------------------------------------------------------------
 template <int KW, int KS>
 __global__ __launch_bounds__(64 * KW * KS, 2) void attn_bwd_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ d_o,
@@ -580,29 +582,23 @@ __global__ __launch_bounds__(64 * KW * KS, 2) void attn_bwd_dkv_kernel(const bf1
 
   const int t_first = kb0 / 64, n_tiles = S / 64 - t_first, n_iter = (n_tiles + KS - 1) / KS;
   TileFeed<KW> feed(base, dobase, ld, d, lane, kg, smem + ks * (2 * T64));
+  // Tile i of this block's into a stage; the statistics through registers of two wavefronts of each share, which cut one kind each.
   char* stats = smem + 4 * KS * T64 + ks * 1024;
-  float st_l = 0.0f, st_d = 0.0f;
-  // Tile i of this block's into a stage; the statistics through registers of the first wavefront of each share.
+  const float* stat_b = kg ? D_b : lse_b;
+  const float stat_mul = kg ? -1.0f : -inv_scale;
+  float stat = 0.0f;
   auto issue = [&](int i, int stage) {
     i = i < n_tiles ? i : n_tiles - 1;
-    if (kg == 0) { st_l = lse_b[(t_first + i) * 64 + lane]; st_d = D_b[(t_first + i) * 64 + lane]; }
+    if (kg < 2) stat = stat_b[(t_first + i) * 64 + lane];
     feed.issue(t_first + i, stage);
   };
-  auto cut = [](float x, bf16x8& r, int at) {   // three parts of 8 significant bits
-#pragma unroll
-    for (int i = 0; i < 3; i++) {
-      const float part = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, x) & 0xffff0000u);
-      r[at + i] = __builtin_bit_cast(bf16, (unsigned short)(__builtin_bit_cast(unsigned, x) >> 16));
-      x -= part;
-    }
-    r[at + 3] = (bf16)0.0f;
-  };
   auto stats_store = [&](int stage) {
-    if (kg == 0) {
-      bf16x8 r;
-      cut(-st_l * inv_scale, r, 0);
-      cut(-st_d, r, 4);
-      *reinterpret_cast<bf16x8*>(stats + stage * 1024 + lane * 16) = r;
+    if (kg < 2) {   // three parts of 8 significant bits, an infinity has a first part only
+      const float x = stat * stat_mul;
+      const auto top = [](float v) { return __builtin_bit_cast(unsigned, v) & 0xffff0000u; };
+      const auto real = [](unsigned v) { return __builtin_bit_cast(float, v); };
+      const float mid = real(top(x)) == x ? 0.0f : x - real(top(x)), low = mid - real(top(mid));
+      *reinterpret_cast<u32x2*>(stats + stage * 1024 + lane * 16 + kg * 8) = (u32x2){top(x) >> 16 | top(mid), top(low) >> 16};
     }
   };
   issue(ks, 0);
@@ -616,12 +612,8 @@ __global__ __launch_bounds__(64 * KW * KS, 2) void attn_bwd_dkv_kernel(const bf1
       vf[kk] = *reinterpret_cast<const bf16x8*>(row + 2 * d + kk * 16 + hf * 8);
     }
   }
-  bf16x8 one_l, one_d;   // contraction slots 0..2 and 4..6; the upper half of the lanes holds slots 8..15
-#pragma unroll
-  for (int e = 0; e < 8; e++) {
-    one_l[e] = (bf16)(hf == 0 && e < 3 ? 1.0f : 0.0f);
-    one_d[e] = (bf16)(hf == 0 && e >= 4 && e < 7 ? 1.0f : 0.0f);
-  }
+  const s16x4 ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
+  const unsigned lower = hf ? 0u : ~0u;   // the parts are contraction slots 0..2; the upper half of the lanes holds slots 4..7
   int r_off[4], t_off[2][2];
 #pragma unroll
   for (int kk = 0; kk < 4; kk++) r_off[kk] = frag_off(lane, kk);
@@ -640,14 +632,15 @@ __global__ __launch_bounds__(64 * KW * KS, 2) void attn_bwd_dkv_kernel(const bf1
     bf16x8 qT[2][2], gT[2][2];   // [16 queries][32 head dimensions]
     auto scores = [&](int qh) {
       bf16x8 qa[4], ga[4];
-      const bf16x8 sa = lds_direct(St + (qh * 32 + (lane & 31)) * 16);
+      const u32x4 sa = *reinterpret_cast<const u32x4*>(St + (qh * 32 + (lane & 31)) * 16);
+      const s16x4 sl = __builtin_bit_cast(s16x4, (u32x2){sa[0] & lower, sa[1] & lower}), sd = __builtin_bit_cast(s16x4, (u32x2){sa[2] & lower, sa[3] & lower});
 #pragma unroll
       for (int kk = 0; kk < 4; kk++) {
         qa[kk] = lds_direct(Qs + qh * 4096 + r_off[kk]);
         ga[kk] = lds_direct(Gs + qh * 4096 + r_off[kk]);
       }
-      s[qh] = MFMA(sa, one_l, zero16());
-      dp[qh] = MFMA(sa, one_d, zero16());
+      s[qh] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(sl, ones, zero16(), 0, 0, 0);
+      dp[qh] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(sd, ones, zero16(), 0, 0, 0);
 #pragma unroll
       for (int kk = 0; kk < 4; kk++) {
         s[qh] = MFMA(qa[kk], kf[kk], s[qh]);

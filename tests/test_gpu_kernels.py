@@ -219,6 +219,42 @@ def test_step_attention_on_both_sides_of_the_choice(B, S, h):
     assert _rel(dq, rdq) < 1.5e-2
 
 
+def _attention_mfma_run(x, d_o, B, S, h, fwd=A.k_attention_fwd, bwd=A.k_attention_bwd, **kw):
+    d = h * 64
+    o, lse, sc = torch.empty(B * S, d, device=DEV, dtype=torch.bfloat16), torch.empty(B * h * S, device=DEV), torch.empty(B * h * S, device=DEV)
+    g = torch.empty(B * S, 3 * d, device=DEV, dtype=torch.bfloat16)
+    fwd(x, o, lse, B, S, h, 64, **kw)
+    bwd(x, o, d_o, lse, sc, g, B, S, h, 64, **kw)
+    torch.cuda.synchronize()
+    return o.float().cpu(), lse.cpu(), g.float().cpu()
+
+
+# two, four and one wavefront to a block of keys
+@pytest.mark.parametrize("B,S,h", [(1, 384, 2), (2, 1024, 2), (4, 512, 32)])
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_attention_mfma_dv_does_not_depend_on_the_row_dots(B, S, h, bad):
+    """dV = P^T dO.  A row of v that is not finite makes the outputs and D = dO . O of every later query so, and leaves dV the same,
+    bit for bit; a row of dO that is not finite reaches the keys that its query sees (dV: an infinity, not NaN), and no key past its
+    block of 32."""
+    d, row = h * 64, 100
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    x = torch.randn(B * S, 3 * d, device=DEV, generator=gen).bfloat16()
+    d_o = torch.randn(B * S, d, device=DEV, generator=gen).bfloat16()
+    run = lambda x, d_o: _attention_mfma_run(x, d_o, B, S, h, use_mfma=True)
+    _, _, clean = run(x, d_o)
+    xv, dov = x.clone(), d_o.clone()
+    xv[row, 2 * d:] = bad
+    dov[row] = bad
+    o, _, g = run(xv, d_o)
+    assert not torch.isfinite(o[row:S]).any()
+    assert torch.equal(g[:, 2 * d:], clean[:, 2 * d:])
+    _, _, g = run(x, dov)
+    seen = g[:row + 1, 2 * d:]
+    assert torch.isinf(seen).all() if np.isinf(bad) else torch.isnan(seen).all()
+    past = (row // 32 + 1) * 32
+    assert torch.equal(g[past:, d:], clean[past:, d:])
+
+
 @pytest.mark.parametrize("scale", [3.0, 0.05])
 def test_attention_mfma_score_ranges(scale):
     """Scores with a standard deviation of 9 (the running reference point of the online softmax must
