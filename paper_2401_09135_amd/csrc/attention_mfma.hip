@@ -232,6 +232,7 @@ __global__ __launch_bounds__(64 * QW * KS, 2) void attn_fwd_kernel(const bf16* _
 
   f32x16 oacc[2][2] = {{zero16(), zero16()}, {zero16(), zero16()}};
   float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.0f, 0.0f};
+  float neg[2] = {0.0f, 0.0f};   // -m_run in log2 units, 0 while every score seen is -inf (their probabilities are then 0, not NaN)
 
   // One tile of 64 keys.  DIAG: the tile that starts at this wavefront's first query: block A sees its first half up to the
   // diagonal, block B all of the first half and the second up to the diagonal.
@@ -287,27 +288,27 @@ __global__ __launch_bounds__(64 * QW * KS, 2) void attn_fwd_kernel(const bf16* _
     // The reference point m_run only has to keep the exponentials in range, it need not be the
     // exact running maximum: it moves (and the accumulators are rescaled) only when some row's
     // maximum has grown by more than 2^8 in probability units since it was last set.  The first
-    // tile always sets it (m_run = -inf; a tile's first key is visible to every query, so mx is finite).
+    // tile with a score above -inf always sets it (m_run = -inf).
     if (__any((mx[0] - m_run[0]) * scale_log2 > 8.0f || (mx[1] - m_run[1]) * scale_log2 > 8.0f)) {  // wave-uniform
 #pragma unroll
       for (int x = 0; x < 2; x++) {
-        const float m_new = fmaxf(m_run[x], mx[x]);
-        const float alpha = fast_exp2((m_run[x] - m_new) * scale_log2);
+        const float m_new = fmaxf(m_run[x], mx[x]), ref = m_new == -INFINITY ? 0.0f : m_new;
+        const float alpha = fast_exp2((m_run[x] - ref) * scale_log2);
         l_run[x] *= alpha;
 #pragma unroll
         for (int dt = 0; dt < 2; dt++)
 #pragma unroll
           for (int v = 0; v < 16; v++) oacc[x][dt][v] *= alpha;
         m_run[x] = m_new;
+        neg[x] = -ref * scale_log2;
       }
     }
     // the products of one 32 x 32 block run while the probabilities of the next are formed
     auto probs = [&](int x, int kt) {
-      const float neg = -m_run[x] * scale_log2;
       float lsum = 0.0f;
 #pragma unroll
       for (int v = 0; v < 16; v++) {
-        const float p = fast_exp2(fmaf(s[x][kt][v], scale_log2, neg));
+        const float p = fast_exp2(fmaf(s[x][kt][v], scale_log2, neg[x]));
         s[x][kt][v] = p;
         lsum += p;
       }

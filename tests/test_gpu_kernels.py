@@ -255,6 +255,30 @@ def test_attention_mfma_dv_does_not_depend_on_the_row_dots(B, S, h, bad):
     assert torch.equal(g[past:, d:], clean[past:, d:])
 
 
+@pytest.mark.parametrize("B,S,h", [(1, 384, 2), (2, 1024, 2), (4, 512, 32)])
+@pytest.mark.parametrize("far", [64, 0])
+def test_attention_mfma_scores_of_minus_infinity(B, S, h, far):
+    """Finite operands whose products overflow: in the first head every key of sample 0 from `far` on (0: of its first two tiles) scores
+    -inf against every query.  Such a key has probability 0 wherever a query sees another one, also where a wavefront that shares
+    the keys sees no other: outputs and gradients are those of the vector kernels."""
+    d = h * 64
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    x = torch.randn(B * S, 3 * d, device=DEV, generator=gen).bfloat16()
+    d_o = torch.randn(B * S, d, device=DEV, generator=gen).bfloat16()
+    x[:, 0], x[:, d] = 1e19, 0
+    keys = slice(far, S) if far else slice(0, 128)
+    x[keys, d] = -3e20
+    first = 0 if far else 128            # queries before it see only such keys: 0 / 0
+    got = _attention_mfma_run(x, d_o, B, S, h, use_mfma=True)
+    want = _attention_mfma_run(x, d_o, B, S, h)
+    for g, w in ((got[0][first:], want[0][first:]), (got[1].view(B, h, S)[..., first:], want[1].view(B, h, S)[..., first:])):
+        assert torch.isfinite(w).all() and _rel(g.numpy(), w.numpy()) < 1e-2
+    if far:                              # column 0 of dk is sums of the queries' 1e19
+        assert torch.isfinite(want[2]).all() and torch.isfinite(got[2]).all()
+        for sl in (slice(0, d), slice(d + 1, 2 * d), slice(2 * d, 3 * d)):
+            assert _rel(got[2][:, sl].numpy(), want[2][:, sl].numpy()) < 1.5e-2
+
+
 @pytest.mark.parametrize("scale", [3.0, 0.05])
 def test_attention_mfma_score_ranges(scale):
     """Scores with a standard deviation of 9 (the running reference point of the online softmax must
