@@ -261,7 +261,9 @@ int als_k_gemm_dw_grouped(int n, const void* const* X, const void* const* dY, fl
 int als_k_gemm_static_ws(const void* A, const void* B, void* C, int M, int N, int K, int a_layout,
                          int b_layout, int out_dtype, void* stream);
 /* Causal attention forward / backward on packed qkv [B*S, 3d] (q|k|v, head-major), dtype
- * ALS_DTYPE_*: o [B*S,d] same dtype, lse fp32 [B,h,S]; backward takes d_o and returns dqkv. */
+ * ALS_DTYPE_*: o [B*S,d] same dtype, lse fp32 [B,h,S]; backward takes d_o and returns dqkv.
+ * use_mfma != 0 selects the MFMA kernels (bf16, dh 64, S a multiple of 128 up to 1024) where qkv and d_o are 16-byte
+ * aligned, and the generic one at other addresses; 0 the generic one. */
 int als_k_attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int h, int dh,
                         int dtype, int use_mfma, void* stream);
 int als_k_attention_bwd(const void* qkv, const void* o, const void* d_o, const float* lse,

@@ -222,7 +222,8 @@ static bool wide_pays(int B, int S, int h) { return S > 256 || (int64_t)B * h * 
 
 int attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int h, int dh, int bf, bool allow_mfma, hipStream_t st) {
   const bool any = attention_mfma_any_supported(qkv, o, qkv, o, B, S, h, dh);
-  if (allow_mfma && attention_mfma_supported(S, dh, bf) && (wide_pays(B, S, h) || !any)) return attention_fwd_mfma(qkv, o, lse, B, S, h, dh, st);
+  if (allow_mfma && attention_mfma_supported(S, dh, bf) && attention_mfma_aligned(qkv, nullptr) && (wide_pays(B, S, h) || !any))
+    return attention_fwd_mfma(qkv, o, lse, B, S, h, dh, st);
   if (allow_mfma && any)
     return bf ? attention_fwd_mfma_any(qkv, o, lse, B, S, h, dh, st) : attention_fwd_mfma_f32(qkv, o, lse, B, S, h, dh, st);
   return attention_fwd_generic(qkv, o, lse, B, S, h, dh, bf, st);
@@ -231,7 +232,7 @@ int attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int h, int
 int attention_bwd(const void* qkv, const void* o, const void* d_o, const float* lse, float* dscratch, void* dqkv, int B, int S,
                   int h, int dh, int bf, bool allow_mfma, hipStream_t st) {
   const bool any = attention_mfma_any_supported(qkv, o, d_o, dqkv, B, S, h, dh);
-  if (allow_mfma && attention_mfma_supported(S, dh, bf) && (wide_pays(B, S, h) || !any))
+  if (allow_mfma && attention_mfma_supported(S, dh, bf) && attention_mfma_aligned(qkv, d_o) && (wide_pays(B, S, h) || !any))
     return attention_bwd_mfma(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, st);
   if (allow_mfma && any)
     return bf ? attention_bwd_mfma_any(qkv, o, d_o, lse, dqkv, B, S, h, dh, st)

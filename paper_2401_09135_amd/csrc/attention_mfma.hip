@@ -731,6 +731,8 @@ __global__ __launch_bounds__(64 * KW * KS, 2) void attn_bwd_dkv_kernel(const bf1
 
 }  // namespace
 
+// Tiles go from memory to LDS 16 bytes at a time, which asks for the alignment of the tensors that they come from (rows are then aligned too).
+bool attention_mfma_aligned(const void* qkv, const void* d_o) { return ((uintptr_t)qkv | (uintptr_t)d_o) % 16 == 0; }
 bool attention_mfma_supported(int S, int dh, int bf) { return bf && dh == 64 && S >= 128 && S % 128 == 0 && S <= 1024; }
 
 // How many wavefronts share a block of 64 queries (32 keys).  On its own a wavefront takes 1.1 (forward) to 1.5 us for each tile of 64 x 64, so
@@ -758,7 +760,8 @@ static int launch(int64_t blocks, int waves, int lds, hipStream_t st, const Args
 }
 
 int attention_fwd_mfma(const void* qkv, void* o, float* lse, int B, int S, int h, int dh, hipStream_t st) {
-  if (!attention_mfma_supported(S, dh, 1) || B < 1 || h < 1) return set_error(ALS_ERR_INVALID, "attention_fwd_mfma: unsupported shape");
+  if (!attention_mfma_supported(S, dh, 1) || !attention_mfma_aligned(qkv, nullptr) || B < 1 || h < 1)
+    return set_error(ALS_ERR_INVALID, "attention_fwd_mfma: unsupported shape or alignment");
   float scale_log2 = (1.0f / sqrtf((float)dh)) * LOG2E;
 #define ALS_FWD(QW, KS) \
   launch<attn_fwd_kernel<QW, KS>>((int64_t)S / (64 * QW) * h * B, QW * KS, KS * 4 * T64, st, (const bf16*)qkv, (bf16*)o, lse, S, h, B, scale_log2)
@@ -769,7 +772,8 @@ int attention_fwd_mfma(const void* qkv, void* o, float* lse, int B, int S, int h
 
 int attention_bwd_mfma(const void* qkv, const void* o, const void* d_o, const float* lse, float* dscratch,
                        void* dqkv, int B, int S, int h, int dh, hipStream_t st) {
-  if (!attention_mfma_supported(S, dh, 1) || B < 1 || h < 1) return set_error(ALS_ERR_INVALID, "attention_bwd_mfma: unsupported shape");
+  if (!attention_mfma_supported(S, dh, 1) || !attention_mfma_aligned(qkv, d_o) || B < 1 || h < 1)
+    return set_error(ALS_ERR_INVALID, "attention_bwd_mfma: unsupported shape or alignment");
   float scale = 1.0f / sqrtf((float)dh);
 #define ALS_DQ(QW, KS) \
   launch<attn_bwd_dq_kernel<QW, KS>>((int64_t)S / (64 * QW) * h * B, QW * KS, KS * 4 * T64, st, (const bf16*)qkv, (const bf16*)o, \

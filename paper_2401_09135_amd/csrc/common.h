@@ -176,6 +176,7 @@ int attention_fwd_mfma_any(const void* qkv, void* o, float* lse, int B, int S, i
 int attention_bwd_mfma_any(const void* qkv, const void* o, const void* d_o, const float* lse, void* dqkv, int B, int S, int h, int dh,
                            hipStream_t st);
 bool attention_mfma_supported(int S, int dh, int bf);
+bool attention_mfma_aligned(const void* qkv, const void* d_o);   // d_o may be null
 int attention_fwd_mfma(const void* qkv, void* o, float* lse, int B, int S, int h, int dh,
                        hipStream_t st);
 int attention_bwd_mfma(const void* qkv, const void* o, const void* d_o, const float* lse,

@@ -938,7 +938,8 @@ extern "C" int als_k_attention_fwd(const void* qkv, void* o, float* lse, int B, 
   int bf = dtype == ALS_DTYPE_BF16;
   if (use_mfma) {
     if (!attention_mfma_supported(S, dh, bf)) return set_error(ALS_ERR_INVALID, "shape/dtype not supported by the MFMA attention");
-    return attention_fwd_mfma(qkv, o, lse, B, S, h, dh, (hipStream_t)stream);
+    // tensors at any other address are taken by the vector code
+    if (attention_mfma_aligned(qkv, nullptr)) return attention_fwd_mfma(qkv, o, lse, B, S, h, dh, (hipStream_t)stream);
   }
   return attention_fwd_generic(qkv, o, lse, B, S, h, dh, bf, (hipStream_t)stream);
 }
@@ -950,7 +951,7 @@ extern "C" int als_k_attention_bwd(const void* qkv, const void* o, const void* d
   int bf = dtype == ALS_DTYPE_BF16;
   if (use_mfma) {
     if (!attention_mfma_supported(S, dh, bf)) return set_error(ALS_ERR_INVALID, "shape/dtype not supported by the MFMA attention");
-    return attention_bwd_mfma(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, (hipStream_t)stream);
+    if (attention_mfma_aligned(qkv, d_o)) return attention_bwd_mfma(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, (hipStream_t)stream);
   }
   return attention_bwd_generic(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, bf, (hipStream_t)stream);
 }

@@ -279,6 +279,27 @@ def test_attention_mfma_scores_of_minus_infinity(B, S, h, far):
             assert _rel(got[2][:, sl].numpy(), want[2][:, sl].numpy()) < 1.5e-2
 
 
+@pytest.mark.parametrize("qkv_off,do_off", [(1, 0), (4, 4), (0, 1), (0, 4)])
+def test_attention_mfma_takes_tensors_at_any_address(qkv_off, do_off):
+    """Tensors that are not 16-byte aligned (2 and 8 bytes off) go to the vector code, the same bits as with use_mfma = 0; the forward
+    kernel reads no dO and stays on the matrix cores for an aligned qkv.  A step's choice takes them too."""
+    B, S, h = 2, 384, 2
+    d = h * 64
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    at = lambda off, *s: torch.randn(off + s[0] * s[1], device=DEV, generator=gen).bfloat16()[off:].view(*s)
+    x, d_o = at(qkv_off, B * S, 3 * d), at(do_off, B * S, d)
+    got = _attention_mfma_run(x, d_o, B, S, h, use_mfma=True)
+    vec = _attention_mfma_run(x, d_o, B, S, h)
+    step = _attention_mfma_run(x, d_o, B, S, h, fwd=A.step_attention_fwd, bwd=A.step_attention_bwd)
+    aligned = _attention_mfma_run(x.clone(), d_o.clone(), B, S, h, use_mfma=True)
+    assert torch.equal(got[0], vec[0] if qkv_off else aligned[0])
+    if qkv_off:
+        assert torch.equal(got[2], vec[2])
+    for r in (got, step):
+        for a, b in zip(r, aligned):
+            assert _rel(a.numpy(), b.numpy()) < 1.5e-2
+
+
 @pytest.mark.parametrize("scale", [3.0, 0.05])
 def test_attention_mfma_score_ranges(scale):
     """Scores with a standard deviation of 9 (the running reference point of the online softmax must
