@@ -19,7 +19,9 @@
  *   - "dev" pointers are device (HBM) addresses, "host" pointers are host addresses.
  *   - The library never allocates device memory: als_init() carves everything out of one
  *     caller-owned arena, and the als_k_* entry points work on the caller's buffers only.
- *     Streams are borrowed hipStream_t handles passed as void*.
+ *     Streams are borrowed hipStream_t handles passed as void*.  Calls on a context refuse a worker's
+ *     stream that is being captured (ALS_ERR_HIP, nothing enqueued or changed); the als_k_* entry points
+ *     can be captured, als_k_gemm_dw_grouped apart, which waits.
  *   - Flat parameter vector layout (row-major tensors, fp32), P elements in total:
  *       E [V,d], Ppos [S,d], per layer: Wqkv [d,3a] (columns q|k|v, head-major inside each,
  *       a = h * head width = attention width, equal to d unless head_dim is set), Wo [a,d],

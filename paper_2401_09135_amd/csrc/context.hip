@@ -312,6 +312,15 @@ int wait_event(hipStream_t st, hipEvent_t ev, hipStream_t recorded_on) {
   return ALS_OK;
 }
 
+// Calls that advance a worker or the server (step counts, the order of events, losses in host memory) are no work that a graph could replay:
+// a stream under capture is refused, before anything is enqueued or changed.
+int check_not_captured(hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();   // the launches report what is wrong with the stream, if anything is
+  if (cap != hipStreamCaptureStatusNone) return set_error(ALS_ERR_HIP, "the worker's stream is being captured");
+  return ALS_OK;
+}
+
 int sync_all(als_ctx* ctx) {
   for (Worker& w : ctx->w) ALS_HIP(hipStreamSynchronize(w.stream));
   return ALS_OK;
@@ -437,16 +446,10 @@ extern "C" int als_worker_local_steps(als_ctx* ctx, int worker, int n_steps, con
     return set_error(ALS_ERR_INVALID, "n_steps %d outside 0..max_local_steps=%d", n_steps, g.max_local_steps);
   if (n_steps > 0 && (!tokens || !lr_host)) return set_error(ALS_ERR_INVALID, "tokens_dev and lr_host must be non-null");
   Worker& w = ctx->w[worker];
+  RUN(check_not_captured(w.stream));
   RUN(wait_event(w.stream, w.ready_ev, w.ready_st));
   int64_t per = (int64_t)g.batch * (g.seq_len + 1);
-  // The graph is left out where a call has to see the launches: under the measurement hooks of the GEMM kernels and while the
-  // caller captures this stream.
-  bool replay = w.step_graph && !gemm_hooks_active();
-  if (replay) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    replay = hipStreamIsCapturing(w.stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-    if (!replay) (void)hipGetLastError();   // the launches report what is wrong with the stream, if anything is
-  }
+  const bool replay = w.step_graph && !gemm_hooks_active();   // the measurement hooks of the GEMM kernels have to see the launches
   auto adam_args = [&](int s, int64_t n) {   // of step s, the worker's n-th
     AdamArgs a;
     a.lr = lr_host[s];
@@ -503,6 +506,7 @@ extern "C" int als_worker_loss_grad(als_ctx* ctx, int worker, const int32_t* tok
   if (rc) return rc;
   if (!tokens || !loss_host) return set_error(ALS_ERR_INVALID, "tokens_dev and loss_host must be non-null");
   Worker& w = ctx->w[worker];
+  RUN(check_not_captured(w.stream));
   RUN(wait_event(w.stream, w.ready_ev, w.ready_st));
   RUN(embed_sort(tokens, 1, ctx->cfg.batch, ctx->cfg.seq_len, ctx->cfg.vocab, w.sort_offset, w.sort_rank,
                  w.sort_pos, w.stream));
@@ -530,6 +534,7 @@ static int outer_apply(als_ctx* ctx, const int32_t* workers, int n_group, int re
   }
   const als_config& g = ctx->cfg;
   hipStream_t st = ctx->w[workers[0]].stream;
+  RUN(check_not_captured(st));
   RUN(wait_event(st, ctx->server_ev, ctx->server_st));
   for (int j = 0; j < n_group; j++) RUN(wait_event(st, ctx->w[workers[j]].done_ev, ctx->w[workers[j]].done_st));
   int64_t P = ctx->L.P;

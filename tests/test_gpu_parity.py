@@ -540,3 +540,41 @@ def test_steps_replayed_as_graphs_equal_launched_ones(name):
         assert (a is None and b is None) or np.array_equal(a, b)
     for a, b in zip(out[0][1], out[1][1]):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("k", [1, 4])       # steps launched kernel by kernel, and replayed
+def test_a_stream_under_capture_is_refused(k):
+    """What advances a worker or the server is no work for a caller's graph: the calls are refused before anything changes, the
+    capture stays whole, and afterwards the same calls give what an undisturbed context gives."""
+    w = I.workload("tiny")
+    theta0 = I.theta0(lm.param_layout(w), w["seed"])
+    cfg = A.Config.from_workload(w)
+    cfg.n_workers = k
+    tok = torch.from_numpy(np.ascontiguousarray(_stream(w)(0).take(2))).to("cuda:0")
+    y = torch.zeros(4, device="cuda:0")
+    out = []
+    for captured in (True, False):
+        ctx = A.Context(cfg, theta0, n_streams=k)
+        ctx.worker_local_steps(0, tok, 1e-3)
+        if captured:
+            g = torch.cuda.CUDAGraph()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(ctx.streams[0]):
+                g.capture_begin(capture_error_mode="relaxed")
+                for call in (lambda: ctx.worker_local_steps(0, tok, 1e-3), lambda: ctx.worker_loss_grad(0, tok[0]),
+                             lambda: ctx.outer_apply_dn([0])):
+                    with pytest.raises(A.AlsError, match="captured"):
+                        call()
+                y += 1
+                g.capture_end()
+            for _ in range(3):
+                g.replay()
+            torch.cuda.synchronize()
+            assert y.tolist() == [3.0] * 4
+            assert ctx.adam_steps(0) == 2 and ctx.server_t == 0
+        ctx.worker_local_steps(0, tok, 1e-3)
+        ctx.outer_apply_dn([0])
+        out.append([ctx.get_vector(v) for v in ("theta", "momentum", "delta", "adam_m")])
+        ctx.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
