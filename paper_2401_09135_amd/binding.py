@@ -409,6 +409,16 @@ def gemm_route(M, N, K, a_layout=0, b_layout=0, in_dtype=ALS_DTYPE_BF16, out_dty
     return buf.value.decode()
 
 
+lib.als_k_token_order_route.argtypes = [C.c_int, C.c_int, C.c_int, C.c_char_p, C.c_int]
+
+
+def token_order_route(T, V, n_steps) -> str:
+    """The kernel that orders a call's tokens by id (host only)."""
+    buf = C.create_string_buffer(64)
+    _check(lib.als_k_token_order_route(T, V, n_steps, buf, 64))
+    return buf.value.decode()
+
+
 def k_attention_fwd(qkv, o, lse, B, S, h, dh, use_mfma=False, stream=None):
     _check(lib.als_k_attention_fwd(qkv.data_ptr(), o.data_ptr(), lse.data_ptr(), B, S, h, dh, _dt(qkv),
                                    int(bool(use_mfma)), _stream_handle(stream)))

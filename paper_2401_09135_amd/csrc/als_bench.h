@@ -42,6 +42,8 @@ int als_k_gemm_dw_grouped_plan(int n, const int* M, const int* N, int K, int max
  * borders of the dispatch.  Arguments as als_k_gemm_ex, operands taken as 256-byte aligned; flags as als_config.flags. */
 int als_k_gemm_route(int M, int N, int K, int a_layout, int b_layout, int in_dtype, int out_dtype, int epi, int flags,
                      size_t ws_bytes, char* out, int out_len);
+/* Host only: the kernel that orders a call's tokens by id (n_steps steps of T positions, vocabulary V). */
+int als_k_token_order_route(int T, int V, int n_steps, char* out, int out_len);
 /* A product and an attention as a worker step issues them: the kernel that als_config.flags, the shape and the alignment select.
  * Arguments as als_k_gemm_ex and als_k_attention_fwd / _bwd, with flags in the place of use_mfma. */
 int als_k_step_gemm(const void* A, const void* B, void* C, int M, int N, int K, int a_layout, int b_layout, int in_dtype,

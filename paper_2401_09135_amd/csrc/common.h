@@ -225,6 +225,8 @@ int cross_entropy(const void* logits, const int32_t* tok, float* loss_row, void*
 // first (with its contents v): the state that the replayed steps begin with
 int embed_sort(const int32_t* tok, int n_steps, int B, int S, int V, int32_t* offset, int32_t* rank,
                int32_t* pos, hipStream_t st, StepState* first = nullptr, const StepState* v = nullptr);
+// which kernel that is (no GPU call)
+const char* token_order_route(int64_t T, int V, int n_steps);
 // nset consecutive sets of [nblk][d] partials and the gain gradients that they add up to, nset consecutive rows of d
 struct NormPartials { const float* partial; float* dg; int nblk, nset; };
 // dE, dPpos, the mean loss and the norms' gain gradients; scratch: 2 * ceil(B*S / 32) * d floats (partial rows of position lists that cross 32-position chunks)

@@ -937,6 +937,12 @@ extern "C" int als_k_gemm_route(int M, int N, int K, int a_layout, int b_layout,
   return ALS_OK;
 }
 
+extern "C" int als_k_token_order_route(int T, int V, int n_steps, char* out, int out_len) {
+  if (!out || out_len < 1 || T < 1 || V < 2 || n_steps < 1) return set_error(ALS_ERR_INVALID, "null argument or bad size");
+  snprintf(out, out_len, "%s", token_order_route(T, V, n_steps));
+  return ALS_OK;
+}
+
 extern "C" int als_k_attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int h, int dh,
                                    int dtype, int use_mfma, void* stream) {
   if (!qkv || !o || !lse) return set_error(ALS_ERR_INVALID, "null argument");

@@ -758,9 +758,7 @@ __global__ __launch_bounds__(1024) void embed_sort_lds_kernel(const int32_t* __r
 // The same by counting, for small steps: a position's place in the order is the number of (token, position) pairs before its own, and
 // offset[v] the number of tokens below v.  A lane has one of the T + V + 1 questions and the 16 wavefronts of a workgroup share the pairs,
 // read from LDS by all lanes at once; the questions of a step are dealt to as many workgroups as they need, where the sort above is
-// a chain of passes in one.  Between the two by the number of comparisons, one launch at a time in us, sort / counting:
-//   T = 256, V = 256: 9.5 / 3.3    T = 512, V = 1024: 11 / 3.9    T = 2048, V = 4096: 13 / 8.5    T = 1024, V = 32000: 24 / 17
-constexpr int64_t RANK_MAX = 150000000;   // comparisons of all steps of a call
+// a chain of passes in one.  It grows with the steps of a call, which the sort takes side by side.
 __global__ __launch_bounds__(1024) void embed_rank_kernel(const int32_t* __restrict__ tok, int B, int S, int V,
                                                           int32_t* __restrict__ offset, int32_t* __restrict__ pos, StepState* first,
                                                           StepState state) {
@@ -800,17 +798,32 @@ __global__ __launch_bounds__(1024) void embed_rank_kernel(const int32_t* __restr
   }
 }
 
+// About what each of them takes, in us, from T = 64..12000, V = 64..131072, 1 to 200 steps in a call.  Counting: the comparisons and a
+// part per workgroup; the sort, one workgroup a step: T, and V for the offsets, in LDS below SORT_LDS_V.  Counting / sort measured:
+//   T 256, V 256: 3.2 / 8.1, 200 steps 7.2 / 8.6        T 512, V 1024: 3.2 / 9.2, 50 steps 6.7 / 9.7, 200 steps 21 / 10
+//   T 512, V 8192, 16 steps: 10.4 / 12.3, 50: 28 / 13   T 1024, V 32000: 6.1 / 20.5, 4 steps 15 / 21, 8 steps 27 / 21
+//   T 2048, V 4096: 5.0 / 12.0, 16 steps 20.5 / 12.4    T 4096, V 32000: 16.6 / 24.9, 2 steps 26 / 25
+//   T 8192, V 1024: 13 / 18, 2 steps 21 / 19            T 512, V 131072: 9.9 / 92
+// The list of positions in LDS ends the range at T = 12247.
+constexpr double RANK_MAX = 150e6;   // comparisons of all steps of a call
+static bool counting_pays(int64_t T, int V, int n_steps) {
+  const double questions = (double)T + V + 1, comparisons = T * questions * n_steps, blocks = ceil(questions / 64) * n_steps;
+  const double counting = 3.0 + 1e-3 * blocks + 1.05e-7 * comparisons, sort = 7.5 + 1.3e-3 * T + (V < SORT_LDS_V ? 3.7e-4 : 7e-4) * V;
+  return T <= SORT_TILE && V <= 1 << 17 && n_steps <= 4096 && comparisons <= RANK_MAX && counting <= sort;
+}
+const char* token_order_route(int64_t T, int V, int n_steps) {
+  return counting_pays(T, V, n_steps) ? "counting" : T <= SORT_TILE && V < SORT_LDS_V ? "sort in LDS" : "sort";
+}
+
 int embed_sort(const int32_t* tok, int n_steps, int B, int S, int V, int32_t* offset, int32_t* rank,
                int32_t* pos, hipStream_t st, StepState* first, const StepState* v) {
   if (n_steps <= 0) return ALS_OK;
-  {
+  if (counting_pays((int64_t)B * S, V, n_steps)) {
     const int64_t T = (int64_t)B * S, questions = T + V + 1;
-    if (T <= SORT_TILE && V <= 1 << 17 && n_steps <= 4096 && T * questions <= RANK_MAX / n_steps) {
-      hipLaunchKernelGGL(embed_rank_kernel, dim3((unsigned)((questions + 63) / 64), n_steps), dim3(1024), (size_t)((T + 63) & ~63) * 4, st, tok,
-                         B, S, V, offset, pos, first, first ? *v : StepState{});
-      ALS_CHECK_LAUNCH();
-      return ALS_OK;
-    }
+    hipLaunchKernelGGL(embed_rank_kernel, dim3((unsigned)((questions + 63) / 64), n_steps), dim3(1024), (size_t)((T + 63) & ~63) * 4, st, tok,
+                       B, S, V, offset, pos, first, first ? *v : StepState{});
+    ALS_CHECK_LAUNCH();
+    return ALS_OK;
   }
   if (first) {
     const int rc = set_step_state(first, *v, st);

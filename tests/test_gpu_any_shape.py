@@ -165,6 +165,26 @@ def test_token_order_by_counting_and_sorting(V, B, S):
     test_token_order_of_the_embedding_gradient(V, B, S)
 
 
+@pytest.mark.parametrize("V,B,S,n,parts", [(256, 8, 32, 400, 2), (1000, 1, 63, 500, 4), (4094, 3, 341, 40, 8), (40000, 1, 65, 160, 8)])
+def test_calls_of_many_steps_sort_their_tokens(V, B, S, n, parts):
+    """Long calls sort the tokens of all their steps side by side where short ones count: the same order, so the same bits as the
+    same steps in several calls."""
+    assert A.token_order_route(B * S, V, n).startswith("sort") and A.token_order_route(B * S, V, n // parts) == "counting"
+    w = _model(L=1, d=64, h=1, ff=64, V=V, S=S, B=B)
+    cfg = A.Config.from_workload(w, max_local_steps=n)
+    cfg.n_workers = 1
+    tok = torch.from_numpy(I.TokenStream(1, 0, B, S, V).take(n)).to(DEV)
+    out = []
+    for m in (1, parts):
+        ctx = A.Context(cfg, I.theta0(lm.param_layout(w), 3), n_streams=1)
+        for i in range(m):
+            ctx.worker_local_steps(0, tok[i * (n // m):(i + 1) * (n // m)], 1e-3)
+        out.append([ctx.get_vector(v) for v in ("worker_theta", "adam_v", "grad")])
+        ctx.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("V", [64, 65, 71, 2048, 2049, 8192, 8193, 8200, 32767, 32768, 32769])   # whole and partial groups of 8; 256 and 1024 threads; three passes
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_cross_entropy_of_any_vocabulary(V, dtype):

@@ -75,3 +75,17 @@ def test_gelu_with_fp32_outputs_has_vector_code_only():
 ])
 def test_fp32_products(M, N, K, layout, want):
     assert A.gemm_route(M, N, K, *layout, F32) == want
+
+
+@pytest.mark.parametrize("T,V,n,want", [
+    (256, 256, 1, "counting"), (256, 256, 200, "counting"), (256, 256, 400, "sort in LDS"),
+    (512, 1024, 50, "counting"), (512, 1024, 100, "sort in LDS"),        # 39 and 79 million comparisons: 6.7 us counted, 13; sorted 10
+    (2048, 4096, 4, "counting"), (2048, 4096, 16, "sort in LDS"),        # 7.2 and 20.5 us; 12
+    (1024, 32000, 4, "counting"), (1024, 32000, 8, "sort in LDS"),       # 15 and 27; 21
+    (8192, 1024, 1, "counting"), (8192, 1024, 2, "sort in LDS"),         # 13 and 21; 18
+    (1024, 50257, 2, "counting"), (1024, 50257, 4, "sort"),              # past 150 million comparisons
+    (12288, 2, 1, "sort in LDS"), (16384, 32000, 1, "sort in LDS"), (16385, 100, 1, "sort"), (512, 131073, 1, "sort"),
+])
+def test_order_of_a_calls_tokens(T, V, n, want):
+    """Counting takes longer with every step of a call, the sort takes the steps side by side."""
+    assert A.token_order_route(T, V, n) == want
