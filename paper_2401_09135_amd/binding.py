@@ -419,6 +419,16 @@ def token_order_route(T, V, n_steps) -> str:
     return buf.value.decode()
 
 
+lib.als_k_embed_grad_route.argtypes = [C.c_int, C.c_int, C.c_int, C.c_char_p, C.c_int]
+
+
+def embed_grad_route(T, V, d) -> str:
+    """How the embedding gradient of a step is formed (host only)."""
+    buf = C.create_string_buffer(64)
+    _check(lib.als_k_embed_grad_route(T, V, d, buf, 64))
+    return buf.value.decode()
+
+
 def k_attention_fwd(qkv, o, lse, B, S, h, dh, use_mfma=False, stream=None):
     _check(lib.als_k_attention_fwd(qkv.data_ptr(), o.data_ptr(), lse.data_ptr(), B, S, h, dh, _dt(qkv),
                                    int(bool(use_mfma)), _stream_handle(stream)))

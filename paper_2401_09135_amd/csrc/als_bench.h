@@ -44,6 +44,8 @@ int als_k_gemm_route(int M, int N, int K, int a_layout, int b_layout, int in_dty
                      size_t ws_bytes, char* out, int out_len);
 /* Host only: the kernel that orders a call's tokens by id (n_steps steps of T positions, vocabulary V). */
 int als_k_token_order_route(int T, int V, int n_steps, char* out, int out_len);
+/* Host only: how the embedding gradient of a step of T positions is formed (vocabulary V, width d). */
+int als_k_embed_grad_route(int T, int V, int d, char* out, int out_len);
 /* A product and an attention as a worker step issues them: the kernel that als_config.flags, the shape and the alignment select.
  * Arguments as als_k_gemm_ex and als_k_attention_fwd / _bwd, with flags in the place of use_mfma. */
 int als_k_step_gemm(const void* A, const void* B, void* C, int M, int N, int K, int a_layout, int b_layout, int in_dtype,

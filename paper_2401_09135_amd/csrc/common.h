@@ -233,6 +233,8 @@ struct NormPartials { const float* partial; float* dg; int nblk, nset; };
 int embed_bwd(const int32_t* tok, const int32_t* offset, const int32_t* pos, const float* dx, float* dE,
               float* dPpos, float* scratch, const float* loss_row, float* loss_out, int B, int S, int d, int V, const NormPartials& np,
               hipStream_t st, const StepState* ss);
+// how many launches that takes (no GPU call)
+const char* embed_grad_route(int T, int V, int d);
 int cast_copy(const float* src, void* dst, int64_t n, int dst_bf16, hipStream_t st);
 
 int adamw(float* theta, const float* grad, float* m, float* v, bf16* lp, int64_t P,

@@ -943,6 +943,12 @@ extern "C" int als_k_token_order_route(int T, int V, int n_steps, char* out, int
   return ALS_OK;
 }
 
+extern "C" int als_k_embed_grad_route(int T, int V, int d, char* out, int out_len) {
+  if (!out || out_len < 1 || T < 1 || V < 2 || d < 64 || d > 1024) return set_error(ALS_ERR_INVALID, "null argument or bad size");
+  snprintf(out, out_len, "%s", embed_grad_route(T, V, d));
+  return ALS_OK;
+}
+
 extern "C" int als_k_attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int h, int dh,
                                    int dtype, int use_mfma, void* stream) {
   if (!qkv || !o || !lse) return set_error(ALS_ERR_INVALID, "null argument");

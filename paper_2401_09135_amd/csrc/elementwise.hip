@@ -1046,8 +1046,7 @@ __global__ __launch_bounds__(256) void embed_bwd_rows_kernel(const int32_t* __re
 }
 
 // Small steps in one launch: a workgroup per vocabulary row, whose four wavefronts share its list, every fourth position each, and add
-// their sums in order.  T = 512, V = 1024, d = 256: 10.2 + 4.8 us in two launches, 10.6 in one; at T = 1024, V = 2000 (10.4 + 4.8 and 17.5) and
-// T = 2048, V = 4096 (10.5 + 4.9 and 30) the most frequent token's list, a sixth of the positions of a Zipf(1.1) text, is too long for one workgroup.
+// their sums in order, 256 columns at a time.
 __global__ __launch_bounds__(256) void embed_bwd_lists_kernel(const int32_t* __restrict__ offset, const int32_t* __restrict__ pos,
                                                               const float* __restrict__ dx, float* __restrict__ dE, float* __restrict__ dPpos,
                                                               const float* __restrict__ loss_row, float* __restrict__ loss_out, int B, int S, int V,
@@ -1084,12 +1083,21 @@ __global__ __launch_bounds__(256) void embed_bwd_lists_kernel(const int32_t* __r
   }
 }
 
+// The most frequent token's list, a sixth of the positions of a Zipf(1.1) text, is one workgroup's in the one launch, once for every 256
+// columns: that product bounds it, and the fewer rows there are the longer their lists.  Above 8192 rows most workgroups find an empty list.  One launch / two, in us (V = 64 / 1024 / 8192):
+//   T 256, d 256: 4.6 / 4.1 / 6.7 and 9.7 / 11 / 12       T 256, d 512: 6.4 / 5.9 / 8.2 and 10 / 12 / 14     T 128, d 1024: 6.7 / 7.2 / 11 and 11 / 12 / 17
+//   T 512, d 256: 7.3 / 6.0 / 6.8 and 10 / 11 / 12        T 512, d 512: 12 / 9.4 / 11 and 11 / 12 / 14       T 256, d 1024: 11 / 12 / 16 and 12 / 13 / 17
+//   T 512, d 1024: 21 / 19 / 32 and 13 / 15 / 18          T 1024, d 256: 11 / 8.4 / 8.4 and 10 / 12 / 13
+//   T 256, V 32000, d 256: 15.2 and 16.4
+static bool one_launch_pays(int T, int V, int d) { return T <= 512 && V <= 8192 && T * ((d + 255) / 256) <= (V < 256 ? 768 : 1024); }
+const char* embed_grad_route(int T, int V, int d) { return one_launch_pays(T, V, d) ? "one launch" : "two launches"; }
+
 int embed_bwd(const int32_t* tok, const int32_t* offset, const int32_t* pos, const float* dx, float* dE,
               float* dPpos, float* scratch, const float* loss_row, float* loss_out, int B, int S, int d, int V, const NormPartials& np,
               hipStream_t st, const StepState* ss) {
   if (d > 256 * EMB_MAXD4 || d % 4) return set_error(ALS_ERR_INVALID, "embed_bwd: d unsupported");
   const int rest = S + 1 + np.nset * ((d + 31) / 32);
-  if (B * S <= 512 && V <= 8192) {
+  if (one_launch_pays(B * S, V, d)) {
     hipLaunchKernelGGL(embed_bwd_lists_kernel, dim3(V + rest), dim3(256), 0, st, offset, pos, dx, dE, dPpos, loss_row, loss_out, B, S, V, d, np,
                        ss);
     ALS_CHECK_LAUNCH();

@@ -200,6 +200,19 @@ def test_cross_entropy_of_any_vocabulary(V, dtype):
     assert _rel(lm.views(g, w)["gf"], lm.views(rg, w)["gf"]) < (1e-5 if dtype == "f32" else 2e-2)
 
 
+@pytest.mark.parametrize("d,S", [(512, 256), (576, 256), (1024, 128), (1024, 129)])    # T = 2 S: the last in one launch, the first in two
+def test_embedding_gradient_of_wide_small_steps(d, S):
+    """The same sums over a token's positions in either form: fp32 gradients against the oracle."""
+    w = _model(d=d, h=d // 64, ff=64, V=300, S=S, B=2)
+    assert A.embed_grad_route(2 * S, 300, d) == ("one launch" if S in (256, 128) and d != 576 else "two launches")
+    tok = I.TokenStream(1, 0, 2, S, 300).take(1)[0]
+    theta0, loss, g = _loss_grad(w, tok)
+    rloss, rg = lm.loss_and_grad(theta0, tok, w)
+    assert abs(loss - rloss) < 1e-5 * abs(rloss)
+    for name in ("E", "Ppos", "g10", "gf"):
+        assert _rel(lm.views(g, w)[name], lm.views(rg, w)[name]) < 1e-5, name
+
+
 @pytest.mark.parametrize("dtype,kw", [("f32", dict(L=17, S=7, B=1)),                              # more products than one launch takes
                                       ("f32", dict(L=2, d=192, h=3, ff=320, V=333, S=31, B=2)),       # 32 x 32 tiles
                                       ("f32", dict(L=1, d=128, h=2, ff=192, V=130, S=103, B=5)),      # 8 shares

@@ -89,3 +89,14 @@ def test_fp32_products(M, N, K, layout, want):
 def test_order_of_a_calls_tokens(T, V, n, want):
     """Counting takes longer with every step of a call, the sort takes the steps side by side."""
     assert A.token_order_route(T, V, n) == want
+
+
+@pytest.mark.parametrize("T,V,d,want", [
+    (512, 8192, 256, "one launch"), (513, 8192, 256, "two launches"), (512, 8193, 256, "two launches"),
+    (512, 256, 512, "one launch"), (512, 256, 576, "two launches"), (384, 255, 512, "one launch"), (385, 255, 512, "two launches"),
+    (256, 8192, 1024, "one launch"), (257, 8192, 1024, "two launches"), (512, 8192, 1024, "two launches"),  # 32 us in one launch, 18 in two
+    (32, 64, 64, "one launch"),
+])
+def test_embedding_gradient(T, V, d, want):
+    """One launch leaves the longest list to one workgroup, once for every 256 columns."""
+    assert A.embed_grad_route(T, V, d) == want
