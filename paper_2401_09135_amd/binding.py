@@ -429,6 +429,25 @@ def embed_grad_route(T, V, d) -> str:
     return buf.value.decode()
 
 
+lib.als_replay_route.argtypes = [C.POINTER(Config), C.c_int]
+lib.als_replay_info.argtypes = [_P, C.POINTER(C.c_int32), C.POINTER(C.c_int64)]
+
+
+def replay_route(cfg: Config, streams: int) -> bool:
+    """Whether workers on that many different streams replay their steps as graphs (host only)."""
+    rc = lib.als_replay_route(C.byref(cfg), streams)
+    if rc < 0:
+        _check(rc)
+    return bool(rc)
+
+
+def replay_info(ctx: Context):
+    """(workers that have a graph of their step, steps that ran as one)"""
+    graphs, steps = C.c_int32(), C.c_int64()
+    _check(lib.als_replay_info(ctx._ctx, C.byref(graphs), C.byref(steps)))
+    return graphs.value, steps.value
+
+
 def k_attention_fwd(qkv, o, lse, B, S, h, dh, use_mfma=False, stream=None):
     _check(lib.als_k_attention_fwd(qkv.data_ptr(), o.data_ptr(), lse.data_ptr(), B, S, h, dh, _dt(qkv),
                                    int(bool(use_mfma)), _stream_handle(stream)))

@@ -8,6 +8,7 @@
 
 #include <stddef.h>
 #include <stdint.h>
+#include "../../include/als.h"
 
 #ifdef __cplusplus
 extern "C" {
@@ -46,6 +47,11 @@ int als_k_gemm_route(int M, int N, int K, int a_layout, int b_layout, int in_dty
 int als_k_token_order_route(int T, int V, int n_steps, char* out, int out_len);
 /* Host only: how the embedding gradient of a step of T positions is formed (vocabulary V, width d). */
 int als_k_embed_grad_route(int T, int V, int d, char* out, int out_len);
+/* Host only: 1 if als_init makes a graph of every worker's step for this configuration when its workers run on that many different
+ * streams, 0 if steps are launched kernel by kernel; negative error. */
+int als_replay_route(const als_config* cfg, int streams);
+/* How many of a context's workers have a graph of their step, and how many of their steps so far ran as one. */
+int als_replay_info(als_ctx* ctx, int32_t* graphs_out, int64_t* steps_out);
 /* A product and an attention as a worker step issues them: the kernel that als_config.flags, the shape and the alignment select.
  * Arguments as als_k_gemm_ex and als_k_attention_fwd / _bwd, with flags in the place of use_mfma. */
 int als_k_step_gemm(const void* A, const void* B, void* C, int M, int N, int K, int a_layout, int b_layout, int in_dtype,

@@ -41,6 +41,7 @@ struct Worker {
   hipStream_t done_st, ready_st;   // where these were last recorded
   StepState* state;            // of the steps that are replayed, in the arena
   hipGraphExec_t step_graph;   // one local step with its arguments in *state; null: launched kernel by kernel
+  int64_t replayed;            // steps that ran as that graph
 };
 
 }  // namespace
@@ -305,6 +306,34 @@ void capture_step(als_ctx* ctx, Worker& w, hipStream_t cs) {
   (void)hipGetLastError();
 }
 
+// Whether the launches of the workers' steps hold the host longer than the chip (streams: different ones that the workers run on).  A launch
+// takes the host 1.3 to 2.4 us, a node of a graph 0.4 to 1.2; of the workers that run side by side each advances by one kernel in about 5 us
+// where the kernels are small.  Side by side are four at most: a process has four hardware queues, further streams share them.  Where
+// the chip is the slower side a graph's start costs more than it saves, so with one or two streams steps are always launched.  Rounds of 2
+// steps in us, kernel by kernel / as graphs, on a box whose host takes 1.3 us for a launch (workers on streams):
+//                                     1 on 1       2 on 2       3 on 3        4 on 4        8 on 4        8 on 8        16 on 16      16 on 4
+//   T 64, d 64, 2 layers              338 / 335    697 / 378    957 / 443     1315 / 843    2444 / 1644   1946 / 1323   3765 / 2249   4023 / 3180
+//   T 256, d 64, 2 layers, fp32       347 / 344    445 / 406    653 / 466     892 / 903     1693 / 1754   1583 / 1388   3202 / 2239   3283 / 3483
+//   T 512, d 256, 2 layers            398 / 411    480 / 485    665 / 574     1036 / 1048   2056 / 2092   1637 / 1727   3212 / 2997   4063 / 4193
+//   T 512, d 256, 6 layers            953 / 964    1128 / 1124  1585 / 1315   2509 / 2472   5014 / 5035   5588 / 4147   8728 / 7158   11482 / 10029
+//   T 2048, d 128, V 32000, 12 layers 2283 / 2296  3384 / 3215  4839 / 4187   6677 / 6695   13317 / 13296 11783 / 11813 21847 / 21708 26033 / 26448
+//   T 4096, d 256, 2 layers           757 / 773    1048 / 1058  1379 / 1383   2187 / 2225   4331 / 4350   3851 / 3866   7156 / 7134   8652 / 8699
+// and on one whose host takes 2.4 us: 4 on 4 of the second 1191 / 647, of the third 1274 / 922.  Beyond the line nothing is gained on any number
+// of streams: T 4096, d 256, V 8192: 2553 / 2564, 5021 / 5008 (8 on 8), 9940 / 9880 (16 on 16); T 1024, d 896, 4 layers: 6536 / 6519, 12767 / 12787, 25322 / 25340.
+constexpr int HW_QUEUES = 4;
+bool replay_pays(const als_config& c, int streams) {
+  const double T = (double)c.batch * c.seq_len, da = (double)c.n_heads * head_width(c), d = c.d_model;
+  const double flops = 6.0 * T * (c.n_layers * (4.0 * d * da + 2.0 * d * c.d_ff + c.seq_len * da) + d * c.vocab);
+  const int launches = 15 * c.n_layers + 12, side_by_side = std::min(std::min(c.n_workers, streams), HW_QUEUES);
+  return side_by_side * 2.4 > 5.0 + flops / launches / 250e6;
+}
+int used_streams(const als_config& c, void* const* streams, int n_streams) {   // worker i runs on streams[i % n_streams]
+  const int n = std::min(c.n_workers, n_streams);
+  int different = 0;
+  for (int i = 0; i < n; i++) different += std::find(streams, streams + i, streams[i]) == streams + i;
+  return different;
+}
+
 // A wait costs the host 4 to 6 us: none where the stream's own order gives it.  (The handle of the per-thread default stream stands
 // for another stream in every thread.)
 int wait_event(hipStream_t st, hipEvent_t ev, hipStream_t recorded_on) {
@@ -371,7 +400,7 @@ extern "C" int als_init(const als_config* cfg, void* arena, size_t arena_bytes, 
   int64_t P = c->L.P;
   hipStream_t s0 = (hipStream_t)streams[0];
   c->server_ev = nullptr;
-  for (Worker& w : c->w) { w.done_ev = nullptr; w.ready_ev = nullptr; w.losses_host = nullptr; w.step_graph = nullptr; }
+  for (Worker& w : c->w) { w.done_ev = nullptr; w.ready_ev = nullptr; w.losses_host = nullptr; w.step_graph = nullptr; w.replayed = 0; }
   auto fail = [&](int code) { als_destroy(c); return code; };
   if (hipEventCreateWithFlags(&c->server_ev, hipEventDisableTiming) != hipSuccess)
     return fail(set_error(ALS_ERR_HIP, "hipEventCreate failed"));
@@ -403,14 +432,7 @@ extern "C" int als_init(const als_config* cfg, void* arena, size_t arena_bytes, 
   if (hipEventRecord(c->server_ev, s0) != hipSuccess) return fail(set_error(ALS_ERR_HIP, "hipEventRecord failed"));
   rc = sync_all(c);
   if (rc) return fail(rc);
-  // Whether the launches of the workers' steps hold the host longer than the chip.  A launch takes the host 2.4 us, a node of a graph
-  // 0.4 to 1.2; of the workers that run side by side each advances by one kernel in about 5 us where the kernels are small.  Where the
-  // chip is the slower side a graph's start costs more than it saves.  Rounds in us, kernel by kernel / as graphs, when graphs came in: 4 streams
-  // of 32 x 8 tokens, d = 64: 1191 / 647; 4 of 128 x 4, d = 256: 1274 / 922; 2 of 256 x 8, d = 256: 702 / 715; one of 128 x 8, d = 256 in fp32: 445 / 452.
-  const int64_t T = c->T, da = (int64_t)cfg->n_heads * head_width(*cfg), d = cfg->d_model;
-  const double flops = 6.0 * T * (cfg->n_layers * (4.0 * d * da + 2.0 * d * cfg->d_ff + (double)cfg->seq_len * da) + (double)d * cfg->vocab);
-  const int launches = 15 * cfg->n_layers + 12, side_by_side = std::min(cfg->n_workers, n_streams);
-  if (side_by_side * 2.4 > 5.0 + flops / launches / 250e6 && !gemm_hooks_active()) {
+  if (replay_pays(*cfg, used_streams(*cfg, streams, n_streams)) && !gemm_hooks_active()) {
     hipStream_t cs = nullptr;
     if (hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) == hipSuccess) {
       for (Worker& w : c->w) capture_step(c, w, cs);
@@ -483,6 +505,7 @@ extern "C" int als_worker_local_steps(als_ctx* ctx, int worker, int n_steps, con
       }
       ALS_HIP(hipGraphLaunch(w.step_graph, w.stream));
       w.adam_n += 1;
+      w.replayed += 1;
       continue;
     }
     const int32_t* tok = tokens + (int64_t)s * per;
@@ -925,6 +948,19 @@ extern "C" int als_k_step_attention_bwd(const void* qkv, const void* o, const vo
                                         void* dqkv, int B, int S, int h, int dh, int dtype, int flags, void* stream) {
   if (!qkv || !o || !d_o || !lse || !dscratch || !dqkv) return set_error(ALS_ERR_INVALID, "null argument");
   return attention_bwd(qkv, o, d_o, lse, dscratch, dqkv, B, S, h, dh, dtype == ALS_DTYPE_BF16, !(flags & 1), (hipStream_t)stream);
+}
+
+extern "C" int als_replay_route(const als_config* cfg, int streams) {
+  int rc = validate_config(cfg);
+  if (rc) return rc;
+  return replay_pays(*cfg, streams);
+}
+
+extern "C" int als_replay_info(als_ctx* ctx, int32_t* graphs_out, int64_t* steps_out) {
+  if (!ctx || !graphs_out || !steps_out) return set_error(ALS_ERR_INVALID, "null argument");
+  *graphs_out = 0; *steps_out = 0;
+  for (const Worker& w : ctx->w) { *graphs_out += w.step_graph != nullptr; *steps_out += w.replayed; }
+  return ALS_OK;
 }
 
 extern "C" int als_k_gemm_route(int M, int N, int K, int a_layout, int b_layout, int in_dtype, int out_dtype, int epi, int flags,

@@ -1,4 +1,6 @@
 """GPU parity of the whole hot path against the oracle, through the C ABI."""
+import concurrent.futures
+
 import numpy as np
 import pytest
 import torch
@@ -502,43 +504,94 @@ def test_bf16_operand_rounding_sets_the_scale_of_the_deviation(name):
     assert worst_lib < max(3.0 * worst_round, TOL["bf16"]["loss"])
 
 
-@pytest.mark.parametrize("name", ["tiny", "tiny_ln", "mini_bf16"])
-def test_steps_replayed_as_graphs_equal_launched_ones(name):
-    """Four small workers on four streams replay their steps as graphs; under als_prof_enable the same calls launch kernel by
+@pytest.mark.parametrize("name,kw,k,streams,least", [
+    ("tiny", {}, 4, 4, 1), ("tiny_ln", {}, 4, 4, 1), ("mini_bf16", {}, 4, 4, 1),
+    ("tiny", {}, 3, 3, 1), ("tiny", {}, 8, 8, 1), ("tiny", {}, 8, 4, 1),
+    # two launches for the embedding gradient, cross-entropy of an odd vocabulary with 1024 threads
+    ("mini_bf16", dict(B=5, V=8209), 4, 4, 1),
+    # tokens sorted, not counted, behind the state's own launch; a vocabulary beyond the registers of cross-entropy
+    ("mini_bf16", dict(L=12, d=64, h=1, ff=128, V=39001, B=8), 4, 4, 4)])
+def test_steps_replayed_as_graphs_equal_launched_ones(name, kw, k, streams, least):
+    """Small workers on three streams and more replay their steps as graphs; under als_prof_enable the same calls launch kernel by
     kernel.  The kernels and their operands are the same, so every vector and loss is, bit for bit: over several rounds, with
     other step counts, learning rates and tokens each, eager work, gradients and synchronisations between them."""
-    w = I.workload(name)
+    w = dict(I.workload(name), **kw)
     theta0 = I.theta0(lm.param_layout(w), w["seed"])
     busy = torch.randn(256, 256, device="cuda:0")
+    if least > 1:
+        assert A.token_order_route(w["B"] * w["S"], w["V"], least) == "sort"
     out = []
     for launched in (False, True):
         cfg = A.Config.from_workload(w)
-        cfg.n_workers, cfg.max_local_steps = 4, 70
-        ctx = A.Context(cfg, theta0, n_streams=4)
-        streams = [_stream(w)(i) for i in range(4)]
-        seen = []
+        cfg.n_workers, cfg.max_local_steps = k, 70
+        ctx = A.Context(cfg, theta0, n_streams=streams)
+        tokens = [_stream(w)(i) for i in range(k)]
+        seen, steps = [], 0
         A.prof_enable(launched)
         try:
             for rnd in range(3):
-                for i in range(4):
-                    n = 70 if name == "tiny" and rnd == 2 and i == 1 else 1 + (i + rnd) % 3   # more than the 64 that one state holds
-                    tok = torch.from_numpy(np.ascontiguousarray(streams[i].take(n))).to("cuda:0")
+                for i in range(k):
+                    n = 70 if (name, k) == ("tiny", 4) and rnd == 2 and i == 1 else least + (i + rnd) % 3   # more than the 64 that one state holds
+                    tok = torch.from_numpy(np.ascontiguousarray(tokens[i].take(n))).to("cuda:0")
                     seen.append(ctx.worker_local_steps(i, tok, [1e-3 * (1 + rnd + s) for s in range(n)], want_losses=rnd == 1))
+                    steps += n
                     busy = busy @ busy * 1e-3
-                tok = torch.from_numpy(np.ascontiguousarray(streams[rnd].take(1))).to("cuda:0")
+                tok = torch.from_numpy(np.ascontiguousarray(tokens[rnd].take(1))).to("cuda:0")
                 seen.extend(ctx.worker_loss_grad(rnd, tok[0]))
-                ctx.outer_apply_dn([0, 1, 2, 3], restart=rnd != 1)
+                ctx.outer_apply_dn(list(range(k)), restart=rnd != 1)
                 torch.cuda.synchronize()
         finally:
             A.prof_enable(False)
             A.prof_collect()
+        assert A.replay_info(ctx) == (k, 0 if launched else steps)
         vec = [ctx.get_vector(v) for v in ("theta", "momentum", "delta")]
-        vec += [ctx.get_vector(v, i) for i in range(4) for v in ("worker_theta", "worker_start", "adam_m", "adam_v", "grad")]
+        vec += [ctx.get_vector(v, i) for i in range(k) for v in ("worker_theta", "worker_start", "adam_m", "adam_v", "grad")]
         ctx.close()
         out.append((seen, vec))
     for a, b in zip(out[0][0], out[1][0]):
         assert (a is None and b is None) or np.array_equal(a, b)
     for a, b in zip(out[0][1], out[1][1]):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("order,graphs", [((0, 0, 0, 0), 0), ((0, 1, 0, 1), 0), ((0, 1, 2, 0), 4), ((0, 1, 2, 3), 4)])
+def test_a_stream_passed_twice_counts_once(order, graphs):
+    """Replay pays from three streams on that run side by side; workers on one stream do not."""
+    w = I.workload("tiny")
+    s = [torch.cuda.Stream() for _ in range(4)]
+    ctx = A.Context(A.Config.from_workload(w), I.theta0(lm.param_layout(w), w["seed"]), streams=[s[i] for i in order])
+    assert A.replay_info(ctx) == (graphs, 0)
+    ctx.close()
+
+
+def test_workers_on_the_per_thread_default_stream():
+    """The handle stands for another stream in every thread, so no wait is left out on it: a round that two threads take turns in, without
+    waiting for the device, gives what one thread gives on streams of its own."""
+    class PerThread:
+        cuda_stream = 2          # hipStreamPerThread
+    w = I.workload("tiny")
+    theta0 = I.theta0(lm.param_layout(w), w["seed"])
+    cfg = A.Config.from_workload(w)
+    cfg.n_workers, cfg.max_local_steps = 3, 8
+    tok = [torch.from_numpy(np.ascontiguousarray(_stream(w)(i).take(8))).to("cuda:0") for i in range(3)]
+    torch.cuda.synchronize()
+    out = []
+    for per_thread in (True, False):
+        s = [torch.cuda.Stream() for _ in range(3)]
+        ctx = A.Context(cfg, theta0, streams=[PerThread] + s[1:] if per_thread else s)
+        assert A.replay_info(ctx)[0] == 3
+        with concurrent.futures.ThreadPoolExecutor(1) as one, concurrent.futures.ThreadPoolExecutor(1) as two:
+            for rnd in range(3):
+                one.submit(ctx.worker_local_steps, 0, tok[0], 1e-3).result()
+                two.submit(ctx.outer_apply_dn, [0, 1]).result()
+                two.submit(ctx.worker_local_steps, 1, tok[1], 1e-3).result()
+                two.submit(ctx.worker_local_steps, 0, tok[0], 1e-3).result()
+                one.submit(ctx.outer_apply_dn, [0, 2]).result()
+            torch.cuda.synchronize()
+            out.append([ctx.get_vector(v) for v in ("theta", "momentum", "delta")] +
+                       [ctx.get_vector(v, i) for i in range(3) for v in ("worker_theta", "adam_m", "grad")])
+            ctx.close()
+    for a, b in zip(*out):
         assert np.array_equal(a, b)
 
 

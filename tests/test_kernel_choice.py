@@ -1,6 +1,7 @@
 """Which kernel a product of a worker step takes, at the borders of the rules (host only, no GPU call)."""
 import pytest
 
+import als_inputs as I
 import paper_2401_09135_amd as A
 
 F32, BF16 = A.ALS_DTYPE_F32, A.ALS_DTYPE_BF16
@@ -100,3 +101,21 @@ def test_order_of_a_calls_tokens(T, V, n, want):
 def test_embedding_gradient(T, V, d, want):
     """One launch leaves the longest list to one workgroup, once for every 256 columns."""
     assert A.embed_grad_route(T, V, d) == want
+
+
+def _config(name, workers, **kw):
+    cfg = A.Config.from_workload(dict(I.workload(name), **kw))
+    cfg.n_workers = workers
+    return cfg
+
+
+@pytest.mark.parametrize("name,kw", [("tiny", {}), ("mini_bf16", {}), ("mini_bf16", dict(B=16, V=8192)), ("mini_bf16", dict(B=32, V=8192)),
+                                     ("mini_bf16", dict(d=512, h=8, ff=2048, B=16)), ("lm20m", {}), ("lm150m_b1", {})])
+def test_steps_replayed_as_graphs(name, kw):
+    """Four hardware queues: workers on more streams do not run side by side, so more of them replay nothing that four do not."""
+    four = A.replay_route(_config(name, 4, **kw), 4)
+    assert four == (name == "tiny" or kw in ({}, dict(B=16, V=8192)) and name == "mini_bf16")
+    for streams in (8, 16, 64):
+        assert A.replay_route(_config(name, 64, **kw), streams) == four
+    for workers, streams in ((1, 1), (2, 2), (4, 2), (64, 1), (2, 16)):       # the chip is the slower side
+        assert not A.replay_route(_config(name, workers, **kw), streams)
