@@ -17,8 +17,13 @@
  *     and nothing aborts; als_last_error() returns the text of the calling thread's last
  *     error.
  *   - "dev" pointers are device (HBM) addresses, "host" pointers are host addresses.
- *   - The library never allocates device memory: als_init() carves everything out of one
- *     caller-owned arena, and the als_k_* entry points work on the caller's buffers only.
+ *   - The library allocates no device memory of its own: als_init() carves everything out of one
+ *     caller-owned arena, and the als_k_* entry points work on the caller's buffers only.  What the
+ *     HIP runtime keeps for its objects is its own: the events and pinned loss buffer of every worker and,
+ *     for models whose steps are so short that launching their kernels takes the host longer than the chip
+ *     (workers on three different streams or more), one executable graph per worker.  als_init() captures
+ *     those on a stream that it creates and destroys, als_destroy() frees them; a capture that fails
+ *     is no error, such a worker's steps are launched kernel by kernel.
  *     Streams are borrowed hipStream_t handles passed as void*.  Calls on a context refuse a worker's
  *     stream that is being captured (ALS_ERR_HIP, nothing enqueued or changed); the als_k_* entry points
  *     can be captured, als_k_gemm_dw_grouped apart, which waits.
@@ -74,7 +79,8 @@ typedef struct als_config {
   int32_t flags;           /* bit 0: disable the matrix-core kernels (the generic ones in vector code, in both
                               modes); bit 1: one weight-gradient product per matrix inside the backward loop instead
                               of one launch of all of them at its end (the layers' in bf16 with widths that are
-                              multiples of 128; the output matrix's too in fp32 or with other sizes) */
+                              multiples of 128; the output matrix's too in fp32, with other sizes, and for small models
+                              and steps: up to 2048 tokens and 128 tiles of 256 x 256 in all weight gradients) */
   int32_t head_dim;        /* 0 = d/h; otherwise the attention width h*head_dim may differ from d
                               (the paper's 60M / 150M models: 16 heads of 64 on d = 896) */
   int32_t norm_kind;       /* ALS_NORM_RMS (0): y = x rsqrt(mean x^2 + eps) g ; ALS_NORM_LAYER (1): layer

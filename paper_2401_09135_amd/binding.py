@@ -430,7 +430,7 @@ def embed_grad_route(T, V, d) -> str:
 
 
 lib.als_replay_route.argtypes = [C.POINTER(Config), C.c_int]
-lib.als_replay_info.argtypes = [_P, C.POINTER(C.c_int32), C.POINTER(C.c_int64)]
+lib.als_replay_info.argtypes = [_P, C.POINTER(C.c_int32), C.POINTER(C.c_int64), C.c_char_p, C.c_int]
 
 
 def replay_route(cfg: Config, streams: int) -> bool:
@@ -442,10 +442,10 @@ def replay_route(cfg: Config, streams: int) -> bool:
 
 
 def replay_info(ctx: Context):
-    """(workers that have a graph of their step, steps that ran as one)"""
-    graphs, steps = C.c_int32(), C.c_int64()
-    _check(lib.als_replay_info(ctx._ctx, C.byref(graphs), C.byref(steps)))
-    return graphs.value, steps.value
+    """(workers that have a graph of their step, steps that ran as one, why a step could not be captured)"""
+    graphs, steps, why = C.c_int32(), C.c_int64(), C.create_string_buffer(512)
+    _check(lib.als_replay_info(ctx._ctx, C.byref(graphs), C.byref(steps), why, 512))
+    return graphs.value, steps.value, why.value.decode()
 
 
 def k_attention_fwd(qkv, o, lse, B, S, h, dh, use_mfma=False, stream=None):

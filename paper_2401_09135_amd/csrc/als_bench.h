@@ -50,8 +50,11 @@ int als_k_embed_grad_route(int T, int V, int d, char* out, int out_len);
 /* Host only: 1 if als_init makes a graph of every worker's step for this configuration when its workers run on that many different
  * streams, 0 if steps are launched kernel by kernel; negative error. */
 int als_replay_route(const als_config* cfg, int streams);
-/* How many of a context's workers have a graph of their step, and how many of their steps so far ran as one. */
-int als_replay_info(als_ctx* ctx, int32_t* graphs_out, int64_t* steps_out);
+/* How many of a context's workers have a graph of their step, how many of their steps so far ran as one, and why a step could not
+ * be captured (empty: none failed). */
+int als_replay_info(als_ctx* ctx, int32_t* graphs_out, int64_t* steps_out, char* error_out, int error_len);
+/* Test hook: 1 makes the captures of als_init fail behind their last kernel, 0 no longer does. */
+int als_fail_capture(int on);
 /* A product and an attention as a worker step issues them: the kernel that als_config.flags, the shape and the alignment select.
  * Arguments as als_k_gemm_ex and als_k_attention_fwd / _bwd, with flags in the place of use_mfma. */
 int als_k_step_gemm(const void* A, const void* B, void* C, int M, int N, int K, int a_layout, int b_layout, int in_dtype,

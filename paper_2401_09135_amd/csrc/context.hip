@@ -4,7 +4,9 @@
 // against the workers with events.
 #include "common.h"
 #include <algorithm>
+#include <atomic>
 #include <math.h>
+#include <stdio.h>
 #include <string.h>
 #include <mutex>
 #include <new>
@@ -53,6 +55,7 @@ struct als_ctx {
   float *theta, *m, *delta;
   int64_t t;
   std::vector<Worker> w;
+  char capture_error[512];   // why a step could not be captured, empty if none failed
   hipEvent_t server_ev; hipStream_t server_st;
   bool bf; bool allow_mfma;
   bool grouped_dw;   // the layers' weight gradients run as one grouped launch at the end of the backward pass
@@ -292,16 +295,29 @@ int check_ctx_worker(als_ctx* ctx, int worker) {
   return ALS_OK;
 }
 
+std::atomic<bool> g_fail_capture{false};
+
 // The step of one worker as a graph, captured on a stream of its own (nothing runs there).  On any failure the context goes on
-// without: a step is then launched kernel by kernel.
+// without: a step is then launched kernel by kernel, and the reason is kept for als_replay_info; the calling thread's last error stays what it was.
 void capture_step(als_ctx* ctx, Worker& w, hipStream_t cs) {
+  char last[sizeof ctx->capture_error];
+  snprintf(last, sizeof last, "%s", als_last_error());
   hipGraph_t graph = nullptr;
-  if (hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed) != hipSuccess) { (void)hipGetLastError(); return; }
-  int rc = forward(ctx, w, nullptr, cs, w.state);
-  if (!rc) rc = backward(ctx, w, nullptr, 0, nullptr, cs, w.state);
-  if (!rc) rc = adamw(w.theta, w.grad, w.adam_m, w.adam_v, w.lp, ctx->L.P, ctx->L.P_decay, AdamArgs{}, cs, w.state);
-  const bool ok = hipStreamEndCapture(cs, &graph) == hipSuccess && !rc;
-  if (!ok || hipGraphInstantiate(&w.step_graph, graph, nullptr, nullptr, 0) != hipSuccess) w.step_graph = nullptr;
+  int rc = ALS_OK;
+  hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed);
+  if (e == hipSuccess) {
+    rc = forward(ctx, w, nullptr, cs, w.state);
+    if (!rc) rc = backward(ctx, w, nullptr, 0, nullptr, cs, w.state);
+    if (!rc) rc = adamw(w.theta, w.grad, w.adam_m, w.adam_v, w.lp, ctx->L.P, ctx->L.P_decay, AdamArgs{}, cs, w.state);
+    if (!rc && g_fail_capture.load()) rc = set_error(ALS_ERR_HIP, "capture made to fail");
+    e = hipStreamEndCapture(cs, &graph);
+  }
+  if (e == hipSuccess && !rc) e = hipGraphInstantiate(&w.step_graph, graph, nullptr, nullptr, 0);
+  if (e != hipSuccess || rc) {
+    w.step_graph = nullptr;
+    snprintf(ctx->capture_error, sizeof ctx->capture_error, "%s", rc ? als_last_error() : hipGetErrorString(e));
+    set_error(rc, "%s", last);
+  }
   if (graph) (void)hipGraphDestroy(graph);
   (void)hipGetLastError();
 }
@@ -385,6 +401,7 @@ extern "C" int als_init(const als_config* cfg, void* arena, size_t arena_bytes, 
   c->allow_mfma = !(cfg->flags & 1);
   c->T = cfg->batch * cfg->seq_len;
   c->t = 0;
+  c->capture_error[0] = 0;
   Carver cv{(char*)arena, 0};
   carve(c, cv);
   if (c->grouped_dw)
@@ -438,7 +455,7 @@ extern "C" int als_init(const als_config* cfg, void* arena, size_t arena_bytes, 
       for (Worker& w : c->w) capture_step(c, w, cs);
       (void)hipStreamDestroy(cs);
     } else {
-      (void)hipGetLastError();
+      snprintf(c->capture_error, sizeof c->capture_error, "%s", hipGetErrorString(hipGetLastError()));
     }
   }
   *out = c;
@@ -956,8 +973,14 @@ extern "C" int als_replay_route(const als_config* cfg, int streams) {
   return replay_pays(*cfg, streams);
 }
 
-extern "C" int als_replay_info(als_ctx* ctx, int32_t* graphs_out, int64_t* steps_out) {
-  if (!ctx || !graphs_out || !steps_out) return set_error(ALS_ERR_INVALID, "null argument");
+extern "C" int als_fail_capture(int on) {
+  g_fail_capture = on != 0;
+  return ALS_OK;
+}
+
+extern "C" int als_replay_info(als_ctx* ctx, int32_t* graphs_out, int64_t* steps_out, char* error_out, int error_len) {
+  if (!ctx || !graphs_out || !steps_out || !error_out || error_len < 1) return set_error(ALS_ERR_INVALID, "null argument");
+  snprintf(error_out, error_len, "%s", ctx->capture_error);
   *graphs_out = 0; *steps_out = 0;
   for (const Worker& w : ctx->w) { *graphs_out += w.step_graph != nullptr; *steps_out += w.replayed; }
   return ALS_OK;

@@ -543,7 +543,7 @@ def test_steps_replayed_as_graphs_equal_launched_ones(name, kw, k, streams, leas
         finally:
             A.prof_enable(False)
             A.prof_collect()
-        assert A.replay_info(ctx) == (k, 0 if launched else steps)
+        assert A.replay_info(ctx) == (k, 0 if launched else steps, "")
         vec = [ctx.get_vector(v) for v in ("theta", "momentum", "delta")]
         vec += [ctx.get_vector(v, i) for i in range(k) for v in ("worker_theta", "worker_start", "adam_m", "adam_v", "grad")]
         ctx.close()
@@ -560,8 +560,32 @@ def test_a_stream_passed_twice_counts_once(order, graphs):
     w = I.workload("tiny")
     s = [torch.cuda.Stream() for _ in range(4)]
     ctx = A.Context(A.Config.from_workload(w), I.theta0(lm.param_layout(w), w["seed"]), streams=[s[i] for i in order])
-    assert A.replay_info(ctx) == (graphs, 0)
+    assert A.replay_info(ctx) == (graphs, 0, "")
     ctx.close()
+
+
+def test_a_capture_that_fails():
+    """als_init goes on without the graphs: steps are launched with the same bits, the reason can be asked for, and the thread's last error is
+    still the one that it was told."""
+    w = I.workload("tiny")
+    theta0 = I.theta0(lm.param_layout(w), w["seed"])
+    tok = torch.from_numpy(np.ascontiguousarray(_stream(w)(0).take(2))).to("cuda:0")
+    out = []
+    for fail in (True, False):
+        assert A.lib.als_dylu_schedule(None, 0, 1, 0.0, 0, None, None, None, None) != 0
+        told = A.lib.als_last_error()
+        A.lib.als_fail_capture(int(fail))
+        try:
+            ctx = A.Context(A.Config.from_workload(w), theta0, n_streams=4)
+        finally:
+            A.lib.als_fail_capture(0)
+        assert told and A.lib.als_last_error() == told
+        ctx.worker_local_steps(0, tok, 1e-3)
+        assert A.replay_info(ctx) == ((0, 0, "capture made to fail") if fail else (4, 2, ""))
+        out.append([ctx.get_vector(v) for v in ("worker_theta", "adam_v", "grad")])
+        ctx.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
 
 
 def test_workers_on_the_per_thread_default_stream():
