@@ -435,14 +435,19 @@ def test_comparison_outer_rules_match_oracle(name, N, rule):
     assert _rel(plain["theta"], ref["theta"]) > (10 if w["dtype"] == "f32" else 3) * _rel(got["theta"], ref["theta"])
 
 
-@pytest.mark.parametrize("name", ["tiny", "wide_attn_f32", "mini_bf16"])
+# What forms it: one launch for the first three; two, over 32-position chunks, above 512 positions (544 = 17 whole chunks, of which token 1
+# of "two_tokens" fills 16; 527 = 16 and 15 positions, 516 = 16 and 4) and above 8192 rows, where 72 positions are 2 chunks and 8
+@pytest.mark.parametrize("name,kw,launches", [("tiny", {}, "one"), ("wide_attn_f32", {}, "one"), ("mini_bf16", {}, "one"),
+                                              ("tiny", dict(B=17), "two"), ("tiny", dict(B=17, S=31), "two"), ("mini_bf16", dict(B=4, S=129), "two"),
+                                              ("wide_attn_f32", dict(V=8200), "two")])
 @pytest.mark.parametrize("pattern", ["one_token", "two_tokens", "all_distinct_cycle", "out_of_range"])
-def test_embedding_gradient_token_patterns(name, pattern):
-    """The embedding gradient is built from a sorted position list cut into 32-position chunks:
-    one token filling every chunk, lists that end exactly on chunk borders, a ragged last chunk
-    (B*S = 72 in wide_attn_f32), many absent tokens, and ids the kernels clamp."""
-    w = I.workload(name)
+def test_embedding_gradient_token_patterns(name, kw, launches, pattern):
+    """The embedding gradient is built from a sorted position list, by a workgroup per token or cut into 32-position chunks:
+    one token filling every chunk, lists that end exactly on chunk borders, a ragged last chunk, many absent tokens, and ids the
+    kernels clamp."""
+    w = dict(I.workload(name), **kw)
     B, S, V = w["B"], w["S"], w["V"]
+    assert A.embed_grad_route(B * S, V, w["d"]).startswith(launches)
     n = B * (S + 1)
     if pattern == "one_token":
         tok = np.full(n, 3, np.int32)
@@ -473,7 +478,7 @@ def test_embedding_gradient_token_patterns(name, pattern):
     absent = sorted(set(range(V)) - set(ref_tok[:, :-1].reshape(-1).tolist()))
     if absent:
         assert not gv["E"][absent].any()                      # exact zeros for tokens that do not occur
-    _record(f"embed_patterns {name} {pattern}: E rel {_rel(gv['E'], rv['E']):.3e} Ppos rel {_rel(gv['Ppos'], rv['Ppos']):.3e}")
+    _record(f"embed_patterns {name} {kw} {pattern}: E rel {_rel(gv['E'], rv['E']):.3e} Ppos rel {_rel(gv['Ppos'], rv['Ppos']):.3e}")
 
 
 @pytest.mark.parametrize("name", ["mini_bf16", "paper60m"])
