@@ -4,8 +4,8 @@
 //
 // The operands of the score products are bf16 as they lie in memory: their products are exact and the sums fp32.  The
 // operands that are computed (probabilities and score gradients) stay whole fp32 values: each is cut into three bf16 parts of 8
-// bits of its significand, high, middle and low, which give it back exactly, and the second products take one matrix instruction
-// per part.  Against the fp32 instruction (v_mfma_f32_16x16x4_f32: a 16th of the rate; what attention_mfma_f32.hip does for fp32
+// bits of its significand, high, middle and low, which give it back exactly from 2^-110 on and to 2^-133 (the smallest bf16) below, and the
+// second products take one matrix instruction per part.  Against the fp32 instruction (v_mfma_f32_16x16x4_f32: a 16th of the rate; what attention_mfma_f32.hip does for fp32
 // storage) that is 16 times fewer cycles for the scores and 5 times fewer for the rest.
 //
 // One wavefront owns 16 NT queries (forward, dQ) or 16 NT keys (dK and dV) of one head and walks the other side in steps of 32
@@ -70,8 +70,8 @@ __device__ __forceinline__ f32x4 row_product(const RowFrag<DH>& a, const RowFrag
   return acc;
 }
 
-// 8 fp32 values of a lane as three bf16 parts whose sum they are: the upper 8 bits of the significand, the next 8, the last 8.
-// An infinity has a high part only.
+// 8 fp32 values of a lane as three bf16 parts: the upper 8 bits of the significand, the next 8, the last 8.  Their sum is the value for
+// |x| >= 2^-110; below that the last bits lie under 2^-133, the smallest bf16, and are left out.  An infinity has a high part only.
 struct Parts3 {
   u32x4 hi, mid, lo;
   __device__ __forceinline__ Parts3(const float (&x)[8]) {
