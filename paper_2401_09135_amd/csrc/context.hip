@@ -466,6 +466,8 @@ extern "C" int als_destroy(als_ctx* c) {
   if (!c) return ALS_OK;
   for (Worker& w : c->w) {
     if (w.stream) (void)hipStreamSynchronize(w.stream);
+    // on the per-thread default stream the last steps may be another thread's, and their graph has to outlive them
+    if (w.step_graph) (void)hipEventSynchronize(w.done_ev);
     if (w.done_ev) (void)hipEventDestroy(w.done_ev);
     if (w.ready_ev) (void)hipEventDestroy(w.ready_ev);
     if (w.losses_host) (void)hipHostFree(w.losses_host);

@@ -593,11 +593,13 @@ def test_a_capture_that_fails():
         assert np.array_equal(a, b)
 
 
-def test_workers_on_the_per_thread_default_stream():
-    """The handle stands for another stream in every thread, so no wait is left out on it: a round that two threads take turns in, without
-    waiting for the device, gives what one thread gives on streams of its own."""
-    class PerThread:
-        cuda_stream = 2          # hipStreamPerThread
+@pytest.mark.parametrize("handle", [0, 2])      # the legacy default stream, hipStreamPerThread
+def test_workers_on_a_default_stream(handle):
+    """A worker on the default stream replays its steps like any other.  hipStreamPerThread stands for another stream in every thread, so no wait
+    is left out on it: a round that two threads take turns in, without waiting for the device, gives what it gives on streams of its
+    own, and a context may be closed while another thread's steps run."""
+    class Default:
+        cuda_stream = handle
     w = I.workload("tiny")
     theta0 = I.theta0(lm.param_layout(w), w["seed"])
     cfg = A.Config.from_workload(w)
@@ -605,9 +607,9 @@ def test_workers_on_the_per_thread_default_stream():
     tok = [torch.from_numpy(np.ascontiguousarray(_stream(w)(i).take(8))).to("cuda:0") for i in range(3)]
     torch.cuda.synchronize()
     out = []
-    for per_thread in (True, False):
+    for default in (True, False):
         s = [torch.cuda.Stream() for _ in range(3)]
-        ctx = A.Context(cfg, theta0, streams=[PerThread] + s[1:] if per_thread else s)
+        ctx = A.Context(cfg, theta0, streams=[Default] + s[1:] if default else s)
         assert A.replay_info(ctx)[0] == 3
         with concurrent.futures.ThreadPoolExecutor(1) as one, concurrent.futures.ThreadPoolExecutor(1) as two:
             for rnd in range(3):
@@ -619,7 +621,9 @@ def test_workers_on_the_per_thread_default_stream():
             torch.cuda.synchronize()
             out.append([ctx.get_vector(v) for v in ("theta", "momentum", "delta")] +
                        [ctx.get_vector(v, i) for i in range(3) for v in ("worker_theta", "adam_m", "grad")])
+            one.submit(ctx.worker_local_steps, 0, tok[0], 1e-3).result()
             ctx.close()
+            torch.cuda.synchronize()
     for a, b in zip(*out):
         assert np.array_equal(a, b)
 
