@@ -102,7 +102,9 @@ void carve(als_ctx* c, Carver& cv) {
   // Aligned products of few 256 x 256 tiles and a short K too: grouped, they are split 5 to 8 times along K and their partials are most of
   // the traffic (2048 tokens, d = 256, 4 layers, V = 4096: 28 us, 18 for the partials' sum and 19 for the output matrix; as a list 41).
   // Rounds of one worker, grouped / list: 64 tiles, 2048 tokens: 557 / 531; 128, 1024: 506 / 482; 28, 512: 253 / 240; above the line 148, 1024:
-  // 1109 / 1115; 208, 2048: 915 / 921; 64, 8192: 1035 / 1055; 197, 8192: 2232 / 2294.
+  // 1109 / 1115; 208, 2048: 915 / 921; 64, 8192: 1035 / 1055; 197, 8192: 2232 / 2294.  Inside the lines, d = 128 to 1024, one and two workers: 64 tokens,
+  // 6 tiles 212 / 201, 128 tiles 483 / 471; 128 tokens, 7 tiles 228 / 206, 104 tiles 1074 / 1061; 512 tokens, d = 1024, 128 tiles 639 / 595; 2048 tokens,
+  // 6 tiles 306 / 267, 128 tiles (V = 24576) 1432 / 1328.
   {
     const bool aligned = bf && T % 64 == 0 && d % 128 == 0 && (da % 128 == 0 || ff % 128 == 0);
     c->list_dw = !(g.flags & 3) && (!aligned || few) && (int64_t)g.n_layers * T * (2 * d + ff + 3 * da) * (bf ? 2 : 4) <= (int64_t)256 << 20;
