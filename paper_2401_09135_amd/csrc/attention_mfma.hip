@@ -741,10 +741,14 @@ bool attention_mfma_supported(int S, int dh, int bf) { return bf && dh == 64 && 
 //   B 8, S 512, 8 heads (512): 12.6 + 29 / 10 + 26 / 12.7 + 34                B 32, S 512, 8 heads (2048): 21 + 63 / 31 + 80 / 49 + 134
 //   B 3, S 384, 5 heads (90): 10 + 23 / 7.4 + 17 / 7.4 + 19                   B 4, S 128, 4 heads (32): 5.4 + 13 / 5.0 + 11.5 / 5.9 + 15
 // The lines lie below where one call alone gains, since workers run side by side: with 4 at 224 blocks and 2 at 512, rounds of two workers
-// took 7706 us (B 1, S 1024, 14 heads) and 3343 (B 32, S 256, 4 heads), with 2 and 1 there 7476 and 3298.
+// took 7706 us (B 1, S 1024, 14 heads) and 3343 (B 32, S 256, 4 heads), with 2 and 1 there 7476 and 3298.  Long rows share up to 384 blocks:
+// on its own a block of 16 tiles in one wavefront is a longer chain than the blocks of 32 queries that were there before (B 6, S 1024, 4 heads:
+// 66.6 us forward and backward with those, 69.3 / 49.1 with 1 / 2; rounds of 8 heads, B 3, one worker 3688, 3704 / 3480, two 2814, 2815 / 2706, and
+// no longer where several contexts overlap: 2328, 2328 / 2323).  At 512 blocks they would lose there (four workers 5531, 5479 / 5706) what one
+// worker alone gains (3986, 4010 / 3821); the same from 384 blocks on at S 640 (overlapped 2275, 2266 / 2311) and S 512 (2224, 2206 / 2233).
 static int sharing(int B, int S, int h) {
   const int64_t blocks = (int64_t)B * h * (S / 64);
-  return blocks <= 128 && S >= 512 ? 4 : blocks <= 256 ? 2 : 1;
+  return blocks <= 128 && S >= 512 ? 4 : blocks <= (S > 768 ? 384 : 256) ? 2 : 1;
 }
 
 template <auto Kern, typename... Args>

@@ -204,8 +204,10 @@ def test_attention_mfma(B, S, h):
 
 
 # Four wavefronts to a block of 64 queries (128 blocks, the last that do), two (144; and one tile for two, so that one has none), one with
-# pairs that are no multiple of 8 (650 blocks), and pairs in two groups of unequal size (518 pairs).
-@pytest.mark.parametrize("B,S,h", [(1, 1024, 8), (1, 1024, 9), (2, 128, 3), (5, 640, 13), (37, 128, 14)])
+# pairs that are no multiple of 8 (650 blocks), and pairs in two groups of unequal size (518 pairs).  Rows of more than 768 share up to 384 blocks
+# (the last and the first that does not), shorter ones 256 (252 and 264).
+@pytest.mark.parametrize("B,S,h", [(1, 1024, 8), (1, 1024, 9), (2, 128, 3), (5, 640, 13), (37, 128, 14), (3, 1024, 8), (5, 1024, 5), (3, 768, 7),
+                                   (2, 768, 11)])
 def test_attention_mfma_sharing_and_order_of_blocks(B, S, h):
     test_attention_mfma(B, S, h)
 
